@@ -245,10 +245,7 @@ __device__ inline void finish(v16i (&a)[TNE][TME], const float (&scv)[(TNE * 32 
                 if (ALIGNED) {       // N % 8 == 0: the segment is whole and 16-byte aligned
                     __builtin_nontemporal_store(v4i{(int)v.x, (int)v.y, (int)v.z, (int)v.w}, reinterpret_cast<v4i *>(dst));
                 } else {
-                    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (nn + e < N) dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+                    store_row_segment(dst, v, nn, N);
                 }
             }
         }
