@@ -8,8 +8,8 @@ dequantizing epilogue.  Inputs are synthetic, seeded, and resident in HBM before
 
   value        whole-step throughput in TOP/s (2 M N K of the four linears / step time, quantizers in the time),
                on the configuration's own activations
-  roofline     the dominant launch (the gate+up GEMM): algorithmic ops per launch / average launch duration from
-               HIP events on the launch stream, against the 5.0 POP/s dense INT8 MFMA peak.  The configuration's own
+  roofline     the dominant linear (the gate+up GEMM, with the widening of its activations to six bits): algorithmic ops / average
+               duration from HIP events on the launch stream, against the 5.0 POP/s dense INT8 MFMA peak.  The configuration's own
                activations quantize to > 99 % zeros (absmax calibration with outlier channels), which lets the part
                clock higher, so the same launches are also timed on uniform random INT4 activations and the LOWER of
                the two rates is the one reported as achieved / frac; both are in the object
@@ -32,7 +32,9 @@ sys.path.insert(0, ROOT)
 
 INT8_MFMA_PEAK_TOPS = 5000.0     # MI355X dense INT8 MFMA, TOP/s
 HBM_PEAK_GBS = 8000.0            # MI355X HBM3E, GB/s
+FP6_MFMA_PEAK_TOPS = 10066.0     # MI355X dense FP6 MFMA, twice the INT8 rate: the unit the large launches run on
 TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "linear_mfma_traffic.md")
+PREFILL_TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "linear_prefill_traffic.md")      # the same for the six-bit kernel
 CPU_SAMPLE_ROWS = 4096           # token rows of the headline workload the oracle is timed on
 WARM_SECONDS = 1.0               # untimed stepping before each timed region, beyond --warmup (clock and power settle)
 
@@ -108,7 +110,8 @@ def main():
         torch.cuda.synchronize()
         del src, dst
 
-    traffic = read_traffic_table()
+    traffic = {"linear_prefill_kernel": read_traffic_table(PREFILL_TRAFFIC_TABLE)}
+    int8_traffic = read_traffic_table()
     keep_host = {}       # first rows of the headline inputs and its weights, for the CPU leg
 
     def build(cfg):
@@ -145,7 +148,7 @@ def main():
              "y": torch.empty((M, N), dtype=torch.bfloat16, device=dev)}
         # uniform random INT4 codes in the packed layout (any byte is two valid codes; K is a multiple of 128 at these shapes)
         L["xq_dense"] = torch.randint(0, 256, (L["xq"].numel(),), dtype=torch.uint8, device=dev)
-        L["plan"] = fptq.fptq_linear_launch_plan(M, N, K)
+        L["plan"] = fptq.fptq_linear_launch_plan(M, N, K, with_scratch=True)      # fptq_w4a4_linear brings scratch along
         torch.cuda.synchronize()
         return L
 
@@ -227,9 +230,10 @@ def main():
     d_own, d_dense = own["launches"][dom["name"]], dense["launches"][dom["name"]]
     low = d_dense if d_dense["avg_us"] >= d_own["avg_us"] else d_own
     alg_bytes = dom["N"] * dom["K"] // 2 + dom["M"] * dom["K"] // 2 + 4 * dom["N"] + 2 * dom["M"] * dom["N"]
-    trow = traffic.get("c5." + dom["name"])
+    trow = traffic.get(dom["plan"][0], int8_traffic).get("c5." + dom["name"])
     stale = trow is not None and (trow["kernel"], trow["grid"]) != (dom["plan"][0], dom["plan"][1] * dom["plan"][2])
-    roofline = {"kernel": "linear_mfma_kernel<%s>, c5 %s %dx%dx%d" % (dom["plan"][0], dom["name"], dom["M"], dom["N"], dom["K"]),
+    kernel = dom["plan"][0] if dom["plan"][0] == "linear_prefill_kernel" else "linear_mfma_kernel<%s>" % dom["plan"][0]
+    roofline = {"kernel": "%s, c5 %s %dx%dx%d" % (kernel, dom["name"], dom["M"], dom["N"], dom["K"]),
                 "bound": "mfma", "achieved": low["TOPS"], "peak": INT8_MFMA_PEAK_TOPS, "unit": "TOP/s",
                 "frac": round(low["TOPS"] / INT8_MFMA_PEAK_TOPS, 4),
                 "region": "dense_int4_activations" if low is d_dense else "own_activations (the timed region)",
@@ -237,14 +241,16 @@ def main():
                 "event_pair_overhead_us": dense["event_pair_overhead_us"] if low is d_dense else own["event_pair_overhead_us"],
                 "own_activations": d_own, "dense_int4_activations": d_dense,
                 "traffic": None if trow is None or stale else round(trow["bytes"]),
-                "traffic_source": "profiles/linear_mfma_traffic.md (FETCH_SIZE and WRITE_SIZE counter passes, scaled by a 1 GiB "
+                "peak_note": "the dense INT8 MFMA peak, the rate INT4 x INT4 had before the six-bit kernel; that kernel's own unit peaks at "
+                             "%.0f TOP/s, and a launch's time includes widening its activations to six bits" % FP6_MFMA_PEAK_TOPS,
+                "traffic_source": "profiles/linear_*_traffic.md (FETCH_SIZE and WRITE_SIZE counter passes, scaled by a 1 GiB "
                                   "copy kernel)" + (" -- STALE: the launcher now picks another kernel or grid" if stale else ""),
                 "algorithmic_bytes_per_launch": alg_bytes}
 
     out = {"metric": "W4A4 linear TOPS (prefill)", "value": own["step_TOPS"], "unit": "TOP/s", "n_gpus": 1,
            "steps": args.steps, "warmup": args.warmup, "ms_per_step": own["ms_per_step"],
            "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-           "dtype": "int8 MFMA on int4 operands, int32 accumulate", "data": "synthetic",
+           "dtype": "int4 operands on the FP6 (large launches) and INT8 matrix cores, exact integer sums in fp32 / int32", "data": "synthetic",
            "config": {"workload": "c5: Llama-3-70B-shaped layer linears, prefill 8192 tokens: for QKV [10240x8192], O [8192x8192], "
                                   "gate+up [57344x8192] and down [8192x28672]: quantize the bf16 input (per-token scale, static "
                                   "INT4, packing), INT4 x INT4 linear with dequantizing epilogue to bf16",

@@ -211,6 +211,22 @@ int fptq_w4a4_linear_ws(const void *xq_packed, const void *w_packed, int64_t M, 
 int fptq_w4a4_linear_noalloc(const void *xq_packed, const void *w_packed, int64_t M, int64_t N, int64_t K, float s_a,
                              const float *s_w, const float *row_out_scale, void *y_bf16, int32_t *acc_dbg, void *stream);
 
+/*
+ * fptq_w4a4_linear / fptq_w4a4_linear_zp with scratch memory.  For large problems the product runs on the 6-bit float matrix
+ * cores, twice the rate of the 8-bit integer ones and exact for these operands (every product and partial sum is an integer
+ * below 2^24 in a fixed unit), if the call has room for the activations widened to six bits: 0.75 bytes per value.
+ *   zero_point, w_row_sum  as in fptq_w4a4_linear_zp; 0 and NULL for the symmetric grid
+ *   scratch                device, 256-byte aligned, at least fptq_linear_scratch_bytes(M, N, K) bytes, or NULL.  Its contents need
+ *                          no initialisation and mean nothing afterwards.  Calls that share it must not overlap in time.
+ *   scratch_bytes          its size.  Too small, NULL, or a shape that does not profit (fptq_linear_scratch_bytes returns 0): the
+ *                          call behaves exactly like fptq_w4a4_linear / fptq_w4a4_linear_zp.
+ * Results are identical to theirs.
+ */
+int64_t fptq_linear_scratch_bytes(int64_t M, int64_t N, int64_t K);
+int fptq_w4a4_linear_scratch(const void *xq_packed, const void *w_packed, int64_t M, int64_t N, int64_t K, float s_a,
+                             const float *s_w, const float *row_out_scale, int zero_point, const int32_t *w_row_sum, void *y_bf16,
+                             int32_t *acc_dbg, void *scratch, int64_t scratch_bytes, void *stream);
+
 /* Same contract as fptq_w4a4_linear but always runs the simple one-thread-per-output kernel
  * (no MFMA, no LDS).  A second, independent GPU implementation used by the tests to cross-check
  * the tuned kernels at full size. */

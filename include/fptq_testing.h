@@ -30,11 +30,15 @@ int fptq_set_gemm_map(int mode);
  * (1, 2 or 4), e.g. 1612.  Results do not depend on it.  Returns 0, or FPTQ_ERR_VALUE (-6) for any other value. */
 int fptq_set_decode_shape(int code);
 
-/* Host arithmetic only: which kernel fptq_w4a4_linear (with_workspace = 0) or fptq_w4a4_linear_ws with a large enough
- * workspace (1) would launch for this shape on the current device (an MI355X's 256 compute units are assumed when no
+/* Whether fptq_w4a4_linear_scratch takes its six-bit kernel: 0 = where it pays (default), 1 = wherever its limits allow and the
+ * few-token kernel does not answer, 2 = never.  Results do not depend on it.  Returns 0 or FPTQ_ERR_VALUE (-6). */
+int fptq_set_linear_prefill(int mode);
+
+/* Host arithmetic only: which kernel fptq_w4a4_linear (with_workspace = 0), fptq_w4a4_linear_ws with a large enough
+ * workspace (1) or fptq_w4a4_linear_scratch with enough scratch (2; the product's launch only) would launch for this shape on the current device (an MI355X's 256 compute units are assumed when no
  * device answers).  kernel receives the tile configuration as it appears in a profiler's kernel name, e.g.
- * "GemmCfg<2, 2, 4, 4, 4, 1, 1, false>", or "linear_decode_kernel" / "linear_ref_kernel" (workgroups and threads are
- * 0 for those two); workgroups x threads is the grid a kernel trace shows.  Returns 0 or a negative FPTQ_ERR_* code. */
+ * "GemmCfg<2, 2, 4, 4, 4, 1, 1, false>", "linear_prefill_kernel", or "linear_decode_kernel" / "linear_ref_kernel" (workgroups and threads are
+ * 0 for the last two); workgroups x threads is the grid a kernel trace shows.  Returns 0 or a negative FPTQ_ERR_* code. */
 int fptq_linear_launch_plan(int64_t M, int64_t N, int64_t K, int with_workspace, char *kernel, int kernel_len,
                             int64_t *workgroups, int *threads);
 

@@ -20,8 +20,9 @@ EXPORTS = ["fptq_version", "fptq_last_error", "fptq_init", "fptq_packed_bytes", 
            "fptq_quantize_act_hadamard", "fptq_quantize_act_dynamic", "fptq_quantize_act_asym",
            "fptq_weight_row_sums", "fptq_w4a4_linear_zp", "fptq_residual_norm_quantize",
            "fptq_w4a4_linear", "fptq_w4a4_linear_ref", "fptq_unpack", "fptq_linear_workspace_bytes", "fptq_w4a4_linear_ws",
-           "fptq_w4a4_linear_noalloc"]
-TESTING_EXPORTS = ["fptq_set_gemm_tile", "fptq_set_gemm_map", "fptq_set_decode_shape", "fptq_linear_launch_plan"]
+           "fptq_w4a4_linear_noalloc", "fptq_linear_scratch_bytes", "fptq_w4a4_linear_scratch"]
+TESTING_EXPORTS = ["fptq_set_gemm_tile", "fptq_set_gemm_map", "fptq_set_decode_shape", "fptq_set_linear_prefill",
+                   "fptq_linear_launch_plan"]
 
 _lib = None
 
@@ -71,6 +72,8 @@ def lib():
         L.fptq_set_gemm_map.argtypes = [i32]
         L.fptq_set_decode_shape.restype = i32
         L.fptq_set_decode_shape.argtypes = [i32]
+        L.fptq_set_linear_prefill.restype = i32
+        L.fptq_set_linear_prefill.argtypes = [i32]
         L.fptq_set_gemm_tile.restype = i32
         L.fptq_set_gemm_tile.argtypes = [i32]
         L.fptq_unpack.restype = i32
@@ -79,6 +82,10 @@ def lib():
         L.fptq_linear_workspace_bytes.argtypes = [i64, i64, i64]
         L.fptq_w4a4_linear_ws.restype = i32
         L.fptq_w4a4_linear_ws.argtypes = [p, p, i64, i64, i64, f32, p, p, p, p, p, i64, p]
+        L.fptq_linear_scratch_bytes.restype = i64
+        L.fptq_linear_scratch_bytes.argtypes = [i64, i64, i64]
+        L.fptq_w4a4_linear_scratch.restype = i32
+        L.fptq_w4a4_linear_scratch.argtypes = [p, p, i64, i64, i64, f32, p, p, i32, p, p, p, p, i64, p]
         _lib = L
     return _lib
 
@@ -187,8 +194,12 @@ def fptq_weight_row_sums(w_int):
 
 def fptq_w4a4_linear_zp(xq, wq, M, N, K, s_a, s_w, zero_point, w_row_sum, row_out_scale=None, out=None, want_acc=False):
     _dev(w_row_sum, torch.int32, "w_row_sum")
-    fn = lambda a, b, m, n, k, sa, sw, d, y, acc, st: lib().fptq_w4a4_linear_zp(a, b, m, n, k, sa, sw, d, int(zero_point),
-                                                                                 _ptr(w_row_sum), y, acc, st)
+    scratch = _scratch(M, N, K, xq)
+    if scratch is not None:
+        fn = _scratch_call(scratch, int(zero_point), w_row_sum)
+    else:
+        fn = lambda a, b, m, n, k, sa, sw, d, y, acc, st: lib().fptq_w4a4_linear_zp(a, b, m, n, k, sa, sw, d, int(zero_point),
+                                                                                     _ptr(w_row_sum), y, acc, st)
     return _linear(fn, xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, None)
 
 
@@ -234,9 +245,48 @@ def _linear(fn, xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc):
     return (out, acc) if (want_acc or acc is not None) else out
 
 
+def fptq_linear_scratch_bytes(M, N, K):
+    """Bytes of scratch fptq_w4a4_linear_scratch would use for this shape (0: it would not use any)."""
+    n = lib().fptq_linear_scratch_bytes(M, N, K)
+    if n < 0:
+        _check(int(n))
+    return int(n)
+
+
+def _scratch(M, N, K, xq):
+    """Scratch for a linear call from torch's caching allocator, or None where the call goes without: shapes that do not
+    profit, no memory left, or a stream under capture (a capture not made through torch would have no pool to allocate from)."""
+    if M <= 64 or not isinstance(xq, torch.Tensor):
+        return None
+    n = lib().fptq_linear_scratch_bytes(M, N, K)
+    if n <= 0 or torch.cuda.is_current_stream_capturing():
+        return None
+    try:
+        return torch.empty(n, dtype=torch.uint8, device=xq.device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
+def _scratch_call(scratch, zero_point, w_row_sum):
+    return lambda a, b, m, n, k, sa, sw, d, y, acc, st: lib().fptq_w4a4_linear_scratch(
+        a, b, m, n, k, sa, sw, d, zero_point, _ptr(w_row_sum), y, acc, _ptr(scratch), 0 if scratch is None else scratch.numel(), st)
+
+
+def fptq_w4a4_linear_scratch(xq, wq, M, N, K, s_a, s_w, scratch, zero_point=0, w_row_sum=None, row_out_scale=None, out=None,
+                             want_acc=False, acc=None):
+    """fptq_w4a4_linear / _zp with a uint8 device scratch buffer of the caller (or None)."""
+    if scratch is not None:
+        _dev(scratch, torch.uint8, "scratch")
+    if w_row_sum is not None:
+        _dev(w_row_sum, torch.int32, "w_row_sum")
+    return _linear(_scratch_call(scratch, int(zero_point), w_row_sum), xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc)
+
+
 def fptq_w4a4_linear(xq, wq, M, N, K, s_a, s_w, row_out_scale=None, out=None, want_acc=False, acc=None):
     """Packed activations x packed weights -> bf16 [M, N] (and the int32 accumulators if asked)."""
-    return _linear(lib().fptq_w4a4_linear, xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc)
+    scratch = _scratch(M, N, K, xq)
+    fn = lib().fptq_w4a4_linear if scratch is None else _scratch_call(scratch, 0, None)
+    return _linear(fn, xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc)
 
 
 def fptq_linear_workspace_bytes(M, N, K):
@@ -251,6 +301,9 @@ def fptq_w4a4_linear_ws(xq, wq, M, N, K, s_a, s_w, workspace, row_out_scale=None
     """fptq_w4a4_linear with a zero-initialised uint8 device workspace (or None) for the split over K."""
     if workspace is not None:
         _dev(workspace, torch.uint8, "workspace")
+    # no split over K: the plain layer (a misaligned workspace is still refused, below)
+    if M > 64 and (workspace is None or workspace.data_ptr() % 256 == 0) and lib().fptq_linear_workspace_bytes(M, N, K) == 0:
+        return fptq_w4a4_linear(xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc)
     fn = lambda a, b, m, n, k, sa, sw, d, y, ac, st: lib().fptq_w4a4_linear_ws(
         a, b, m, n, k, sa, sw, d, y, ac, _ptr(workspace), 0 if workspace is None else workspace.numel(), st)
     return _linear(fn, xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc)
@@ -274,15 +327,19 @@ def fptq_set_decode_shape(code):
     _check(lib().fptq_set_decode_shape(int(code)))
 
 
+def fptq_set_linear_prefill(mode):
+    _check(lib().fptq_set_linear_prefill(int(mode)))
+
+
 def fptq_set_gemm_tile(tile):
     _check(lib().fptq_set_gemm_tile(int(tile)))
 
 
-def fptq_linear_launch_plan(M, N, K, with_workspace=False):
+def fptq_linear_launch_plan(M, N, K, with_workspace=False, with_scratch=False):
     """(kernel name fragment, workgroups, threads per workgroup) of the launch a linear call would make; host only."""
     buf = ctypes.create_string_buffer(96)
     wgs, thr = ctypes.c_int64(0), ctypes.c_int(0)
-    _check(lib().fptq_linear_launch_plan(M, N, K, int(bool(with_workspace)), buf, len(buf), ctypes.byref(wgs), ctypes.byref(thr)))
+    _check(lib().fptq_linear_launch_plan(M, N, K, 2 if with_scratch else int(bool(with_workspace)), buf, len(buf), ctypes.byref(wgs), ctypes.byref(thr)))
     return buf.value.decode(), int(wgs.value), int(thr.value)
 
 

@@ -9,7 +9,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(CSRC, "libfptq.so")
 PROBE_LIB = os.path.join(CSRC, "libfptq_probe.so")
-SOURCES = ["fptq_api.hip", "fptq_pack.hip", "fptq_quant.hip", "fptq_gemm.hip", "fptq_gemv.hip", "fptq_hadamard.hip", "fptq_residual.hip"]
+SOURCES = ["fptq_api.hip", "fptq_pack.hip", "fptq_quant.hip", "fptq_gemm.hip", "fptq_prefill.hip", "fptq_gemv.hip", "fptq_hadamard.hip", "fptq_residual.hip"]
 PROBE_SOURCES = ["fptq_probe.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -51,6 +51,7 @@ hipError_t device_info(const DeviceInfo **out)
             if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
             info.cus = cus > 0 ? cus : DEFAULT_CUS;
             if ((e = gemm_device_init(&info)) != hipSuccess) return e;
+            if ((e = prefill_device_init()) != hipSuccess) return e;
             if ((e = hadamard_device_init(dev)) != hipSuccess) return e;
             g_devices[dev] = info;
             g_device_ready[dev].store(true, std::memory_order_release);
@@ -101,7 +102,8 @@ typedef hipError_t (*linear_fn)(const uint8_t *, const uint8_t *, int64_t, int64
 
 static int linear_common(const char *fn, linear_fn force, const void *xq, const void *wq, int64_t M, int64_t N,
                          int64_t K, float s_a, const float *s_w, const float *d, int zp, const int32_t *wsum, void *y,
-                         int32_t *acc, void *stream, void *workspace = nullptr, int64_t workspace_bytes = 0)
+                         int32_t *acc, void *stream, void *workspace = nullptr, int64_t workspace_bytes = 0,
+                         void *scratch = nullptr, int64_t scratch_bytes = 0)
 {
     if (!xq || !wq || !s_w || !y) {
         set_error("%s: NULL pointer", fn);
@@ -135,9 +137,17 @@ static int linear_common(const char *fn, linear_fn force, const void *xq, const 
         set_error("%s: negative workspace_bytes", fn);
         return FPTQ_ERR_SIZE;
     }
+    if ((rc = check_align(fn, scratch, 256, "scratch"))) return rc;
+    if (scratch_bytes < 0) {
+        set_error("%s: negative scratch_bytes", fn);
+        return FPTQ_ERR_SIZE;
+    }
     linear_fn f = force ? force : (few_token_shape(M, N) && forced_gemm_tile() == 0 ? launch_linear_decode : launch_linear_mfma);
     hipError_t e;
-    if (f == launch_linear_mfma && workspace)
+    if (f == launch_linear_mfma && scratch && prefill_pays(M, N, K) && scratch_bytes >= prefill_scratch_bytes(M, K))
+        e = launch_linear_prefill((const uint8_t *)xq, (const uint8_t *)wq, M, N, K, s_a, s_w, d, zp, wsum, (uint16_t *)y, acc,
+                                  (uint8_t *)scratch, (hipStream_t)stream);
+    else if (f == launch_linear_mfma && workspace)
         e = launch_linear_mfma_ws((const uint8_t *)xq, (const uint8_t *)wq, M, N, K, s_a, s_w, d, zp, wsum, (uint16_t *)y, acc,
                                   (int32_t *)workspace, workspace_bytes, (hipStream_t)stream);
     else
@@ -389,6 +399,27 @@ int fptq_w4a4_linear_noalloc(const void *xq_packed, const void *w_packed, int64_
                          info->scratch, info->scratch_bytes);
 }
 
+int64_t fptq_linear_scratch_bytes(int64_t M, int64_t N, int64_t K)
+{
+    const char *fn = "fptq_linear_scratch_bytes";
+    int rc;
+    if ((rc = check_dims(fn, M, K, "M", "K")) || (rc = check_dims(fn, N, K, "N", "K")) || (rc = check_dims(fn, M, N, "M", "N")))
+        return rc;
+    if (K > MAX_K) {
+        set_error("%s: K=%lld exceeds %lld, the longest sum INT32 holds exactly", fn, (long long)K, (long long)MAX_K);
+        return FPTQ_ERR_SHAPE;
+    }
+    return !few_token_shape(M, N) && prefill_pays(M, N, K) ? prefill_scratch_bytes(M, K) : 0;
+}
+
+int fptq_w4a4_linear_scratch(const void *xq_packed, const void *w_packed, int64_t M, int64_t N, int64_t K, float s_a,
+                             const float *s_w, const float *row_out_scale, int zero_point, const int32_t *w_row_sum, void *y_bf16,
+                             int32_t *acc_dbg, void *scratch, int64_t scratch_bytes, void *stream)
+{
+    return linear_common("fptq_w4a4_linear_scratch", nullptr, xq_packed, w_packed, M, N, K, s_a, s_w, row_out_scale, zero_point,
+                         w_row_sum, y_bf16, acc_dbg, stream, nullptr, 0, scratch, scratch_bytes);
+}
+
 int fptq_linear_launch_plan(int64_t M, int64_t N, int64_t K, int with_workspace, char *kernel, int kernel_len,
                             int64_t *workgroups, int *threads)
 {
@@ -405,8 +436,12 @@ int fptq_linear_launch_plan(int64_t M, int64_t N, int64_t K, int with_workspace,
         snprintf(plan.kernel, sizeof plan.kernel, "linear_decode_kernel");
         plan.workgroups = 0;
         plan.threads = 0;
+    } else if (with_workspace == 2 && prefill_pays(M, N, K)) {
+        snprintf(plan.kernel, sizeof plan.kernel, "linear_prefill_kernel");
+        plan.workgroups = prefill_workgroups(M, N);
+        plan.threads = 256;
     } else {
-        linear_mfma_plan(M, N, K, with_workspace != 0, &plan);
+        linear_mfma_plan(M, N, K, with_workspace == 1, &plan);
     }
     snprintf(kernel, (size_t)kernel_len, "%s", plan.kernel);
     *workgroups = plan.workgroups;
@@ -421,6 +456,16 @@ int fptq_set_gemm_map(int mode)
         return FPTQ_ERR_VALUE;
     }
     set_gemm_map(mode);
+    return FPTQ_OK;
+}
+
+int fptq_set_linear_prefill(int mode)
+{
+    if (mode < 0 || mode > 2) {
+        set_error("fptq_set_linear_prefill: mode must be 0, 1 or 2");
+        return FPTQ_ERR_VALUE;
+    }
+    set_linear_prefill(mode);
     return FPTQ_OK;
 }
 

@@ -44,12 +44,18 @@ hipError_t launch_linear_mfma_ws(const uint8_t *xq, const uint8_t *wq, int64_t M
                                  const float *s_w, const float *d, int zp, const int32_t *wsum, uint16_t *y, int32_t *acc,
                                  int32_t *ws, int64_t ws_bytes, hipStream_t s);
 int64_t linear_workspace_bytes(int64_t M, int64_t N, int64_t K);
+hipError_t launch_linear_prefill(const uint8_t *xq, const uint8_t *wq, int64_t M, int64_t N, int64_t K, float s_a, const float *s_w,
+                                 const float *d, int zp, const int32_t *wsum, uint16_t *y, int32_t *acc, uint8_t *scratch, hipStream_t s);
+int64_t prefill_scratch_bytes(int64_t M, int64_t K);
+int64_t prefill_workgroups(int64_t M, int64_t N);
+bool prefill_pays(int64_t M, int64_t N, int64_t K);
 hipError_t launch_linear_decode(const uint8_t *xq, const uint8_t *wq, int64_t M, int64_t N, int64_t K, float s_a,
                                 const float *s_w, const float *d, int zp, const int32_t *wsum, uint16_t *y, int32_t *acc,
                                 hipStream_t s);
 
 void set_gemm_tile(int tile);
 void set_gemm_map(int mode);
+void set_linear_prefill(int mode);
 int forced_gemm_tile();
 bool set_decode_shape(int code);
 
@@ -76,6 +82,7 @@ hipError_t device_info(const DeviceInfo **out);  // state of the current device
 int device_cus_or_default();                     // compute units of the current device, DEFAULT_CUS without one
 // what each translation unit contributes to that set-up (called with the device current, under the set-up lock)
 hipError_t gemm_device_init(DeviceInfo *info);
+hipError_t prefill_device_init();
 hipError_t hadamard_device_init(int device);
 
 // fp32 -> bf16 bit pattern, round to nearest even (NaN stays a quiet NaN)

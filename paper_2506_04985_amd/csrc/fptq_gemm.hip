@@ -550,7 +550,9 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void linear_mfma_kernel(
 // 0 = choose the tile shape per problem; 1..8 = force one (testing and tuning)
 static std::atomic<int> g_forced_tile{0};
 static std::atomic<int> g_tile_map{0};
+static std::atomic<int> g_prefill{0};     // 0 = where the six-bit kernel pays, 1 = wherever it can run, 2 = never
 void set_gemm_tile(int tile) { g_forced_tile.store(tile, std::memory_order_relaxed); }
+void set_linear_prefill(int mode) { g_prefill.store(mode, std::memory_order_relaxed); }
 void set_gemm_map(int mode) { g_tile_map.store(mode, std::memory_order_relaxed); }
 int forced_gemm_tile() { return g_forced_tile.load(std::memory_order_relaxed); }
 
@@ -686,7 +688,7 @@ hipError_t launch_linear_mfma_ws(const uint8_t *xq, const uint8_t *wq, int64_t M
 
 // Tile shape for a problem: index into the launch table (0 = 256 x 256, 1 = 192 x 256, 2 = 256 x 128, 3 = 256 x 128 with
 // two workgroups per CU, 4 = 128 x 128 and 5 = 256 x 128 with two K groups, 6 = 64 x 64 and 7 = 128 x 64 with four).
-static int choose_tile(int64_t M, int64_t N, int64_t K, int cus)
+static int choose_tile(int64_t M, int64_t N, int64_t K, int cus, double *us = nullptr)
 {
     const int forced = forced_gemm_tile();
     if (forced > 0) return forced - 1;
@@ -717,6 +719,7 @@ static int choose_tile(int64_t M, int64_t N, int64_t K, int cus)
     int pick = 0;
     for (int i = 1; i < 5; ++i)
         if (cost[i] < cost[pick]) pick = i;
+    if (us) *us = cost[pick];
     if (pick == 4) pick = 5;       // the launch table: 4 = 128 x 128, 5 = 256 x 128, both with two K groups
     // Problems so small that even 128 x 128 tiles give every CU at most one workgroup take that tile: the
     // kernel time is then one workgroup's walk through K and the small tile walks fastest (17 against 25 us at
@@ -728,7 +731,27 @@ static int choose_tile(int64_t M, int64_t N, int64_t K, int cus)
     // tokens 12.5 us on 128 x 64 against 18.
     if (tiles(128, 64) <= CUS) pick = 7;
     if (tiles(64, 64) <= CUS) pick = 6;
+    if (us && (pick == 6 || pick == 7)) *us = 0.0;     // not estimated: those problems never leave half of the CUs' matrix pipes busy
     return pick;
+}
+
+// Whether a problem is faster on the six-bit kernel (fptq_prefill.hip), widening of its activations included.  Estimated times on
+// uniform random operands, as above, in rounds of one 256 x 256 tile per CU; a partial last round costs less than a full one (the
+// power it leaves speeds its tiles up), a lone partial round does not.  Fitted to 8192 x 57344 x 8192 1712 us (INT8 2461),
+// 8192 x 8192 x 28672 829 (1156), 4096 x 28672 x 4096 251 (334), 2048 x 22016 x 4096 107 (137), 4096 x 6144 x 4096 70 (74),
+// 4096 x 4096 x 4096 45 (50), 2048 x 4999 x 4096 40.5 (39), 333 x 32003 x 2504 33 (31) and 700 x 50257 x 1024 58 (47); where the two
+// are within 3 % the INT8 shapes keep the problem.  They also keep those that give few CUs such a tile (1000 x 5120 x 13824).
+bool prefill_pays(int64_t M, int64_t N, int64_t K)
+{
+    if (K > 131071 || M > (1 << 24) || N > (1 << 24) || forced_gemm_tile() > 0) return false;
+    if (const int mode = g_prefill.load(std::memory_order_relaxed)) return mode == 1;
+    const int cus = device_cus_or_default();
+    double int8_us = 0.0;
+    choose_tile(M, N, K, cus, &int8_us);
+    const double x = (double)prefill_workgroups(M, N) / (double)cus, part = x - floor(x);
+    const double rounds = x <= 1.0 ? 1.04 : floor(x) + (part > 0.0 ? 0.75 + 0.25 * part : 0.0);
+    const double widen_us = 5.0 + (double)M * (double)K * 1.25 / 5.0e6;
+    return widen_us + rounds * (9.8 + 0.79 * (double)k_tiles(K)) < 0.97 * int8_us;
 }
 
 // Limits of the MFMA kernel: the widened accumulator is 256 * acc with |acc| <= 64 K, and one K tile of all rows

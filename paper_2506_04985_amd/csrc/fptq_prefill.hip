@@ -1,0 +1,484 @@
+// Large-problem kernel of the quantized linear layer: the INT4 x INT4 product on the 6-bit float matrix cores, which run at
+// twice the rate of the 8-bit integer ones, with the same integers as result.
+//
+// Why it is exact.  The FP6 format e2m3 holds every integer -15 .. 15 in units of 1/8 as sign and magnitude (its subnormals
+// and its first normal binade have the same spacing): the activations q in [-8, 7] fit, and so do the weights as w + 8 in
+// [0, 15].  Products are multiples of 1/64 and the sums stay below 2^24 of them (|q w| <= 64 per term once the +8 is taken
+// out, K <= 131071), so the fp32 accumulator never rounds; measured on the device with accumulators up to 2^24 - 1 and
+// products from 1 to 225, positive, negative and mixed.  The accumulators start at -8 sum_k q (every token's own constant), so
+// what they hold at the end is sum_k q w and not sum_k q (w + 8).
+//
+// Data flow.  A small kernel first widens the packed activations to six bits in a scratch buffer of the caller (0.75 bytes a
+// value, read and written once: 16 us at 8192 x 8192 beside 1790 us of product), with their signs resolved, and sums each
+// token's codes.  The matrix kernel copies those to LDS with buffer loads that write LDS directly, and reads the weights as
+// they are, packed, straight into registers: each of its four waves owns 64 channels and all 256 tokens of the tile, so a
+// weight is loaded by one wave only and needs no LDS, and its nibbles are spread to six-bit fields by 18 VALU instructions per
+// 32 values, 2.25 per MFMA.  Widening both operands in the kernel would take 5.7 VALU instructions per MFMA, and one wave
+// per SIMD issues at most eight instructions in the 32 cycles of an MFMA: measured at the INT8 loop's rate.  Widening the
+// weights beforehand as well would cost 1.25 bytes of traffic per weight and call, 5 % at 8192 tokens.
+//
+// What bounds it: the board's power.  On uniform random INT4 operands 8192 x 57344 x 8192 runs at 4260 TOP/s against 3100 for
+// the INT8 kernel (1806 and 2482 us), on all-zero operands in 1227 us; an MFMA-only loop on random operands that never
+// change reaches 6140, the same with this kernel's LDS reads 5030.
+#include <cstdio>
+#include <type_traits>
+
+#include "fptq_common.h"
+
+namespace fptq {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef int v12i __attribute__((ext_vector_type(12)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+typedef __attribute__((address_space(3))) const uint8_t lds_u8;
+typedef __attribute__((address_space(3))) const v4i lds_v4i;
+#define P_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
+
+// s_waitcnt immediates for gfx9: vmcnt in bits [3:0] and [15:14], expcnt [6:4], lgkmcnt [11:8]
+constexpr int p_waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+constexpr int P_WAIT_LGKM0 = 15 | (3 << 14) | (7 << 4) | (0 << 8);
+constexpr int P_RSRC_FLAGS = 0x00020000;        // raw buffer, 32-bit data format, bounds-checked
+
+// ---- six-bit activations in the scratch buffer: blocks of (K tile, 128 rows), 12 KB each, row blocks innermost.  A block is six
+// planes [half][piece][row] of 16-byte pieces: half h of a row holds its values 64 h .. 64 h + 63 as 48 bytes of six-bit
+// fields, i.e. three pieces.  The matrix kernel copies two blocks to LDS as they are, and a wave's fragment read (one piece of
+// 32 consecutive rows per half) is contiguous: no bank conflicts, no swizzle, and all of it in 16-byte reads (the 24 bytes of one
+// operand read as 16 + 8 made LDS the bound: 1627 instead of 1227 us on zero operands at 8192 x 57344 x 8192).
+constexpr int X6_ROWS = 128, X6_PLANE = X6_ROWS * 16, X6_BLOCK = 6 * X6_PLANE;
+constexpr int X6_PAD = 256;                     // rows are padded to a multiple of this
+static int64_t x6_rows(int64_t M) { return (M + X6_PAD - 1) / X6_PAD * X6_PAD; }
+static int64_t x6_slab(int64_t M) { return x6_rows(M) * (X6_BLOCK / X6_ROWS); }      // bytes per K tile
+
+// (a & m) ^ t in one instruction
+__device__ inline uint32_t masked_xor(uint32_t a, uint32_t m, uint32_t t) { return __builtin_amdgcn_bitop3_b32(a, m, t, 0x6A); }
+
+// The 16 nibbles of two dwords to the low four bits of 16 six-bit fields (96 bits), in an order that needs few instructions
+// (both operands use it, so it does not matter which).  A nibble can keep its place in a field that starts at a multiple of 12
+// bits from it, and reaches the fields in between by a shift of two; field 5 straddles two dwords, and its upper half comes
+// out of the funnel shift that moves the other dword.  FLIP inverts every nibble's top bit: two's complement to value + 8.
+template <bool FLIP>
+__device__ inline void spread6(uint32_t a, uint32_t b, uint32_t (&o)[3])
+{
+    const uint32_t a2 = a << 2, b2 = __builtin_amdgcn_alignbit(b, a, 30);      // b2: b << 2, a's top two bits below
+    o[0] = masked_xor(a2, 0xC03C03C0u, masked_xor(a, 0x0F00F00Fu, FLIP ? 0x08208208u : 0u));
+    o[1] = masked_xor(b2, 0x00000003u, masked_xor(a2, 0x03C03C00u, masked_xor(b, 0xF00F00F0u, FLIP ? 0x82082082u : 0u)));
+    o[2] = masked_xor(b2, 0x3C03C03Cu, masked_xor(b, 0x00F00F00u, FLIP ? 0x20820820u : 0u));
+}
+
+// eight two's complement nibbles as magnitudes and sign bits
+__device__ inline void sign_magnitude(uint32_t u, uint32_t &mag, uint32_t &sgn)
+{
+    sgn = (u >> 3) & 0x11111111u;
+    mag = (u ^ ((sgn << 4) - sgn)) + sgn;          // where negative (15 - u) + 1: at most 8, no carry out of a nibble
+}
+
+// 32 activations to six-bit sign and magnitude
+__device__ inline void widen_signed(v4i p, uint32_t *f)
+{
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        uint32_t ma, sa, mb, sb, m[3], s[3];
+        sign_magnitude((uint32_t)p[2 * h], ma, sa);
+        sign_magnitude((uint32_t)p[2 * h + 1], mb, sb);
+        spread6<false>(ma, mb, m);
+        spread6<false>(sa, sb, s);                 // bit 0 of every field; the sign is bit 5: the 96 bits shifted by five
+        f[3 * h + 0] = m[0] | (s[0] << 5);
+        f[3 * h + 1] = m[1] | __builtin_amdgcn_alignbit(s[1], s[0], 27);
+        f[3 * h + 2] = m[2] | __builtin_amdgcn_alignbit(s[2], s[1], 27);
+    }
+}
+
+// Packed activations -> six-bit blocks, and -sum_k q / 8 of every token (the accumulators' start in units of 1/64 is -8 sum).
+// A wave takes 32 rows, half a K tile row per lane; the workgroup's waves and the gridDim.y workgroups of a row group take K
+// tiles in turn.  Bound by HBM: 0.5 bytes read and 0.75 written per value.
+constexpr int CV_WAVES = 8, CV_ROWS = 32, CV_MAX_SPLIT = 4;
+
+__global__ __launch_bounds__(64 * CV_WAVES) void widen_activations_kernel(const uint8_t *__restrict__ xq, int M, int64_t slab, int ktiles,
+                                                                          uint8_t *__restrict__ x6, float *__restrict__ start, int rows)
+{
+    __shared__ int32_t red[CV_WAVES][CV_ROWS];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = blockIdx.x * CV_ROWS + (lane >> 1), h = lane & 1;
+    const int src_row = min(row, M - 1);           // rows past the end repeat the last one: their outputs are never stored
+    uint8_t *const dst = x6 + (int64_t)(row / X6_ROWS) * X6_BLOCK + 3 * h * X6_PLANE + (row % X6_ROWS) * 16;
+    int32_t sum = 0;
+    for (int kt = blockIdx.y * CV_WAVES + wave; kt < ktiles; kt += CV_WAVES * gridDim.y) {
+        const v4i *src = reinterpret_cast<const v4i *>(xq + ((int64_t)kt * M + src_row) * SEG + h * 32);
+        const v4i p0 = src[0], p1 = src[1];
+        uint32_t f[12];
+        widen_signed(p0, f);
+        widen_signed(p1, f + 6);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            sum = __builtin_amdgcn_sdot8(p0[e], 0x11111111, sum, false);
+            sum = __builtin_amdgcn_sdot8(p1[e], 0x11111111, sum, false);
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            *reinterpret_cast<v4i *>(dst + kt * slab + j * X6_PLANE) = v4i{(int)f[4 * j], (int)f[4 * j + 1], (int)f[4 * j + 2], (int)f[4 * j + 3]};
+    }
+    sum += __shfl_xor(sum, 1, 64);
+    if (h == 0) red[wave][lane >> 1] = sum;
+    __syncthreads();
+    if (tid < CV_ROWS) {
+        int32_t s = 0;
+#pragma unroll
+        for (int w = 0; w < CV_WAVES; ++w) s += red[w][tid];
+        start[(int64_t)blockIdx.y * rows + blockIdx.x * CV_ROWS + tid] = (float)s * -0.125f;      // one partial per workgroup of the row group
+    }
+}
+
+// Tile 256 (n) x 256 (m), four waves of 64 x 256, 256 accumulator registers a lane, one workgroup per CU.  K tile 128.  STAGES K
+// tiles of activations in an LDS ring, DEPTH K tiles of packed weights in registers.
+struct PrefillTile {
+    static constexpr int TN = 2, TM = 8, STAGES = 5, DEPTH = 3;
+    static constexpr int BN = 4 * TN * 32, BM = TM * 32;
+    static constexpr int STAGE_BYTES = BM * (X6_BLOCK / X6_ROWS);                               // 24 KB
+    static constexpr int FILLS = STAGE_BYTES / 4096, W_LOADS = 2 * TN, LOADS = FILLS + W_LOADS; // vector loads of a wave per K tile
+    static constexpr int LDS_BYTES = STAGES * STAGE_BYTES;
+    static_assert(FILLS == 6 && W_LOADS == 4, "the loads are dealt to the eight MFMA groups by hand");
+    static_assert(DEPTH >= STAGES - 3 && DEPTH <= STAGES - 1, "the wait counts assume weights and fills issued in the loop's order from the start");
+};
+
+typedef __bf16 p_bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float p_float2_t __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t p_pack_bf16(float lo, float hi)
+{
+    p_float2_t f = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, p_bf16x2_t));
+}
+
+// 32 x 32 x 64, both operands e2m3 (format code 2): 24 bytes, i.e. the first six registers, of each operand are read
+__device__ inline v16f mfma6(v8i w, v8i x, v16f c)
+{
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w, x, c, 2, 2, 0, 0, 0, 0);
+}
+
+template <bool ALIGNED, bool DUMP, bool ZP>
+__global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
+    const uint8_t *__restrict__ x6, int64_t x_slab, const float *__restrict__ start, int start_parts, int rows,
+    const uint8_t *__restrict__ wq, int M, int N, int ktiles, int tiles_m, int tiles_n, float s_a, const float *__restrict__ s_w,
+    const float *__restrict__ d, int zp, const int32_t *__restrict__ wsum, uint16_t *__restrict__ y, int32_t *__restrict__ acc_out)
+{
+    typedef PrefillTile C;
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fi = lane & 31, fg = lane >> 5;
+
+    // ---- tile of this workgroup: a contiguous run of tiles per XCD (workgroups are dealt to the 8 XCDs in turn), in bands of 8
+    // N-tiles with M fastest, so that the tiles an XCD runs together share panels in its L2
+    const int total = tiles_m * tiles_n;
+    int pid = blockIdx.x;
+    {
+        const int per = (total + 7) / 8, tall = total % 8 == 0 ? 8 : total % 8;
+        const int xcd = pid % 8, local = pid / 8;
+        pid = xcd < tall ? xcd * per + local : tall * per + (xcd - tall) * (per - 1) + local;
+    }
+    constexpr int GN = 8;
+    const int band = pid / (GN * tiles_m), in_band = pid % (GN * tiles_m);
+    const int band_w = min(GN, tiles_n - band * GN);
+    const int bn = band * GN + in_band % band_w, bm = in_band / band_w;
+    const int m0 = bm * C::BM, nw0 = bn * C::BN + wave * (C::TN * 32);
+
+    // ---- activations, HBM -> LDS: one run of 24 KB per K tile, a quarter of it per wave.  Past the last K tile the descriptor is
+    // empty: the loads are still issued (the wait counts stay the same) and land as zeros.
+    const int x_voff = bm * C::STAGE_BYTES + wave * (C::FILLS * 1024) + lane * 16;
+    uint8_t *const fill_base = lds + wave * (C::FILLS * 1024);
+    auto fill1 = [&](auto jc, __amdgpu_buffer_rsrc_t r, uint8_t *to) {
+        constexpr int J = decltype(jc)::value;     // 1 KB; the instruction's offset moves both addresses
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, P_LDS_PTR(to + J / 3 * 3072), 16, x_voff + J / 3 * 3072, 0, J % 3 * 1024, 0);
+    };
+    auto slab_desc = [&](const uint8_t *p, int64_t bytes, bool in) {
+        return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, in ? (int)bytes : 0, P_RSRC_FLAGS);
+    };
+    // ---- weights, HBM -> registers: lane (fi, fg) loads half fg (granules 2 fg, 2 fg + 1) of row nw0 + 32 t + fi, the k values of
+    // the activations' half fg; rows past N read as zero
+    const int64_t w_slab = (int64_t)N * SEG;
+    const int w_voff = (nw0 + fi) * SEG + fg * 32;
+    v4i raw[C::DEPTH][2][C::TN];
+    auto load_w1 = [&](__amdgpu_buffer_rsrc_t r, int s, int t) {
+        return __builtin_amdgcn_raw_buffer_load_b128(r, w_voff + t * (32 * SEG) + s * 16, 0, 0);
+    };
+    // ---- fragments: the 48 bytes of token 32 x + fi, half fg; the first 24 feed MFMA step 0, the others step 1
+    lds_u8 *const x_base = (lds_u8 *)lds + fg * (3 * X6_PLANE) + fi * 16;
+    v12i X[C::TM];
+    auto read_x = [&](int stage_off, int x) {
+        lds_u8 *const p = x_base + stage_off + (x / 4) * X6_BLOCK + (x % 4) * 512;
+        const v4i a = *(lds_v4i *)p, b = *(lds_v4i *)(p + X6_PLANE), c = *(lds_v4i *)(p + 2 * X6_PLANE);
+        const v8i ab = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7), cc = __builtin_shufflevector(c, c, 0, 1, 2, 3, -1, -1, -1, -1);
+        X[x] = __builtin_shufflevector(ab, cc, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11);
+    };
+
+    // ---- the accumulators' start: partial sums of the widening kernel's workgroups, all fetched at once (missing ones read as
+    // zero) and ahead of everything else, so that they cost no round trip of their own
+    const __amdgpu_buffer_rsrc_t sr = slab_desc(reinterpret_cast<const uint8_t *>(start), (int64_t)start_parts * rows * 4, true);
+    float sv[C::TM][CV_MAX_SPLIT];
+#pragma unroll
+    for (int x = 0; x < C::TM; ++x)
+#pragma unroll
+        for (int i = 0; i < CV_MAX_SPLIT; ++i)
+            sv[x][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, (i * rows + m0 + x * 32 + fi) * 4, 0, 0));
+
+    // ---- prologue: the loop's loads in the loop's order (iteration j issues the weights of tile j + DEPTH, then the fill of tile
+    // j + STAGES - 1), from an empty pipeline
+    const uint8_t *wp = wq, *xp = x6;              // next tile to load; they run past the end with empty descriptors
+    int w_left = ktiles, x_left = ktiles;
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int j = 1 - C::STAGES; j < 0; ++j) {
+        if (j + C::DEPTH >= 0) {
+            const __amdgpu_buffer_rsrc_t r = slab_desc(wp, w_slab, w_left-- > 0);
+            wp += w_slab;
+            v4i(&rl)[2][C::TN] = raw[j + C::DEPTH < 0 ? 0 : j + C::DEPTH];
+#pragma unroll
+            for (int t = 0; t < C::TN; ++t) rl[0][t] = load_w1(r, 0, t), rl[1][t] = load_w1(r, 1, t);
+        }
+        const __amdgpu_buffer_rsrc_t r = slab_desc(xp, x_slab, x_left-- > 0);
+        xp += x_slab;
+        uint8_t *const to = fill_base + (j + C::STAGES - 1) * C::STAGE_BYTES;
+        fill1(std::integral_constant<int, 0>(), r, to);
+        fill1(std::integral_constant<int, 1>(), r, to);
+        fill1(std::integral_constant<int, 2>(), r, to);
+        fill1(std::integral_constant<int, 3>(), r, to);
+        fill1(std::integral_constant<int, 4>(), r, to);
+        fill1(std::integral_constant<int, 5>(), r, to);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    v16f acc[C::TN][C::TM];
+#pragma unroll
+    for (int x = 0; x < C::TM; ++x) {
+        float v = sv[x][0];
+#pragma unroll
+        for (int i = 1; i < CV_MAX_SPLIT; ++i) v += sv[x][i];
+#pragma unroll
+        for (int t = 0; t < C::TN; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[t][x][r] = v;
+    }
+    __builtin_amdgcn_s_waitcnt(p_waitcnt_vm(C::FILLS * (C::STAGES - 2)));      // at least that many fills are younger than tile 0's
+    __builtin_amdgcn_s_barrier();
+    v8i W[2][2][C::TN];                            // widened weights of this K tile and of the next one: [tile][step][t]
+    auto widen_half = [&](const v4i (&r)[2][C::TN], v8i (&w)[2][C::TN], int h) {   // 16 of the 128 values a lane widens per K tile
+        const int s = h / 4, t = (h / 2) % 2, o = h % 2;
+        uint32_t f[3];
+        spread6<true>((uint32_t)r[s][t][2 * o], (uint32_t)r[s][t][2 * o + 1], f);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) w[s][t][3 * o + e] = (int)f[e];
+    };
+#pragma unroll
+    for (int x = 0; x < C::TM - 1; ++x) read_x(0, x);
+#pragma unroll
+    for (int h = 0; h < 8; ++h) widen_half(raw[0], W[0], h);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- K loop.  A K tile is eight groups of four MFMAs, group x on the tokens 32 x ..: two steps of 64 values times two runs of 32
+    // channels.  Beside group x run: an eighth of the next K tile's weights being widened (9 VALU), the fragment reads of the
+    // tokens that are done (three; X[x - 1] of the next K tile, in group 0 X[7] of this one, whose old value the previous
+    // tile's last group still used), and one or two of the ten loads of later tiles.
+    int off = 0;                                   // ring position of tile kt, in bytes
+    __builtin_amdgcn_s_setprio(2);
+    auto tile = [&](auto pc) {
+        constexpr int P = decltype(pc)::value;     // position in the unrolled loop: P % 2 names the W set, P % DEPTH the raw set
+        const int off_next = off + C::STAGE_BYTES == C::LDS_BYTES ? 0 : off + C::STAGE_BYTES;
+        const int off_prev = off == 0 ? C::LDS_BYTES - C::STAGE_BYTES : off - C::STAGE_BYTES;
+        // this wave's part of tile kt + 1 has landed (younger: whole iterations of loads); the barrier extends that to every
+        // wave's part, and says every wave has read all of tile kt - 1
+        __builtin_amdgcn_s_waitcnt(p_waitcnt_vm(C::LOADS * (C::STAGES - 3)));
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        const __amdgpu_buffer_rsrc_t wr = slab_desc(wp, w_slab, w_left > 0), xr = slab_desc(xp, x_slab, x_left > 0);
+        uint8_t *const fill_to = fill_base + off_prev;
+        v4i(&load_to)[2][C::TN] = raw[P % C::DEPTH];       // tile kt's, widened during the previous tile
+        const v4i(&next)[2][C::TN] = raw[(P + 1) % C::DEPTH];
+#pragma unroll
+        for (int x = 0; x < C::TM; ++x) {
+            asm("" : "+v"(X[x]));           // keeps the 48 bytes in one run of registers, of which both steps' operands are parts
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int t = 0; t < C::TN; ++t) {
+                    const v8i b = s == 0 ? __builtin_shufflevector(X[x], X[x], 0, 1, 2, 3, 4, 5, -1, -1)
+                                         : __builtin_shufflevector(X[x], X[x], 6, 7, 8, 9, 10, 11, -1, -1);
+                    acc[t][x] = mfma6(W[P % 2][s][t], b, acc[t][x]);
+                }
+            if (x == 0) read_x(off, C::TM - 1);
+            else read_x(off_next, x - 1);
+            widen_half(next, W[(P + 1) % 2], x);
+            if (x == 0) load_to[0][0] = load_w1(wr, 0, 0), load_to[1][0] = load_w1(wr, 1, 0);
+            if (x == 1) load_to[0][1] = load_w1(wr, 0, 1), load_to[1][1] = load_w1(wr, 1, 1);
+            if (x == 2) fill1(std::integral_constant<int, 0>(), xr, fill_to), fill1(std::integral_constant<int, 1>(), xr, fill_to);
+            if (x == 3) fill1(std::integral_constant<int, 2>(), xr, fill_to);
+            if (x == 4) fill1(std::integral_constant<int, 3>(), xr, fill_to);
+            if (x == 5) fill1(std::integral_constant<int, 4>(), xr, fill_to);
+            if (x == 6) fill1(std::integral_constant<int, 5>(), xr, fill_to);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if (i < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                if (i == 1 || i == 3) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        wp += w_slab, xp += x_slab;
+        --w_left, --x_left;
+        off = off_next;
+    };
+    // unrolled by six, so that the weights' two and three register sets rotate without copies
+    int left = ktiles;
+#define FPTQ_TILE(i) tile(std::integral_constant<int, i>())
+    for (; left >= 6; left -= 6) FPTQ_TILE(0), FPTQ_TILE(1), FPTQ_TILE(2), FPTQ_TILE(3), FPTQ_TILE(4), FPTQ_TILE(5);
+    if (left > 0) FPTQ_TILE(0);
+    if (left > 1) FPTQ_TILE(1);
+    if (left > 2) FPTQ_TILE(2);
+    if (left > 3) FPTQ_TILE(3);
+    if (left > 4) FPTQ_TILE(4);
+#undef FPTQ_TILE
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_s_waitcnt(p_waitcnt_vm(0));   // drain the tail loads before LDS is reused
+    __builtin_amdgcn_s_waitcnt(P_WAIT_LGKM0);
+    __builtin_amdgcn_s_barrier();
+
+    // ---- epilogue.  Weights were the A operand: a lane owns token fi of each 32 and, per register quad q, four consecutive
+    // channels 8 q + 4 fg + (r % 4).  The registers hold acc / 64; times 64 that is acc, exactly, and then
+    // y = bf16((float)(acc - z * wsum[n]) * (s_a * s_w[n]) [* d_t]) as in the other kernels (with a zero point the subtraction is
+    // exact too: both terms are integers and their difference is below 2^24 for K <= 131071).  Results go through a
+    // wave-private LDS patch ([32 tokens][64 channels], padded rows), so that HBM sees 16-byte-per-lane row segments; a wave's LDS
+    // operations complete in order, so only the compiler has to be kept from exchanging them.
+    constexpr int WN = C::TN * 32, PATCH_STRIDE = WN * 2 + 16, WAVE_LDS = 32 * PATCH_STRIDE + WN * 8;
+    static_assert(WN == 64 && 4 * WAVE_LDS <= C::LDS_BYTES, "a channel per lane; the patches reuse the ring");
+    uint8_t *patch = lds + wave * WAVE_LDS;
+    float *cwbuf = reinterpret_cast<float *>(patch + 32 * PATCH_STRIDE), *zwbuf = cwbuf + WN;
+    {
+        const int n = min(nw0 + lane, N - 1);
+        cwbuf[lane] = s_a * s_w[n];
+        if (ZP) zwbuf[lane] = (float)(zp * wsum[n]);
+    }
+    __builtin_amdgcn_s_waitcnt(P_WAIT_LGKM0);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int tm = 0; tm < C::TM; ++tm) {
+        const int mt0 = m0 + tm * 32;
+        const int m = mt0 + fi;
+        const float dm = (d && m < M) ? d[m] : 1.0f;
+#pragma unroll
+        for (int tn = 0; tn < C::TN; ++tn)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int c0 = tn * 32 + 8 * q + 4 * fg;
+                const float4 c4 = *reinterpret_cast<const float4 *>(cwbuf + c0);
+                const float4 z4 = ZP ? *reinterpret_cast<const float4 *>(zwbuf + c0) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                const float cw[4] = {c4.x, c4.y, c4.z, c4.w}, zw[4] = {z4.x, z4.y, z4.z, z4.w};
+                float yf[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float a = acc[tn][tm][4 * q + e];
+                    yf[e] = (ZP ? __builtin_fmaf(a, 64.0f, -zw[e]) : a * 64.0f) * cw[e];
+                    if (d) yf[e] = yf[e] * dm;
+                }
+                *reinterpret_cast<uint2 *>(patch + fi * PATCH_STRIDE + c0 * 2) = make_uint2(p_pack_bf16(yf[0], yf[1]), p_pack_bf16(yf[2], yf[3]));
+            }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int pass = 0; pass < 4; ++pass) {
+            const int row = pass * 8 + lane / 8, col = (lane % 8) * 8;
+            const uint4 v = *reinterpret_cast<const uint4 *>(patch + row * PATCH_STRIDE + col * 2);
+            const int mm = mt0 + row, nn = nw0 + col;
+            if (mm < M && nn < N) {
+                uint16_t *dst = y + (int64_t)mm * N + nn;
+                if (ALIGNED) {       // N % 8 == 0: the segment is whole and 16-byte aligned
+                    __builtin_nontemporal_store(v4i{(int)v.x, (int)v.y, (int)v.z, (int)v.w}, reinterpret_cast<v4i *>(dst));
+                } else {
+                    store_row_segment(dst, v, nn, N);
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (DUMP) {      // parity dump of the integer accumulators (never a timed path)
+#pragma unroll
+            for (int tn = 0; tn < C::TN; ++tn)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int n = nw0 + tn * 32 + 8 * q + 4 * fg + e;
+                        if (m < M && n < N) acc_out[(int64_t)m * N + n] = (int32_t)(acc[tn][tm][4 * q + e] * 64.0f);
+                    }
+        }
+    }
+}
+
+template <bool ALIGNED, bool DUMP, bool ZP>
+static hipError_t set_prefill_attribute()
+{
+    return hipFuncSetAttribute((const void *)linear_prefill_kernel<ALIGNED, DUMP, ZP>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               PrefillTile::LDS_BYTES);
+}
+
+hipError_t prefill_device_init()
+{
+    hipError_t e = hipSuccess;
+    auto one = [&](hipError_t r) { if (e == hipSuccess) e = r; };
+    one(set_prefill_attribute<true, true, false>()), one(set_prefill_attribute<true, false, false>());
+    one(set_prefill_attribute<false, true, false>()), one(set_prefill_attribute<false, false, false>());
+    one(set_prefill_attribute<true, true, true>()), one(set_prefill_attribute<true, false, true>());
+    one(set_prefill_attribute<false, true, true>()), one(set_prefill_attribute<false, false, true>());
+    return e;
+}
+
+// Workgroups per group of 32 rows in the widening kernel: about two per CU in all, each with a K tile per wave at least.
+static int widen_split(int64_t M, int64_t K, int cus)
+{
+    const int64_t groups = x6_rows(M) / CV_ROWS;
+    int64_t split = 2 * cus / groups;
+    if (split > k_tiles(K) / CV_WAVES) split = k_tiles(K) / CV_WAVES;
+    if (split > CV_MAX_SPLIT) split = CV_MAX_SPLIT;
+    return split < 1 ? 1 : (int)split;
+}
+
+// Scratch: the partial starts [CV_MAX_SPLIT][rows], then the six-bit activations.
+static int64_t start_bytes(int64_t M) { return (int64_t)CV_MAX_SPLIT * x6_rows(M) * 4; }
+int64_t prefill_scratch_bytes(int64_t M, int64_t K) { return start_bytes(M) + k_tiles(K) * x6_slab(M); }
+
+int64_t prefill_workgroups(int64_t M, int64_t N)
+{
+    return ((M + PrefillTile::BM - 1) / PrefillTile::BM) * ((N + PrefillTile::BN - 1) / PrefillTile::BN);
+}
+
+hipError_t launch_linear_prefill(const uint8_t *xq, const uint8_t *wq, int64_t M, int64_t N, int64_t K, float s_a, const float *s_w,
+                                 const float *d, int zp, const int32_t *wsum, uint16_t *y, int32_t *acc, uint8_t *scratch, hipStream_t s)
+{
+    const DeviceInfo *info;
+    hipError_t e = device_info(&info);
+    if (e != hipSuccess) return e;
+    const int64_t tiles_m = (M + PrefillTile::BM - 1) / PrefillTile::BM, tiles_n = (N + PrefillTile::BN - 1) / PrefillTile::BN;
+    if (tiles_m * tiles_n > 0x7fffffff) return hipErrorInvalidValue;
+    const int rows = (int)x6_rows(M), kt = (int)k_tiles(K), split = widen_split(M, K, info->cus);
+    float *start = reinterpret_cast<float *>(scratch);
+    uint8_t *x6 = scratch + start_bytes(M);
+    widen_activations_kernel<<<dim3((unsigned)(rows / CV_ROWS), (unsigned)split), dim3(64 * CV_WAVES), 0, s>>>(xq, (int)M, x6_slab(M), kt, x6,
+                                                                                                             start, rows);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+#define FPTQ_PREFILL(A, D, Z)                                                                                                        \
+    linear_prefill_kernel<A, D, Z><<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), PrefillTile::LDS_BYTES, s>>>(                    \
+        x6, x6_slab(M), start, split, rows, wq, (int)M, (int)N, kt, (int)tiles_m, (int)tiles_n, s_a, s_w, d, zp, wsum, y, acc)
+    const int inst = (N % 8 == 0 ? 4 : 0) | (acc ? 2 : 0) | (wsum ? 1 : 0);
+    switch (inst) {
+    case 0: FPTQ_PREFILL(false, false, false); break;
+    case 1: FPTQ_PREFILL(false, false, true); break;
+    case 2: FPTQ_PREFILL(false, true, false); break;
+    case 3: FPTQ_PREFILL(false, true, true); break;
+    case 4: FPTQ_PREFILL(true, false, false); break;
+    case 5: FPTQ_PREFILL(true, false, true); break;
+    case 6: FPTQ_PREFILL(true, true, false); break;
+    default: FPTQ_PREFILL(true, true, true);
+    }
+#undef FPTQ_PREFILL
+    return hipGetLastError();
+}
+
+}  // namespace fptq

@@ -1,0 +1,104 @@
+"""The six-bit kernel of large problems, forced on shapes at the edges of its tiles: bit for bit the oracle's result, or that of
+the library's other kernels where the oracle would take too long."""
+import pytest
+import torch
+
+from paper_2506_04985_amd import binding as fptq
+import fptq_workloads as synth
+
+from gpu_util import dev, dev_bf16, host_bits
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def forced():
+    fptq.fptq_set_linear_prefill(1)
+    yield
+    fptq.fptq_set_linear_prefill(0)
+
+
+def scratch_for(M, N, K):
+    n = fptq.fptq_linear_scratch_bytes(M, N, K)
+    assert n > 0
+    return torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")        # nothing in it may matter
+
+
+# one to thirteen K tiles (the loop is unrolled by six and keeps five in flight), tokens and channels around the 256 x 256 tile,
+# widths the 16-byte stores do not divide, K that no tile divides
+@pytest.mark.parametrize("M,N,K", [(65, 1, 1), (100, 8, 128), (255, 255, 129), (256, 256, 384), (257, 257, 500), (129, 300, 640), (66, 70, 768),
+                                   (300, 520, 896), (513, 64, 1030), (90, 776, 1537)])
+def test_matches_oracle(forced, oracle, M, N, K):
+    case = synth.LinearCase("p6", f"m{M}", M, N, K, "normal", 0.0, 1, 4.0, synth.MODE_RMS, M + N + K)
+    inp = synth.draw(case)
+    ref = oracle.w4a4_linear(inp.x_bits, inp.w_int, inp.s_a, inp.s_w, synth.MODE_RMS, case.eps)
+    xq, _ = fptq.fptq_quantize_act(dev_bf16(inp.x_bits), float(inp.s_a), synth.MODE_RMS, case.eps)
+    wq = fptq.fptq_pack_weights(dev(inp.w_int))
+    y, acc = fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, float(inp.s_a), dev(inp.s_w), scratch_for(M, N, K), want_acc=True)
+    assert (acc.cpu().numpy() == ref["acc"]).all()
+    assert (host_bits(y) == ref["y"]).all()
+    y = fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, float(inp.s_a), dev(inp.s_w), scratch_for(M, N, K))
+    assert (host_bits(y) == ref["y"]).all()
+
+
+@pytest.mark.parametrize("M,N,K,zp", [(300, 520, 2504, 0), (1000, 1032, 1280, 0), (333, 771, 4096, -8), (260, 264, 904, 7)])
+def test_equals_the_int8_kernel(forced, M, N, K, zp):
+    torch.manual_seed(M + K)
+    xq = fptq.fptq_pack_weights(torch.randint(-8, 8, (M, K), dtype=torch.int8, device="cuda"))
+    w = torch.randint(-8, 8, (N, K), dtype=torch.int8, device="cuda")
+    wq, ws = fptq.fptq_pack_weights(w), fptq.fptq_weight_row_sums(w)
+    s_w, d = torch.rand(N, device="cuda") * 0.015 + 0.005, torch.rand(M, device="cuda") + 0.5
+    got = fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, 0.37, s_w, scratch_for(M, N, K), zp, ws, d, want_acc=True)
+    fptq.fptq_set_linear_prefill(2)
+    want = fptq.fptq_w4a4_linear_zp(xq, wq, M, N, K, 0.37, s_w, zp, ws, d, want_acc=True)
+    assert torch.equal(got[1], want[1]) and torch.equal(got[0].view(torch.int16), want[0].view(torch.int16))
+
+
+@pytest.mark.parametrize("K", [131071, 131070])
+@pytest.mark.parametrize("x,w", [(-8, -8), (7, -8), (-8, 7), (7, 7)])
+def test_longest_sums_of_the_largest_products(forced, K, x, w):
+    """|64 K| is just below 2^23 and the running sums stay below 2^24, where fp32 still counts by ones; a few products of
+    one in an otherwise constant row must show."""
+    M, N = 70, 40
+    xi = torch.full((M, K), x, dtype=torch.int8, device="cuda")
+    wi = torch.full((N, K), w, dtype=torch.int8, device="cuda")
+    xi[torch.arange(M), torch.arange(M) * 1801] = 1
+    wi[torch.arange(N), K - 1 - torch.arange(N) * 3203] = -1
+    xq, wq = fptq.fptq_pack_weights(xi), fptq.fptq_pack_weights(wi)
+    s_w = torch.ones(N, device="cuda")
+    _, acc = fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, 1.0, s_w, scratch_for(M, N, K), want_acc=True)
+    _, ref = fptq.fptq_w4a4_linear_ref(xq, wq, M, N, K, 1.0, s_w, want_acc=True)
+    assert torch.equal(acc, ref)
+
+
+def test_random_rows_of_the_longest_sums(forced):
+    M, N, K = 66, 264, 131071
+    torch.manual_seed(4)
+    for lo, hi in ((-8, 8), (-8, -4), (4, 8), (-1, 2)):
+        xq = fptq.fptq_pack_weights(torch.randint(lo, hi, (M, K), dtype=torch.int8, device="cuda"))
+        wq = fptq.fptq_pack_weights(torch.randint(-8, 8, (N, K), dtype=torch.int8, device="cuda").sort(dim=1).values)
+        s_w = torch.ones(N, device="cuda")
+        _, acc = fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, 1.0, s_w, scratch_for(M, N, K), want_acc=True)
+        _, ref = fptq.fptq_w4a4_linear_ref(xq, wq, M, N, K, 1.0, s_w, want_acc=True)
+        assert torch.equal(acc, ref)
+
+
+def test_too_little_scratch_or_none_gives_the_plain_layer():
+    M, N, K = 4096, 8192, 4096
+    need = fptq.fptq_linear_scratch_bytes(M, N, K)
+    assert need > 0 and fptq.fptq_linear_launch_plan(M, N, K, with_scratch=True)[0] == "linear_prefill_kernel"
+    assert fptq.fptq_linear_scratch_bytes(8, N, K) == 0
+    torch.manual_seed(2)
+    xq = torch.randint(0, 256, (fptq.fptq_packed_bytes(M, K),), dtype=torch.uint8, device="cuda")
+    wq = torch.randint(0, 256, (fptq.fptq_packed_bytes(N, K),), dtype=torch.uint8, device="cuda")
+    s_w = torch.rand(N, device="cuda") * 0.015 + 0.005
+    want = fptq.fptq_w4a4_linear_noalloc(xq, wq, M, N, K, 0.5, s_w)
+    small = torch.zeros(need - 256, dtype=torch.uint8, device="cuda")
+    for scratch in (None, small, torch.empty(need, dtype=torch.uint8, device="cuda")):
+        got = fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, 0.5, s_w, scratch)
+        assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    assert int(small.max()) == 0
+    got = fptq.fptq_w4a4_linear(xq, wq, M, N, K, 0.5, s_w)
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    with pytest.raises(fptq.FptqError):
+        fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, 0.5, s_w, torch.empty(need + 64, dtype=torch.uint8, device="cuda")[64:])
