@@ -30,8 +30,8 @@ __device__ inline uint32_t pack8(uint32_t lo, uint32_t hi)
 }
 
 // Bound by HBM: a byte read and half a byte written per value.  A thread makes the 16-byte granules (32 values) at one place of
-// PACK_TILES K tiles in a row: a wave reads PACK_TILES x 128 contiguous bytes of 16 rows and writes 1 KB runs.  28672 x 4096: 38 us
-// (4.6 TB/s); a byte per load, one granule per thread, took 221.
+// PACK_TILES K tiles in a row: a wave reads PACK_TILES x 128 contiguous bytes of 16 rows and writes 1 KB runs.  28672 x 4096: 40 us
+// (4.4 TB/s); a byte per load, one granule per thread, took 221.  Half granules (8 lanes a row) and eight tiles per thread: the same.
 constexpr int PACK_TILES = 4;
 
 __global__ __launch_bounds__(256) void pack_weights_kernel(const int8_t *__restrict__ w, int64_t N, int64_t K, int64_t row_blocks,
@@ -112,7 +112,8 @@ hipError_t launch_unpack(const uint8_t *packed, int64_t rows, int64_t K, int8_t 
 }
 
 // sum_k w[o][k] per output channel (what an activation zero point multiplies); one wave per row, four 16-byte loads in flight
-// per lane.  28672 x 4096: 24 us (4.9 TB/s); a byte per load took 83.
+// per lane.  28672 x 4096: 17 us behind the packer, which leaves part of the matrix in the last-level cache; a byte per
+// load took 83.
 __global__ __launch_bounds__(256) void weight_row_sums_kernel(const int8_t *__restrict__ w, int64_t N, int64_t K,
                                                               int32_t *__restrict__ sums)
 {
