@@ -1,5 +1,5 @@
-"""ctypes view of the fptq C-ABI library (include/fptq.h).  Argument marshalling only: every
-step of the layer runs in the library's HIP kernels.  PyTorch supplies device memory and the
+"""ctypes view of the fptq C-ABI library (include/fptq.h), with a native fast path for plain calls (csrc/fptq_native.cpp).
+Argument marshalling only: every step of the layer runs in the library's HIP kernels.  PyTorch supplies device memory and the
 current stream, nothing else.  Without the built library (csrc/libfptq.so) importing works but
 every call raises -- there is no CPU fallback.
 """
@@ -25,6 +25,7 @@ TESTING_EXPORTS = ["fptq_set_gemm_tile", "fptq_set_gemm_map", "fptq_set_decode_s
                    "fptq_linear_launch_plan"]
 
 _lib = None
+_native = None      # the native fast path (csrc/fptq_native.cpp), loaded with the library: a call returns None where it leaves the call to Python
 
 
 class FptqError(RuntimeError):
@@ -35,7 +36,7 @@ class FptqError(RuntimeError):
 
 def lib():
     """Load csrc/libfptq.so (build it first with paper_2506_04985_amd.build.build())."""
-    global _lib
+    global _lib, _native
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"{LIB_PATH} is missing: run `python -m paper_2506_04985_amd.build` "
@@ -86,7 +87,8 @@ def lib():
         L.fptq_linear_scratch_bytes.argtypes = [i64, i64, i64]
         L.fptq_w4a4_linear_scratch.restype = i32
         L.fptq_w4a4_linear_scratch.argtypes = [p, p, i64, i64, i64, f32, p, p, i32, p, p, p, p, i64, p]
-        _lib = L
+        from . import _native as native      # built next to this file, with the library
+        _lib, _native = L, native
     return _lib
 
 
@@ -132,6 +134,9 @@ def _need(rows, K):
 
 def fptq_pack_weights(w_int, out=None):
     """int8 [N, K] device tensor with values in [-8, 7] -> packed uint8 blob."""
+    done = None if _native is None else _native.pack_weights(w_int, out)
+    if done is not None:
+        return done
     _dev(w_int, torch.int8, "w_int")
     N, K = w_int.shape
     nbytes = fptq_packed_bytes(N, K)
@@ -143,6 +148,9 @@ def fptq_pack_weights(w_int, out=None):
 def fptq_quantize_act(x_bf16, s_a, scale_mode=SCALE_RMS, eps=0.0, row_scale_in=None, out=None, row_scale_out=None,
                       want_row_scale=True):
     """bf16 [M, K] -> (packed uint8 blob, fp32 [M] per-token scale or None)."""
+    done = None if _native is None else _native.quantize_act(x_bf16, s_a, scale_mode, eps, row_scale_in, out, row_scale_out, want_row_scale, None, None)
+    if done is not None:
+        return done
     _dev(x_bf16, torch.bfloat16, "x_bf16")
     M, K = x_bf16.shape
     if row_scale_in is not None:
@@ -158,6 +166,10 @@ def fptq_quantize_act(x_bf16, s_a, scale_mode=SCALE_RMS, eps=0.0, row_scale_in=N
 def fptq_quantize_act_hadamard(x_bf16, s_a, hadamard_block=256, scale_mode=SCALE_GIVEN, eps=0.0, row_scale_in=None, out=None,
                                row_scale_out=None, want_row_scale=True):
     """bf16 [M, K] -> block-wise Hadamard, per-token scale, static INT4 quantizer, packed."""
+    done = None if _native is None else _native.quantize_act(x_bf16, s_a, scale_mode, eps, row_scale_in, out, row_scale_out, want_row_scale,
+                                                                 hadamard_block, None)
+    if done is not None:
+        return done
     _dev(x_bf16, torch.bfloat16, "x_bf16")
     M, K = x_bf16.shape
     if row_scale_in is not None:
@@ -173,6 +185,9 @@ def fptq_quantize_act_hadamard(x_bf16, s_a, hadamard_block=256, scale_mode=SCALE
 
 def fptq_quantize_act_asym(x_bf16, s_a, zero_point, scale_mode=SCALE_NONE, eps=0.0, row_scale_in=None, out=None):
     """bf16 [M, K] -> packed codes of the asymmetric grid v = clamp(rne(x S / s_a) + z, -8, 7)."""
+    done = None if _native is None else _native.quantize_act(x_bf16, s_a, scale_mode, eps, row_scale_in, out, None, True, None, zero_point)
+    if done is not None:
+        return done
     _dev(x_bf16, torch.bfloat16, "x_bf16")
     M, K = x_bf16.shape
     if row_scale_in is not None:
@@ -185,6 +200,9 @@ def fptq_quantize_act_asym(x_bf16, s_a, zero_point, scale_mode=SCALE_NONE, eps=0
 
 
 def fptq_weight_row_sums(w_int):
+    done = None if _native is None else _native.weight_row_sums(w_int)
+    if done is not None:
+        return done
     _dev(w_int, torch.int8, "w_int")
     N, K = w_int.shape
     out = torch.empty(N, dtype=torch.int32, device=w_int.device)
@@ -193,6 +211,9 @@ def fptq_weight_row_sums(w_int):
 
 
 def fptq_w4a4_linear_zp(xq, wq, M, N, K, s_a, s_w, zero_point, w_row_sum, row_out_scale=None, out=None, want_acc=False):
+    done = None if _native is None else _native.linear(xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, None, zero_point, w_row_sum, None, 0)
+    if done is not None:
+        return done
     _dev(w_row_sum, torch.int32, "w_row_sum")
     scratch = _scratch(M, N, K, xq)
     if scratch is not None:
@@ -205,6 +226,9 @@ def fptq_w4a4_linear_zp(xq, wq, M, N, K, s_a, s_w, zero_point, w_row_sum, row_ou
 
 def fptq_residual_norm_quantize(x_res, y_blk, s_a, s_prev=None, eps=0.0, x_next=None, s_next=None, out=None):
     """Residual add + norm + S_n update + quantizer in one pass: returns (X~_n bf16, S_n fp32 [M], packed uint8)."""
+    done = None if _native is None else _native.residual_norm_quantize(x_res, y_blk, s_a, s_prev, eps, x_next, s_next, out)
+    if done is not None:
+        return done
     _dev(x_res, torch.bfloat16, "x_res")
     _dev(y_blk, torch.bfloat16, "y_blk")
     M, K = x_res.shape
@@ -220,6 +244,9 @@ def fptq_residual_norm_quantize(x_res, y_blk, s_a, s_prev=None, eps=0.0, x_next=
 
 def fptq_quantize_act_dynamic(x_bf16, out=None, token_scale_out=None):
     """bf16 [M, K] -> (packed uint8 blob, fp32 [M] per-token scales s_t computed at run time)."""
+    done = None if _native is None else _native.quantize_act_dynamic(x_bf16, out, token_scale_out)
+    if done is not None:
+        return done
     _dev(x_bf16, torch.bfloat16, "x_bf16")
     M, K = x_bf16.shape
     out = torch.empty(_need(M, K), dtype=torch.uint8, device=x_bf16.device) if out is None else out
@@ -284,6 +311,9 @@ def fptq_w4a4_linear_scratch(xq, wq, M, N, K, s_a, s_w, scratch, zero_point=0, w
 
 def fptq_w4a4_linear(xq, wq, M, N, K, s_a, s_w, row_out_scale=None, out=None, want_acc=False, acc=None):
     """Packed activations x packed weights -> bf16 [M, N] (and the int32 accumulators if asked)."""
+    done = None if _native is None else _native.linear(xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc, None, None, None, 0)
+    if done is not None:
+        return done
     scratch = _scratch(M, N, K, xq)
     fn = lib().fptq_w4a4_linear if scratch is None else _scratch_call(scratch, 0, None)
     return _linear(fn, xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc)
@@ -304,6 +334,10 @@ def fptq_w4a4_linear_ws(xq, wq, M, N, K, s_a, s_w, workspace, row_out_scale=None
     # no split over K: the plain layer (a misaligned workspace is still refused, below)
     if M > 64 and (workspace is None or workspace.data_ptr() % 256 == 0) and lib().fptq_linear_workspace_bytes(M, N, K) == 0:
         return fptq_w4a4_linear(xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc)
+    if workspace is not None:
+        done = None if _native is None else _native.linear(xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc, None, None, workspace, 1)
+        if done is not None:
+            return done
     fn = lambda a, b, m, n, k, sa, sw, d, y, ac, st: lib().fptq_w4a4_linear_ws(
         a, b, m, n, k, sa, sw, d, y, ac, _ptr(workspace), 0 if workspace is None else workspace.numel(), st)
     return _linear(fn, xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc)
@@ -312,6 +346,9 @@ def fptq_w4a4_linear_ws(xq, wq, M, N, K, s_a, s_w, workspace, row_out_scale=None
 def fptq_w4a4_linear_noalloc(xq, wq, M, N, K, s_a, s_w, row_out_scale=None, out=None, want_acc=False, acc=None):
     """fptq_w4a4_linear_ws on the library's built-in scratch area.  The library allocates nothing; pass `out` (and `acc`)
     to keep this wrapper from allocating the result tensors."""
+    done = None if _native is None else _native.linear(xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc, None, None, None, 2)
+    if done is not None:
+        return done
     return _linear(lib().fptq_w4a4_linear_noalloc, xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc)
 
 

@@ -1,7 +1,8 @@
-"""Compile the HIP sources under csrc/ for gfx950 into csrc/libfptq.so, and the measurement aids into
-csrc/libfptq_probe.so (in-tree, so that the built libraries travel with the source tree)."""
+"""Compile the HIP sources under csrc/ for gfx950 into csrc/libfptq.so, the measurement aids into csrc/libfptq_probe.so and
+the Python binding's native fast path into _native.so (in-tree, so that the built libraries travel with the source tree)."""
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -11,6 +12,7 @@ LIB = os.path.join(CSRC, "libfptq.so")
 PROBE_LIB = os.path.join(CSRC, "libfptq_probe.so")
 SOURCES = ["fptq_api.hip", "fptq_pack.hip", "fptq_quant.hip", "fptq_gemm.hip", "fptq_prefill.hip", "fptq_gemv.hip", "fptq_hadamard.hip", "fptq_residual.hip"]
 PROBE_SOURCES = ["fptq_probe.hip"]
+NATIVE_SOURCE, NATIVE = "fptq_native.cpp", os.path.join(HERE, "_native.so")      # the binding's fast path: host code, torch's C++ API
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
@@ -28,8 +30,25 @@ def _compile(src):
     return obj, out
 
 
+def _native_command(obj):
+    import torch
+    from torch.utils import cpp_extension
+    inc = [f for d in [INCLUDE, *cpp_extension.include_paths(), sysconfig.get_paths()["include"]] for f in ("-I", d)]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-w", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc,
+            "-c", os.path.join(CSRC, NATIVE_SOURCE), "-o", obj]
+
+
+def _link_native(obj):
+    from torch.utils import cpp_extension
+    dirs = [f"-L{d}" for d in cpp_extension.library_paths()]
+    subprocess.check_call(["g++", "-shared", obj, "-o", NATIVE, *dirs, "-ltorch_python", "-ltorch_cpu", "-lc10", f"-L{CSRC}", "-l:libfptq.so",
+                           "-Wl,-rpath,$ORIGIN/csrc"])
+
+
 def build(verbose: bool = False) -> str:
-    with ThreadPoolExecutor(max_workers=len(SOURCES) + len(PROBE_SOURCES)) as ex:
+    native_obj = os.path.join(CSRC, "fptq_native.o")
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + len(PROBE_SOURCES) + 1) as ex:
+        native = ex.submit(subprocess.run, _native_command(native_obj), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         results = list(ex.map(_compile, SOURCES + PROBE_SOURCES))
     if verbose:
         for _, out in results:
@@ -38,6 +57,9 @@ def build(verbose: bool = False) -> str:
     objs = [o for o, _ in results]
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs[:len(SOURCES)], "-o", LIB])
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *objs[len(SOURCES):], "-o", PROBE_LIB])
+    if native.result().returncode:
+        raise RuntimeError(f"g++ failed on {NATIVE_SOURCE}:\n{native.result().stdout}")
+    _link_native(native_obj)
     return LIB
 
 

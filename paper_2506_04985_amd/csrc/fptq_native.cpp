@@ -1,0 +1,316 @@
+// The fast path of the Python binding: argument checks, output allocation and the library call in one native call.
+//
+// What a Python wrapper with ctypes spends before the launch (about 7 us of 10.5 a call: torch.empty from Python 1.7 us each, the
+// current stream's object 2.7, pointer objects and argument conversion the rest) is longer than the kernels of a token step
+// run.  Every function here takes exactly the arguments of its wrapper in binding.py, positionally, and returns what the
+// wrapper returns -- or None whenever anything is not the plain case (an argument of another type, a tensor that is not
+// contiguous or not on the device, a buffer too small, an error of the library): then the wrapper goes on in Python, which
+// raises what there is to raise.  A failing library call launches nothing, so it can be repeated.  Nothing is kept between calls.
+#include <torch/extension.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include "fptq.h"
+
+namespace {
+
+// torch._C functions: the device, the raw handle of its current stream, and whether that stream is being captured
+PyObject *g_device = nullptr, *g_stream = nullptr, *g_capturing = nullptr;
+
+struct Slow {};        // thrown where the call is left to the Python wrapper
+
+int64_t need(int64_t rows, int64_t K) { return (K + 127) / 128 * rows * 64; }
+
+const at::Tensor &device_tensor(PyObject *o)
+{
+    if (!THPVariable_CheckExact(o)) throw Slow();
+    const at::Tensor &t = THPVariable_Unpack(o);
+    if (!t.is_cuda()) throw Slow();
+    return t;
+}
+
+const at::Tensor &input(PyObject *o, at::ScalarType type)
+{
+    const at::Tensor &t = device_tensor(o);
+    if (t.scalar_type() != type || !t.is_contiguous()) throw Slow();
+    return t;
+}
+
+void *input_or_null(PyObject *o, at::ScalarType type) { return o == Py_None ? nullptr : input(o, type).data_ptr(); }
+
+int64_t integer(PyObject *o)
+{
+    if (!PyLong_CheckExact(o)) throw Slow();
+    const long long v = PyLong_AsLongLong(o);
+    if (v == -1 && PyErr_Occurred()) throw Slow();
+    return v;
+}
+
+float number(PyObject *o)
+{
+    if (PyFloat_CheckExact(o)) return (float)PyFloat_AS_DOUBLE(o);
+    if (PyLong_CheckExact(o)) {
+        const double v = PyLong_AsDouble(o);
+        if (v == -1.0 && PyErr_Occurred()) throw Slow();
+        return (float)v;
+    }
+    throw Slow();
+}
+
+bool truth(PyObject *o)
+{
+    if (o == Py_True) return true;
+    if (o == Py_False) return false;
+    throw Slow();
+}
+
+// an output: the caller's tensor, or a new one; `object` is a new reference to what the wrapper returns
+struct Output {
+    PyObject *object = nullptr;
+    void *ptr = nullptr;
+    int64_t numel = 0;
+    Output() = default;
+    Output(PyObject *given, at::IntArrayRef shape, at::ScalarType type, const at::Tensor &like)
+    {
+        if (given != Py_None) {
+            const at::Tensor &t = device_tensor(given);
+            ptr = t.data_ptr(), numel = t.numel();
+            Py_INCREF(given);
+            object = given;
+            return;
+        }
+        at::Tensor t = at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
+        ptr = t.data_ptr(), numel = t.numel();
+        object = THPVariable_Wrap(std::move(t));
+        if (!object) throw Slow();
+    }
+    Output(Output &&o) : object(o.object), ptr(o.ptr), numel(o.numel) { o.object = nullptr; }
+    Output &operator=(Output &&o)
+    {
+        std::swap(object, o.object), std::swap(ptr, o.ptr), std::swap(numel, o.numel);
+        return *this;
+    }
+    ~Output() { Py_XDECREF(object); }
+    PyObject *take()
+    {
+        PyObject *o = object;
+        object = nullptr;
+        return o;
+    }
+};
+
+PyObject *pair(Output &a, Output &b)
+{
+    PyObject *t = PyTuple_New(2);
+    if (!t) throw Slow();
+    PyTuple_SET_ITEM(t, 0, a.take());
+    if (b.object) {
+        PyTuple_SET_ITEM(t, 1, b.take());
+    } else {
+        Py_INCREF(Py_None);
+        PyTuple_SET_ITEM(t, 1, Py_None);
+    }
+    return t;
+}
+
+PyObject *device()
+{
+    PyObject *d = PyObject_CallNoArgs(g_device);
+    if (!d) throw Slow();
+    return d;
+}
+
+void *stream()
+{
+    PyObject *d = device();
+    PyObject *s = PyObject_CallOneArg(g_stream, d);
+    Py_DECREF(d);
+    if (!s) throw Slow();
+    void *p = PyLong_AsVoidPtr(s);
+    Py_DECREF(s);
+    if (!p && PyErr_Occurred()) throw Slow();
+    return p;
+}
+
+bool capturing()
+{
+    PyObject *c = PyObject_CallNoArgs(g_capturing);
+    if (!c) throw Slow();
+    const int yes = PyObject_IsTrue(c);
+    Py_DECREF(c);
+    if (yes < 0) throw Slow();
+    return yes;
+}
+
+void done(int rc)
+{
+    if (rc != FPTQ_OK) throw Slow();
+}
+
+// runs f(args), leaving the call to Python where it throws
+template <class F>
+PyObject *guarded(Py_ssize_t got, Py_ssize_t want, F f)
+{
+    try {
+        if (got != want) throw Slow();
+        return f();
+    } catch (...) {
+        PyErr_Clear();
+    }
+    Py_RETURN_NONE;
+}
+
+void matrix(const at::Tensor &x, int64_t &M, int64_t &K)
+{
+    if (x.dim() != 2) throw Slow();
+    M = x.size(0), K = x.size(1);
+    if (M < 1 || K < 1) throw Slow();
+}
+
+// (w_int, out)
+PyObject *pack_weights(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    return guarded(n, 2, [&]() -> PyObject * {
+        const at::Tensor &w = input(a[0], at::kChar);
+        int64_t N, K;
+        matrix(w, N, K);
+        Output out(a[1], {need(N, K)}, at::kByte, w);
+        done(fptq_pack_weights((const int8_t *)w.data_ptr(), N, K, out.ptr, out.numel, stream()));
+        return out.take();
+    });
+}
+
+// (w_int)
+PyObject *weight_row_sums(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    return guarded(n, 1, [&]() -> PyObject * {
+        const at::Tensor &w = input(a[0], at::kChar);
+        int64_t N, K;
+        matrix(w, N, K);
+        Output out(Py_None, {N}, at::kInt, w);
+        done(fptq_weight_row_sums((const int8_t *)w.data_ptr(), N, K, (int32_t *)out.ptr, stream()));
+        return out.take();
+    });
+}
+
+// (x, s_a, scale_mode, eps, row_scale_in, out, row_scale_out, want_row_scale, hadamard_block, zero_point): hadamard_block None for
+// the plain quantizer, zero_point None for the symmetric grid
+PyObject *quantize_act(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    return guarded(n, 10, [&]() -> PyObject * {
+        const at::Tensor &x = input(a[0], at::kBFloat16);
+        int64_t M, K;
+        matrix(x, M, K);
+        const float s_a = number(a[1]), eps = number(a[3]);
+        const int mode = (int)integer(a[2]);
+        const float *r_in = (const float *)input_or_null(a[4], at::kFloat);
+        Output out(a[5], {need(M, K)}, at::kByte, x), r;
+        if (a[6] != Py_None || truth(a[7])) r = Output(a[6], {M}, at::kFloat, x);
+        if (a[8] != Py_None)
+            done(fptq_quantize_act_hadamard(x.data_ptr(), M, K, (int)integer(a[8]), mode, eps, r_in, s_a, out.ptr, out.numel, (float *)r.ptr, stream()));
+        else if (a[9] != Py_None)
+            done(fptq_quantize_act_asym(x.data_ptr(), M, K, mode, eps, r_in, s_a, (int)integer(a[9]), out.ptr, out.numel, (float *)r.ptr, stream()));
+        else
+            done(fptq_quantize_act(x.data_ptr(), M, K, mode, eps, r_in, s_a, out.ptr, out.numel, (float *)r.ptr, stream()));
+        return pair(out, r);
+    });
+}
+
+// (x, out, token_scale_out)
+PyObject *quantize_act_dynamic(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    return guarded(n, 3, [&]() -> PyObject * {
+        const at::Tensor &x = input(a[0], at::kBFloat16);
+        int64_t M, K;
+        matrix(x, M, K);
+        Output out(a[1], {need(M, K)}, at::kByte, x), s(a[2], {M}, at::kFloat, x);
+        done(fptq_quantize_act_dynamic(x.data_ptr(), M, K, out.ptr, out.numel, (float *)s.ptr, stream()));
+        return pair(out, s);
+    });
+}
+
+// (x_res, y_blk, s_a, s_prev, eps, x_next, s_next, out)
+PyObject *residual_norm_quantize(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    return guarded(n, 8, [&]() -> PyObject * {
+        const at::Tensor &x = input(a[0], at::kBFloat16), &y = input(a[1], at::kBFloat16);
+        int64_t M, K;
+        matrix(x, M, K);
+        const float s_a = number(a[2]), eps = number(a[4]);
+        const float *s_prev = (const float *)input_or_null(a[3], at::kFloat);
+        Output x_next(a[5], {M, K}, at::kBFloat16, x), s_next(a[6], {M}, at::kFloat, x), out(a[7], {need(M, K)}, at::kByte, x);
+        done(fptq_residual_norm_quantize(x.data_ptr(), y.data_ptr(), M, K, s_prev, eps, s_a, x_next.ptr, (float *)s_next.ptr, out.ptr, out.numel,
+                                         stream()));
+        PyObject *t = PyTuple_New(3);
+        if (!t) throw Slow();
+        PyTuple_SET_ITEM(t, 0, x_next.take());
+        PyTuple_SET_ITEM(t, 1, s_next.take());
+        PyTuple_SET_ITEM(t, 2, out.take());
+        return t;
+    });
+}
+
+// (xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc, zero_point, w_row_sum, workspace, kind): kind 0 the plain linear
+// (zero_point None) or the one with a zero point, with scratch where it pays; 1 with a workspace; 2 the one that allocates nothing
+PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    return guarded(n, 15, [&]() -> PyObject * {
+        const at::Tensor &xq = input(a[0], at::kByte), &wq = input(a[1], at::kByte), &s_w = input(a[6], at::kFloat);
+        const int64_t M = integer(a[2]), N = integer(a[3]), K = integer(a[4]);
+        if (M < 1 || N < 1 || K < 1 || M > (1ll << 40) / K || N > (1ll << 40) / K || M > (1ll << 40) / N) throw Slow();
+        if (xq.numel() < need(M, K) || wq.numel() < need(N, K) || s_w.numel() < N) throw Slow();
+        const float s_a = number(a[5]);
+        const float *d = (const float *)input_or_null(a[7], at::kFloat);
+        const bool want_acc = truth(a[9]);
+        const int64_t kind = integer(a[14]);
+        if (a[11] != Py_None && a[12] == Py_None) throw Slow();
+        const int zp = a[11] == Py_None ? 0 : (int)integer(a[11]);
+        const int32_t *wsum = (const int32_t *)input_or_null(a[12], at::kInt);
+        Output y(a[8], {M, N}, at::kBFloat16, xq), acc;
+        if (want_acc || a[10] != Py_None) acc = Output(a[10], {M, N}, at::kInt, xq);
+        at::Tensor scratch;
+        int64_t scratch_bytes = 0;
+        if (kind == 0 && M > 64 && (scratch_bytes = fptq_linear_scratch_bytes(M, N, K)) > 0) {
+            scratch_bytes = capturing() ? 0 : scratch_bytes;
+            if (scratch_bytes > 0) {
+                try {
+                    scratch = at::empty({scratch_bytes}, at::TensorOptions().dtype(at::kByte).device(xq.device()));
+                } catch (const c10::OutOfMemoryError &) {
+                    scratch_bytes = 0;
+                }
+            }
+        }
+        const void *px = xq.data_ptr(), *pw = wq.data_ptr();
+        const float *ps = (const float *)s_w.data_ptr();
+        if (scratch_bytes > 0)
+            done(fptq_w4a4_linear_scratch(px, pw, M, N, K, s_a, ps, d, zp, wsum, y.ptr, (int32_t *)acc.ptr, scratch.data_ptr(), scratch_bytes, stream()));
+        else if (kind == 2)
+            done(fptq_w4a4_linear_noalloc(px, pw, M, N, K, s_a, ps, d, y.ptr, (int32_t *)acc.ptr, stream()));
+        else if (kind == 1) {
+            const at::Tensor &ws = input(a[13], at::kByte);
+            done(fptq_w4a4_linear_ws(px, pw, M, N, K, s_a, ps, d, y.ptr, (int32_t *)acc.ptr, ws.data_ptr(), ws.numel(), stream()));
+        } else if (a[11] != Py_None)
+            done(fptq_w4a4_linear_zp(px, pw, M, N, K, s_a, ps, d, zp, wsum, y.ptr, (int32_t *)acc.ptr, stream()));
+        else
+            done(fptq_w4a4_linear(px, pw, M, N, K, s_a, ps, d, y.ptr, (int32_t *)acc.ptr, stream()));
+        return acc.object ? pair(y, acc) : y.take();
+    });
+}
+
+#define FPTQ_FAST(f) {#f, (PyCFunction)(void (*)(void))f, METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {FPTQ_FAST(pack_weights), FPTQ_FAST(weight_row_sums), FPTQ_FAST(quantize_act), FPTQ_FAST(quantize_act_dynamic),
+                         FPTQ_FAST(residual_norm_quantize), FPTQ_FAST(linear), {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+extern "C" PyObject *PyInit__native()
+{
+    PyObject *c = PyImport_ImportModule("torch._C");
+    if (!c) return nullptr;
+    g_device = PyObject_GetAttrString(c, "_cuda_getDevice");
+    g_stream = PyObject_GetAttrString(c, "_cuda_getCurrentRawStream");
+    g_capturing = PyObject_GetAttrString(c, "_cuda_isCurrentStreamCapturing");
+    Py_DECREF(c);
+    if (!g_device || !g_stream || !g_capturing) return nullptr;
+    return PyModule_Create(&module);
+}
