@@ -144,9 +144,10 @@ static int linear_common(const char *fn, linear_fn force, const void *xq, const 
     }
     linear_fn f = force ? force : (few_token_shape(M, N) && forced_gemm_tile() == 0 ? launch_linear_decode : launch_linear_mfma);
     hipError_t e;
-    if (f == launch_linear_mfma && scratch && prefill_pays(M, N, K) && scratch_bytes >= prefill_scratch_bytes(M, K))
+    const int tile_tokens = f == launch_linear_mfma && scratch ? prefill_tile(M, N, K) : 0;
+    if (tile_tokens && scratch_bytes >= prefill_scratch_bytes(M, K))
         e = launch_linear_prefill((const uint8_t *)xq, (const uint8_t *)wq, M, N, K, s_a, s_w, d, zp, wsum, (uint16_t *)y, acc,
-                                  (uint8_t *)scratch, (hipStream_t)stream);
+                                  (uint8_t *)scratch, tile_tokens, (hipStream_t)stream);
     else if (f == launch_linear_mfma && workspace)
         e = launch_linear_mfma_ws((const uint8_t *)xq, (const uint8_t *)wq, M, N, K, s_a, s_w, d, zp, wsum, (uint16_t *)y, acc,
                                   (int32_t *)workspace, workspace_bytes, (hipStream_t)stream);
@@ -409,7 +410,7 @@ int64_t fptq_linear_scratch_bytes(int64_t M, int64_t N, int64_t K)
         set_error("%s: K=%lld exceeds %lld, the longest sum INT32 holds exactly", fn, (long long)K, (long long)MAX_K);
         return FPTQ_ERR_SHAPE;
     }
-    return !few_token_shape(M, N) && prefill_pays(M, N, K) ? prefill_scratch_bytes(M, K) : 0;
+    return !few_token_shape(M, N) && prefill_tile(M, N, K) ? prefill_scratch_bytes(M, K) : 0;
 }
 
 int fptq_w4a4_linear_scratch(const void *xq_packed, const void *w_packed, int64_t M, int64_t N, int64_t K, float s_a,
@@ -436,9 +437,9 @@ int fptq_linear_launch_plan(int64_t M, int64_t N, int64_t K, int with_workspace,
         snprintf(plan.kernel, sizeof plan.kernel, "linear_decode_kernel");
         plan.workgroups = 0;
         plan.threads = 0;
-    } else if (with_workspace == 2 && prefill_pays(M, N, K)) {
+    } else if (const int tile_tokens = with_workspace == 2 ? prefill_tile(M, N, K) : 0) {
         snprintf(plan.kernel, sizeof plan.kernel, "linear_prefill_kernel");
-        plan.workgroups = prefill_workgroups(M, N);
+        plan.workgroups = prefill_workgroups(M, N, tile_tokens);
         plan.threads = 256;
     } else {
         linear_mfma_plan(M, N, K, with_workspace == 1, &plan);
@@ -461,8 +462,8 @@ int fptq_set_gemm_map(int mode)
 
 int fptq_set_linear_prefill(int mode)
 {
-    if (mode < 0 || mode > 2) {
-        set_error("fptq_set_linear_prefill: mode must be 0, 1 or 2");
+    if ((mode < 0 || mode > 2) && mode != 128 && mode != 256) {
+        set_error("fptq_set_linear_prefill: mode must be 0, 1, 2, 128 or 256");
         return FPTQ_ERR_VALUE;
     }
     set_linear_prefill(mode);

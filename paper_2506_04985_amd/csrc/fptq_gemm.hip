@@ -550,7 +550,7 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void linear_mfma_kernel(
 // 0 = choose the tile shape per problem; 1..8 = force one (testing and tuning)
 static std::atomic<int> g_forced_tile{0};
 static std::atomic<int> g_tile_map{0};
-static std::atomic<int> g_prefill{0};     // 0 = where the six-bit kernel pays, 1 = wherever it can run, 2 = never
+static std::atomic<int> g_prefill{0};     // 0 = where the six-bit kernel pays, 1 = wherever it can run, 2 = never, 128 / 256 = as 1, with that tile
 void set_gemm_tile(int tile) { g_forced_tile.store(tile, std::memory_order_relaxed); }
 void set_linear_prefill(int mode) { g_prefill.store(mode, std::memory_order_relaxed); }
 void set_gemm_map(int mode) { g_tile_map.store(mode, std::memory_order_relaxed); }
@@ -724,7 +724,10 @@ static int choose_tile(int64_t M, int64_t N, int64_t K, int cus, double *us = nu
     // Problems so small that even 128 x 128 tiles give every CU at most one workgroup take that tile: the
     // kernel time is then one workgroup's walk through K and the small tile walks fastest (17 against 25 us at
     // K = 4096).  A deeper ring does not help there.
-    if (tiles(128, 128) <= CUS) pick = 4;
+    if (tiles(128, 128) <= CUS) {
+        pick = 4;
+        if (us) *us = 8.0 + (0.30 + 0.08 * tiles(128, 128) / CUS) * kt;
+    }
     // Fewer tiles still: the smallest tile shape that still gives every CU at most one workgroup, as four K
     // groups whose waves each hold a whole 64 x 64 block of outputs (half the LDS reads per MFMA of a 32 x 32
     // block).  Measured at K = 4096, N = 4096: 256 tokens 9 us on 64 x 64 tiles against 17 on 128 x 128; 512
@@ -735,23 +738,39 @@ static int choose_tile(int64_t M, int64_t N, int64_t K, int cus, double *us = nu
     return pick;
 }
 
-// Whether a problem is faster on the six-bit kernel (fptq_prefill.hip), widening of its activations included.  Estimated times on
-// uniform random operands, as above, in rounds of one 256 x 256 tile per CU; a partial last round costs less than a full one (the
-// power it leaves speeds its tiles up), a lone partial round does not.  Fitted to 8192 x 57344 x 8192 1712 us (INT8 2461),
-// 8192 x 8192 x 28672 829 (1156), 4096 x 28672 x 4096 251 (334), 2048 x 22016 x 4096 107 (137), 4096 x 6144 x 4096 70 (74),
-// 4096 x 4096 x 4096 45 (50), 2048 x 4999 x 4096 40.5 (39), 333 x 32003 x 2504 33 (31) and 700 x 50257 x 1024 58 (47); where the two
-// are within 3 % the INT8 shapes keep the problem.  They also keep those that give few CUs such a tile (1000 x 5120 x 13824).
-bool prefill_pays(int64_t M, int64_t N, int64_t K)
+// Whether a problem is faster on the six-bit kernel (fptq_prefill.hip), widening of its activations included, and with how many tokens
+// per tile.  Estimated times on uniform random operands, as above, in rounds of one tile of 256 channels per CU: a partial
+// last round costs less than a full one (the power it leaves speeds its tiles up), and so does a lone one.  Fitted to (us, the
+// better INT8 shape / 256 / 128 tokens)
+//     8192 x 57344 x 8192   2461 / 1712 / 1950        1000 x 5120 x 13824   77 / 84 / 59        333 x 32003 x 2504   32 / 34 / 36
+//     4096 x 28672 x 4096    340 / 262 / 297          2048 x 4096 x 11008   68 / 69 / 58        1024 x 4096 x 14336  54 / 78 / 57
+//     2048 x 22016 x 4096    143 / 112 / 125          4096 x 6144 x 4096    78 / 73 / 70        512 x 8192 x 8192    33 / 50 / 37
+//     4096 x 4096 x 4096      53 / 48 / 50            256 x 28672 x 4096    29 / 34 / 26        2720 x 30592 x 1062  97 / 104 / 108
+// i.e. the small tile wins where the large one leaves CUs without work, and INT8 where even the small one does.  Where the two
+// paths are estimated within 5 % the INT8 shapes keep the problem; within 10 % below 24 K tiles, where stores and launches weigh more
+// than in what the estimates were fitted to (1601 x 23384 x 2472 takes 85 us on INT8 tiles and 89 on six-bit ones).
+int prefill_tile(int64_t M, int64_t N, int64_t K)
 {
-    if (K > 131071 || M > (1 << 24) || N > (1 << 24) || forced_gemm_tile() > 0) return false;
-    if (const int mode = g_prefill.load(std::memory_order_relaxed)) return mode == 1;
+    if (K > 131071 || M > (1 << 24) || N > (1 << 24) || forced_gemm_tile() > 0) return 0;
+    const int mode = g_prefill.load(std::memory_order_relaxed);
+    if (mode == 2) return 0;
+    if (mode > 2) return mode;
     const int cus = device_cus_or_default();
+    const double kt = (double)k_tiles(K), widen_us = 5.0 + (double)M * (double)K * 1.25 / 5.0e6;
+    auto rounds = [&](int tokens, double lone, double least) {
+        const double x = (double)prefill_workgroups(M, N, tokens) / (double)cus, part = x - floor(x);
+        return x < 1.0 ? lone + (1.0 - lone) * x : floor(x) + (part > 0.0 ? least + (1.0 - least) * part : 0.0);
+    };
+    const double us256 = widen_us + rounds(256, 0.50, 0.75) * (12.0 + 0.76 * kt);
+    double us128 = widen_us + rounds(128, 0.75, 0.62) * (6.2 + 0.453 * kt);
+    // A single row of tiles streams its weights once, from HBM: with few workgroups that is bound by what one CU keeps in flight
+    // (119 x 32856 x 18822, 129 workgroups: 106 us against 92; 123 x 54336 x 5992, 213 workgroups: 34 against 39).
+    if (M <= 128 && 4 * prefill_workgroups(M, N, 128) < 3 * cus) us128 = us256;
+    const int tokens = us128 < us256 ? 128 : 256;
+    if (mode == 1) return tokens;
     double int8_us = 0.0;
     choose_tile(M, N, K, cus, &int8_us);
-    const double x = (double)prefill_workgroups(M, N) / (double)cus, part = x - floor(x);
-    const double rounds = x <= 1.0 ? 1.04 : floor(x) + (part > 0.0 ? 0.75 + 0.25 * part : 0.0);
-    const double widen_us = 5.0 + (double)M * (double)K * 1.25 / 5.0e6;
-    return widen_us + rounds * (9.8 + 0.79 * (double)k_tiles(K)) < 0.97 * int8_us;
+    return fmin(us128, us256) < (kt < 24 ? 0.90 : 0.95) * int8_us ? tokens : 0;
 }
 
 // Limits of the MFMA kernel: the widened accumulator is 256 * acc with |acc| <= 64 K, and one K tile of all rows

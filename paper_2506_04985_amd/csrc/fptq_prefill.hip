@@ -11,14 +11,14 @@
 // Data flow.  A small kernel first widens the packed activations to six bits in a scratch buffer of the caller (0.75 bytes a
 // value, read and written once: 16 us at 8192 x 8192 beside 1790 us of product), with their signs resolved, and sums each
 // token's codes.  The matrix kernel copies those to LDS with buffer loads that write LDS directly, and reads the weights as
-// they are, packed, straight into registers: each of its four waves owns 64 channels and all 256 tokens of the tile, so a
+// they are, packed, straight into registers: each of its four waves owns 64 channels and all tokens of the tile (256 or 128), so a
 // weight is loaded by one wave only and needs no LDS, and its nibbles are spread to six-bit fields by 18 VALU instructions per
 // 32 values, 2.25 per MFMA.  Widening both operands in the kernel would take 5.7 VALU instructions per MFMA, and one wave
 // per SIMD issues at most eight instructions in the 32 cycles of an MFMA: measured at the INT8 loop's rate.  Widening the
 // weights beforehand as well would cost 1.25 bytes of traffic per weight and call, 5 % at 8192 tokens.
 //
-// What bounds it: the board's power.  On uniform random INT4 operands 8192 x 57344 x 8192 runs at 4260 TOP/s against 3100 for
-// the INT8 kernel (1806 and 2482 us), on all-zero operands in 1227 us; an MFMA-only loop on random operands that never
+// What bounds it: the board's power.  On uniform random INT4 operands 8192 x 57344 x 8192 runs at 4490 TOP/s against 3130 for
+// the INT8 kernel (1712 and 2461 us), on all-zero operands in 1240 us; an MFMA-only loop on random operands that never
 // change reaches 6140, the same with this kernel's LDS reads 5030.
 #include <cstdio>
 #include <type_traits>
@@ -43,7 +43,7 @@ constexpr int P_RSRC_FLAGS = 0x00020000;        // raw buffer, 32-bit data forma
 
 // ---- six-bit activations in the scratch buffer: blocks of (K tile, 128 rows), 12 KB each, row blocks innermost.  A block is six
 // planes [half][piece][row] of 16-byte pieces: half h of a row holds its values 64 h .. 64 h + 63 as 48 bytes of six-bit
-// fields, i.e. three pieces.  The matrix kernel copies two blocks to LDS as they are, and a wave's fragment read (one piece of
+// fields, i.e. three pieces.  The matrix kernel copies one or two blocks to LDS as they are, and a wave's fragment read (one piece of
 // 32 consecutive rows per half) is contiguous: no bank conflicts, no swizzle, and all of it in 16-byte reads (the 24 bytes of one
 // operand read as 16 + 8 made LDS the bound: 1627 instead of 1227 us on zero operands at 8192 x 57344 x 8192).
 constexpr int X6_ROWS = 128, X6_PLANE = X6_ROWS * 16, X6_BLOCK = 6 * X6_PLANE;
@@ -131,15 +131,19 @@ __global__ __launch_bounds__(64 * CV_WAVES) void widen_activations_kernel(const 
     }
 }
 
-// Tile 256 (n) x 256 (m), four waves of 64 x 256, 256 accumulator registers a lane, one workgroup per CU.  K tile 128.  STAGES K
-// tiles of activations in an LDS ring, DEPTH K tiles of packed weights in registers.
+// Tile 256 (n) x 32 TM (m), four waves of 64 x 32 TM, 32 TM accumulator registers a lane, one workgroup per CU.  K tile 128.  STAGES K
+// tiles of activations in an LDS ring, DEPTH K tiles of packed weights in registers.  256 tokens (TM = 8) widen each weight
+// for eight MFMAs, 128 (TM = 4) for four and load twice the weights per operation; they are for problems that the large tile cuts
+// into fewer pieces than there are CUs: 1000 x 5120 x 13824 takes 59 us with them, 84 without and 77 on INT8 tiles, 2048 x 4096 x
+// 11008 58, 69 and 68, but 4096 x 28672 x 4096 297, 262 and 340.
+template <int TM_>
 struct PrefillTile {
-    static constexpr int TN = 2, TM = 8, STAGES = 5, DEPTH = 3;
+    static constexpr int TN = 2, TM = TM_, STAGES = 5, DEPTH = 3;
     static constexpr int BN = 4 * TN * 32, BM = TM * 32;
-    static constexpr int STAGE_BYTES = BM * (X6_BLOCK / X6_ROWS);                               // 24 KB
+    static constexpr int STAGE_BYTES = BM * (X6_BLOCK / X6_ROWS);                               // 3 KB per 32 tokens
     static constexpr int FILLS = STAGE_BYTES / 4096, W_LOADS = 2 * TN, LOADS = FILLS + W_LOADS; // vector loads of a wave per K tile
     static constexpr int LDS_BYTES = STAGES * STAGE_BYTES;
-    static_assert(FILLS == 6 && W_LOADS == 4, "the loads are dealt to the eight MFMA groups by hand");
+    static_assert(TM == 8 || TM == 4, "the loads and the widening are dealt to eight or four MFMA groups by hand");
     static_assert(DEPTH >= STAGES - 3 && DEPTH <= STAGES - 1, "the wait counts assume weights and fills issued in the loop's order from the start");
 };
 
@@ -157,13 +161,13 @@ __device__ inline v16f mfma6(v8i w, v8i x, v16f c)
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w, x, c, 2, 2, 0, 0, 0, 0);
 }
 
-template <bool ALIGNED, bool DUMP, bool ZP>
+template <int TM, bool ALIGNED, bool DUMP, bool ZP>
 __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     const uint8_t *__restrict__ x6, int64_t x_slab, const float *__restrict__ start, int start_parts, int rows,
     const uint8_t *__restrict__ wq, int M, int N, int ktiles, int tiles_m, int tiles_n, float s_a, const float *__restrict__ s_w,
     const float *__restrict__ d, int zp, const int32_t *__restrict__ wsum, uint16_t *__restrict__ y, int32_t *__restrict__ acc_out)
 {
-    typedef PrefillTile C;
+    typedef PrefillTile<TM> C;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -184,7 +188,7 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     const int bn = band * GN + in_band % band_w, bm = in_band / band_w;
     const int m0 = bm * C::BM, nw0 = bn * C::BN + wave * (C::TN * 32);
 
-    // ---- activations, HBM -> LDS: one run of 24 KB per K tile, a quarter of it per wave.  Past the last K tile the descriptor is
+    // ---- activations, HBM -> LDS: one run of 3 TM KB per K tile, a quarter of it per wave.  Past the last K tile the descriptor is
     // empty: the loads are still issued (the wait counts stay the same) and land as zeros.
     const int x_voff = bm * C::STAGE_BYTES + wave * (C::FILLS * 1024) + lane * 16;
     uint8_t *const fill_base = lds + wave * (C::FILLS * 1024);
@@ -243,9 +247,11 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
         fill1(std::integral_constant<int, 0>(), r, to);
         fill1(std::integral_constant<int, 1>(), r, to);
         fill1(std::integral_constant<int, 2>(), r, to);
-        fill1(std::integral_constant<int, 3>(), r, to);
-        fill1(std::integral_constant<int, 4>(), r, to);
-        fill1(std::integral_constant<int, 5>(), r, to);
+        if constexpr (C::FILLS > 3) {
+            fill1(std::integral_constant<int, 3>(), r, to);
+            fill1(std::integral_constant<int, 4>(), r, to);
+            fill1(std::integral_constant<int, 5>(), r, to);
+        }
         __builtin_amdgcn_sched_barrier(0);
     }
     v16f acc[C::TN][C::TM];
@@ -275,10 +281,10 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     for (int h = 0; h < 8; ++h) widen_half(raw[0], W[0], h);
     __builtin_amdgcn_sched_barrier(0);
 
-    // ---- K loop.  A K tile is eight groups of four MFMAs, group x on the tokens 32 x ..: two steps of 64 values times two runs of 32
-    // channels.  Beside group x run: an eighth of the next K tile's weights being widened (9 VALU), the fragment reads of the
-    // tokens that are done (three; X[x - 1] of the next K tile, in group 0 X[7] of this one, whose old value the previous
-    // tile's last group still used), and one or two of the ten loads of later tiles.
+    // ---- K loop.  A K tile is TM groups of four MFMAs, group x on the tokens 32 x ..: two steps of 64 values times two runs of 32
+    // channels.  Beside group x run: 1 / TM of the next K tile's weights being widened (9 VALU per eighth), the fragment reads of
+    // the tokens that are done (three; X[x - 1] of the next K tile, in group 0 the last X of this one, whose old value the
+    // previous tile's last group still used), and one or two of the loads of later tiles.
     int off = 0;                                   // ring position of tile kt, in bytes
     __builtin_amdgcn_s_setprio(2);
     auto tile = [&](auto pc) {
@@ -307,20 +313,23 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
                 }
             if (x == 0) read_x(off, C::TM - 1);
             else read_x(off_next, x - 1);
-            widen_half(next, W[(P + 1) % 2], x);
+#pragma unroll
+            for (int h = x * (8 / C::TM); h < (x + 1) * (8 / C::TM); ++h) widen_half(next, W[(P + 1) % 2], h);
             if (x == 0) load_to[0][0] = load_w1(wr, 0, 0), load_to[1][0] = load_w1(wr, 1, 0);
             if (x == 1) load_to[0][1] = load_w1(wr, 0, 1), load_to[1][1] = load_w1(wr, 1, 1);
             if (x == 2) fill1(std::integral_constant<int, 0>(), xr, fill_to), fill1(std::integral_constant<int, 1>(), xr, fill_to);
             if (x == 3) fill1(std::integral_constant<int, 2>(), xr, fill_to);
-            if (x == 4) fill1(std::integral_constant<int, 3>(), xr, fill_to);
-            if (x == 5) fill1(std::integral_constant<int, 4>(), xr, fill_to);
-            if (x == 6) fill1(std::integral_constant<int, 5>(), xr, fill_to);
+            if constexpr (C::FILLS > 3) {
+                if (x == 4) fill1(std::integral_constant<int, 3>(), xr, fill_to);
+                if (x == 5) fill1(std::integral_constant<int, 4>(), xr, fill_to);
+                if (x == 6) fill1(std::integral_constant<int, 5>(), xr, fill_to);
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 if (i < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                 if (i == 1 || i == 3) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 24 / C::TM, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -412,22 +421,29 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     }
 }
 
-template <bool ALIGNED, bool DUMP, bool ZP>
+template <int TM, bool ALIGNED, bool DUMP, bool ZP>
 static hipError_t set_prefill_attribute()
 {
-    return hipFuncSetAttribute((const void *)linear_prefill_kernel<ALIGNED, DUMP, ZP>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               PrefillTile::LDS_BYTES);
+    return hipFuncSetAttribute((const void *)linear_prefill_kernel<TM, ALIGNED, DUMP, ZP>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               PrefillTile<TM>::LDS_BYTES);
+}
+
+template <int TM>
+static hipError_t set_prefill_attributes()
+{
+    hipError_t e = hipSuccess;
+    auto one = [&](hipError_t r) { if (e == hipSuccess) e = r; };
+    one(set_prefill_attribute<TM, true, true, false>()), one(set_prefill_attribute<TM, true, false, false>());
+    one(set_prefill_attribute<TM, false, true, false>()), one(set_prefill_attribute<TM, false, false, false>());
+    one(set_prefill_attribute<TM, true, true, true>()), one(set_prefill_attribute<TM, true, false, true>());
+    one(set_prefill_attribute<TM, false, true, true>()), one(set_prefill_attribute<TM, false, false, true>());
+    return e;
 }
 
 hipError_t prefill_device_init()
 {
-    hipError_t e = hipSuccess;
-    auto one = [&](hipError_t r) { if (e == hipSuccess) e = r; };
-    one(set_prefill_attribute<true, true, false>()), one(set_prefill_attribute<true, false, false>());
-    one(set_prefill_attribute<false, true, false>()), one(set_prefill_attribute<false, false, false>());
-    one(set_prefill_attribute<true, true, true>()), one(set_prefill_attribute<true, false, true>());
-    one(set_prefill_attribute<false, true, true>()), one(set_prefill_attribute<false, false, true>());
-    return e;
+    const hipError_t e = set_prefill_attributes<8>();
+    return e == hipSuccess ? set_prefill_attributes<4>() : e;
 }
 
 // Workgroups per group of 32 rows in the widening kernel: about two per CU in all, each with a K tile per wave at least.
@@ -444,28 +460,22 @@ static int widen_split(int64_t M, int64_t K, int cus)
 static int64_t start_bytes(int64_t M) { return (int64_t)CV_MAX_SPLIT * x6_rows(M) * 4; }
 int64_t prefill_scratch_bytes(int64_t M, int64_t K) { return start_bytes(M) + k_tiles(K) * x6_slab(M); }
 
-int64_t prefill_workgroups(int64_t M, int64_t N)
+int64_t prefill_workgroups(int64_t M, int64_t N, int tile_tokens)
 {
-    return ((M + PrefillTile::BM - 1) / PrefillTile::BM) * ((N + PrefillTile::BN - 1) / PrefillTile::BN);
+    return ((M + tile_tokens - 1) / tile_tokens) * ((N + PrefillTile<8>::BN - 1) / PrefillTile<8>::BN);
 }
 
-hipError_t launch_linear_prefill(const uint8_t *xq, const uint8_t *wq, int64_t M, int64_t N, int64_t K, float s_a, const float *s_w,
-                                 const float *d, int zp, const int32_t *wsum, uint16_t *y, int32_t *acc, uint8_t *scratch, hipStream_t s)
+template <int TM>
+static hipError_t launch_tile(const uint8_t *x6, const float *start, int split, const uint8_t *wq, int64_t M, int64_t N, int64_t K, float s_a,
+                              const float *s_w, const float *d, int zp, const int32_t *wsum, uint16_t *y, int32_t *acc, hipStream_t s)
 {
-    const DeviceInfo *info;
-    hipError_t e = device_info(&info);
-    if (e != hipSuccess) return e;
-    const int64_t tiles_m = (M + PrefillTile::BM - 1) / PrefillTile::BM, tiles_n = (N + PrefillTile::BN - 1) / PrefillTile::BN;
+    typedef PrefillTile<TM> C;
+    const int64_t tiles_m = (M + C::BM - 1) / C::BM, tiles_n = (N + C::BN - 1) / C::BN;
     if (tiles_m * tiles_n > 0x7fffffff) return hipErrorInvalidValue;
-    const int rows = (int)x6_rows(M), kt = (int)k_tiles(K), split = widen_split(M, K, info->cus);
-    float *start = reinterpret_cast<float *>(scratch);
-    uint8_t *x6 = scratch + start_bytes(M);
-    widen_activations_kernel<<<dim3((unsigned)(rows / CV_ROWS), (unsigned)split), dim3(64 * CV_WAVES), 0, s>>>(xq, (int)M, x6_slab(M), kt, x6,
-                                                                                                             start, rows);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
 #define FPTQ_PREFILL(A, D, Z)                                                                                                        \
-    linear_prefill_kernel<A, D, Z><<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), PrefillTile::LDS_BYTES, s>>>(                    \
-        x6, x6_slab(M), start, split, rows, wq, (int)M, (int)N, kt, (int)tiles_m, (int)tiles_n, s_a, s_w, d, zp, wsum, y, acc)
+    linear_prefill_kernel<TM, A, D, Z><<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), C::LDS_BYTES, s>>>(                          \
+        x6, x6_slab(M), start, split, (int)x6_rows(M), wq, (int)M, (int)N, (int)k_tiles(K), (int)tiles_m, (int)tiles_n, s_a, s_w, d,   \
+        zp, wsum, y, acc)
     const int inst = (N % 8 == 0 ? 4 : 0) | (acc ? 2 : 0) | (wsum ? 1 : 0);
     switch (inst) {
     case 0: FPTQ_PREFILL(false, false, false); break;
@@ -479,6 +489,23 @@ hipError_t launch_linear_prefill(const uint8_t *xq, const uint8_t *wq, int64_t M
     }
 #undef FPTQ_PREFILL
     return hipGetLastError();
+}
+
+hipError_t launch_linear_prefill(const uint8_t *xq, const uint8_t *wq, int64_t M, int64_t N, int64_t K, float s_a, const float *s_w,
+                                 const float *d, int zp, const int32_t *wsum, uint16_t *y, int32_t *acc, uint8_t *scratch, int tile_tokens,
+                                 hipStream_t s)
+{
+    const DeviceInfo *info;
+    hipError_t e = device_info(&info);
+    if (e != hipSuccess) return e;
+    const int rows = (int)x6_rows(M), split = widen_split(M, K, info->cus);
+    float *start = reinterpret_cast<float *>(scratch);
+    uint8_t *x6 = scratch + start_bytes(M);
+    widen_activations_kernel<<<dim3((unsigned)(rows / CV_ROWS), (unsigned)split), dim3(64 * CV_WAVES), 0, s>>>(
+        xq, (int)M, x6_slab(M), (int)k_tiles(K), x6, start, rows);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    return tile_tokens == 256 ? launch_tile<8>(x6, start, split, wq, M, N, K, s_a, s_w, d, zp, wsum, y, acc, s)
+                              : launch_tile<4>(x6, start, split, wq, M, N, K, s_a, s_w, d, zp, wsum, y, acc, s);
 }
 
 }  // namespace fptq

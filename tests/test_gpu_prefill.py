@@ -11,9 +11,9 @@ from gpu_util import dev, dev_bf16, host_bits
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture
-def forced():
-    fptq.fptq_set_linear_prefill(1)
+@pytest.fixture(params=[256, 128])
+def forced(request):
+    fptq.fptq_set_linear_prefill(request.param)         # tokens per tile
     yield
     fptq.fptq_set_linear_prefill(0)
 
@@ -24,10 +24,10 @@ def scratch_for(M, N, K):
     return torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")        # nothing in it may matter
 
 
-# one to thirteen K tiles (the loop is unrolled by six and keeps five in flight), tokens and channels around the 256 x 256 tile,
+# one to thirteen K tiles (the loop is unrolled by six and keeps five in flight), tokens and channels around the tiles,
 # widths the 16-byte stores do not divide, K that no tile divides
-@pytest.mark.parametrize("M,N,K", [(65, 1, 1), (100, 8, 128), (255, 255, 129), (256, 256, 384), (257, 257, 500), (129, 300, 640), (66, 70, 768),
-                                   (300, 520, 896), (513, 64, 1030), (90, 776, 1537)])
+@pytest.mark.parametrize("M,N,K", [(65, 1, 1), (100, 8, 128), (128, 260, 256), (385, 40, 700), (255, 255, 129), (256, 256, 384),
+                                   (257, 257, 500), (129, 300, 640), (66, 70, 768), (300, 520, 896), (513, 64, 1030), (90, 776, 1537)])
 def test_matches_oracle(forced, oracle, M, N, K):
     case = synth.LinearCase("p6", f"m{M}", M, N, K, "normal", 0.0, 1, 4.0, synth.MODE_RMS, M + N + K)
     inp = synth.draw(case)
@@ -81,6 +81,14 @@ def test_random_rows_of_the_longest_sums(forced):
         _, acc = fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, 1.0, s_w, scratch_for(M, N, K), want_acc=True)
         _, ref = fptq.fptq_w4a4_linear_ref(xq, wq, M, N, K, 1.0, s_w, want_acc=True)
         assert torch.equal(acc, ref)
+
+
+@pytest.mark.parametrize("M,N,K,workgroups", [(4096, 8192, 4096, 16 * 32), (2048, 4096, 11008, 16 * 16), (512, 8192, 8192, 0)])
+def test_tile_per_problem(M, N, K, workgroups):
+    """Large tiles, small ones where the large ones would leave compute units idle, neither where the small ones would."""
+    plan = fptq.fptq_linear_launch_plan(M, N, K, with_scratch=True)
+    assert plan[:2] == ("linear_prefill_kernel", workgroups) if workgroups else plan[0].startswith("GemmCfg")
+    assert (fptq.fptq_linear_scratch_bytes(M, N, K) > 0) == (workgroups > 0)
 
 
 def test_too_little_scratch_or_none_gives_the_plain_layer():
