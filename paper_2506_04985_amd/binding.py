@@ -148,7 +148,7 @@ def fptq_pack_weights(w_int, out=None):
 def fptq_quantize_act(x_bf16, s_a, scale_mode=SCALE_RMS, eps=0.0, row_scale_in=None, out=None, row_scale_out=None,
                       want_row_scale=True):
     """bf16 [M, K] -> (packed uint8 blob, fp32 [M] per-token scale or None)."""
-    done = None if _native is None else _native.quantize_act(x_bf16, s_a, scale_mode, eps, row_scale_in, out, row_scale_out, want_row_scale, None, None)
+    done = None if _native is None else _native.quantize_act(x_bf16, s_a, scale_mode, eps, row_scale_in, out, row_scale_out, want_row_scale, 0, None)
     if done is not None:
         return done
     _dev(x_bf16, torch.bfloat16, "x_bf16")
@@ -167,7 +167,7 @@ def fptq_quantize_act_hadamard(x_bf16, s_a, hadamard_block=256, scale_mode=SCALE
                                row_scale_out=None, want_row_scale=True):
     """bf16 [M, K] -> block-wise Hadamard, per-token scale, static INT4 quantizer, packed."""
     done = None if _native is None else _native.quantize_act(x_bf16, s_a, scale_mode, eps, row_scale_in, out, row_scale_out, want_row_scale,
-                                                                 hadamard_block, None)
+                                                                 1, hadamard_block)
     if done is not None:
         return done
     _dev(x_bf16, torch.bfloat16, "x_bf16")
@@ -185,7 +185,7 @@ def fptq_quantize_act_hadamard(x_bf16, s_a, hadamard_block=256, scale_mode=SCALE
 
 def fptq_quantize_act_asym(x_bf16, s_a, zero_point, scale_mode=SCALE_NONE, eps=0.0, row_scale_in=None, out=None):
     """bf16 [M, K] -> packed codes of the asymmetric grid v = clamp(rne(x S / s_a) + z, -8, 7)."""
-    done = None if _native is None else _native.quantize_act(x_bf16, s_a, scale_mode, eps, row_scale_in, out, None, True, None, zero_point)
+    done = None if _native is None else _native.quantize_act(x_bf16, s_a, scale_mode, eps, row_scale_in, out, None, True, 2, zero_point)
     if done is not None:
         return done
     _dev(x_bf16, torch.bfloat16, "x_bf16")
@@ -211,7 +211,7 @@ def fptq_weight_row_sums(w_int):
 
 
 def fptq_w4a4_linear_zp(xq, wq, M, N, K, s_a, s_w, zero_point, w_row_sum, row_out_scale=None, out=None, want_acc=False):
-    done = None if _native is None else _native.linear(xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, None, zero_point, w_row_sum, None, 0)
+    done = None if _native is None else _native.linear(xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, None, zero_point, w_row_sum, None, 3)
     if done is not None:
         return done
     _dev(w_row_sum, torch.int32, "w_row_sum")

@@ -192,8 +192,9 @@ PyObject *weight_row_sums(PyObject *, PyObject *const *a, Py_ssize_t n)
     });
 }
 
-// (x, s_a, scale_mode, eps, row_scale_in, out, row_scale_out, want_row_scale, hadamard_block, zero_point): hadamard_block None for
-// the plain quantizer, zero_point None for the symmetric grid
+// (x, s_a, scale_mode, eps, row_scale_in, out, row_scale_out, want_row_scale, kind, parameter): kind 0 the plain quantizer, 1 behind the
+// Hadamard transform with blocks of `parameter`, 2 on the asymmetric grid with that zero point.  The wrapper says which call it is: no
+// value of the caller's may.
 PyObject *quantize_act(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 10, [&]() -> PyObject * {
@@ -202,13 +203,14 @@ PyObject *quantize_act(PyObject *, PyObject *const *a, Py_ssize_t n)
         matrix(x, M, K);
         const float s_a = number(a[1]), eps = number(a[3]);
         const int mode = (int)integer(a[2]);
+        const int64_t kind = integer(a[8]), parameter = kind ? integer(a[9]) : 0;
         const float *r_in = (const float *)input_or_null(a[4], at::kFloat);
         Output out(a[5], {need(M, K)}, at::kByte, x), r;
         if (a[6] != Py_None || truth(a[7])) r = Output(a[6], {M}, at::kFloat, x);
-        if (a[8] != Py_None)
-            done(fptq_quantize_act_hadamard(x.data_ptr(), M, K, (int)integer(a[8]), mode, eps, r_in, s_a, out.ptr, out.numel, (float *)r.ptr, stream()));
-        else if (a[9] != Py_None)
-            done(fptq_quantize_act_asym(x.data_ptr(), M, K, mode, eps, r_in, s_a, (int)integer(a[9]), out.ptr, out.numel, (float *)r.ptr, stream()));
+        if (kind == 1)
+            done(fptq_quantize_act_hadamard(x.data_ptr(), M, K, (int)parameter, mode, eps, r_in, s_a, out.ptr, out.numel, (float *)r.ptr, stream()));
+        else if (kind == 2)
+            done(fptq_quantize_act_asym(x.data_ptr(), M, K, mode, eps, r_in, s_a, (int)parameter, out.ptr, out.numel, (float *)r.ptr, stream()));
         else
             done(fptq_quantize_act(x.data_ptr(), M, K, mode, eps, r_in, s_a, out.ptr, out.numel, (float *)r.ptr, stream()));
         return pair(out, r);
@@ -249,8 +251,8 @@ PyObject *residual_norm_quantize(PyObject *, PyObject *const *a, Py_ssize_t n)
     });
 }
 
-// (xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc, zero_point, w_row_sum, workspace, kind): kind 0 the plain linear
-// (zero_point None) or the one with a zero point, with scratch where it pays; 1 with a workspace; 2 the one that allocates nothing
+// (xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc, zero_point, w_row_sum, workspace, kind): kind 0 the plain linear and 3
+// the one with a zero point, both with scratch where it pays; 1 with a workspace; 2 the one that allocates nothing
 PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     return guarded(n, 15, [&]() -> PyObject * {
@@ -262,14 +264,13 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
         const float *d = (const float *)input_or_null(a[7], at::kFloat);
         const bool want_acc = truth(a[9]);
         const int64_t kind = integer(a[14]);
-        if (a[11] != Py_None && a[12] == Py_None) throw Slow();
-        const int zp = a[11] == Py_None ? 0 : (int)integer(a[11]);
-        const int32_t *wsum = (const int32_t *)input_or_null(a[12], at::kInt);
+        const int zp = kind == 3 ? (int)integer(a[11]) : 0;
+        const int32_t *wsum = kind == 3 ? (const int32_t *)input(a[12], at::kInt).data_ptr() : nullptr;
         Output y(a[8], {M, N}, at::kBFloat16, xq), acc;
         if (want_acc || a[10] != Py_None) acc = Output(a[10], {M, N}, at::kInt, xq);
         at::Tensor scratch;
         int64_t scratch_bytes = 0;
-        if (kind == 0 && M > 64 && (scratch_bytes = fptq_linear_scratch_bytes(M, N, K)) > 0) {
+        if ((kind == 0 || kind == 3) && M > 64 && (scratch_bytes = fptq_linear_scratch_bytes(M, N, K)) > 0) {
             scratch_bytes = capturing() ? 0 : scratch_bytes;
             if (scratch_bytes > 0) {
                 try {
@@ -288,7 +289,7 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
         else if (kind == 1) {
             const at::Tensor &ws = input(a[13], at::kByte);
             done(fptq_w4a4_linear_ws(px, pw, M, N, K, s_a, ps, d, y.ptr, (int32_t *)acc.ptr, ws.data_ptr(), ws.numel(), stream()));
-        } else if (a[11] != Py_None)
+        } else if (kind == 3)
             done(fptq_w4a4_linear_zp(px, pw, M, N, K, s_a, ps, d, zp, wsum, y.ptr, (int32_t *)acc.ptr, stream()));
         else
             done(fptq_w4a4_linear(px, pw, M, N, K, s_a, ps, d, y.ptr, (int32_t *)acc.ptr, stream()));

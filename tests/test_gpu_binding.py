@@ -114,6 +114,20 @@ def test_what_was_refused_is_refused(both):
         assert a is not None and a == b, i
 
 
+def test_none_is_no_value_for_a_block_or_a_zero_point(both):
+    """None is not "no transform" or "symmetric grid": the calls that need a number refuse it on either path."""
+    M, N, K = 40, 72, 1024
+    x, w, s, r = data(M, N, K)
+    wq, sums, xq = fptq.fptq_pack_weights(w), fptq.fptq_weight_row_sums(w), fptq.fptq_quantize_act(x, 0.4, 2, 0.0, r)[0]
+    for f in (lambda: fptq.fptq_quantize_act_hadamard(x, 0.4, hadamard_block=None, row_scale_in=r), lambda: fptq.fptq_quantize_act_asym(x, 0.4, None),
+              lambda: fptq.fptq_w4a4_linear_zp(xq, wq, M, N, K, 0.4, s, None, sums)):
+        def refused():
+            with pytest.raises(TypeError):
+                f()
+            return True
+        assert both(refused) == (True, True)
+
+
 def test_runs_on_the_current_stream():
     """A call inside a side stream's context waits for what that stream did before."""
     M, N, K = 40, 72, 1024
