@@ -6,6 +6,9 @@
 // wrapper returns -- or None whenever anything is not the plain case (an argument of another type, a tensor that is not
 // contiguous or not on the device, a buffer too small, an error of the library): then the wrapper goes on in Python, which
 // raises what there is to raise.  A failing library call launches nothing, so it can be repeated.  Nothing is kept between calls.
+#include <array>
+#include <initializer_list>
+
 #include <torch/extension.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -17,6 +20,18 @@ namespace {
 PyObject *g_device = nullptr, *g_stream = nullptr, *g_capturing = nullptr;
 
 struct Slow {};        // thrown where the call is left to the Python wrapper
+
+// Runs f without the interpreter lock.  A launch can wait for room in its queue and an allocation for the device; other threads, and a
+// host callback that the stream is waiting for, need the lock meanwhile.  It is taken again before anything thrown is handled.
+template <class F>
+auto without_gil(F f)
+{
+    struct Released {
+        PyThreadState *state = PyEval_SaveThread();
+        ~Released() { PyEval_RestoreThread(state); }
+    } released;
+    return f();
+}
 
 int64_t need(int64_t rows, int64_t K) { return (K + 127) / 128 * rows * 64; }
 
@@ -63,51 +78,59 @@ bool truth(PyObject *o)
     throw Slow();
 }
 
-// an output: the caller's tensor, or a new one; `object` is a new reference to what the wrapper returns
+// An output: the caller's tensor, or a new one, made by `allocate` without the interpreter lock and wrapped by `take` with it.
 struct Output {
-    PyObject *object = nullptr;
+    PyObject *given = nullptr;       // the caller's, who holds it
+    at::Tensor made;
+    std::array<int64_t, 2> shape = {0, 1};
+    int dims = 0;
+    at::ScalarType type = at::kByte;
+    at::Device device = at::kCPU;
     void *ptr = nullptr;
     int64_t numel = 0;
-    Output() = default;
-    Output(PyObject *given, at::IntArrayRef shape, at::ScalarType type, const at::Tensor &like)
+    Output() = default;              // none: ptr is NULL
+    Output(PyObject *o, std::initializer_list<int64_t> sizes, at::ScalarType t, const at::Tensor &like)
     {
-        if (given != Py_None) {
-            const at::Tensor &t = device_tensor(given);
-            ptr = t.data_ptr(), numel = t.numel();
-            Py_INCREF(given);
-            object = given;
+        if (o != Py_None) {
+            const at::Tensor &v = device_tensor(o);
+            given = o, ptr = v.data_ptr(), numel = v.numel();
             return;
         }
-        at::Tensor t = at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
-        ptr = t.data_ptr(), numel = t.numel();
-        object = THPVariable_Wrap(std::move(t));
-        if (!object) throw Slow();
+        for (int64_t n : sizes) shape[dims++] = n;
+        type = t, device = like.device();
     }
-    Output(Output &&o) : object(o.object), ptr(o.ptr), numel(o.numel) { o.object = nullptr; }
-    Output &operator=(Output &&o)
+    void allocate()
     {
-        std::swap(object, o.object), std::swap(ptr, o.ptr), std::swap(numel, o.numel);
-        return *this;
+        if (dims == 0) return;
+        made = at::empty(at::IntArrayRef(shape.data(), dims), at::TensorOptions().dtype(type).device(device));
+        ptr = made.data_ptr(), numel = made.numel();
     }
-    ~Output() { Py_XDECREF(object); }
-    PyObject *take()
+    PyObject *take()                 // a new reference to the tensor, None for no output
     {
-        PyObject *o = object;
-        object = nullptr;
+        PyObject *o = given ? given : Py_None;
+        if (made.defined()) {
+            o = THPVariable_Wrap(std::move(made));
+            if (!o) throw Slow();
+            return o;
+        }
+        Py_INCREF(o);
         return o;
     }
 };
 
-PyObject *pair(Output &a, Output &b)
+PyObject *tuple(std::initializer_list<Output *> outputs)
 {
-    PyObject *t = PyTuple_New(2);
+    PyObject *t = PyTuple_New((Py_ssize_t)outputs.size());
     if (!t) throw Slow();
-    PyTuple_SET_ITEM(t, 0, a.take());
-    if (b.object) {
-        PyTuple_SET_ITEM(t, 1, b.take());
-    } else {
-        Py_INCREF(Py_None);
-        PyTuple_SET_ITEM(t, 1, Py_None);
+    Py_ssize_t i = 0;
+    try {
+        for (Output *o : outputs) {
+            PyTuple_SET_ITEM(t, i, o->take());
+            ++i;
+        }
+    } catch (...) {
+        Py_DECREF(t);
+        throw;
     }
     return t;
 }
@@ -141,8 +164,14 @@ bool capturing()
     return yes;
 }
 
-void done(int rc)
+// The part of a call that may wait: the new outputs, then the library's call.
+template <class F>
+void launch(std::initializer_list<Output *> outputs, F f)
 {
+    const int rc = without_gil([&] {
+        for (Output *o : outputs) o->allocate();
+        return f();
+    });
     if (rc != FPTQ_OK) throw Slow();
 }
 
@@ -174,7 +203,8 @@ PyObject *pack_weights(PyObject *, PyObject *const *a, Py_ssize_t n)
         int64_t N, K;
         matrix(w, N, K);
         Output out(a[1], {need(N, K)}, at::kByte, w);
-        done(fptq_pack_weights((const int8_t *)w.data_ptr(), N, K, out.ptr, out.numel, stream()));
+        void *const st = stream();
+        launch({&out}, [&] { return fptq_pack_weights((const int8_t *)w.data_ptr(), N, K, out.ptr, out.numel, st); });
         return out.take();
     });
 }
@@ -187,7 +217,8 @@ PyObject *weight_row_sums(PyObject *, PyObject *const *a, Py_ssize_t n)
         int64_t N, K;
         matrix(w, N, K);
         Output out(Py_None, {N}, at::kInt, w);
-        done(fptq_weight_row_sums((const int8_t *)w.data_ptr(), N, K, (int32_t *)out.ptr, stream()));
+        void *const st = stream();
+        launch({&out}, [&] { return fptq_weight_row_sums((const int8_t *)w.data_ptr(), N, K, (int32_t *)out.ptr, st); });
         return out.take();
     });
 }
@@ -207,13 +238,14 @@ PyObject *quantize_act(PyObject *, PyObject *const *a, Py_ssize_t n)
         const float *r_in = (const float *)input_or_null(a[4], at::kFloat);
         Output out(a[5], {need(M, K)}, at::kByte, x), r;
         if (a[6] != Py_None || truth(a[7])) r = Output(a[6], {M}, at::kFloat, x);
-        if (kind == 1)
-            done(fptq_quantize_act_hadamard(x.data_ptr(), M, K, (int)parameter, mode, eps, r_in, s_a, out.ptr, out.numel, (float *)r.ptr, stream()));
-        else if (kind == 2)
-            done(fptq_quantize_act_asym(x.data_ptr(), M, K, mode, eps, r_in, s_a, (int)parameter, out.ptr, out.numel, (float *)r.ptr, stream()));
-        else
-            done(fptq_quantize_act(x.data_ptr(), M, K, mode, eps, r_in, s_a, out.ptr, out.numel, (float *)r.ptr, stream()));
-        return pair(out, r);
+        void *const st = stream();
+        launch({&out, &r}, [&] {
+            float *const r_out = (float *)r.ptr;
+            if (kind == 1) return fptq_quantize_act_hadamard(x.data_ptr(), M, K, (int)parameter, mode, eps, r_in, s_a, out.ptr, out.numel, r_out, st);
+            if (kind == 2) return fptq_quantize_act_asym(x.data_ptr(), M, K, mode, eps, r_in, s_a, (int)parameter, out.ptr, out.numel, r_out, st);
+            return fptq_quantize_act(x.data_ptr(), M, K, mode, eps, r_in, s_a, out.ptr, out.numel, r_out, st);
+        });
+        return tuple({&out, &r});
     });
 }
 
@@ -225,8 +257,9 @@ PyObject *quantize_act_dynamic(PyObject *, PyObject *const *a, Py_ssize_t n)
         int64_t M, K;
         matrix(x, M, K);
         Output out(a[1], {need(M, K)}, at::kByte, x), s(a[2], {M}, at::kFloat, x);
-        done(fptq_quantize_act_dynamic(x.data_ptr(), M, K, out.ptr, out.numel, (float *)s.ptr, stream()));
-        return pair(out, s);
+        void *const st = stream();
+        launch({&out, &s}, [&] { return fptq_quantize_act_dynamic(x.data_ptr(), M, K, out.ptr, out.numel, (float *)s.ptr, st); });
+        return tuple({&out, &s});
     });
 }
 
@@ -240,14 +273,12 @@ PyObject *residual_norm_quantize(PyObject *, PyObject *const *a, Py_ssize_t n)
         const float s_a = number(a[2]), eps = number(a[4]);
         const float *s_prev = (const float *)input_or_null(a[3], at::kFloat);
         Output x_next(a[5], {M, K}, at::kBFloat16, x), s_next(a[6], {M}, at::kFloat, x), out(a[7], {need(M, K)}, at::kByte, x);
-        done(fptq_residual_norm_quantize(x.data_ptr(), y.data_ptr(), M, K, s_prev, eps, s_a, x_next.ptr, (float *)s_next.ptr, out.ptr, out.numel,
-                                         stream()));
-        PyObject *t = PyTuple_New(3);
-        if (!t) throw Slow();
-        PyTuple_SET_ITEM(t, 0, x_next.take());
-        PyTuple_SET_ITEM(t, 1, s_next.take());
-        PyTuple_SET_ITEM(t, 2, out.take());
-        return t;
+        void *const st = stream();
+        launch({&x_next, &s_next, &out}, [&] {
+            return fptq_residual_norm_quantize(x.data_ptr(), y.data_ptr(), M, K, s_prev, eps, s_a, x_next.ptr, (float *)s_next.ptr, out.ptr,
+                                               out.numel, st);
+        });
+        return tuple({&x_next, &s_next, &out});
     });
 }
 
@@ -266,34 +297,32 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
         const int64_t kind = integer(a[14]);
         const int zp = kind == 3 ? (int)integer(a[11]) : 0;
         const int32_t *wsum = kind == 3 ? (const int32_t *)input(a[12], at::kInt).data_ptr() : nullptr;
+        const at::Tensor *const ws = kind == 1 ? &input(a[13], at::kByte) : nullptr;
         Output y(a[8], {M, N}, at::kBFloat16, xq), acc;
-        if (want_acc || a[10] != Py_None) acc = Output(a[10], {M, N}, at::kInt, xq);
+        const bool with_acc = want_acc || a[10] != Py_None;
+        if (with_acc) acc = Output(a[10], {M, N}, at::kInt, xq);
+        const bool may_scratch = (kind == 0 || kind == 3) && M > 64 && !capturing();
+        void *const st = stream();
         at::Tensor scratch;
-        int64_t scratch_bytes = 0;
-        if ((kind == 0 || kind == 3) && M > 64 && (scratch_bytes = fptq_linear_scratch_bytes(M, N, K)) > 0) {
-            scratch_bytes = capturing() ? 0 : scratch_bytes;
+        launch({&y, &acc}, [&] {
+            const void *px = xq.data_ptr(), *pw = wq.data_ptr();
+            const float *ps = (const float *)s_w.data_ptr();
+            int32_t *const pa = (int32_t *)acc.ptr;
+            const int64_t scratch_bytes = may_scratch ? fptq_linear_scratch_bytes(M, N, K) : 0;
             if (scratch_bytes > 0) {
                 try {
                     scratch = at::empty({scratch_bytes}, at::TensorOptions().dtype(at::kByte).device(xq.device()));
                 } catch (const c10::OutOfMemoryError &) {
-                    scratch_bytes = 0;
                 }
             }
-        }
-        const void *px = xq.data_ptr(), *pw = wq.data_ptr();
-        const float *ps = (const float *)s_w.data_ptr();
-        if (scratch_bytes > 0)
-            done(fptq_w4a4_linear_scratch(px, pw, M, N, K, s_a, ps, d, zp, wsum, y.ptr, (int32_t *)acc.ptr, scratch.data_ptr(), scratch_bytes, stream()));
-        else if (kind == 2)
-            done(fptq_w4a4_linear_noalloc(px, pw, M, N, K, s_a, ps, d, y.ptr, (int32_t *)acc.ptr, stream()));
-        else if (kind == 1) {
-            const at::Tensor &ws = input(a[13], at::kByte);
-            done(fptq_w4a4_linear_ws(px, pw, M, N, K, s_a, ps, d, y.ptr, (int32_t *)acc.ptr, ws.data_ptr(), ws.numel(), stream()));
-        } else if (kind == 3)
-            done(fptq_w4a4_linear_zp(px, pw, M, N, K, s_a, ps, d, zp, wsum, y.ptr, (int32_t *)acc.ptr, stream()));
-        else
-            done(fptq_w4a4_linear(px, pw, M, N, K, s_a, ps, d, y.ptr, (int32_t *)acc.ptr, stream()));
-        return acc.object ? pair(y, acc) : y.take();
+            if (scratch.defined())
+                return fptq_w4a4_linear_scratch(px, pw, M, N, K, s_a, ps, d, zp, wsum, y.ptr, pa, scratch.data_ptr(), scratch_bytes, st);
+            if (kind == 1) return fptq_w4a4_linear_ws(px, pw, M, N, K, s_a, ps, d, y.ptr, pa, ws->data_ptr(), ws->numel(), st);
+            if (kind == 2) return fptq_w4a4_linear_noalloc(px, pw, M, N, K, s_a, ps, d, y.ptr, pa, st);
+            if (kind == 3) return fptq_w4a4_linear_zp(px, pw, M, N, K, s_a, ps, d, zp, wsum, y.ptr, pa, st);
+            return fptq_w4a4_linear(px, pw, M, N, K, s_a, ps, d, y.ptr, pa, st);
+        });
+        return with_acc ? tuple({&y, &acc}) : y.take();
     });
 }
 

@@ -1,5 +1,9 @@
 """The binding's native fast path against its Python path: the same results and the same objects on plain calls, the same exceptions
 on the others."""
+import sys
+import threading
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -126,6 +130,34 @@ def test_none_is_no_value_for_a_block_or_a_zero_point(both):
                 f()
             return True
         assert both(refused) == (True, True)
+
+
+def test_other_threads_run_during_a_call():
+    """The interpreter lock is free while the library launches.  With a switch interval of minutes a thread that wants it gets in only
+    where a call lets go of it."""
+    x, _, _, r = data(1, 8, 256)
+    out = fptq.fptq_quantize_act(x, 0.4, 2, 0.0, r, want_row_scale=False)[0]
+    turns, stop, interval = [0], threading.Event(), sys.getswitchinterval()
+
+    def other():
+        while not stop.is_set():
+            turns[0] += 1
+            time.sleep(0)
+    thread = threading.Thread(target=other)
+    sys.setswitchinterval(600)
+    try:
+        thread.start()
+        before, calls = turns[0], 0
+        while turns[0] == before and calls < 200000:
+            fptq.fptq_quantize_act(x, 0.4, 2, 0.0, r, out=out, want_row_scale=False)
+            calls += 1
+        seen = turns[0] > before
+    finally:
+        sys.setswitchinterval(interval)
+        stop.set()
+        thread.join()
+        torch.cuda.synchronize()
+    assert seen, calls
 
 
 def test_runs_on_the_current_stream():
