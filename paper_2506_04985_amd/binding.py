@@ -282,11 +282,13 @@ def fptq_linear_scratch_bytes(M, N, K):
 
 def _scratch(M, N, K, xq):
     """Scratch for a linear call from torch's caching allocator, or None where the call goes without: shapes that do not
-    profit, no memory left, or a stream under capture (a capture not made through torch would have no pool to allocate from)."""
-    if M <= 64 or not isinstance(xq, torch.Tensor):
+    profit, no memory left, a stream under capture (a capture not made through torch would have no pool to allocate from), or
+    operands on another device than the current one, whose stream the launch goes to: the scratch is handed back when the call
+    returns, and only the order of its own stream keeps it from being given out again while the kernel reads it."""
+    if M <= 64 or not isinstance(xq, torch.Tensor) or not xq.is_cuda:
         return None
     n = lib().fptq_linear_scratch_bytes(M, N, K)
-    if n <= 0 or torch.cuda.is_current_stream_capturing():
+    if n <= 0 or xq.device.index != torch.cuda.current_device() or torch.cuda.is_current_stream_capturing():
         return None
     try:
         return torch.empty(n, dtype=torch.uint8, device=xq.device)

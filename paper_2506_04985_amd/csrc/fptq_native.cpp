@@ -164,6 +164,15 @@ bool capturing()
     return yes;
 }
 
+bool on_current_device(const at::Tensor &t)
+{
+    PyObject *d = device();
+    const long v = PyLong_AsLong(d);
+    Py_DECREF(d);
+    if (v == -1 && PyErr_Occurred()) throw Slow();
+    return t.device().index() == v;
+}
+
 // The part of a call that may wait: the new outputs, then the library's call.
 template <class F>
 void launch(std::initializer_list<Output *> outputs, F f)
@@ -301,7 +310,9 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
         Output y(a[8], {M, N}, at::kBFloat16, xq), acc;
         const bool with_acc = want_acc || a[10] != Py_None;
         if (with_acc) acc = Output(a[10], {M, N}, at::kInt, xq);
-        const bool may_scratch = (kind == 0 || kind == 3) && M > 64 && !capturing();
+        // Scratch is handed back when the call returns and then guarded by stream order alone: it has to come from the stream that the
+        // launch goes to, i.e. from the current device.  Operands on another one (peer access) go without.
+        const bool may_scratch = (kind == 0 || kind == 3) && M > 64 && on_current_device(xq) && !capturing();
         void *const st = stream();
         at::Tensor scratch;
         launch({&y, &acc}, [&] {
