@@ -282,9 +282,11 @@ def fptq_linear_scratch_bytes(M, N, K):
 
 def _scratch(M, N, K, xq):
     """Scratch for a linear call from torch's caching allocator, or None where the call goes without: shapes that do not
-    profit, no memory left, a stream under capture (a capture not made through torch would have no pool to allocate from), or
-    operands on another device than the current one, whose stream the launch goes to: the scratch is handed back when the call
-    returns, and only the order of its own stream keeps it from being given out again while the kernel reads it."""
+    profit, an allocation that fails (the kernels that need none answer then, so it is no reason to refuse a call), a stream
+    under capture (a capture not made through torch would have no pool to allocate from), or operands on another device than
+    the current one, whose stream the launch goes to: the scratch is handed back when the call returns, and only the order of
+    its own stream keeps it from being given out again while the kernel reads it.  Up to 0.75 bytes per activation value; with a
+    full allocator torch empties its cache first, call by call, which fptq_w4a4_linear_noalloc spares a program that has no room."""
     if M <= 64 or not isinstance(xq, torch.Tensor) or not xq.is_cuda:
         return None
     n = lib().fptq_linear_scratch_bytes(M, N, K)
@@ -292,7 +294,7 @@ def _scratch(M, N, K, xq):
         return None
     try:
         return torch.empty(n, dtype=torch.uint8, device=xq.device)
-    except torch.cuda.OutOfMemoryError:
+    except RuntimeError:
         return None
 
 

@@ -44,3 +44,12 @@ def test_not_under_capture_and_not_where_it_does_not_pay(taken, monkeypatch):
     assert fptq._scratch(64, N, K, operand(0)) is None and fptq._scratch(M, 64, 64, operand(0)) is None
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: True)
     assert fptq._scratch(M, N, K, operand(0)) is None and taken == []
+
+
+@pytest.mark.parametrize("error", [torch.cuda.OutOfMemoryError, RuntimeError])
+def test_a_failing_allocation_refuses_no_call(taken, monkeypatch, error):
+    """No memory, or an allocator that may not allocate now (a capture going on in another thread): the call goes without."""
+    def empty(n, dtype, device):
+        raise error("no")
+    monkeypatch.setattr(torch, "empty", empty)
+    assert fptq._scratch(M, N, K, operand(0)) is None

@@ -74,6 +74,27 @@ def test_split_k_workspace_and_scratch_shapes(both):
         same(*both(lambda: fptq.fptq_w4a4_linear(xq, wq, M, N, K, 0.4, s, r)))
 
 
+def test_without_memory_for_scratch_the_call_goes_without(both):
+    M, N, K = 8192, 8192, 8192
+    assert fptq.fptq_linear_scratch_bytes(M, N, K) > 32 << 20                 # more than what the segments in use can have left
+    xq, wq = (torch.randint(0, 256, (fptq.fptq_packed_bytes(n, K),), dtype=torch.uint8, device="cuda") for n in (M, N))
+    s = torch.rand(N, device="cuda") * 0.015 + 0.005
+    want = fptq.fptq_w4a4_linear_noalloc(xq, wq, M, N, K, 0.4, s)
+    outputs = [torch.zeros_like(want) for _ in range(2)]
+    left = iter(outputs)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    failed = lambda: torch.cuda.memory_stats()["num_ooms"]
+    before = failed()
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (8 << 20)) / torch.cuda.get_device_properties(0).total_memory)
+    try:
+        both(lambda: fptq.fptq_w4a4_linear(xq, wq, M, N, K, 0.4, s, out=next(left)))
+        assert failed() == before + 2
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert all(torch.equal(y, want) for y in outputs)
+
+
 def test_given_outputs_are_filled_and_returned():
     M, N, K = 40, 72, 1024
     x, w, s, r = data(M, N, K)
