@@ -215,12 +215,9 @@ def fptq_w4a4_linear_zp(xq, wq, M, N, K, s_a, s_w, zero_point, w_row_sum, row_ou
     if done is not None:
         return done
     _dev(w_row_sum, torch.int32, "w_row_sum")
-    scratch = _scratch(M, N, K, xq)
-    if scratch is not None:
-        fn = _scratch_call(scratch, int(zero_point), w_row_sum)
-    else:
-        fn = lambda a, b, m, n, k, sa, sw, d, y, acc, st: lib().fptq_w4a4_linear_zp(a, b, m, n, k, sa, sw, d, int(zero_point),
-                                                                                     _ptr(w_row_sum), y, acc, st)
+    fn = lambda a, b, m, n, k, sa, sw, d, y, acc, st: lib().fptq_w4a4_linear_zp(a, b, m, n, k, sa, sw, d, int(zero_point),
+                                                                                 _ptr(w_row_sum), y, acc, st)
+    fn = _with_scratch(fn, _scratch(M, N, K, xq), int(zero_point), w_row_sum)
     return _linear(fn, xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, None)
 
 
@@ -303,6 +300,15 @@ def _scratch_call(scratch, zero_point, w_row_sum):
         a, b, m, n, k, sa, sw, d, zero_point, _ptr(w_row_sum), y, acc, _ptr(scratch), 0 if scratch is None else scratch.numel(), st)
 
 
+def _with_scratch(plain, scratch, zero_point=0, w_row_sum=None):
+    """The entry point `plain`, through the one with scratch if there is some.  What that one refuses it has not begun, and the plain
+    one refuses it in its own name."""
+    if scratch is None:
+        return plain
+    call = _scratch_call(scratch, zero_point, w_row_sum)
+    return lambda *args: call(*args) and plain(*args)
+
+
 def fptq_w4a4_linear_scratch(xq, wq, M, N, K, s_a, s_w, scratch, zero_point=0, w_row_sum=None, row_out_scale=None, out=None,
                              want_acc=False, acc=None):
     """fptq_w4a4_linear / _zp with a uint8 device scratch buffer of the caller (or None)."""
@@ -318,8 +324,7 @@ def fptq_w4a4_linear(xq, wq, M, N, K, s_a, s_w, row_out_scale=None, out=None, wa
     done = None if _native is None else _native.linear(xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc, None, None, None, 0)
     if done is not None:
         return done
-    scratch = _scratch(M, N, K, xq)
-    fn = lib().fptq_w4a4_linear if scratch is None else _scratch_call(scratch, 0, None)
+    fn = _with_scratch(lib().fptq_w4a4_linear, _scratch(M, N, K, xq))
     return _linear(fn, xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc)
 
 
@@ -336,14 +341,15 @@ def fptq_w4a4_linear_ws(xq, wq, M, N, K, s_a, s_w, workspace, row_out_scale=None
     if workspace is not None:
         _dev(workspace, torch.uint8, "workspace")
     # no split over K: the plain layer (a misaligned workspace is still refused, below)
-    if M > 64 and (workspace is None or workspace.data_ptr() % 256 == 0) and lib().fptq_linear_workspace_bytes(M, N, K) == 0:
-        return fptq_w4a4_linear(xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc)
-    if workspace is not None:
-        done = None if _native is None else _native.linear(xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc, None, None, workspace, 1)
+    plain = M > 64 and (workspace is None or workspace.data_ptr() % 256 == 0) and lib().fptq_linear_workspace_bytes(M, N, K) == 0
+    if plain or workspace is not None:
+        done = None if _native is None else _native.linear(xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc, None, None, workspace, 0 if plain else 1)
         if done is not None:
             return done
     fn = lambda a, b, m, n, k, sa, sw, d, y, ac, st: lib().fptq_w4a4_linear_ws(
         a, b, m, n, k, sa, sw, d, y, ac, _ptr(workspace), 0 if workspace is None else workspace.numel(), st)
+    if plain:
+        fn = _with_scratch(fn, _scratch(M, N, K, xq))
     return _linear(fn, xq, wq, M, N, K, s_a, s_w, row_out_scale, out, want_acc, acc)
 
 

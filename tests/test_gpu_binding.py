@@ -153,6 +153,22 @@ def test_none_is_no_value_for_a_block_or_a_zero_point(both):
         assert both(refused) == (True, True)
 
 
+@pytest.mark.parametrize("call", ["fptq_w4a4_linear", "fptq_w4a4_linear_zp", "fptq_w4a4_linear_ws", "fptq_w4a4_linear_noalloc"])
+def test_a_refusal_names_the_call_that_was_made(both, call):
+    """Whatever memory the wrapper would have brought along, the message is that of the entry point of the wrapper's name."""
+    M, N, K = 2048, 22016, 4096
+    assert fptq.fptq_linear_scratch_bytes(M, N, K) > 0
+    xq, wq = (torch.empty(fptq.fptq_packed_bytes(rows, K), dtype=torch.uint8, device="cuda") for rows in (M, N))
+    s, sums = torch.ones(N, device="cuda"), torch.zeros(N, dtype=torch.int32, device="cuda")
+    more = {"fptq_w4a4_linear_zp": (3, sums), "fptq_w4a4_linear_ws": (None,)}.get(call, ())
+
+    def message():
+        with pytest.raises(fptq.FptqError) as e:
+            getattr(fptq, call)(xq, wq, M, N, K, -1.0, s, *more)
+        return str(e.value)
+    assert both(message) == 2 * (f"FPTQ_ERR_VALUE: {call}: s_a must be finite and > 0",)
+
+
 def test_other_threads_run_during_a_call():
     """The interpreter lock is free while the library launches.  With a switch interval of minutes a thread that wants it gets in only
     where a call lets go of it."""
