@@ -5,6 +5,7 @@ every call raises -- there is no CPU fallback.
 """
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -87,7 +88,11 @@ def lib():
         L.fptq_linear_scratch_bytes.argtypes = [i64, i64, i64]
         L.fptq_w4a4_linear_scratch.restype = i32
         L.fptq_w4a4_linear_scratch.argtypes = [p, p, i64, i64, i64, f32, p, p, i32, p, p, p, p, i64, p]
-        from . import _native as native      # built next to this file, with the library
+        try:
+            from . import _native as native      # built next to this file, with the library
+        except ImportError as e:                 # only the library was built, or for another torch: the Python path makes the same calls
+            warnings.warn(f"the binding's native fast path cannot be loaded, calls take about 6 us longer: {e}", RuntimeWarning, stacklevel=2)
+            native = None
         _lib, _native = L, native
     return _lib
 

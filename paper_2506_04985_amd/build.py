@@ -33,8 +33,8 @@ def _compile(src):
 def _native_command(obj):
     import torch
     from torch.utils import cpp_extension
-    inc = [f for d in [INCLUDE, *cpp_extension.include_paths(), sysconfig.get_paths()["include"]] for f in ("-I", d)]
-    return ["g++", "-O2", "-std=c++17", "-fPIC", "-w", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc,
+    inc = ["-I", INCLUDE] + [f for d in [*cpp_extension.include_paths(), sysconfig.get_paths()["include"]] for f in ("-isystem", d)]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-Wextra", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc,
             "-c", os.path.join(CSRC, NATIVE_SOURCE), "-o", obj]
 
 
@@ -51,7 +51,7 @@ def build(verbose: bool = False) -> str:
         native = ex.submit(subprocess.run, _native_command(native_obj), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         results = list(ex.map(_compile, SOURCES + PROBE_SOURCES))
     if verbose:
-        for _, out in results:
+        for _, out in [*results, ("", native.result().stdout)]:
             if out.strip():
                 print(out)
     objs = [o for o, _ in results]
