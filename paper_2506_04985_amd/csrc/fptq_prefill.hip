@@ -11,9 +11,9 @@
 // Data flow.  A small kernel first widens the packed activations to six bits in a scratch buffer of the caller (0.75 bytes a
 // value, read and written once: 16 us at 8192 x 8192 beside 1790 us of product), with their signs resolved, and sums each
 // token's codes.  The matrix kernel copies those to LDS with buffer loads that write LDS directly, and reads the weights as
-// they are, packed, straight into registers: each of its four waves owns 64 channels and all tokens of the tile (256 or 128), so a
-// weight is loaded by one wave only and needs no LDS, and its nibbles are spread to six-bit fields by 18 VALU instructions per
-// 32 values, 2.25 per MFMA.  Widening both operands in the kernel would take 5.7 VALU instructions per MFMA, and one wave
+// they are, packed: each of its four waves owns 64 channels and all tokens of the tile (256 or 128), so a weight is loaded by one
+// wave only, into registers (256 tokens) or through LDS of the wave's own (128), and its nibbles are spread to six-bit fields by
+// 18 VALU instructions per 32 values, 2.25 per MFMA.  Widening both operands in the kernel would take 5.7 VALU instructions per MFMA, and one wave
 // per SIMD issues at most eight instructions in the 32 cycles of an MFMA: measured at the INT8 loop's rate.  Widening the
 // weights beforehand as well would cost 1.25 bytes of traffic per weight and call, 5 % at 8192 tokens.
 //
@@ -132,19 +132,26 @@ __global__ __launch_bounds__(64 * CV_WAVES) void widen_activations_kernel(const 
 }
 
 // Tile 256 (n) x 32 TM (m), four waves of 64 x 32 TM, 32 TM accumulator registers a lane, one workgroup per CU.  K tile 128.  STAGES K
-// tiles of activations in an LDS ring, DEPTH K tiles of packed weights in registers.  256 tokens (TM = 8) widen each weight
+// tiles of activations in an LDS ring; of packed weights DEPTH K tiles in registers, or (W_LDS) the ring's STAGES.  In operand order a
+// load touches 32 rows, a quarter of each row's 64 bytes twice, and every line is touched by two loads: four times the tag lookups of
+// a contiguous copy, which by all signs bounds what a CU has in flight.  A large tile's MFMAs cover that; on a small one the latency of HBM showed,
+// with three and with six K tiles ahead: 1000 x 5120 x 13824 took 73 us on weights from HBM (53 from the last-level cache), 589 x 7391 x
+// 17552 91 (67); copied to LDS as they lie and read back 61 (52) and 77 (62).  Where the CUs are full and the weights are in
+// the cache the extra LDS traffic costs up to 4 % (2048 x 4096 x 11008 54 -> 56, from HBM 63 -> 57).  256 tokens (TM = 8) widen each weight
 // for eight MFMAs, 128 (TM = 4) for four and load twice the weights per operation; they are for problems that the large tile cuts
 // into fewer pieces than there are CUs: 1000 x 5120 x 13824 takes 59 us with them, 84 without and 77 on INT8 tiles, 2048 x 4096 x
 // 11008 58, 69 and 68, but 4096 x 28672 x 4096 297, 262 and 340.
 template <int TM_>
 struct PrefillTile {
     static constexpr int TN = 2, TM = TM_, STAGES = 5, DEPTH = 3;
+    static constexpr bool W_LDS = TM == 4;          // five stages of both operands are 140 of the 160 KB of LDS; the large tile's would not fit
     static constexpr int BN = 4 * TN * 32, BM = TM * 32;
-    static constexpr int STAGE_BYTES = BM * (X6_BLOCK / X6_ROWS);                               // 3 KB per 32 tokens
-    static constexpr int FILLS = STAGE_BYTES / 4096, W_LOADS = 2 * TN, LOADS = FILLS + W_LOADS; // vector loads of a wave per K tile
+    static constexpr int X_BYTES = BM * (X6_BLOCK / X6_ROWS), W_BYTES = TN * 32 * SEG;          // 3 KB per 32 tokens; a wave's 4 KB of weights
+    static constexpr int STAGE_BYTES = X_BYTES + (W_LDS ? 4 * W_BYTES : 0);
+    static constexpr int FILLS = X_BYTES / 4096, W_LOADS = 2 * TN, LOADS = FILLS + W_LOADS;     // vector loads of a wave per K tile
     static constexpr int RING_BYTES = STAGES * STAGE_BYTES, LDS_BYTES = RING_BYTES + (2 * BN + BM) * 4;
     static_assert(TM == 8 || TM == 4, "the loads and the widening are dealt to eight or four MFMA groups by hand");
-    static_assert(DEPTH >= STAGES - 3 && DEPTH <= STAGES - 1, "the wait counts assume weights and fills issued in the loop's order from the start");
+    static_assert(W_LDS || (DEPTH >= STAGES - 3 && DEPTH <= STAGES - 1), "the wait counts assume weights and fills issued in the loop's order from the start");
 };
 
 typedef __bf16 p_bf16x2_t __attribute__((ext_vector_type(2)));
@@ -190,7 +197,7 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
 
     // ---- activations, HBM -> LDS: one run of 3 TM KB per K tile, a quarter of it per wave.  Past the last K tile the descriptor is
     // empty: the loads are still issued (the wait counts stay the same) and land as zeros.
-    const int x_voff = bm * C::STAGE_BYTES + wave * (C::FILLS * 1024) + lane * 16;
+    const int x_voff = bm * C::X_BYTES + wave * (C::FILLS * 1024) + lane * 16;
     uint8_t *const fill_base = lds + wave * (C::FILLS * 1024);
     auto fill1 = [&](auto jc, __amdgpu_buffer_rsrc_t r, uint8_t *to) {
         constexpr int J = decltype(jc)::value;     // 1 KB; the instruction's offset moves both addresses
@@ -199,13 +206,32 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     auto slab_desc = [&](const uint8_t *p, int64_t bytes, bool in) {
         return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, in ? (int)bytes : 0, P_RSRC_FLAGS);
     };
-    // ---- weights, HBM -> registers: lane (fi, fg) loads half fg (granules 2 fg, 2 fg + 1) of row nw0 + 32 t + fi, the k values of
+    // ---- weights, HBM -> registers (W_LDS: LDS -> registers): lane (fi, fg) loads half fg (granules 2 fg, 2 fg + 1) of row nw0 + 32 t + fi, the k values of
     // the activations' half fg; rows past N read as zero
     const int64_t w_slab = (int64_t)N * SEG;
     const int w_voff = (nw0 + fi) * SEG + fg * 32;
-    v4i raw[C::DEPTH][2][C::TN];
+    constexpr int RAWS = C::W_LDS ? 2 : C::DEPTH;          // sets of packed weights: being widened and being read, or in flight
+    v4i raw[RAWS][2][C::TN];
     auto load_w1 = [&](__amdgpu_buffer_rsrc_t r, int s, int t) {
         return __builtin_amdgcn_raw_buffer_load_b128(r, w_voff + t * (32 * SEG) + s * 16, 0, 0);
+    };
+    // W_LDS: a wave first copies the 4 KB of its rows as they lie in HBM to its own part of the ring's stage, behind the activations, the
+    // 16-byte granules of a row permuted (granule g of row r in slot g ^ (r / 4) % 4) so that the reads back are free of bank conflicts.
+    const int w_lane = (nw0 + (lane >> 2)) * SEG + (((lane & 3) ^ ((lane >> 4) & 3)) << 4);
+    uint8_t *const w_fill_base = lds + C::X_BYTES + wave * C::W_BYTES;
+    auto w_fill1 = [&](auto jc, __amdgpu_buffer_rsrc_t r, uint8_t *to) {
+        constexpr int J = decltype(jc)::value;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, P_LDS_PTR(to), 16, w_lane, 0, J * 1024, 0);
+    };
+    lds_u8 *const w_base = (lds_u8 *)lds + C::X_BYTES + wave * C::W_BYTES + fi * SEG;
+    const int w_slot0 = ((2 * fg) ^ ((fi >> 2) & 3)) << 4;
+    auto read_w = [&](int stage_off, v4i (&r)[2][C::TN]) {
+#pragma unroll
+        for (int t = 0; t < C::TN; ++t) {
+            lds_u8 *const p = w_base + stage_off + t * (32 * SEG);
+            r[0][t] = *(lds_v4i *)(p + w_slot0);
+            r[1][t] = *(lds_v4i *)(p + (w_slot0 ^ 16));
+        }
     };
     // ---- fragments: the 48 bytes of token 32 x + fi, half fg; the first 24 feed MFMA step 0, the others step 1
     lds_u8 *const x_base = (lds_u8 *)lds + fg * (3 * X6_PLANE) + fi * 16;
@@ -235,14 +261,20 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     const float cw0 = s_w[cn], zw0 = ZP ? (float)(zp * wsum[cn]) : 0.0f;
     const float d0 = d && tid < C::BM ? d[min(m0 + tid, M - 1)] : 1.0f;
 
-    // ---- prologue: the loop's loads in the loop's order (iteration j issues the weights of tile j + DEPTH, then the fill of tile
-    // j + STAGES - 1), from an empty pipeline
+    // ---- prologue: the loop's loads in the loop's order (iteration j issues the weights of tile j + DEPTH, with W_LDS of tile
+    // j + STAGES - 1, then the fill of tile j + STAGES - 1), from an empty pipeline
     const uint8_t *wp = wq, *xp = x6;              // next tile to load; they run past the end with empty descriptors
     int w_left = ktiles, x_left = ktiles;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 1 - C::STAGES; j < 0; ++j) {
-        if (j + C::DEPTH >= 0) {
+        if constexpr (C::W_LDS) {
+            const __amdgpu_buffer_rsrc_t r = slab_desc(wp, w_slab, w_left-- > 0);
+            wp += w_slab;
+            uint8_t *const to = w_fill_base + (j + C::STAGES - 1) * C::STAGE_BYTES;
+            w_fill1(std::integral_constant<int, 0>(), r, to), w_fill1(std::integral_constant<int, 1>(), r, to);
+            w_fill1(std::integral_constant<int, 2>(), r, to), w_fill1(std::integral_constant<int, 3>(), r, to);
+        } else if (j + C::DEPTH >= 0) {
             const __amdgpu_buffer_rsrc_t r = slab_desc(wp, w_slab, w_left-- > 0);
             wp += w_slab;
             v4i(&rl)[2][C::TN] = raw[j + C::DEPTH < 0 ? 0 : j + C::DEPTH];
@@ -277,7 +309,8 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     if (ZP) zwbuf[tid] = zw0;
     if (tid < C::BM) dbuf[tid] = d0;
     __builtin_amdgcn_s_waitcnt(P_WAIT_LGKM0);
-    __builtin_amdgcn_s_waitcnt(p_waitcnt_vm(C::FILLS * (C::STAGES - 2)));      // at least that many fills are younger than tile 0's
+    // weights in registers: at least that many fills are younger than tile 0's; through LDS: tile 1's weights are in as well
+    __builtin_amdgcn_s_waitcnt(p_waitcnt_vm(C::W_LDS ? C::LOADS * (C::STAGES - 3) : C::FILLS * (C::STAGES - 2)));
     __builtin_amdgcn_s_barrier();
     v8i W[2][2][C::TN];                            // widened weights of this K tile and of the next one: [tile][step][t]
     auto widen_half = [&](const v4i (&r)[2][C::TN], v8i (&w)[2][C::TN], int h) {   // 16 of the 128 values a lane widens per K tile
@@ -289,6 +322,7 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     };
 #pragma unroll
     for (int x = 0; x < C::TM - 1; ++x) read_x(0, x);
+    if constexpr (C::W_LDS) read_w(0, raw[0]), read_w(C::STAGE_BYTES, raw[1]);
 #pragma unroll
     for (int h = 0; h < 8; ++h) widen_half(raw[0], W[0], h);
     __builtin_amdgcn_sched_barrier(0);
@@ -309,11 +343,17 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         const __amdgpu_buffer_rsrc_t wr = slab_desc(wp, w_slab, w_left > 0), xr = slab_desc(xp, x_slab, x_left > 0);
-        uint8_t *const fill_to = fill_base + off_prev;
-        v4i(&load_to)[2][C::TN] = raw[P % C::DEPTH];       // tile kt's, widened during the previous tile
-        const v4i(&next)[2][C::TN] = raw[(P + 1) % C::DEPTH];
+        uint8_t *const fill_to = fill_base + off_prev, *const w_fill_to = w_fill_base + off_prev;
+        const int off_next2 = off_next + C::STAGE_BYTES == C::RING_BYTES ? 0 : off_next + C::STAGE_BYTES;
+        v4i(&load_to)[2][C::TN] = raw[P % RAWS];           // tile kt's, widened during the previous tile
+        const v4i(&next)[2][C::TN] = raw[(P + 1) % RAWS];
 #pragma unroll
         for (int x = 0; x < C::TM; ++x) {
+            // this wave's weights of tile kt + 2 are in (its own copies: no barrier); younger: an iteration's loads and this one's so far
+            if (C::W_LDS && x == C::TM - 1) {
+                __builtin_amdgcn_s_waitcnt(p_waitcnt_vm(C::LOADS * (C::STAGES - 4) + C::W_LOADS + 2));
+                __builtin_amdgcn_sched_barrier(0);
+            }
             asm("" : "+v"(X[x]));           // keeps the 48 bytes in one run of registers, of which both steps' operands are parts
 #pragma unroll
             for (int s = 0; s < 2; ++s)
@@ -327,8 +367,14 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
             else read_x(off_next, x - 1);
 #pragma unroll
             for (int h = x * (8 / C::TM); h < (x + 1) * (8 / C::TM); ++h) widen_half(next, W[(P + 1) % 2], h);
-            if (x == 0) load_to[0][0] = load_w1(wr, 0, 0), load_to[1][0] = load_w1(wr, 1, 0);
-            if (x == 1) load_to[0][1] = load_w1(wr, 0, 1), load_to[1][1] = load_w1(wr, 1, 1);
+            if constexpr (C::W_LDS) {
+                if (x == 0) w_fill1(std::integral_constant<int, 0>(), wr, w_fill_to), w_fill1(std::integral_constant<int, 1>(), wr, w_fill_to);
+                if (x == 1) w_fill1(std::integral_constant<int, 2>(), wr, w_fill_to), w_fill1(std::integral_constant<int, 3>(), wr, w_fill_to);
+                if (x == C::TM - 1) read_w(off_next2, load_to);
+            } else {
+                if (x == 0) load_to[0][0] = load_w1(wr, 0, 0), load_to[1][0] = load_w1(wr, 1, 0);
+                if (x == 1) load_to[0][1] = load_w1(wr, 0, 1), load_to[1][1] = load_w1(wr, 1, 1);
+            }
             if (x == 2) fill1(std::integral_constant<int, 0>(), xr, fill_to), fill1(std::integral_constant<int, 1>(), xr, fill_to);
             if (x == 3) fill1(std::integral_constant<int, 2>(), xr, fill_to);
             if constexpr (C::FILLS > 3) {
@@ -340,6 +386,7 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
             for (int i = 0; i < 4; ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 if (i < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                if (C::W_LDS && x == C::TM - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                 if (i == 1 || i == 3) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x002, 24 / C::TM, 0);
             }
@@ -349,7 +396,7 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
         --w_left, --x_left;
         off = off_next;
     };
-    // unrolled by six, so that the weights' two and three register sets rotate without copies
+    // unrolled by six, so that the weights' two or three register sets rotate without copies
     int left = ktiles;
 #define FPTQ_TILE(i) tile(std::integral_constant<int, i>())
     for (; left >= 6; left -= 6) FPTQ_TILE(0), FPTQ_TILE(1), FPTQ_TILE(2), FPTQ_TILE(3), FPTQ_TILE(4), FPTQ_TILE(5);
