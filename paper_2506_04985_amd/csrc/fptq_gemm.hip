@@ -740,37 +740,42 @@ static int choose_tile(int64_t M, int64_t N, int64_t K, int cus, double *us = nu
 
 // Whether a problem is faster on the six-bit kernel (fptq_prefill.hip), widening of its activations included, and with how many tokens
 // per tile.  Estimated times on uniform random operands, as above, in rounds of one tile of 256 channels per CU: a partial
-// last round costs less than a full one (the power it leaves speeds its tiles up), and so does a lone one.  Fitted to (us, the
-// better INT8 shape / 256 / 128 tokens)
-//     8192 x 57344 x 8192   2461 / 1712 / 1950        1000 x 5120 x 13824   77 / 84 / 59        333 x 32003 x 2504   32 / 34 / 36
-//     4096 x 28672 x 4096    340 / 262 / 297          2048 x 4096 x 11008   68 / 69 / 58        1024 x 4096 x 14336  54 / 78 / 57
-//     2048 x 22016 x 4096    143 / 112 / 125          4096 x 6144 x 4096    78 / 73 / 70        512 x 8192 x 8192    33 / 50 / 37
-//     4096 x 4096 x 4096      53 / 48 / 50            256 x 28672 x 4096    29 / 34 / 26        2720 x 30592 x 1062  97 / 104 / 108
-// i.e. the small tile wins where the large one leaves CUs without work, and INT8 where even the small one does.  Where the two
-// paths are estimated within 5 % the INT8 shapes keep the problem; within 10 % below 24 K tiles, where stores and launches weigh more
-// than in what the estimates were fitted to (1601 x 23384 x 2472 takes 85 us on INT8 tiles and 89 on six-bit ones).
+// last round costs less than a full one (the power it leaves speeds its tiles up), and so does a lone one.  Fitted to 440 shapes of 65 to
+// 8192 tokens and checked on 220 others, both with the weights read from HBM, as in a model larger than the last-level cache, and with
+// them in that cache, e.g. (us from HBM, the better INT8 shape / 256 / 128 tokens; in brackets from the cache)
+//     4096 x 28672 x 4096   345 / 261 / 312  (339 / 249 / 309)      1000 x 5120 x 13824   63 /  93 / 62  (61 / 73 / 53)
+//     2048 x 22016 x 4096   142 / 107 / 131  (139 / 103 / 128)      2048 x 4096 x 11008   66 /  77 / 60  (65 / 64 / 55)
+//     4096 x 6144 x 4096     78 /  69 /  72  ( 76 /  67 /  71)       589 x 7391 x 17552   76 / 115 / 77  (74 / 90 / 64)
+//      512 x 8192 x 8192     33 /  59 /  40  ( 31 /  48 /  34)       133 x 18816 x 13312  58 /  89 / 62  (56 / 68 / 48)
+// i.e. the small tile wins where the large one leaves CUs without work, and INT8 where even the small one does.  The margins (wider
+// for few K tiles, where stores and launches weigh more than in what the estimates were fitted to) leave six of the 660 more than 5 %
+// slower than INT8 with the weights read from HBM (91 x 55040 x 5808 43 / 55 / 49 is the worst, then 139 x 37504 x 3456 31 / 34 / 40) and
+// one from the cache (the first of these, 36 / 47 / 39).
 int prefill_tile(int64_t M, int64_t N, int64_t K)
 {
     if (K > 131071 || M > (1 << 24) || N > (1 << 24) || forced_gemm_tile() > 0) return 0;
     const int mode = g_prefill.load(std::memory_order_relaxed);
     if (mode == 2) return 0;
     if (mode > 2) return mode;
+    // Half of a tile or more would be padding, and at best it is even: 64 x 57344 x 28672 takes 161 us on INT8 tiles and 159 here, 64 x
+    // 57344 x 8192 50 and 52, 64 x 32000 x 16384 58 and 82, 64 x 28672 x 4096 17 and 27.
+    if (mode == 0 && M <= 64) return 0;
     const int cus = device_cus_or_default();
-    const double kt = (double)k_tiles(K), widen_us = 5.0 + (double)M * (double)K * 1.25 / 5.0e6;
+    const double kt = (double)k_tiles(K), widen_us = (double)M * (double)K * 1.25 / 5.0e6;
     auto rounds = [&](int tokens, double lone, double least) {
         const double x = (double)prefill_workgroups(M, N, tokens) / (double)cus, part = x - floor(x);
         return x < 1.0 ? lone + (1.0 - lone) * x : floor(x) + (part > 0.0 ? least + (1.0 - least) * part : 0.0);
     };
-    const double us256 = widen_us + rounds(256, 0.50, 0.75) * (12.0 + 0.76 * kt);
-    double us128 = widen_us + rounds(128, 0.75, 0.62) * (6.2 + 0.453 * kt);
+    const double us256 = 5.1 + widen_us + rounds(256, 0.60, 0.62) * (10.7 + 0.768 * kt);
+    double us128 = 5.0 + widen_us + rounds(128, 0.80, 0.60) * (6.4 + 0.478 * kt);
     // A single row of tiles streams its weights once, from HBM: with few workgroups that is bound by what one CU keeps in flight
-    // (119 x 32856 x 18822, 129 workgroups: 106 us against 92; 123 x 54336 x 5992, 213 workgroups: 34 against 39).
+    // (96 x 37397 x 17536, 147 workgroups: 92 us against 85 on INT8 tiles; 96 x 57344 x 8192, 224 workgroups: 53 against 53).
     if (M <= 128 && 4 * prefill_workgroups(M, N, 128) < 3 * cus) us128 = us256;
     const int tokens = us128 < us256 ? 128 : 256;
     if (mode == 1) return tokens;
     double int8_us = 0.0;
     choose_tile(M, N, K, cus, &int8_us);
-    return fmin(us128, us256) < (kt < 24 ? 0.90 : 0.95) * int8_us ? tokens : 0;
+    return fmin(us128, us256) < (kt < 32 ? 0.90 : 0.94) * int8_us ? tokens : 0;
 }
 
 // Limits of the MFMA kernel: the widened accumulator is 256 * acc with |acc| <= 64 K, and one K tile of all rows

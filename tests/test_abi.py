@@ -107,3 +107,22 @@ def test_testing_knobs_validate_and_the_launch_plan_is_host_arithmetic():
     assert plan(300, 300, 200000)[0] == "linear_ref_kernel"
     with pytest.raises(fptq.FptqError):
         plan(0, 4, 4)
+
+
+@pytest.mark.parametrize("M,N,K,tokens", [
+    # up to 64 tokens at least half of a tile would be padding
+    (40, 57344, 28672, 0), (64, 57344, 8192, 0), (64, 128256, 8192, 0),
+    # faster on INT8 tiles, more so with the weights read from HBM than with the weights in the last-level cache
+    (257, 11136, 5856, 0), (130, 20224, 5376, 0), (161, 19733, 3584, 0), (222, 17344, 5874, 0), (1024, 6144, 4096, 0), (256, 22016, 4096, 0),
+    (1050, 18832, 3072, 0), (512, 8192, 8192, 0),
+    # faster on six-bit tiles from either
+    (96, 57344, 8192, 128), (1000, 5120, 13824, 128), (2048, 4096, 11008, 128), (4096, 6144, 4096, 256), (4096, 28672, 4096, 256), (2048, 22016, 4096, 256)])
+def test_where_the_six_bit_kernel_is_taken(M, N, K, tokens):
+    """Measured on an MI355X, a matrix at a time, with the weights cycled through copies that no cache holds and with one copy."""
+    plan = fptq.fptq_linear_launch_plan(M, N, K, with_scratch=True)
+    tiles = lambda a, b: -(-a // b)
+    if tokens:
+        assert plan == ("linear_prefill_kernel", tiles(M, tokens) * tiles(N, 256), 256)
+    else:
+        assert plan == fptq.fptq_linear_launch_plan(M, N, K)
+    assert (fptq.fptq_linear_scratch_bytes(M, N, K) > 0) == (tokens > 0)
