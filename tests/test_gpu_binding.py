@@ -65,13 +65,46 @@ def test_every_call_gives_the_same(both, M):
         same(*both(f))
 
 
-def test_split_k_workspace_and_scratch_shapes(both):
-    for M, N, K in ((256, 512, 6272), (2048, 22016, 1024)):
-        x, w, s, r = data(M, N, K)
-        wq, xq = fptq.fptq_pack_weights(w), fptq.fptq_quantize_act(x, 0.4, 2, 0.0, r)[0]
-        ws = torch.zeros(max(256, fptq.fptq_linear_workspace_bytes(M, N, K)), dtype=torch.uint8, device="cuda")
-        same(*both(lambda: fptq.fptq_w4a4_linear_ws(xq, wq, M, N, K, 0.4, s, ws, r)))
-        same(*both(lambda: fptq.fptq_w4a4_linear(xq, wq, M, N, K, 0.4, s, r)))
+def test_split_k_workspace_shapes(both):
+    M, N, K = 256, 512, 6272
+    x, w, s, r = data(M, N, K)
+    wq, xq = fptq.fptq_pack_weights(w), fptq.fptq_quantize_act(x, 0.4, 2, 0.0, r)[0]
+    need = fptq.fptq_linear_workspace_bytes(M, N, K)
+    assert need > 0
+    ws = torch.zeros(need, dtype=torch.uint8, device="cuda")
+    same(*both(lambda: fptq.fptq_w4a4_linear_ws(xq, wq, M, N, K, 0.4, s, ws, r)))
+    same(*both(lambda: fptq.fptq_w4a4_linear(xq, wq, M, N, K, 0.4, s, r)))
+
+
+@pytest.mark.parametrize("M,N,K", [(2048, 22016, 4096), (1000, 5120, 13824)])
+def test_scratch_shapes(both, M, N, K):
+    """Calls that bring scratch along, on either path, give what the call without any gives; captured, they go without."""
+    assert fptq.fptq_linear_scratch_bytes(M, N, K) > 0 and fptq.fptq_linear_workspace_bytes(M, N, K) == 0
+    x, w, s, r = data(M, N, K)
+    wq, sums = fptq.fptq_pack_weights(w), fptq.fptq_weight_row_sums(w)
+    xq, xz = fptq.fptq_quantize_act(x, 0.4, 2, 0.0, r)[0], fptq.fptq_quantize_act_asym(x, 0.4, 3, 2, 0.0, r)[0]
+    ws = torch.zeros(256, dtype=torch.uint8, device="cuda")
+    want = fptq.fptq_w4a4_linear_noalloc(xq, wq, M, N, K, 0.4, s, r)
+    for f in (lambda: fptq.fptq_w4a4_linear(xq, wq, M, N, K, 0.4, s, r), lambda: fptq.fptq_w4a4_linear_ws(xq, wq, M, N, K, 0.4, s, ws, r),
+              lambda: fptq.fptq_w4a4_linear_ws(xq, wq, M, N, K, 0.4, s, None, r), lambda: fptq.fptq_w4a4_linear_zp(xq, wq, M, N, K, 0.4, s, 0, sums, r)):
+        native, python = both(f)
+        same(native, want), same(python, want)
+    fptq.fptq_set_linear_prefill(2)
+    want_z = fptq.fptq_w4a4_linear_zp(xz, wq, M, N, K, 0.4, s, 3, sums, r, want_acc=True)
+    fptq.fptq_set_linear_prefill(0)
+    native, python = both(lambda: fptq.fptq_w4a4_linear_zp(xz, wq, M, N, K, 0.4, s, 3, sums, r, want_acc=True))
+    same(native, want_z), same(python, want_z)
+    y, yz = torch.zeros_like(want), torch.zeros_like(want)
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        fptq.fptq_w4a4_linear(xq, wq, M, N, K, 0.4, s, r, out=y)
+        fptq.fptq_w4a4_linear_zp(xz, wq, M, N, K, 0.4, s, 3, sums, r, out=yz)
+    for _ in range(3):
+        y.zero_(), yz.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        same(y, want), same(yz, want_z[0])
 
 
 def test_without_memory_for_scratch_the_call_goes_without(both):

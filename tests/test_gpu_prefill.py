@@ -71,6 +71,28 @@ def test_longest_sums_of_the_largest_products(forced, K, x, w):
     assert torch.equal(acc, ref)
 
 
+@pytest.mark.parametrize("zp", [-8, 7])
+@pytest.mark.parametrize("x,w", [(-8, -8), (7, -8), (-8, 7), (7, 7)])
+def test_zero_point_of_the_longest_sums(forced, x, w, zp):
+    """acc - z sum_k w reaches 120 K, 15 / 16 of 2^24 at the largest K: still an exact integer in fp32, where the INT8 kernel's limit is
+    half the K.  Against the epilogue's definition on host integers, and the simple kernel."""
+    M, N, K = 70, 40, 131071
+    xi = torch.full((M, K), x, dtype=torch.int8, device="cuda")
+    wi = torch.full((N, K), w, dtype=torch.int8, device="cuda")
+    xi[torch.arange(M), torch.arange(M) * 1801] = 1
+    wi[torch.arange(N), K - 1 - torch.arange(N) * 3203] = -1
+    xq, wq, sums = fptq.fptq_pack_weights(xi), fptq.fptq_pack_weights(wi), fptq.fptq_weight_row_sums(wi)
+    s_w, d = torch.rand(N, device="cuda") * 0.015 + 0.005, torch.rand(M, device="cuda") + 0.5
+    y, acc = fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, 0.37, s_w, scratch_for(M, N, K), zp, sums, d, want_acc=True)
+    fptq.fptq_set_linear_prefill(2)
+    y_ref, acc_ref = fptq.fptq_w4a4_linear_zp(xq, wq, M, N, K, 0.37, s_w, zp, sums, d, want_acc=True)
+    assert torch.equal(acc, acc_ref) and torch.equal(y.view(torch.int16), y_ref.view(torch.int16))
+    exact = acc_ref.cpu().long() - zp * wi.cpu().long().sum(1)
+    assert int(exact.abs().max()) < 1 << 24
+    cw = torch.tensor(0.37, dtype=torch.float32) * s_w.cpu()
+    assert torch.equal(y.cpu(), (exact.float() * cw * d.cpu()[:, None]).to(torch.bfloat16))
+
+
 def test_random_rows_of_the_longest_sums(forced):
     M, N, K = 66, 264, 131071
     torch.manual_seed(4)
