@@ -86,6 +86,29 @@ hipError_t gemm_device_init(DeviceInfo *info);
 hipError_t prefill_device_init();
 hipError_t hadamard_device_init(int device);
 
+// ---- what several kernel sources share
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+#define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
+
+// s_waitcnt immediates for gfx9: vmcnt in bits [3:0] and [15:14], expcnt [6:4], lgkmcnt [11:8]
+constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+constexpr int WAIT_LGKM0 = 15 | (3 << 14) | (7 << 4) | (0 << 8);
+
+// raw buffer descriptor, dword 3: 32-bit data format, no swizzle (gfx9 family encoding); reads past num_records return zero
+constexpr int RSRC_FLAGS = 0x00020000;
+
+// two fp32 -> packed bf16 pair (round to nearest even, hardware conversion)
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t pack_bf16(float lo, float hi)
+{
+    float2_t f = {lo, hi};
+    bf16x2_t b = __builtin_convertvector(f, bf16x2_t);
+    return __builtin_bit_cast(uint32_t, b);
+}
+
 // fp32 -> bf16 bit pattern, round to nearest even (NaN stays a quiet NaN)
 __device__ inline uint16_t bf16_rne(float f)
 {

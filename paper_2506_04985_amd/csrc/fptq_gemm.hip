@@ -21,17 +21,7 @@
 
 namespace fptq {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
-
-#define LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
-
-// s_waitcnt immediates for gfx9: vmcnt in bits [3:0] and [15:14], expcnt [6:4], lgkmcnt [11:8]
-constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
-constexpr int WAIT_LGKM0 = 15 | (3 << 14) | (7 << 4) | (0 << 8);
-
-// raw buffer descriptor, dword 3: 32-bit data format, no swizzle (gfx9 family encoding)
-constexpr int RSRC_FLAGS = 0x00020000;
 
 constexpr int MAX_SPLITS = 4;     // K ranges per output tile in the split-K variant
 constexpr int SPLIT_COUNTERS = 1024;   // arrival counters at the start of a split-K workspace (one per output tile)
@@ -79,16 +69,6 @@ __device__ inline v4i widen(int p0, int p1)
     o.z = (p1 << 4) & (int)0xF0F0F0F0;
     o.w = p1 & (int)0xF0F0F0F0;
     return o;
-}
-
-// two fp32 -> packed bf16 pair (round to nearest even, hardware conversion)
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float float2_t __attribute__((ext_vector_type(2)));
-__device__ inline uint32_t pack_bf16(float lo, float hi)
-{
-    float2_t f = {lo, hi};
-    bf16x2_t b = __builtin_convertvector(f, bf16x2_t);
-    return __builtin_bit_cast(uint32_t, b);
 }
 
 // One 1 KB chunk (16 rows) of an operand tile, HBM -> LDS.  J is the chunk number inside the run of

@@ -25,8 +25,6 @@
 
 namespace fptq {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-
 __device__ inline v4i dec_widen(int p0, int p1)
 {
     v4i o;

@@ -27,19 +27,12 @@
 
 namespace fptq {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v12i __attribute__((ext_vector_type(12)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 typedef __attribute__((address_space(3))) const uint8_t lds_u8;
 typedef __attribute__((address_space(3))) const v4i lds_v4i;
-#define P_LDS_PTR(p) ((__attribute__((address_space(3))) void *)(p))
-
-// s_waitcnt immediates for gfx9: vmcnt in bits [3:0] and [15:14], expcnt [6:4], lgkmcnt [11:8]
-constexpr int p_waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
-constexpr int P_WAIT_LGKM0 = 15 | (3 << 14) | (7 << 4) | (0 << 8);
-constexpr int P_RSRC_FLAGS = 0x00020000;        // raw buffer, 32-bit data format, bounds-checked
 
 // ---- six-bit activations in the scratch buffer: blocks of (K tile, 128 rows), 12 KB each, row blocks innermost.  A block is six
 // planes [half][piece][row] of 16-byte pieces: half h of a row holds its values 64 h .. 64 h + 63 as 48 bytes of six-bit
@@ -154,14 +147,6 @@ struct PrefillTile {
     static_assert(W_LDS || (DEPTH >= STAGES - 3 && DEPTH <= STAGES - 1), "the wait counts assume weights and fills issued in the loop's order from the start");
 };
 
-typedef __bf16 p_bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float p_float2_t __attribute__((ext_vector_type(2)));
-__device__ inline uint32_t p_pack_bf16(float lo, float hi)
-{
-    p_float2_t f = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, p_bf16x2_t));
-}
-
 // 32 x 32 x 64, both operands e2m3 (format code 2): 24 bytes, i.e. the first six registers, of each operand are read
 __device__ inline v16f mfma6(v8i w, v8i x, v16f c)
 {
@@ -201,10 +186,10 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     uint8_t *const fill_base = lds + wave * (C::FILLS * 1024);
     auto fill1 = [&](auto jc, __amdgpu_buffer_rsrc_t r, uint8_t *to) {
         constexpr int J = decltype(jc)::value;     // 1 KB; the instruction's offset moves both addresses
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, P_LDS_PTR(to + J / 3 * 3072), 16, x_voff + J / 3 * 3072, 0, J % 3 * 1024, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, LDS_PTR(to + J / 3 * 3072), 16, x_voff + J / 3 * 3072, 0, J % 3 * 1024, 0);
     };
     auto slab_desc = [&](const uint8_t *p, int64_t bytes, bool in) {
-        return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, in ? (int)bytes : 0, P_RSRC_FLAGS);
+        return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, in ? (int)bytes : 0, RSRC_FLAGS);
     };
     // ---- weights, HBM -> registers (W_LDS: LDS -> registers): lane (fi, fg) loads half fg (granules 2 fg, 2 fg + 1) of row nw0 + 32 t + fi, the k values of
     // the activations' half fg; rows past N read as zero
@@ -221,7 +206,7 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     uint8_t *const w_fill_base = lds + C::X_BYTES + wave * C::W_BYTES;
     auto w_fill1 = [&](auto jc, __amdgpu_buffer_rsrc_t r, uint8_t *to) {
         constexpr int J = decltype(jc)::value;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, P_LDS_PTR(to), 16, w_lane, 0, J * 1024, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, LDS_PTR(to), 16, w_lane, 0, J * 1024, 0);
     };
     lds_u8 *const w_base = (lds_u8 *)lds + C::X_BYTES + wave * C::W_BYTES + fi * SEG;
     const int w_slot0 = ((2 * fg) ^ ((fi >> 2) & 3)) << 4;
@@ -308,9 +293,9 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     cwbuf[tid] = s_a * cw0;
     if (ZP) zwbuf[tid] = zw0;
     if (tid < C::BM) dbuf[tid] = d0;
-    __builtin_amdgcn_s_waitcnt(P_WAIT_LGKM0);
+    __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
     // weights in registers: at least that many fills are younger than tile 0's; through LDS: tile 1's weights are in as well
-    __builtin_amdgcn_s_waitcnt(p_waitcnt_vm(C::W_LDS ? C::LOADS * (C::STAGES - 3) : C::FILLS * (C::STAGES - 2)));
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(C::W_LDS ? C::LOADS * (C::STAGES - 3) : C::FILLS * (C::STAGES - 2)));
     __builtin_amdgcn_s_barrier();
     v8i W[2][2][C::TN];                            // widened weights of this K tile and of the next one: [tile][step][t]
     auto widen_half = [&](const v4i (&r)[2][C::TN], v8i (&w)[2][C::TN], int h) {   // 16 of the 128 values a lane widens per K tile
@@ -339,7 +324,7 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
         const int off_prev = off == 0 ? C::RING_BYTES - C::STAGE_BYTES : off - C::STAGE_BYTES;
         // this wave's part of tile kt + 1 has landed (younger: whole iterations of loads); the barrier extends that to every
         // wave's part, and says every wave has read all of tile kt - 1
-        __builtin_amdgcn_s_waitcnt(p_waitcnt_vm(C::LOADS * (C::STAGES - 3)));
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(C::LOADS * (C::STAGES - 3)));
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         const __amdgpu_buffer_rsrc_t wr = slab_desc(wp, w_slab, w_left > 0), xr = slab_desc(xp, x_slab, x_left > 0);
@@ -351,7 +336,7 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
         for (int x = 0; x < C::TM; ++x) {
             // this wave's weights of tile kt + 2 are in (its own copies: no barrier); younger: an iteration's loads and this one's so far
             if (C::W_LDS && x == C::TM - 1) {
-                __builtin_amdgcn_s_waitcnt(p_waitcnt_vm(C::LOADS * (C::STAGES - 4) + C::W_LOADS + 2));
+                __builtin_amdgcn_s_waitcnt(waitcnt_vm(C::LOADS * (C::STAGES - 4) + C::W_LOADS + 2));
                 __builtin_amdgcn_sched_barrier(0);
             }
             asm("" : "+v"(X[x]));           // keeps the 48 bytes in one run of registers, of which both steps' operands are parts
@@ -407,8 +392,8 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     if (left > 4) FPTQ_TILE(4);
 #undef FPTQ_TILE
     __builtin_amdgcn_s_setprio(0);
-    __builtin_amdgcn_s_waitcnt(p_waitcnt_vm(0));   // drain the tail loads before LDS is reused
-    __builtin_amdgcn_s_waitcnt(P_WAIT_LGKM0);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the tail loads before LDS is reused
+    __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
     __builtin_amdgcn_s_barrier();
 
     // ---- epilogue.  Weights were the A operand: a lane owns token fi of each 32 and, per register quad q, four consecutive
@@ -440,7 +425,7 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
                     yf[e] = (ZP ? __builtin_fmaf(a, 64.0f, -zw[e]) : a * 64.0f) * cw[e];
                     if (d) yf[e] = yf[e] * dm;
                 }
-                *reinterpret_cast<uint2 *>(patch + fi * PATCH_STRIDE + c0 * 2) = make_uint2(p_pack_bf16(yf[0], yf[1]), p_pack_bf16(yf[2], yf[3]));
+                *reinterpret_cast<uint2 *>(patch + fi * PATCH_STRIDE + c0 * 2) = make_uint2(pack_bf16(yf[0], yf[1]), pack_bf16(yf[2], yf[3]));
             }
         __builtin_amdgcn_wave_barrier();
 #pragma unroll

@@ -46,7 +46,6 @@ __device__ inline void store_word(uint8_t *out, int64_t M, int64_t t, int64_t k0
 
 typedef unsigned int q_v4u __attribute__((ext_vector_type(4)));
 constexpr int Q_STREAM = 2;      // buffer-load cache policy: non-temporal
-constexpr int Q_RSRC_FLAGS = 0x00020000;     // raw buffer, bounds-checked: reads past num_records return zero
 
 // One workgroup per row.  CH > 0: K % 8 == 0, 16-byte aligned rows of at most 2048 * CH values, kept in
 // registers (CH 16-byte chunks per thread) between the reduction and the quantizer and read through a row-sized
@@ -65,7 +64,7 @@ __global__ __launch_bounds__(QT) void quantize_act_kernel(const uint16_t *__rest
 
     q_v4u regs[CH > 0 ? CH : 1];
     if (CH > 0) {
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)row, 0, (int)K * 2, Q_RSRC_FLAGS);
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)row, 0, (int)K * 2, RSRC_FLAGS);
         if (stream_in) {         // an input larger than the last-level cache: streaming loads, which do not displace what is there
 #pragma unroll
             for (int i = 0; i < CH; ++i) regs[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (i * QT + tid) * 16, 0, Q_STREAM);
@@ -141,7 +140,7 @@ __global__ __launch_bounds__(QT) void quantize_act_wave_kernel(const uint16_t *_
     const int64_t t = (int64_t)blockIdx.x * (QT / 64) + wave;
     if (t >= M) return;
     const int Ki = (int)K, Kpad = (int)(k_tiles(K) * KT);
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)(x + t * K), 0, Ki * 2, Q_RSRC_FLAGS);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)(x + t * K), 0, Ki * 2, RSRC_FLAGS);
 
     q_v4u regs[CH];
     if (stream_in) {
@@ -208,7 +207,7 @@ __global__ __launch_bounds__(QT) void quantize_act_dynamic_kernel(const uint16_t
     q_v4u regs[CH > 0 ? CH : 1];
     uint32_t mx = 0;
     if (CH > 0) {      // the row through a row-sized buffer descriptor: chunks past its end read as zero
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)row, 0, (int)K * 2, Q_RSRC_FLAGS);
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)row, 0, (int)K * 2, RSRC_FLAGS);
 #pragma unroll
         for (int i = 0; i < CH; ++i) regs[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (i * 64 + lane) * 16, 0, 0);
 #pragma unroll
@@ -260,7 +259,7 @@ __global__ __launch_bounds__(QT) void quantize_act_dynamic_row_kernel(const uint
     const int64_t t = blockIdx.x;
     const int tid = threadIdx.x;
     const int64_t Kpad = k_tiles(K) * KT;
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)(x + t * K), 0, (int)K * 2, Q_RSRC_FLAGS);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)(x + t * K), 0, (int)K * 2, RSRC_FLAGS);
     q_v4u regs[CH];
 #pragma unroll
     for (int i = 0; i < CH; ++i) regs[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (i * QT + tid) * 16, 0, 0);

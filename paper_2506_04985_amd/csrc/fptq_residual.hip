@@ -13,13 +13,6 @@ namespace fptq {
 __device__ inline float r_bf16_to_f32(uint32_t bits) { return __uint_as_float(bits << 16); }
 
 typedef unsigned int r_v4u __attribute__((ext_vector_type(4)));
-typedef __bf16 r_bf16x2 __attribute__((ext_vector_type(2)));
-typedef float r_float2 __attribute__((ext_vector_type(2)));
-__device__ inline uint32_t r_pack_bf16(float lo, float hi)
-{
-    r_float2 f = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, r_bf16x2));
-}
 
 // WPR waves per row: 1 (four rows per workgroup; no LDS, no barrier: for many short rows) or 4 (a workgroup per
 // row).  CH > 0: K % 8 == 0, K <= 512 * WPR * CH, rows 16-byte aligned, z kept in registers.
@@ -91,7 +84,7 @@ __global__ __launch_bounds__(256) void residual_norm_quantize_kernel(const uint1
             uint32_t word = 0, o[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                o[j] = r_pack_bf16(z[i][2 * j] * inv, z[i][2 * j + 1] * inv);
+                o[j] = pack_bf16(z[i][2 * j] * inv, z[i][2 * j + 1] * inv);
                 word |= quant_code(z[i][2 * j], c, 8) << (8 * j);
                 word |= quant_code(z[i][2 * j + 1], c, 8) << (8 * j + 4);
             }
@@ -108,7 +101,7 @@ __global__ __launch_bounds__(256) void residual_norm_quantize_kernel(const uint1
                 const int64_t k = k0 + e;
                 if (k < K) {
                     const float v = r_bf16_to_f32(xrow[k]) + r_bf16_to_f32(yrow[k]);
-                    orow[k] = (uint16_t)(r_pack_bf16(v * inv, 0.0f) & 0xffffu);
+                    orow[k] = (uint16_t)(pack_bf16(v * inv, 0.0f) & 0xffffu);
                     word |= (quant_code(v, c, 8) ^ 8u) << (4 * e);
                 }
             }
