@@ -41,6 +41,15 @@ int64_t fptq_probe_mfma_rate(int iters, int dense, int32_t *out, void *stream);
 int64_t fptq_probe_mfma_rate_ex(int iters, int operands, int workgroups_per_cu, int32_t *out, void *stream);
 
 /*
+ * The six-bit counterpart: 256 workgroups of 4 waves, each wave issuing iters x 32 v_mfma_f32_32x32x64_f8f6f4 on e2m3 operands that hold
+ * the integers of the six-bit linear kernel: all zero (dense = 0) or random INT4 (1), the same for the whole run.  lds_reads = 1 reads the
+ * activation operands from LDS as that kernel does (24 16-byte reads per 32 instructions), 0 keeps them in registers.
+ *   out  device, 65536 int32: receives a checksum per thread.
+ * Returns the number of operations launched (> 0) or a negative error.
+ */
+int64_t fptq_probe_mfma6_rate(int iters, int dense, int lds_reads, int32_t *out, void *stream);
+
+/*
  * Streams `bytes` (a multiple of 16; src 16-byte aligned) once and XORs all 16-byte words into xor4 (device,
  * 4 int32, which the caller zeroes first), component by component.
  */

@@ -110,6 +110,102 @@ __global__ __launch_bounds__(256) void probe_mfma_kernel(int iters, int dense, i
     out[blockIdx.x * 256 + threadIdx.x] = r;
 }
 
+// The six-bit counterpart, on the shape of the six-bit linear kernel: 32 v_mfma_f32_32x32x64_f8f6f4 per iteration and wave, 256 tokens by
+// 64 channels.  Weights (w + 8 of random INT4, e2m3 in units of 1/8) stay in registers; activations (random INT4 as six-bit sign and
+// magnitude) stay there too or, with LDS_READS, are read from LDS as that kernel reads them: 24 16-byte reads per iteration, from two K
+// tiles of planes [half][piece][128 rows] in turn.
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef int v12i __attribute__((ext_vector_type(12)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+constexpr int P6_PLANE = 2048, P6_BLOCK = 6 * P6_PLANE, P6_STAGE = 2 * P6_BLOCK;
+
+// 64 six-bit fields drawn from seed s: activations -8 .. 7 as sign and magnitude, or weights 0 .. 15
+__device__ inline void p6_fields(uint32_t s, bool weights, uint32_t (&f)[12])
+{
+#pragma unroll
+    for (int i = 0; i < 12; ++i) f[i] = 0;
+#pragma unroll
+    for (int j = 0; j < 64; ++j) {
+        const int code = (int)(probe_hash(s * 64u + j) & 15u), q = code - 8;
+        const uint32_t v = weights ? (uint32_t)code : (q < 0 ? 32u | (uint32_t)-q : (uint32_t)q);
+        const int bit = 6 * j, w = bit / 32, o = bit % 32;
+        f[w] |= v << o;
+        if (o > 26) f[w + 1] |= v >> (32 - o);
+    }
+}
+
+template <bool LDS_READS>
+__global__ __launch_bounds__(256, 1) void probe_mfma6_kernel(int iters, int dense, int32_t *__restrict__ out)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * P6_STAGE];
+    const int tid = threadIdx.x, lane = tid & 63, fi = lane & 31, fg = lane >> 5;
+    for (int i = tid; i < 2 * P6_STAGE / 48; i += 256) {               // a half row of a block: three pieces, a plane apart
+        const int block = i / 256, half = i / 128 % 2, row = i % 128;
+        uint32_t f[12];
+        p6_fields(i + blockIdx.x * 7919u, false, f);
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            *reinterpret_cast<v4i *>(lds + block * P6_BLOCK + (half * 3 + p) * P6_PLANE + row * 16) =
+                dense ? v4i{(int)f[4 * p], (int)f[4 * p + 1], (int)f[4 * p + 2], (int)f[4 * p + 3]} : v4i{0, 0, 0, 0};
+    }
+    __syncthreads();
+    v8i W[2][2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        uint32_t f[12];
+        p6_fields(1000003u + tid * 2 + t + blockIdx.x * 104729u, true, f);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) W[s][t][e] = dense && e < 6 ? (int)f[6 * s + e] : 0;
+    }
+    v12i X[8];
+    auto read_x = [&](int off, int x) {
+        const uint8_t *p = lds + fg * (3 * P6_PLANE) + fi * 16 + off + (x / 4) * P6_BLOCK + (x % 4) * 512;
+        const v4i a = *reinterpret_cast<const v4i *>(p), b = *reinterpret_cast<const v4i *>(p + P6_PLANE),
+                  c = *reinterpret_cast<const v4i *>(p + 2 * P6_PLANE);
+        const v8i ab = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7), cc = __builtin_shufflevector(c, c, 0, 1, 2, 3, -1, -1, -1, -1);
+        X[x] = __builtin_shufflevector(ab, cc, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11);
+    };
+#pragma unroll
+    for (int x = 0; x < 8; ++x) read_x(0, x);
+    v16f acc[2][8];
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i / 8][i % 8][r] = 0.0f;
+    int off = 0;
+    for (int it = 0; it < iters; ++it) {
+        const int next = P6_STAGE - off;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            asm("" : "+v"(X[x]));           // keeps the 48 bytes in one run of registers
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const v8i b = s == 0 ? __builtin_shufflevector(X[x], X[x], 0, 1, 2, 3, 4, 5, -1, -1)
+                                         : __builtin_shufflevector(X[x], X[x], 6, 7, 8, 9, 10, 11, -1, -1);
+                    acc[t][x] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(W[s][t], b, acc[t][x], 2, 2, 0, 0, 0, 0);
+                }
+            if (LDS_READS) read_x(x == 0 ? off : next, (x + 7) % 8);      // the last tokens of this K tile, the others of the next one
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if (LDS_READS && i < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        off = next;
+    }
+    float r = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) r += acc[i / 8][i % 8][q];
+    out[blockIdx.x * 256 + tid] = __float_as_int(r);
+}
+
 // Streaming read: at most PROBE_READ_WORKGROUPS workgroups walk the buffer in steps of the whole grid, every
 // thread XORing 8 16-byte words per step; one atomic per workgroup and component folds the result into
 // xor4 (few enough not to show in the time), which makes the read observable and checkable.
@@ -228,6 +324,26 @@ int64_t fptq_probe_mfma_rate_ex(int iters, int operands, int workgroups_per_cu, 
         return FPTQ_PROBE_ERR_HIP;
     }
     return (int64_t)wgs * 4 * iters * 64 * (2 * 32 * 32 * 32);
+}
+
+int64_t fptq_probe_mfma6_rate(int iters, int dense, int lds_reads, int32_t *out, void *stream)
+{
+    if (!out) {
+        snprintf(g_err, sizeof g_err, "fptq_probe_mfma6_rate: NULL pointer");
+        return FPTQ_PROBE_ERR_NULL;
+    }
+    if (iters < 1 || iters > (1 << 20)) {
+        snprintf(g_err, sizeof g_err, "fptq_probe_mfma6_rate: iters must be in [1, 2^20]");
+        return FPTQ_PROBE_ERR_VALUE;
+    }
+    if (lds_reads) probe_mfma6_kernel<true><<<dim3(PROBE_MFMA_WORKGROUPS), dim3(256), 0, (hipStream_t)stream>>>(iters, dense, out);
+    else probe_mfma6_kernel<false><<<dim3(PROBE_MFMA_WORKGROUPS), dim3(256), 0, (hipStream_t)stream>>>(iters, dense, out);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+        snprintf(g_err, sizeof g_err, "fptq_probe_mfma6_rate: %s", hipGetErrorString(e));
+        return FPTQ_PROBE_ERR_HIP;
+    }
+    return (int64_t)PROBE_MFMA_WORKGROUPS * 4 * iters * 32 * (2 * 32 * 32 * 64);
 }
 
 int fptq_probe_read(const void *src, int64_t bytes, int32_t *xor4, void *stream)

@@ -1,4 +1,4 @@
-"""ctypes view of the measurement aids (include/fptq_probe.h, csrc/libfptq_probe.so): an MFMA-only loop and a
+"""ctypes view of the measurement aids (include/fptq_probe.h, csrc/libfptq_probe.so): MFMA-only loops and a
 streaming read, so a benchmark can report what the device sustains next to the layer's own kernels.  Not part of
 the quantized linear layer; only the benchmark and its test load this."""
 import ctypes
@@ -8,7 +8,7 @@ import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "csrc", "libfptq_probe.so")
-EXPORTS = ["fptq_probe_last_error", "fptq_probe_mfma_rate", "fptq_probe_read", "fptq_probe_read_burst", "fptq_probe_mfma_rate_ex"]
+EXPORTS = ["fptq_probe_last_error", "fptq_probe_mfma_rate", "fptq_probe_read", "fptq_probe_read_burst", "fptq_probe_mfma_rate_ex", "fptq_probe_mfma6_rate"]
 
 _lib = None
 
@@ -32,6 +32,8 @@ def lib():
         L.fptq_probe_read.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p]
         L.fptq_probe_mfma_rate_ex.restype = ctypes.c_int64
         L.fptq_probe_mfma_rate_ex.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
+        L.fptq_probe_mfma6_rate.restype = ctypes.c_int64
+        L.fptq_probe_mfma6_rate.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p]
         L.fptq_probe_read_burst.restype = ctypes.c_int
         L.fptq_probe_read_burst.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
         _lib = L
@@ -85,6 +87,14 @@ def mfma_rate_ex(iters, operands, workgroups_per_cu, out):
     """The MFMA loop with explicit operand mode (0 zero, 1 fixed, 2 fresh, 3 fresh instruction stream on zeros) and one or
     two workgroups per CU; out: 65536 x workgroups_per_cu int32 on the device.  Returns the operations launched."""
     ops = lib().fptq_probe_mfma_rate_ex(int(iters), int(operands), int(workgroups_per_cu), ctypes.c_void_p(out.data_ptr()), _stream())
+    if ops < 0:
+        _fail(ops)
+    return int(ops)
+
+
+def mfma6_rate(iters, dense, lds_reads, out):
+    """The loop on the 6-bit float matrix cores; out: 65536 int32 on the device.  Returns the operations launched."""
+    ops = lib().fptq_probe_mfma6_rate(int(iters), int(dense), int(lds_reads), ctypes.c_void_p(out.data_ptr()), _stream())
     if ops < 0:
         _fail(ops)
     return int(ops)

@@ -33,6 +33,19 @@ def test_mfma_probe_counts_and_is_deterministic():
         assert e.value.code == -6
 
 
+@pytest.mark.parametrize("lds_reads", [0, 1])
+def test_six_bit_probe_counts_and_is_deterministic(lds_reads):
+    out = torch.full((65536,), -1, dtype=torch.int32, device="cuda")
+    assert probe.mfma6_rate(3, 0, lds_reads, out) == 256 * 4 * 3 * 32 * 131072
+    assert int(out.abs().max()) == 0                        # zero operands: zero accumulators
+    probe.mfma6_rate(5, 1, lds_reads, out)
+    first = out.clone()
+    probe.mfma6_rate(5, 1, lds_reads, out)
+    assert torch.equal(first, out) and int((out != 0).sum()) > 60000
+    with pytest.raises(probe.ProbeError):
+        probe.mfma6_rate(0, 1, lds_reads, out)
+
+
 @pytest.mark.parametrize("nbytes", [16, 48, 16 * 2047, 16 * 2048, 16 * 2049, 16 * 1000003])
 def test_read_probe_sees_every_word(nbytes):
     rng = np.random.default_rng(nbytes)
