@@ -9,8 +9,8 @@ dequantizing epilogue.  Inputs are synthetic, seeded, and resident in HBM before
   value        whole-step throughput in TOP/s (2 M N K of the four linears / step time, quantizers in the time),
                on the configuration's own activations
   roofline     the dominant linear (the gate+up GEMM, with the widening of its activations to six bits): algorithmic ops / average
-               duration from HIP events on the launch stream, against the 5.0 POP/s dense INT8 MFMA peak.  The configuration's own
-               activations quantize to > 99 % zeros (absmax calibration with outlier channels), which lets the part
+               duration from HIP events on the launch stream, against the dense peak of the unit it runs on (10.07 POP/s FP6, 5.0
+               POP/s INT8).  The configuration's own activations quantize to > 99 % zeros (absmax calibration with outlier channels), which lets the part
                clock higher, so the same launches are also timed on uniform random INT4 activations and the LOWER of
                the two rates is the one reported as achieved / frac; both are in the object
   configs      the same two regions for every benchmark configuration with prefill shapes (c2, c3, c5), per launch
@@ -112,6 +112,10 @@ def main():
 
     traffic = {"linear_prefill_kernel": read_traffic_table(PREFILL_TRAFFIC_TABLE)}
     int8_traffic = read_traffic_table()
+
+    def unit_peak(plan):             # of the matrix unit that a launch runs on, TOP/s
+        return FP6_MFMA_PEAK_TOPS if plan[0] == "linear_prefill_kernel" else INT8_MFMA_PEAK_TOPS
+
     keep_host = {}       # first rows of the headline inputs and its weights, for the CPU leg
 
     def build(cfg):
@@ -203,7 +207,7 @@ def main():
                 avg = float(np.mean(t_us))
                 launches[L["name"]] = {"avg_us": round(avg, 2), "min_us": round(min(t_us), 2), "n": len(t_us),
                                        "TOPS": round(L["ops"] / avg / 1e6, 1),
-                                       "pct_peak": round(L["ops"] / avg / 1e6 / INT8_MFMA_PEAK_TOPS * 100, 2)}
+                                       "pct_peak": round(L["ops"] / avg / 1e6 / unit_peak(L["plan"]) * 100, 2)}
             gemm_us = sum(v["avg_us"] for v in launches.values())
             res["dense_int4_activations" if dense else "own_activations"] = {
                 "ms_per_step": round(ms, 4), "step_TOPS": round(ops_step / ms / 1e9, 1), "warmup_steps_run": n_warm,
@@ -213,7 +217,7 @@ def main():
 
     def config_entry(layers, ops_step, res):
         shapes = {L["name"]: {"M": L["M"], "N": L["N"], "K": L["K"], "GOP": round(L["ops"] / 1e9, 2), "kernel": L["plan"][0],
-                              "grid_threads": L["plan"][1] * L["plan"][2]} for L in layers}
+                              "grid_threads": L["plan"][1] * L["plan"][2], "unit_peak_TOPS": unit_peak(L["plan"])} for L in layers}
         worst = min((min(res[k]["launches"][n]["pct_peak"] for k in res), n) for n in shapes)
         return {"ops_per_step": ops_step, "shapes": shapes, **res, "lowest_launch_pct_peak": {"launch": worst[1], "pct_peak": worst[0]}}
 
@@ -230,19 +234,20 @@ def main():
     d_own, d_dense = own["launches"][dom["name"]], dense["launches"][dom["name"]]
     low = d_dense if d_dense["avg_us"] >= d_own["avg_us"] else d_own
     alg_bytes = dom["N"] * dom["K"] // 2 + dom["M"] * dom["K"] // 2 + 4 * dom["N"] + 2 * dom["M"] * dom["N"]
-    trow = traffic.get(dom["plan"][0], int8_traffic).get("c5." + dom["name"])
+    table = traffic.get(dom["plan"][0], int8_traffic)
+    trow, widen = table.get("c5." + dom["name"]), table.get("c5." + dom["name"] + ".widen")
     stale = trow is not None and (trow["kernel"], trow["grid"]) != (dom["plan"][0], dom["plan"][1] * dom["plan"][2])
     kernel = dom["plan"][0] if dom["plan"][0] == "linear_prefill_kernel" else "linear_mfma_kernel<%s>" % dom["plan"][0]
     roofline = {"kernel": "%s, c5 %s %dx%dx%d" % (kernel, dom["name"], dom["M"], dom["N"], dom["K"]),
-                "bound": "mfma", "achieved": low["TOPS"], "peak": INT8_MFMA_PEAK_TOPS, "unit": "TOP/s",
-                "frac": round(low["TOPS"] / INT8_MFMA_PEAK_TOPS, 4),
+                "bound": "mfma", "achieved": low["TOPS"], "peak": unit_peak(dom["plan"]), "unit": "TOP/s",
+                "frac": round(low["TOPS"] / unit_peak(dom["plan"]), 4), "frac_of_int8_peak": round(low["TOPS"] / INT8_MFMA_PEAK_TOPS, 4),
                 "region": "dense_int4_activations" if low is d_dense else "own_activations (the timed region)",
                 "avg_launch_us": low["avg_us"], "ops_per_launch": dom["ops"],
                 "event_pair_overhead_us": dense["event_pair_overhead_us"] if low is d_dense else own["event_pair_overhead_us"],
                 "own_activations": d_own, "dense_int4_activations": d_dense,
-                "traffic": None if trow is None or stale else round(trow["bytes"]),
-                "peak_note": "the dense INT8 MFMA peak, the rate INT4 x INT4 had before the six-bit kernel; that kernel's own unit peaks at "
-                             "%.0f TOP/s, and a launch's time includes widening its activations to six bits" % FP6_MFMA_PEAK_TOPS,
+                "traffic": None if trow is None or stale else round(trow["bytes"] + (widen["bytes"] if widen else 0)),
+                "peak_note": "the dense peak of the matrix unit that the launch runs on (FP6 %.0f TOP/s, INT8 %.0f); its time, and its traffic, "
+                             "include widening the activations to six bits" % (FP6_MFMA_PEAK_TOPS, INT8_MFMA_PEAK_TOPS),
                 "traffic_source": "profiles/linear_*_traffic.md (FETCH_SIZE and WRITE_SIZE counter passes, scaled by a 1 GiB "
                                   "copy kernel)" + (" -- STALE: the launcher now picks another kernel or grid" if stale else ""),
                 "algorithmic_bytes_per_launch": alg_bytes}
@@ -339,9 +344,10 @@ def graph_time_us(torch, fn, iters=20, replays=5):
 
 
 def attainable_summary(torch, probe, dev):
-    """Rates of an MFMA-only loop and of a streaming read, measured in this run: the published peaks are the roofline
-    denominators, these say what the board delivers under sustained load with nothing else going on.  The MFMA loop
-    runs on zero operands, on random INT4 operands (the prefill kernel's operand form) that never change, on such
+    """Rates of MFMA-only loops and of a streaming read, measured in this run: the published peaks are the roofline
+    denominators, these say what the board delivers under sustained load with nothing else going on.  The six-bit loop
+    runs on the six-bit kernel's operands, zero or random INT4, in registers or with the activations read from LDS as that
+    kernel reads them.  The INT8 loop runs on zero operands, on random INT4 operands (the prefill kernel's operand form) that never change, on such
     operands redrawn every iteration in registers (4 VALU instructions pinned behind every MFMA, no memory traffic:
     the rate the power limit leaves a kernel that feeds the matrix pipe fresh dense data), and with that instruction
     stream on operands that stay zero (what the VALU instructions cost by themselves)."""
@@ -356,6 +362,17 @@ def attainable_summary(torch, probe, dev):
             torch.cuda.synchronize()
         e0.record()
         ops = probe.mfma_rate_ex(20000, mode, 1, chk)
+        e1.record()
+        torch.cuda.synchronize()
+        res[name] = round(ops / (e0.elapsed_time(e1) * 1e-3) / 1e12, 1)
+    for name, dense, lds_reads in (("fp6_loop_zero_operands_tops", 0, 0), ("fp6_loop_random_int4_operands_tops", 1, 0),
+                                   ("fp6_loop_random_int4_operands_lds_reads_tops", 1, 1)):
+        t0 = time.perf_counter()
+        while time.perf_counter() - t0 < 0.5:
+            probe.mfma6_rate(20000, dense, lds_reads, chk)
+            torch.cuda.synchronize()
+        e0.record()
+        ops = probe.mfma6_rate(20000, dense, lds_reads, chk)
         e1.record()
         torch.cuda.synchronize()
         res[name] = round(ops / (e0.elapsed_time(e1) * 1e-3) / 1e12, 1)

@@ -23,20 +23,32 @@ def test_more_than_one_gpu_is_refused():
     assert "one GPU" in p.stderr and p.stdout.strip() == ""
 
 
-def test_traffic_table_describes_the_launches_the_library_makes():
-    """roofline.traffic comes from profiles/linear_mfma_traffic.md.  Every row names the kernel instance and grid its
-    counters were read from; the launcher must still pick exactly that for the row's shape, or the figure is stale."""
+@pytest.mark.parametrize("table,with_scratch", [("TRAFFIC_TABLE", False), ("PREFILL_TRAFFIC_TABLE", True)])
+def test_traffic_table_describes_the_launches_the_library_makes(table, with_scratch):
+    """roofline.traffic comes from profiles/linear_prefill_traffic.md, or from linear_mfma_traffic.md where a call has no scratch.  Every row
+    names the kernel instance and grid its counters were read from; the launcher must still pick exactly that for the row's shape, or
+    the figure is stale.  Rows `.widen` are the launches that widen the activations for the row of the same name."""
     from paper_2506_04985_amd import binding as fptq
-    rows = load_bench().read_traffic_table()
+    bench = load_bench()
+    rows = bench.read_traffic_table(getattr(bench, table))
     assert "c5.gate_up" in rows, "the headline launch needs a row"
+    taken = set()
     for name, r in rows.items():
-        kernel, workgroups, threads = fptq.fptq_linear_launch_plan(r["M"], r["N"], r["K"])
-        assert (kernel, workgroups * threads) == (r["kernel"], r["grid"]), name
+        kernel, workgroups, threads = fptq.fptq_linear_launch_plan(r["M"], r["N"], r["K"], with_scratch=with_scratch)
         algorithmic = r["N"] * r["K"] // 2 + r["M"] * r["K"] // 2 + 4 * r["N"] + 2 * r["M"] * r["N"]
+        if name.endswith(".widen"):
+            assert r["kernel"] == "widen_activations_kernel" and name[:-6] in rows and kernel == "linear_prefill_kernel"
+            algorithmic = r["M"] * r["K"] * 5 // 4
+        else:
+            taken.add(name)
+            assert (kernel, workgroups * threads) == (r["kernel"], r["grid"]), name
         assert r["bytes"] >= 0.95 * algorithmic, name          # a launch cannot move less than its operands and its output
         assert r["fetch_scale"] > 0 and r["write_scale"] > 0
+    # one row for every launch of the benchmark's prefill configurations
+    assert taken == {"c5.qkv", "c5.o", "c5.gate_up", "c5.down", "c3.qkv", "c3.o", "c3.gate_up", "c3.down", "c2.gate_up", "c2.down"}
     head = rows["c5.gate_up"]
     assert (head["M"], head["N"], head["K"]) == (8192, 57344, 8192)
+    assert not with_scratch or "c5.gate_up.widen" in rows
 
 
 @pytest.mark.gpu
@@ -58,7 +70,9 @@ def test_json_line_has_the_contract_fields():
     r = d["roofline"]
     for key in ("bound", "achieved", "peak", "unit", "frac", "traffic"):
         assert key in r, key
-    assert r["bound"] == "mfma" and r["peak"] == 5000.0 and abs(r["frac"] - r["achieved"] / r["peak"]) < 1e-3
+    # the peak is that of the unit the launch runs on
+    assert r["bound"] == "mfma" and r["peak"] == (10066.0 if r["kernel"].startswith("linear_prefill_kernel") else 5000.0)
+    assert abs(r["frac"] - r["achieved"] / r["peak"]) < 1e-3
     assert 0.2 < r["frac"] < 1.0
     # the figure held against the roofline is the lower of the two regions' on the dominant launch
     assert r["achieved"] == min(r["own_activations"]["TOPS"], r["dense_int4_activations"]["TOPS"])
