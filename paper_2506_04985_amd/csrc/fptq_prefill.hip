@@ -9,7 +9,7 @@
 // what they hold at the end is sum_k q w and not sum_k q (w + 8).
 //
 // Data flow.  A small kernel first widens the packed activations to six bits in a scratch buffer of the caller (0.75 bytes a
-// value, read and written once: 16 us at 8192 x 8192 beside 1790 us of product), with their signs resolved, and sums each
+// value, read and written once: 15 us at 8192 x 8192 beside 1747 us of a 57344-channel product), with their signs resolved, and sums each
 // token's codes.  The matrix kernel copies those to LDS with buffer loads that write LDS directly, and reads the weights as
 // they are, packed: each of its four waves owns 64 channels and all tokens of the tile (256 or 128), so a weight is loaded by one
 // wave only, into registers (256 tokens) or through LDS of the wave's own (128), and its nibbles are spread to six-bit fields by
@@ -17,9 +17,10 @@
 // per SIMD issues at most eight instructions in the 32 cycles of an MFMA: measured at the INT8 loop's rate.  Widening the
 // weights beforehand as well would cost 1.25 bytes of traffic per weight and call, 5 % at 8192 tokens.
 //
-// What bounds it: the board's power.  On uniform random INT4 operands 8192 x 57344 x 8192 runs at 4490 TOP/s against 3130 for
-// the INT8 kernel (1712 and 2461 us), on all-zero operands in 1240 us; an MFMA-only loop on random operands that never
-// change reaches 6140, the same with this kernel's LDS reads 5030.
+// What bounds it: the board's power, and the cycles without an MFMA in flight.  On uniform random INT4 operands 8192 x 57344 x 8192 takes
+// 1757 us, widening included (4380 TOP/s; boxes differ by 4 %), the INT8 kernel 2537, on all-zero operands 1240.  The matrix pipe is
+// busy in 61 % of the cycles at about 1.9 of 2.4 GHz.  An MFMA-only loop on such operands that never change reaches 6700 TOP/s, with
+// this kernel's LDS reads of activations 5900 to 6250.
 #include <cstdio>
 #include <type_traits>
 
@@ -132,8 +133,8 @@ __global__ __launch_bounds__(64 * CV_WAVES) void widen_activations_kernel(const 
 // 17552 91 (67); copied to LDS as they lie and read back 61 (52) and 77 (62).  Where the CUs are full and the weights are in
 // the cache the extra LDS traffic costs up to 4 % (2048 x 4096 x 11008 54 -> 56, from HBM 63 -> 57).  256 tokens (TM = 8) widen each weight
 // for eight MFMAs, 128 (TM = 4) for four and load twice the weights per operation; they are for problems that the large tile cuts
-// into fewer pieces than there are CUs: 1000 x 5120 x 13824 takes 59 us with them, 84 without and 77 on INT8 tiles, 2048 x 4096 x
-// 11008 58, 69 and 68, but 4096 x 28672 x 4096 297, 262 and 340.
+// into fewer pieces than there are CUs: weights from HBM, 1000 x 5120 x 13824 takes 62 us with them, 93 without and 63 on INT8 tiles,
+// 2048 x 4096 x 11008 60, 77 and 66, but 4096 x 28672 x 4096 312, 261 and 345.
 template <int TM_>
 struct PrefillTile {
     static constexpr int TN = 2, TM = TM_, STAGES = 5, DEPTH = 3;
