@@ -135,23 +135,24 @@ PyObject *tuple(std::initializer_list<Output *> outputs)
     return t;
 }
 
-PyObject *device()
+// where a launch goes: the current device and its current stream
+struct Where {
+    long device;
+    void *stream;
+};
+
+Where where()
 {
     PyObject *d = PyObject_CallNoArgs(g_device);
     if (!d) throw Slow();
-    return d;
-}
-
-void *stream()
-{
-    PyObject *d = device();
+    const long index = PyLong_AsLong(d);
     PyObject *s = PyObject_CallOneArg(g_stream, d);
     Py_DECREF(d);
     if (!s) throw Slow();
     void *p = PyLong_AsVoidPtr(s);
     Py_DECREF(s);
-    if (!p && PyErr_Occurred()) throw Slow();
-    return p;
+    if (PyErr_Occurred()) throw Slow();
+    return {index, p};
 }
 
 bool capturing()
@@ -162,15 +163,6 @@ bool capturing()
     Py_DECREF(c);
     if (yes < 0) throw Slow();
     return yes;
-}
-
-bool on_current_device(const at::Tensor &t)
-{
-    PyObject *d = device();
-    const long v = PyLong_AsLong(d);
-    Py_DECREF(d);
-    if (v == -1 && PyErr_Occurred()) throw Slow();
-    return t.device().index() == v;
 }
 
 // The part of a call that may wait: the new outputs, then the library's call.
@@ -212,7 +204,7 @@ PyObject *pack_weights(PyObject *, PyObject *const *a, Py_ssize_t n)
         int64_t N, K;
         matrix(w, N, K);
         Output out(a[1], {need(N, K)}, at::kByte, w);
-        void *const st = stream();
+        void *const st = where().stream;
         launch({&out}, [&] { return fptq_pack_weights((const int8_t *)w.data_ptr(), N, K, out.ptr, out.numel, st); });
         return out.take();
     });
@@ -226,7 +218,7 @@ PyObject *weight_row_sums(PyObject *, PyObject *const *a, Py_ssize_t n)
         int64_t N, K;
         matrix(w, N, K);
         Output out(Py_None, {N}, at::kInt, w);
-        void *const st = stream();
+        void *const st = where().stream;
         launch({&out}, [&] { return fptq_weight_row_sums((const int8_t *)w.data_ptr(), N, K, (int32_t *)out.ptr, st); });
         return out.take();
     });
@@ -247,7 +239,7 @@ PyObject *quantize_act(PyObject *, PyObject *const *a, Py_ssize_t n)
         const float *r_in = (const float *)input_or_null(a[4], at::kFloat);
         Output out(a[5], {need(M, K)}, at::kByte, x), r;
         if (a[6] != Py_None || truth(a[7])) r = Output(a[6], {M}, at::kFloat, x);
-        void *const st = stream();
+        void *const st = where().stream;
         launch({&out, &r}, [&] {
             float *const r_out = (float *)r.ptr;
             if (kind == 1) return fptq_quantize_act_hadamard(x.data_ptr(), M, K, (int)parameter, mode, eps, r_in, s_a, out.ptr, out.numel, r_out, st);
@@ -266,7 +258,7 @@ PyObject *quantize_act_dynamic(PyObject *, PyObject *const *a, Py_ssize_t n)
         int64_t M, K;
         matrix(x, M, K);
         Output out(a[1], {need(M, K)}, at::kByte, x), s(a[2], {M}, at::kFloat, x);
-        void *const st = stream();
+        void *const st = where().stream;
         launch({&out, &s}, [&] { return fptq_quantize_act_dynamic(x.data_ptr(), M, K, out.ptr, out.numel, (float *)s.ptr, st); });
         return tuple({&out, &s});
     });
@@ -282,7 +274,7 @@ PyObject *residual_norm_quantize(PyObject *, PyObject *const *a, Py_ssize_t n)
         const float s_a = number(a[2]), eps = number(a[4]);
         const float *s_prev = (const float *)input_or_null(a[3], at::kFloat);
         Output x_next(a[5], {M, K}, at::kBFloat16, x), s_next(a[6], {M}, at::kFloat, x), out(a[7], {need(M, K)}, at::kByte, x);
-        void *const st = stream();
+        void *const st = where().stream;
         launch({&x_next, &s_next, &out}, [&] {
             return fptq_residual_norm_quantize(x.data_ptr(), y.data_ptr(), M, K, s_prev, eps, s_a, x_next.ptr, (float *)s_next.ptr, out.ptr,
                                                out.numel, st);
@@ -310,16 +302,18 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
         Output y(a[8], {M, N}, at::kBFloat16, xq), acc;
         const bool with_acc = want_acc || a[10] != Py_None;
         if (with_acc) acc = Output(a[10], {M, N}, at::kInt, xq);
+        const Where w = where();
+        void *const st = w.stream;
         // Scratch is handed back when the call returns and then guarded by stream order alone: it has to come from the stream that the
         // launch goes to, i.e. from the current device.  Operands on another one (peer access) go without.
-        const bool may_scratch = (kind == 0 || kind == 3) && M > 64 && on_current_device(xq) && !capturing();
-        void *const st = stream();
+        const bool may_scratch = (kind == 0 || kind == 3) && M > 64 && xq.device().index() == w.device;
+        int64_t scratch_bytes = may_scratch ? without_gil([&] { return fptq_linear_scratch_bytes(M, N, K); }) : 0;
+        if (scratch_bytes > 0 && capturing()) scratch_bytes = 0;
         at::Tensor scratch;
         launch({&y, &acc}, [&] {
             const void *px = xq.data_ptr(), *pw = wq.data_ptr();
             const float *ps = (const float *)s_w.data_ptr();
             int32_t *const pa = (int32_t *)acc.ptr;
-            const int64_t scratch_bytes = may_scratch ? fptq_linear_scratch_bytes(M, N, K) : 0;
             if (scratch_bytes > 0) {
                 try {
                     scratch = at::empty({scratch_bytes}, at::TensorOptions().dtype(at::kByte).device(xq.device()));

@@ -33,10 +33,12 @@ def test_library_calls_and_allocations_run_without_the_interpreter_lock():
     uses = [m for m in re.finditer(r"\ballocate\(\)", text) if not text[:m.start()].endswith("void ")]
     assert len(uses) == 1 and inside(uses[0], unlocked)
     # nothing inside touches Python objects
-    assert not any(re.search(r"\bPy[A-Z_]|THPVariable|\btake\(|\bstream\(|\bcapturing\(", text[a:b]) for a, b in unlocked + allocate)
+    assert not any(re.search(r"\bPy[A-Z_]|THPVariable|\btake\(|\bwhere\(|\bcapturing\(", text[a:b]) for a, b in unlocked + allocate)
 
 
 def test_scratch_comes_from_the_stream_of_the_launch():
     text = source()
-    assert re.search(r"may_scratch = [^;]*\bon_current_device\(xq\)", text)
-    assert len(re.findall(r"may_scratch \? fptq_linear_scratch_bytes\(", text)) == 1 == len(re.findall(r"scratch = at::empty", text))
+    assert re.search(r"const Where w = where\(\);\s*void \*const st = w\.stream;", text)
+    assert re.search(r"may_scratch = [^;]*\bxq\.device\(\)\.index\(\) == w\.device;", text)
+    assert re.search(r"scratch_bytes = may_scratch \? without_gil\(\[&\] \{ return fptq_linear_scratch_bytes\(M, N, K\); \}\) : 0;", text)
+    assert len(re.findall(r"scratch = at::empty\(\{scratch_bytes\}", text)) == 1
