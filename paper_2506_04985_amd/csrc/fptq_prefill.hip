@@ -18,7 +18,7 @@
 // weights beforehand as well would cost 1.25 bytes of traffic per weight and call, 5 % at 8192 tokens.
 //
 // What bounds it: the board's power, and the cycles without an MFMA in flight.  On uniform random INT4 operands 8192 x 57344 x 8192 takes
-// 1757 us, widening included (4380 TOP/s; boxes differ by 4 %), the INT8 kernel 2537, on all-zero operands 1240.  The matrix pipe is
+// 1757 us, widening included (4380 TOP/s; boards differ by 4 %), the INT8 kernel 2537, on all-zero operands 1240.  The matrix pipe is
 // busy in 61 % of the cycles at about 1.9 of 2.4 GHz.  An MFMA-only loop on such operands that never change reaches 6700 TOP/s, with
 // this kernel's LDS reads of activations 5900 to 6250.
 #include <cstdio>

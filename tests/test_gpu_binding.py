@@ -204,8 +204,8 @@ def test_a_refusal_names_the_call_that_was_made(both, call):
 
 def test_other_threads_run_during_a_call():
     """The interpreter lock is free while the library launches.  With a switch interval of minutes a thread that wants it gets in only
-    where a call lets go of it."""
-    x, _, _, r = data(1, 8, 256)
+    where a call lets go of it, at the latest where the queue is full and a launch waits for room."""
+    x, _, _, r = data(2048, 8, 11008)
     out = fptq.fptq_quantize_act(x, 0.4, 2, 0.0, r, want_row_scale=False)[0]
     turns, stop, interval = [0], threading.Event(), sys.getswitchinterval()
 
@@ -218,7 +218,7 @@ def test_other_threads_run_during_a_call():
     try:
         thread.start()
         before, calls = turns[0], 0
-        while turns[0] == before and calls < 200000:
+        while turns[0] == before and calls < 40000:
             fptq.fptq_quantize_act(x, 0.4, 2, 0.0, r, out=out, want_row_scale=False)
             calls += 1
         seen = turns[0] > before
