@@ -32,6 +32,8 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v12i __attribute__((ext_vector_type(12)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
+constexpr int NON_TEMPORAL = 2;                 // cache policy of a buffer store
+
 typedef __attribute__((address_space(3))) const uint8_t lds_u8;
 typedef __attribute__((address_space(3))) const v4i lds_v4i;
 
@@ -400,61 +402,114 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     // ---- epilogue.  Weights were the A operand: a lane owns token fi of each 32 and, per register quad q, four consecutive
     // channels 8 q + 4 fg + (r % 4).  The registers hold acc / 64; times 64 that is acc, exactly, and then
     // y = bf16((float)(acc - z * wsum[n]) * (s_a * s_w[n]) [* d_t]) as in the other kernels (with a zero point the subtraction is
-    // exact too: both terms are integers and their difference is below 2^24 for K <= 131071).  Results go through a
-    // wave-private LDS patch ([32 tokens][64 channels], padded rows), so that HBM sees 16-byte-per-lane row segments; a wave's LDS
-    // operations complete in order, so only the compiler has to be kept from exchanging them.
-    constexpr int WN = C::TN * 32, PATCH_STRIDE = WN * 2 + 16, WAVE_LDS = 32 * PATCH_STRIDE;
-    static_assert(WN == 64 && 4 * WAVE_LDS <= C::RING_BYTES, "a channel per lane; the patches reuse the ring");
-    uint8_t *patch = lds + wave * WAVE_LDS;
+    // exact too: both terms are integers and their difference is below 2^24 for K <= 131071).  Without a zero point the 64 goes into the
+    // channel's factor, a power of two and so exact, unless that would overflow it (`huge`, never with real scales).
+    //
+    // One wave per SIMD has nothing to hide a latency under, so the 32 (64 with a zero point) channel constants are read once, into the
+    // registers that the K loop's operands leave free, and the results of a group of 32 tokens are read back from LDS while the next
+    // group's are computed and written: 6.1 us a tile with the constants read where they are used and one patch for all groups,
+    // PLACEHOLDER now.  The two halves of a wave exchange quads, so that a lane holds eight consecutive channels (16 bytes); those go
+    // through a wave-private LDS patch of 32 rows of 128 bytes per group, granule g of row r in slot g ^ (r % 8) (no bank
+    // conflicts in either direction), so that HBM sees rows of 128 bytes.  A wave's LDS operations complete in order, so only the
+    // compiler has to be kept from exchanging them.
+    constexpr int WN = C::TN * 32, ROW_BYTES = WN * 2, PATCH_BYTES = 32 * ROW_BYTES;
+    static_assert(WN == 64 && 4 * 2 * PATCH_BYTES <= C::RING_BYTES, "a channel per lane; two patches a wave reuse the ring");
+    uint8_t *const patch = lds + wave * (2 * PATCH_BYTES);
+    float4 cw[C::TN][4], zw[C::TN][4];
 #pragma unroll
-    for (int tm = 0; tm < C::TM; ++tm) {
-        const int mt0 = m0 + tm * 32;
-        const int m = mt0 + fi;
-        const float dm = dbuf[tm * 32 + fi];
+    for (int tn = 0; tn < C::TN; ++tn)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            cw[tn][q] = *reinterpret_cast<const float4 *>(cwbuf + wave * WN + tn * 32 + 8 * q + 4 * fg);
+            if (ZP) zw[tn][q] = *reinterpret_cast<const float4 *>(zwbuf + wave * WN + tn * 32 + 8 * q + 4 * fg);
+        }
+    float dm[C::TM];
+#pragma unroll
+    for (int tm = 0; tm < C::TM; ++tm) dm[tm] = d ? dbuf[tm * 32 + fi] : 1.0f;
+    bool huge = false;
+#pragma unroll
+    for (int tn = 0; tn < C::TN; ++tn)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            huge |= fmaxf(fmaxf(fabsf(cw[tn][q].x), fabsf(cw[tn][q].y)), fmaxf(fabsf(cw[tn][q].z), fabsf(cw[tn][q].w))) >= 0x1p121f;
+    const bool plain = !ZP && !d && __builtin_amdgcn_ballot_w64(huge) == 0;
+    const int slot = fg ^ (fi & 7);
+    // PLAIN: neither zero point nor token scale, and the 64 in the channel's factor
+    auto to_lds = [&](auto plain_c, int tm) {
+        constexpr bool PLAIN = decltype(plain_c)::value;
+        uint8_t *const to = patch + (tm & 1) * PATCH_BYTES + fi * ROW_BYTES;
 #pragma unroll
         for (int tn = 0; tn < C::TN; ++tn)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int c0 = tn * 32 + 8 * q + 4 * fg;
-                const float4 c4 = *reinterpret_cast<const float4 *>(cwbuf + wave * WN + c0);
-                const float4 z4 = ZP ? *reinterpret_cast<const float4 *>(zwbuf + wave * WN + c0) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                const float cw[4] = {c4.x, c4.y, c4.z, c4.w}, zw[4] = {z4.x, z4.y, z4.z, z4.w};
-                float yf[4];
+            for (int j = 0; j < 2; ++j) {
+                uint32_t p[2][2];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float a = acc[tn][tm][4 * q + e];
-                    yf[e] = (ZP ? __builtin_fmaf(a, 64.0f, -zw[e]) : a * 64.0f) * cw[e];
-                    if (d) yf[e] = yf[e] * dm;
+                for (int q = 0; q < 2; ++q) {
+                    const float4 c4 = cw[tn][2 * j + q], z4 = zw[tn][2 * j + q];
+                    const float c[4] = {c4.x, c4.y, c4.z, c4.w}, z[4] = {z4.x, z4.y, z4.z, z4.w};
+                    float yf[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float a = acc[tn][tm][8 * j + 4 * q + e];
+                        yf[e] = PLAIN ? a * c[e] : (ZP ? __builtin_fmaf(a, 64.0f, -z[e]) : a * 64.0f) * c[e] * dm[tm];
+                    }
+                    p[q][0] = pack_bf16(yf[0], yf[1]), p[q][1] = pack_bf16(yf[2], yf[3]);
                 }
-                *reinterpret_cast<uint2 *>(patch + fi * PATCH_STRIDE + c0 * 2) = make_uint2(pack_bf16(yf[0], yf[1]), pack_bf16(yf[2], yf[3]));
+                // lanes 32 .. 63 of the first and 0 .. 31 of the second change places: quads 2 j of both halves, and 2 j + 1
+                const auto lo = __builtin_amdgcn_permlane32_swap(p[0][0], p[1][0], false, false);
+                const auto hi = __builtin_amdgcn_permlane32_swap(p[0][1], p[1][1], false, false);
+                *reinterpret_cast<uint4 *>(to + ((tn * 4 + 2 * j) ^ slot) * 16) = make_uint4(lo[0], hi[0], lo[1], hi[1]);
             }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
+    };
+    // a store instruction takes eight rows; a lane whose channels are past the end gets an offset past every descriptor's end
+    const int col = (lane & 7) * 8, row = lane >> 3;
+    const uint8_t *const from = patch + row * ROW_BYTES + (((lane & 7) ^ row) << 4);
+    const uint32_t row_stride = (uint32_t)N * 2, y_off = nw0 + col < N ? (uint32_t)row * row_stride + (uint32_t)(nw0 + col) * 2 : 0x80000000u;
+    auto write_out = [&](auto plain_c) {
+        to_lds(plain_c, 0);
 #pragma unroll
-        for (int pass = 0; pass < 4; ++pass) {
-            const int row = pass * 8 + lane / 8, col = (lane % 8) * 8;
-            const uint4 v = *reinterpret_cast<const uint4 *>(patch + row * PATCH_STRIDE + col * 2);
-            const int mm = mt0 + row, nn = nw0 + col;
-            if (mm < M && nn < N) {
-                uint16_t *dst = y + (int64_t)mm * N + nn;
-                if (ALIGNED) {       // N % 8 == 0: the segment is whole and 16-byte aligned
-                    __builtin_nontemporal_store(v4i{(int)v.x, (int)v.y, (int)v.z, (int)v.w}, reinterpret_cast<v4i *>(dst));
-                } else {
-                    store_row_segment(dst, v, nn, N);
-                }
+        for (int tm = 0; tm < C::TM; ++tm) {
+            uint4 v[4];
+#pragma unroll
+            for (int p = 0; p < 4; ++p) v[p] = *reinterpret_cast<const uint4 *>(from + (tm & 1) * PATCH_BYTES + p * (8 * ROW_BYTES));
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (tm + 1 < C::TM) to_lds(plain_c, tm + 1);
+            const int mt0 = m0 + tm * 32;
+            if (ALIGNED) {           // N % 8 == 0: the segments are whole and 16-byte aligned; rows past the end fail the descriptor's check
+                const uint32_t bytes = (uint32_t)max(0, min(32, M - mt0)) * row_stride;      // 2^30 at most: N <= 2^24
+                const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(y + (int64_t)mt0 * N, 0, __builtin_amdgcn_readfirstlane((int)bytes), RSRC_FLAGS);
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+                    __builtin_amdgcn_raw_buffer_store_b128(v4i{(int)v[p].x, (int)v[p].y, (int)v[p].z, (int)v[p].w}, yr, y_off + p * 8 * row_stride, 0, NON_TEMPORAL);
+            } else {
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+                    if (mt0 + p * 8 + row < M && nw0 + col < N)
+                        store_row_segment(y + (int64_t)(mt0 + p * 8 + row) * N + nw0 + col, v[p], nw0 + col, N);
             }
         }
-        __builtin_amdgcn_wave_barrier();
-        if (DUMP) {      // parity dump of the integer accumulators (never a timed path)
+    };
+    if (plain) {
+#pragma unroll
+        for (int tn = 0; tn < C::TN; ++tn)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) cw[tn][q].x *= 64.0f, cw[tn][q].y *= 64.0f, cw[tn][q].z *= 64.0f, cw[tn][q].w *= 64.0f;
+        write_out(std::true_type());
+    } else {
+        write_out(std::false_type());
+    }
+    if (DUMP) {      // parity dump of the integer accumulators (never a timed path)
+#pragma unroll
+        for (int tm = 0; tm < C::TM; ++tm)
 #pragma unroll
             for (int tn = 0; tn < C::TN; ++tn)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int n = nw0 + tn * 32 + 8 * q + 4 * fg + e;
-                        if (m < M && n < N) acc_out[(int64_t)m * N + n] = (int32_t)(acc[tn][tm][4 * q + e] * 64.0f);
-                    }
-        }
+                for (int r = 0; r < 16; ++r) {
+                    const int m = m0 + tm * 32 + fi, n = nw0 + tn * 32 + 8 * (r / 4) + 4 * fg + r % 4;
+                    if (m < M && n < N) acc_out[(int64_t)m * N + n] = (int32_t)(acc[tn][tm][r] * 64.0f);
+                }
     }
 }
 

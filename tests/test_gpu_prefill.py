@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 @pytest.fixture(params=[256, 128])
 def forced(request):
     fptq.fptq_set_linear_prefill(request.param)         # tokens per tile
-    yield
+    yield request.param
     fptq.fptq_set_linear_prefill(0)
 
 
@@ -52,6 +52,35 @@ def test_equals_the_int8_kernel(forced, M, N, K, zp):
     fptq.fptq_set_linear_prefill(2)
     want = fptq.fptq_w4a4_linear_zp(xq, wq, M, N, K, 0.37, s_w, zp, ws, d, want_acc=True)
     assert torch.equal(got[1], want[1]) and torch.equal(got[0].view(torch.int16), want[0].view(torch.int16))
+
+
+@pytest.mark.parametrize("M,N,zp,with_d", [(289, 264, None, False), (65, 257, None, False), (289, 264, None, True), (255, 72, 3, False), (130, 515, -8, True)])
+def test_epilogue_of_any_scale(forced, M, N, zp, with_d):
+    """Channel scales from subnormal to infinite and NaN (the kernel folds a factor of 64 into ordinary ones), with and without token
+    scales and a zero point; nothing is written past the last row."""
+    K = 300
+    torch.manual_seed(M)
+    xq = fptq.fptq_pack_weights(torch.randint(-8, 8, (M, K), dtype=torch.int8, device="cuda"))
+    w = torch.randint(-8, 8, (N, K), dtype=torch.int8, device="cuda")
+    w[::5] = 0
+    wq, ws = fptq.fptq_pack_weights(w), fptq.fptq_weight_row_sums(w)
+    d = torch.rand(M, device="cuda") + 0.5 if with_d else None
+    for odd in ([], [1e-42, 2.0 ** -126], [2.0 ** 122, 3e38], [float("inf")], [float("nan")]):
+        s_w = torch.rand(N, device="cuda") * 0.015 + 0.005
+        s_w[torch.arange(len(odd)) * 35] = torch.tensor(odd, device="cuda")
+        buf = torch.full(((M + 300) * N,), 77.0, dtype=torch.bfloat16, device="cuda")
+        scratch = scratch_for(M, N, K)
+        args = (0, None) if zp is None else (zp, ws)
+        fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, 1.0, s_w, scratch, *args, d, out=buf[:M * N].view(M, N))
+        want = fptq.fptq_w4a4_linear_noalloc(xq, wq, M, N, K, 1.0, s_w, d) if zp is None else None
+        if zp is not None:
+            fptq.fptq_set_linear_prefill(2)
+            want = fptq.fptq_w4a4_linear_zp(xq, wq, M, N, K, 1.0, s_w, zp, ws, d)
+            fptq.fptq_set_linear_prefill(forced)
+        got = buf[:M * N].view(M, N)
+        assert torch.equal(got.isnan(), want.isnan())
+        assert torch.equal(got.nan_to_num(nan=0.0).view(torch.int16), want.nan_to_num(nan=0.0).view(torch.int16))
+        assert bool((buf[M * N:] == 77.0).all())
 
 
 @pytest.mark.parametrize("K", [131071, 131070])
