@@ -156,7 +156,17 @@ __device__ inline v16f mfma6(v8i w, v8i x, v16f c)
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w, x, c, 2, 2, 0, 0, 0, 0);
 }
 
-template <int TM, bool ALIGNED, bool DUMP, bool ZP>
+// How results reach memory.  Rows of whole 128-byte lines are streamed (8192 x 57344 x 8192: zeros 1090 us, cached 1365; dense 1632 and 1658).
+// Other widths leave two parts of a line to two waves, which meet in L2 when cached; streamed, each goes to memory by itself: 3000 x
+// 11000 x 2048 76 us, cached 66, 4096 x 4104 x 4096 70 and 65, 1000 x 9000 x 3000 36 and 34.  An output that the 256 MB last-level cache
+// cannot hold is streamed all the same: cached, 8192 x 28680 x 1024 took 271 us instead of 255, 8192 x 16392 x 2048 213 instead of 203.
+enum { ANY_ALIGNMENT, CACHED, STREAMED };          // ANY_ALIGNMENT: N % 8 != 0
+static int store_kind(int64_t M, int64_t N)
+{
+    return N % 8 != 0 ? ANY_ALIGNMENT : N % 64 != 0 && M * N * 2 <= (int64_t)256 << 20 ? CACHED : STREAMED;
+}
+
+template <int TM, int STORE, bool DUMP, bool ZP>
 __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     const uint8_t *__restrict__ x6, int64_t x_slab, const float *__restrict__ start, int start_parts, int rows,
     const uint8_t *__restrict__ wq, int M, int N, int ktiles, int tiles_m, int tiles_n, float s_a, const float *__restrict__ s_w,
@@ -477,12 +487,13 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             if (tm + 1 < C::TM) to_lds(plain_c, tm + 1);
             const int mt0 = m0 + tm * 32;
-            if (ALIGNED) {           // N % 8 == 0: the segments are whole and 16-byte aligned; rows past the end fail the descriptor's check
+            if (STORE != ANY_ALIGNMENT) {       // the segments are whole and 16-byte aligned; rows past the end fail the descriptor's check
                 const uint32_t bytes = (uint32_t)max(0, min(32, M - mt0)) * row_stride;      // 2^30 at most: N <= 2^24
                 const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(y + (int64_t)mt0 * N, 0, __builtin_amdgcn_readfirstlane((int)bytes), RSRC_FLAGS);
 #pragma unroll
                 for (int p = 0; p < 4; ++p)
-                    __builtin_amdgcn_raw_buffer_store_b128(v4i{(int)v[p].x, (int)v[p].y, (int)v[p].z, (int)v[p].w}, yr, y_off + p * 8 * row_stride, 0, NON_TEMPORAL);
+                    __builtin_amdgcn_raw_buffer_store_b128(v4i{(int)v[p].x, (int)v[p].y, (int)v[p].z, (int)v[p].w}, yr, y_off + p * 8 * row_stride, 0,
+                                                           STORE == STREAMED ? NON_TEMPORAL : 0);
             } else {
 #pragma unroll
                 for (int p = 0; p < 4; ++p)
@@ -513,10 +524,10 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     }
 }
 
-template <int TM, bool ALIGNED, bool DUMP, bool ZP>
+template <int TM, int STORE, bool DUMP, bool ZP>
 static hipError_t set_prefill_attribute()
 {
-    return hipFuncSetAttribute((const void *)linear_prefill_kernel<TM, ALIGNED, DUMP, ZP>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    return hipFuncSetAttribute((const void *)linear_prefill_kernel<TM, STORE, DUMP, ZP>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                PrefillTile<TM>::LDS_BYTES);
 }
 
@@ -525,10 +536,13 @@ static hipError_t set_prefill_attributes()
 {
     hipError_t e = hipSuccess;
     auto one = [&](hipError_t r) { if (e == hipSuccess) e = r; };
-    one(set_prefill_attribute<TM, true, true, false>()), one(set_prefill_attribute<TM, true, false, false>());
-    one(set_prefill_attribute<TM, false, true, false>()), one(set_prefill_attribute<TM, false, false, false>());
-    one(set_prefill_attribute<TM, true, true, true>()), one(set_prefill_attribute<TM, true, false, true>());
-    one(set_prefill_attribute<TM, false, true, true>()), one(set_prefill_attribute<TM, false, false, true>());
+#define FPTQ_ATTRIBUTES(S)                                                                              \
+    one(set_prefill_attribute<TM, S, true, false>()), one(set_prefill_attribute<TM, S, false, false>());  \
+    one(set_prefill_attribute<TM, S, true, true>()), one(set_prefill_attribute<TM, S, false, true>())
+    FPTQ_ATTRIBUTES(ANY_ALIGNMENT);
+    FPTQ_ATTRIBUTES(CACHED);
+    FPTQ_ATTRIBUTES(STREAMED);
+#undef FPTQ_ATTRIBUTES
     return e;
 }
 
@@ -568,17 +582,19 @@ static hipError_t launch_tile(const uint8_t *x6, const float *start, int split, 
     linear_prefill_kernel<TM, A, D, Z><<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), C::LDS_BYTES, s>>>(                          \
         x6, x6_slab(M), start, split, (int)x6_rows(M), wq, (int)M, (int)N, (int)k_tiles(K), (int)tiles_m, (int)tiles_n, s_a, s_w, d,   \
         zp, wsum, y, acc)
-    const int inst = (N % 8 == 0 ? 4 : 0) | (acc ? 2 : 0) | (wsum ? 1 : 0);
-    switch (inst) {
-    case 0: FPTQ_PREFILL(false, false, false); break;
-    case 1: FPTQ_PREFILL(false, false, true); break;
-    case 2: FPTQ_PREFILL(false, true, false); break;
-    case 3: FPTQ_PREFILL(false, true, true); break;
-    case 4: FPTQ_PREFILL(true, false, false); break;
-    case 5: FPTQ_PREFILL(true, false, true); break;
-    case 6: FPTQ_PREFILL(true, true, false); break;
-    default: FPTQ_PREFILL(true, true, true);
+#define FPTQ_PREFILL_OF(S)                                                                                                             \
+    switch ((acc ? 2 : 0) | (wsum ? 1 : 0)) {                                                                                         \
+    case 0: FPTQ_PREFILL(S, false, false); break;                                                                                     \
+    case 1: FPTQ_PREFILL(S, false, true); break;                                                                                      \
+    case 2: FPTQ_PREFILL(S, true, false); break;                                                                                      \
+    default: FPTQ_PREFILL(S, true, true);                                                                                             \
     }
+    switch (store_kind(M, N)) {
+    case ANY_ALIGNMENT: FPTQ_PREFILL_OF(ANY_ALIGNMENT); break;
+    case CACHED: FPTQ_PREFILL_OF(CACHED); break;
+    default: FPTQ_PREFILL_OF(STREAMED);
+    }
+#undef FPTQ_PREFILL_OF
 #undef FPTQ_PREFILL
     return hipGetLastError();
 }

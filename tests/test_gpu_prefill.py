@@ -83,6 +83,18 @@ def test_epilogue_of_any_scale(forced, M, N, zp, with_d):
         assert bool((buf[M * N:] == 77.0).all())
 
 
+def test_streamed_rows_of_partial_lines(forced):
+    """A width that is no multiple of 64 and an output above 256 MB: streaming stores whose last channels are cut off."""
+    M, N, K = 8200, 16392, 130
+    torch.manual_seed(1)
+    xq = fptq.fptq_pack_weights(torch.randint(-8, 8, (M, K), dtype=torch.int8, device="cuda"))
+    wq = fptq.fptq_pack_weights(torch.randint(-8, 8, (N, K), dtype=torch.int8, device="cuda"))
+    s_w = torch.rand(N, device="cuda") * 0.015 + 0.005
+    got = fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, 0.37, s_w, scratch_for(M, N, K))
+    want = fptq.fptq_w4a4_linear_noalloc(xq, wq, M, N, K, 0.37, s_w)
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
 @pytest.mark.parametrize("K", [131071, 131070])
 @pytest.mark.parametrize("x,w", [(-8, -8), (7, -8), (-8, 7), (7, 7)])
 def test_longest_sums_of_the_largest_products(forced, K, x, w):
