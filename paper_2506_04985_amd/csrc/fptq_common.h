@@ -145,18 +145,41 @@ __device__ inline int32_t remove_zero_point(int32_t acc, int zp, const int32_t *
     return wsum ? acc - zp * wsum[o] : acc;
 }
 
-// Eight bf16 results to channels nn .. of a row whose address is only 2-byte aligned (N % 8 != 0), those past the row's end left out.
-// The hardware takes unaligned 16-byte stores; as eight 2-byte stores a whole segment made the epilogue the longest part of
-// a launch of few K tiles (333 x 32003 x 2504: 41 us, with N = 32000 30).
-__device__ inline void store_row_segment(uint16_t *dst, uint4 v, int nn, int N)
+// How a matrix kernel's results reach memory.  Rows of whole 64-byte pieces are streamed (six-bit kernel, 8192 x 57344 x 8192: zeros 1090 us, cached
+// 1365; dense 1632 and 1658; INT8 kernel, 1000 x 5120 x 4096 22.9 and 23.7, 300 x 20000 x 1000 11.8 and 12.7).  Other widths leave two
+// parts of a piece to two waves, which meet in L2 when cached; streamed, each goes to memory by itself: 3000 x 11000 x 2048 76 us, cached
+// 66, 4096 x 4104 x 4096 70 and 65, 1000 x 9000 x 3000 36 and 34, on the INT8 kernel 333 x 32008 x 2504 30.2 and 29.7.  An output that the
+// 256 MB last-level cache cannot hold is streamed all the same: cached, 8192 x 28680 x 1024 took 271 us instead of 255, 8192 x 16392 x
+// 2048 213 instead of 203.
+enum { ANY_ALIGNMENT, CACHED, STREAMED };          // ANY_ALIGNMENT: serves every N, chosen for N % 8 != 0
+inline int store_kind(int64_t M, int64_t N)
 {
-    if (nn + 8 <= N) {
-        __builtin_memcpy(dst, &v, 16);
-    } else {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    return N % 8 != 0 ? ANY_ALIGNMENT : N % 32 != 0 && M * N * 2 <= (int64_t)256 << 20 ? CACHED : STREAMED;
+}
+constexpr int NON_TEMPORAL = 2;                    // cache policy of a buffer access
+
+// Stores a wave's row segments of 32 tokens from mt0 on: pass p takes ROWS_PER_PASS rows, this lane channels nn .. nn + 7 of row
+// p * ROWS_PER_PASS + row.  y_off: the lane's byte offset in the first pass, or one past every descriptor's end if its segment is not whole or not
+// there; rows past M fail the descriptor's check.  edge: the row's end falls into this wave's channels.
+template <int STORE, int PASSES, int ROWS_PER_PASS>
+__device__ inline void store_rows(const uint4 (&v)[PASSES], uint16_t *y, uint32_t y_off, int mt0, int row, int nn, bool live, int M, int N, bool edge)
+{
+    const uint32_t row_stride = (uint32_t)N * 2, bytes = (uint32_t)max(0, min(32, M - mt0)) * row_stride;      // 2^30 at most: N <= 2^24
+    const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(y + (int64_t)mt0 * N, 0, __builtin_amdgcn_readfirstlane((int)bytes), RSRC_FLAGS);
 #pragma unroll
-        for (int e = 0; e < 7; ++e)
-            if (nn + e < N) dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+    for (int p = 0; p < PASSES; ++p)
+        __builtin_amdgcn_raw_buffer_store_b128(v4i{(int)v[p].x, (int)v[p].y, (int)v[p].z, (int)v[p].w}, yr, y_off + p * ROWS_PER_PASS * row_stride, 0,
+                                               STORE == STREAMED ? NON_TEMPORAL : 0);
+    if (STORE == ANY_ALIGNMENT && edge) {
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p)
+            if (live && nn + 8 > N && mt0 + p * ROWS_PER_PASS + row < M) {
+                const uint32_t w[4] = {v[p].x, v[p].y, v[p].z, v[p].w};
+                uint16_t *const dst = y + (int64_t)(mt0 + p * ROWS_PER_PASS + row) * N + nn;
+#pragma unroll
+                for (int e = 0; e < 7; ++e)
+                    if (nn + e < N) dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+            }
     }
 }
 

@@ -96,7 +96,7 @@ __device__ inline void load_scales(float (&scv)[(TNE * 32 + 63) / 64], int32_t (
 // What a wave does with its finished sub-tiles a[t][i] (t < TNE along n from channel nw0, i < TME along m from
 // token mw0; sub-tile numbers sub0 .. of the wave's TN x TM, counted along n first): the split-K exchange, then
 // the epilogue.
-template <class C, int TNE, int TME, bool ALIGNED, bool DUMP, bool ZP>
+template <class C, int TNE, int TME, int STORE, bool DUMP, bool ZP>
 __device__ inline void finish(v16i (&a)[TNE][TME], const float (&scv)[(TNE * 32 + 63) / 64],
                               const int32_t (&zwv)[(TNE * 32 + 63) / 64], uint8_t *lds, int wave_all, int wave, int lane,
                               int sub0, int nw0, int mw0, int M, int N, float s_a, const float *__restrict__ d, int zp,
@@ -166,16 +166,21 @@ __device__ inline void finish(v16i (&a)[TNE][TME], const float (&scv)[(TNE * 32 
     // n = 8 q + 4 (lane / 32) + (r % 4).  The register holds 256 * acc; (float)(256 * acc) equals
     // 256 * (float)acc exactly (acc has fewer than 24 significant bits), and the 2^-8 is folded into
     // the channel scale, which is exact as well, so y = bf16((float)acc * (s_a * s_w[n]) [* d_t]) to
-    // the bit.  The bf16 results go through a wave-private LDS patch ([32 tokens][TNE * 32 channels],
-    // padded rows) so that HBM sees whole 16-byte-per-lane row segments instead of scattered quads.
-    constexpr int WN = TNE * 32;                      // channels of this wave's run
-    constexpr int PATCH_STRIDE = WN * 2 + 16;         // bytes per token row in the patch
+    // the bit.  Bound by latencies where a CU has one workgroup, so constants are read once and a group of 32 tokens is read back while the next
+    // one is computed.  The halves of a wave exchange quads, so that a lane holds eight consecutive channels; those 16 bytes go through
+    // a wave-private LDS patch ([32 tokens][TNE * 32 channels], the granules of a row permuted so that eight lanes hit different banks
+    // both ways), so that HBM sees whole row segments.
+    constexpr int WN = TNE * 32, ROW_BYTES = WN * 2;          // this wave's run of channels
+    constexpr int GRANULES = WN / 8;                          // 16-byte pieces of a row
     // With an activation zero point z the sum wanted is sum_k (v - z) w = acc - z * wsum[n]; the
     // correction is staged as 256 * z * wsum[n] next to the scales (|.| < 2^31 for K <= 65535).
-    constexpr int WAVE_LDS = 32 * PATCH_STRIDE + WN * 8;
-    uint8_t *patch = lds + wave_all * WAVE_LDS;
-    float *cwbuf = reinterpret_cast<float *>(patch + 32 * PATCH_STRIDE);
-    int32_t *zwbuf = reinterpret_cast<int32_t *>(cwbuf + WN);
+    constexpr int WAVE_LDS = 32 * ROW_BYTES + WN * 8;
+    uint8_t *const patch = lds + wave_all * WAVE_LDS;
+    float *const cwbuf = reinterpret_cast<float *>(patch + 32 * ROW_BYTES);
+    int32_t *const zwbuf = reinterpret_cast<int32_t *>(cwbuf + WN);
+    float dm[TME];
+#pragma unroll
+    for (int tm = 0; tm < TME; ++tm) dm[tm] = d ? d[min(mw0 + tm * 32 + fi, M - 1)] : 1.0f;
 #pragma unroll
     for (int i = 0; i < (WN + 63) / 64; ++i) {
         const int c = lane + 64 * i;
@@ -184,53 +189,69 @@ __device__ inline void finish(v16i (&a)[TNE][TME], const float (&scv)[(TNE * 32 
             if (ZP) zwbuf[c] = (zp * zwv[i]) * 256;
         }
     }
-    __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
-    __builtin_amdgcn_wave_barrier();
+    auto in_order = [] {       // a wave's LDS operations complete in order: only the compiler has to be kept from exchanging them
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    in_order();
+    float4 cw[TNE][4];
+#pragma unroll
+    for (int tn = 0; tn < TNE; ++tn)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) cw[tn][q] = *reinterpret_cast<const float4 *>(cwbuf + tn * 32 + 8 * q + 4 * fg);
+    // granule g of row r lies in slot g ^ turn(r)
+    auto turn = [](int r) { return GRANULES % 8 == 0 ? r & 7 : (r >> 2) & 3; };
+    auto to_lds = [&](int tm) {
+        uint8_t *const to = patch + fi * ROW_BYTES;
+        const int slot = fg ^ turn(fi);
+#pragma unroll
+        for (int tn = 0; tn < TNE; ++tn)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                uint32_t p[2][2];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const float4 c4 = cw[tn][2 * j + q];
+                    const float c[4] = {c4.x, c4.y, c4.z, c4.w};
+                    const int r0 = 8 * j + 4 * q;
+                    int32_t a4[4] = {a[tn][tm][r0], a[tn][tm][r0 + 1], a[tn][tm][r0 + 2], a[tn][tm][r0 + 3]};
+                    if (ZP) {
+                        const int4 z4 = *reinterpret_cast<const int4 *>(zwbuf + tn * 32 + 2 * r0 + 4 * fg);
+                        a4[0] -= z4.x, a4[1] -= z4.y, a4[2] -= z4.z, a4[3] -= z4.w;
+                    }
+                    float yf[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) yf[e] = (float)a4[e] * c[e] * dm[tm];
+                    p[q][0] = pack_bf16(yf[0], yf[1]), p[q][1] = pack_bf16(yf[2], yf[3]);
+                }
+                // lanes 32 .. 63 of the first and 0 .. 31 of the second change places: quads 2 j of both halves, and 2 j + 1
+                const auto lo = __builtin_amdgcn_permlane32_swap(p[0][0], p[1][0], false, false);
+                const auto hi = __builtin_amdgcn_permlane32_swap(p[0][1], p[1][1], false, false);
+                *reinterpret_cast<uint4 *>(to + ((tn * 4 + 2 * j) ^ slot) * 16) = make_uint4(lo[0], hi[0], lo[1], hi[1]);
+            }
+        in_order();
+    };
+    // read back as row segments: 16 bytes (8 channels) per lane, GRANULES lanes per token row (rounded up to a power of two; the surplus lanes idle)
+    constexpr int LANES_PER_ROW = GRANULES <= 4 ? 4 : GRANULES <= 8 ? 8 : 16, ROWS_PER_PASS = 64 / LANES_PER_ROW, PASSES = 32 / ROWS_PER_PASS;
+    const int row = lane / LANES_PER_ROW, col = lane % LANES_PER_ROW, nn = nw0 + col * 8;
+    const bool live = col < GRANULES && nn < N;
+    // an offset past every descriptor's end for what is not to be stored; rows past M fail the descriptor's check
+    const uint32_t row_stride = (uint32_t)N * 2;
+    const uint32_t y_off = live && (STORE != ANY_ALIGNMENT || nn + 8 <= N) ? (uint32_t)row * row_stride + (uint32_t)nn * 2 : 0x80000000u;
+    to_lds(0);
 #pragma unroll
     for (int tm = 0; tm < TME; ++tm) {
         const int mt0 = mw0 + tm * 32;
         const int m = mt0 + fi;
-        const float dm = (d && m < M) ? d[m] : 1.0f;
+        uint4 v[PASSES];
 #pragma unroll
-        for (int tn = 0; tn < TNE; ++tn)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 c4 = *reinterpret_cast<const float4 *>(cwbuf + tn * 32 + 8 * q + 4 * fg);
-                int32_t a4[4] = {a[tn][tm][4 * q + 0], a[tn][tm][4 * q + 1], a[tn][tm][4 * q + 2], a[tn][tm][4 * q + 3]};
-                if (ZP) {
-                    const int4 z4 = *reinterpret_cast<const int4 *>(zwbuf + tn * 32 + 8 * q + 4 * fg);
-                    a4[0] -= z4.x, a4[1] -= z4.y, a4[2] -= z4.z, a4[3] -= z4.w;
-                }
-                float yf[4] = {(float)a4[0] * c4.x, (float)a4[1] * c4.y, (float)a4[2] * c4.z, (float)a4[3] * c4.w};
-                if (d) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) yf[e] = yf[e] * dm;
-                }
-                *reinterpret_cast<uint2 *>(patch + fi * PATCH_STRIDE + (tn * 32 + 8 * q + 4 * fg) * 2) =
-                    make_uint2(pack_bf16(yf[0], yf[1]), pack_bf16(yf[2], yf[3]));
-            }
-        __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
-        __builtin_amdgcn_wave_barrier();
-        // read back row segments: 16 bytes (8 channels) per lane, WN / 8 lanes per token row
-        // (lanes per row rounded up to a power of two; the surplus lanes idle)
-        constexpr int LANES_PER_ROW = WN / 8 <= 4 ? 4 : WN / 8 <= 8 ? 8 : 16, ROWS_PER_PASS = 64 / LANES_PER_ROW;
-#pragma unroll
-        for (int pass = 0; pass < 32 / ROWS_PER_PASS; ++pass) {
-            const int row = pass * ROWS_PER_PASS + lane / LANES_PER_ROW, col = (lane % LANES_PER_ROW) * 8;
-            const bool live = col < WN;
-            const uint4 v = live ? *reinterpret_cast<const uint4 *>(patch + row * PATCH_STRIDE + col * 2) : make_uint4(0, 0, 0, 0);
-            const int mm = mt0 + row, nn = nw0 + col;
-            if (live && mm < M && nn < N) {
-                uint16_t *dst = y + (int64_t)mm * N + nn;
-                if (ALIGNED) {       // N % 8 == 0: the segment is whole and 16-byte aligned
-                    __builtin_nontemporal_store(v4i{(int)v.x, (int)v.y, (int)v.z, (int)v.w}, reinterpret_cast<v4i *>(dst));
-                } else {
-                    store_row_segment(dst, v, nn, N);
-                }
-            }
+        for (int p = 0; p < PASSES; ++p) {
+            const int r = p * ROWS_PER_PASS + row;
+            v[p] = *reinterpret_cast<const uint4 *>(patch + r * ROW_BYTES + ((GRANULES == LANES_PER_ROW ? col : min(col, GRANULES - 1)) ^ turn(r)) * 16);
         }
-        __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
-        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (tm + 1 < TME) to_lds(tm + 1);
+        store_rows<STORE, PASSES, ROWS_PER_PASS>(v, y, y_off, mt0, row, nn, live, M, N, nw0 + WN > N);
         if (DUMP) {      // parity dump of the integer accumulators (never a timed path)
 #pragma unroll
             for (int tn = 0; tn < TNE; ++tn)
@@ -247,7 +268,7 @@ __device__ inline void finish(v16i (&a)[TNE][TME], const float (&scv)[(TNE * 32 
 
 // ZP: the epilogue removes an activation zero point (wsum is then non-null); a separate instance, so that the symmetric
 // grid's epilogue carries neither its code nor its registers (the 256 x 256 instance spilled 13 registers with both in one).
-template <class C, bool ALIGNED, bool DUMP, bool ZP>
+template <class C, int STORE, bool DUMP, bool ZP>
 __global__ __launch_bounds__(C::THREADS, C::OCC) void linear_mfma_kernel(
     const uint8_t *__restrict__ xq, const uint8_t *__restrict__ wq, int M, int N, int ktiles, int tiles_m,
     int tiles_n, float s_a, const float *__restrict__ s_w, const float *__restrict__ d, int zp,
@@ -518,11 +539,11 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void linear_mfma_kernel(
         }
         __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
         __builtin_amdgcn_s_barrier();                                // the exchange area is free for the epilogue
-        finish<C, C::TNE, C::TME, ALIGNED, DUMP, ZP>(mine, scv, zwv, lds, wave_all, wave, lane, sub0, fin_nw0, fin_mw0, M, N, s_a, d,
+        finish<C, C::TNE, C::TME, STORE, DUMP, ZP>(mine, scv, zwv, lds, wave_all, wave, lane, sub0, fin_nw0, fin_mw0, M, N, s_a, d,
                                                  zp, wsum, y, acc_out, ws, splits, split, pid, total);
     } else {
         load_scales<C::TN, ZP>(scv, zwv, s_w, wsum, fin_nw0, N, lane);
-        finish<C, C::TN, C::TM, ALIGNED, DUMP, ZP>(acc, scv, zwv, lds, wave_all, wave, lane, 0, fin_nw0, fin_mw0, M, N, s_a, d, zp,
+        finish<C, C::TN, C::TM, STORE, DUMP, ZP>(acc, scv, zwv, lds, wave_all, wave, lane, 0, fin_nw0, fin_mw0, M, N, s_a, d, zp,
                                                wsum, y, acc_out, ws, splits, split, pid, total);
     }
 }
@@ -536,12 +557,12 @@ void set_linear_prefill(int mode) { g_prefill.store(mode, std::memory_order_rela
 void set_gemm_map(int mode) { g_tile_map.store(mode, std::memory_order_relaxed); }
 int forced_gemm_tile() { return g_forced_tile.load(std::memory_order_relaxed); }
 
-template <class C, bool ALIGNED, bool DUMP, bool ZP>
+template <class C, int STORE, bool DUMP, bool ZP>
 static hipError_t launch_inst(const uint8_t *xq, const uint8_t *wq, int64_t M, int64_t N, int64_t K, float s_a,
                               const float *s_w, const float *d, int zp, const int32_t *wsum, uint16_t *y, int32_t *acc,
                               hipStream_t s, int32_t *ws = nullptr, int splits = 1)
 {
-    auto kern = linear_mfma_kernel<C, ALIGNED, DUMP, ZP>;
+    auto kern = linear_mfma_kernel<C, STORE, DUMP, ZP>;
     const DeviceInfo *info;
     hipError_t e0 = device_info(&info);          // sets every instantiation's LDS attribute on the device's first use
     if (e0 != hipSuccess) return e0;
@@ -557,16 +578,14 @@ static hipError_t launch_cfg(const uint8_t *xq, const uint8_t *wq, int64_t M, in
                              const float *s_w, const float *d, int zp, const int32_t *wsum, uint16_t *y, int32_t *acc,
                              hipStream_t s, int32_t *ws = nullptr, int splits = 1)
 {
-    const bool aligned = N % 8 == 0;
-#define FPTQ_GEMM_INST(A, D, Z) return launch_inst<C, A, D, Z>(xq, wq, M, N, K, s_a, s_w, d, zp, wsum, y, acc, s, ws, splits)
-    if (wsum) {
-        if (acc) { if (aligned) FPTQ_GEMM_INST(true, true, true); FPTQ_GEMM_INST(false, true, true); }
-        if (aligned) FPTQ_GEMM_INST(true, false, true);
-        FPTQ_GEMM_INST(false, false, true);
+#define FPTQ_GEMM_INST(S, D) return wsum ? launch_inst<C, S, D, true>(xq, wq, M, N, K, s_a, s_w, d, zp, wsum, y, acc, s, ws, splits) \
+                                         : launch_inst<C, S, D, false>(xq, wq, M, N, K, s_a, s_w, d, zp, wsum, y, acc, s, ws, splits)
+    if (acc) FPTQ_GEMM_INST(ANY_ALIGNMENT, true);
+    switch (store_kind(M, N)) {
+    case CACHED: FPTQ_GEMM_INST(CACHED, false);
+    case STREAMED: FPTQ_GEMM_INST(STREAMED, false);
+    default: FPTQ_GEMM_INST(ANY_ALIGNMENT, false);
     }
-    if (acc) { if (aligned) FPTQ_GEMM_INST(true, true, false); FPTQ_GEMM_INST(false, true, false); }
-    if (aligned) FPTQ_GEMM_INST(true, false, false);
-    FPTQ_GEMM_INST(false, false, false);
 #undef FPTQ_GEMM_INST
 }
 
@@ -595,10 +614,10 @@ typedef GemmCfg<1, 1, 2, 2, 4, 1, 4, true> T64x64k4split;
 constexpr int64_t SCRATCH_BYTES = (int64_t)256 * T64x64k4split::ACC_REGS * 64 * 4 + 4096;
 static __device__ __align__(256) int32_t scratch[SCRATCH_BYTES / 4];
 
-template <class C, bool ALIGNED, bool DUMP, bool ZP>
+template <class C, int STORE, bool DUMP, bool ZP>
 static hipError_t set_lds_attribute()
 {
-    return hipFuncSetAttribute((const void *)linear_mfma_kernel<C, ALIGNED, DUMP, ZP>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    return hipFuncSetAttribute((const void *)linear_mfma_kernel<C, STORE, DUMP, ZP>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                C::LDS_BYTES);
 }
 
@@ -608,10 +627,10 @@ static hipError_t set_lds_attributes()
     hipError_t e = hipSuccess;
     auto one = [&](hipError_t r) { if (e == hipSuccess) e = r; };
     (void)one;
-    ((one(set_lds_attribute<Cs, true, true, false>()), one(set_lds_attribute<Cs, true, false, false>()),
-      one(set_lds_attribute<Cs, false, true, false>()), one(set_lds_attribute<Cs, false, false, false>()),
-      one(set_lds_attribute<Cs, true, true, true>()), one(set_lds_attribute<Cs, true, false, true>()),
-      one(set_lds_attribute<Cs, false, true, true>()), one(set_lds_attribute<Cs, false, false, true>())),
+    ((one(set_lds_attribute<Cs, ANY_ALIGNMENT, true, false>()), one(set_lds_attribute<Cs, ANY_ALIGNMENT, true, true>()),
+      one(set_lds_attribute<Cs, ANY_ALIGNMENT, false, false>()), one(set_lds_attribute<Cs, ANY_ALIGNMENT, false, true>()),
+      one(set_lds_attribute<Cs, CACHED, false, false>()), one(set_lds_attribute<Cs, CACHED, false, true>()),
+      one(set_lds_attribute<Cs, STREAMED, false, false>()), one(set_lds_attribute<Cs, STREAMED, false, true>())),
      ...);
     return e;
 }

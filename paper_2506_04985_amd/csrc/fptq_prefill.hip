@@ -32,8 +32,6 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v12i __attribute__((ext_vector_type(12)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-constexpr int NON_TEMPORAL = 2;                 // cache policy of a buffer store
-
 typedef __attribute__((address_space(3))) const uint8_t lds_u8;
 typedef __attribute__((address_space(3))) const v4i lds_v4i;
 
@@ -154,16 +152,6 @@ struct PrefillTile {
 __device__ inline v16f mfma6(v8i w, v8i x, v16f c)
 {
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w, x, c, 2, 2, 0, 0, 0, 0);
-}
-
-// How results reach memory.  Rows of whole 128-byte lines are streamed (8192 x 57344 x 8192: zeros 1090 us, cached 1365; dense 1632 and 1658).
-// Other widths leave two parts of a line to two waves, which meet in L2 when cached; streamed, each goes to memory by itself: 3000 x
-// 11000 x 2048 76 us, cached 66, 4096 x 4104 x 4096 70 and 65, 1000 x 9000 x 3000 36 and 34.  An output that the 256 MB last-level cache
-// cannot hold is streamed all the same: cached, 8192 x 28680 x 1024 took 271 us instead of 255, 8192 x 16392 x 2048 213 instead of 203.
-enum { ANY_ALIGNMENT, CACHED, STREAMED };          // ANY_ALIGNMENT: N % 8 != 0
-static int store_kind(int64_t M, int64_t N)
-{
-    return N % 8 != 0 ? ANY_ALIGNMENT : N % 64 != 0 && M * N * 2 <= (int64_t)256 << 20 ? CACHED : STREAMED;
 }
 
 template <int TM, int STORE, bool DUMP, bool ZP>
@@ -473,10 +461,10 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     };
-    // a store instruction takes eight rows; a lane whose channels are past the end gets an offset past every descriptor's end
+    // a store instruction takes eight rows
     const int col = (lane & 7) * 8, row = lane >> 3;
     const uint8_t *const from = patch + row * ROW_BYTES + (((lane & 7) ^ row) << 4);
-    const uint32_t row_stride = (uint32_t)N * 2, y_off = nw0 + col < N ? (uint32_t)row * row_stride + (uint32_t)(nw0 + col) * 2 : 0x80000000u;
+    const uint32_t y_off = nw0 + col + (STORE == ANY_ALIGNMENT ? 7 : 0) < N ? (uint32_t)row * ((uint32_t)N * 2) + (uint32_t)(nw0 + col) * 2 : 0x80000000u;
     auto write_out = [&](auto plain_c) {
         to_lds(plain_c, 0);
 #pragma unroll
@@ -486,20 +474,7 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
             for (int p = 0; p < 4; ++p) v[p] = *reinterpret_cast<const uint4 *>(from + (tm & 1) * PATCH_BYTES + p * (8 * ROW_BYTES));
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             if (tm + 1 < C::TM) to_lds(plain_c, tm + 1);
-            const int mt0 = m0 + tm * 32;
-            if (STORE != ANY_ALIGNMENT) {       // the segments are whole and 16-byte aligned; rows past the end fail the descriptor's check
-                const uint32_t bytes = (uint32_t)max(0, min(32, M - mt0)) * row_stride;      // 2^30 at most: N <= 2^24
-                const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(y + (int64_t)mt0 * N, 0, __builtin_amdgcn_readfirstlane((int)bytes), RSRC_FLAGS);
-#pragma unroll
-                for (int p = 0; p < 4; ++p)
-                    __builtin_amdgcn_raw_buffer_store_b128(v4i{(int)v[p].x, (int)v[p].y, (int)v[p].z, (int)v[p].w}, yr, y_off + p * 8 * row_stride, 0,
-                                                           STORE == STREAMED ? NON_TEMPORAL : 0);
-            } else {
-#pragma unroll
-                for (int p = 0; p < 4; ++p)
-                    if (mt0 + p * 8 + row < M && nw0 + col < N)
-                        store_row_segment(y + (int64_t)(mt0 + p * 8 + row) * N + nw0 + col, v[p], nw0 + col, N);
-            }
+            store_rows<STORE, 4, 8>(v, y, y_off, m0 + tm * 32, row, nw0 + col, nw0 + col < N, M, N, nw0 + WN > N);
         }
     };
     if (plain) {
@@ -536,13 +511,10 @@ static hipError_t set_prefill_attributes()
 {
     hipError_t e = hipSuccess;
     auto one = [&](hipError_t r) { if (e == hipSuccess) e = r; };
-#define FPTQ_ATTRIBUTES(S)                                                                              \
-    one(set_prefill_attribute<TM, S, true, false>()), one(set_prefill_attribute<TM, S, false, false>());  \
-    one(set_prefill_attribute<TM, S, true, true>()), one(set_prefill_attribute<TM, S, false, true>())
-    FPTQ_ATTRIBUTES(ANY_ALIGNMENT);
-    FPTQ_ATTRIBUTES(CACHED);
-    FPTQ_ATTRIBUTES(STREAMED);
-#undef FPTQ_ATTRIBUTES
+    one(set_prefill_attribute<TM, ANY_ALIGNMENT, true, false>()), one(set_prefill_attribute<TM, ANY_ALIGNMENT, true, true>());
+    one(set_prefill_attribute<TM, ANY_ALIGNMENT, false, false>()), one(set_prefill_attribute<TM, ANY_ALIGNMENT, false, true>());
+    one(set_prefill_attribute<TM, CACHED, false, false>()), one(set_prefill_attribute<TM, CACHED, false, true>());
+    one(set_prefill_attribute<TM, STREAMED, false, false>()), one(set_prefill_attribute<TM, STREAMED, false, true>());
     return e;
 }
 
@@ -582,19 +554,17 @@ static hipError_t launch_tile(const uint8_t *x6, const float *start, int split, 
     linear_prefill_kernel<TM, A, D, Z><<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), C::LDS_BYTES, s>>>(                          \
         x6, x6_slab(M), start, split, (int)x6_rows(M), wq, (int)M, (int)N, (int)k_tiles(K), (int)tiles_m, (int)tiles_n, s_a, s_w, d,   \
         zp, wsum, y, acc)
-#define FPTQ_PREFILL_OF(S)                                                                                                             \
-    switch ((acc ? 2 : 0) | (wsum ? 1 : 0)) {                                                                                         \
-    case 0: FPTQ_PREFILL(S, false, false); break;                                                                                     \
-    case 1: FPTQ_PREFILL(S, false, true); break;                                                                                      \
-    case 2: FPTQ_PREFILL(S, true, false); break;                                                                                      \
-    default: FPTQ_PREFILL(S, true, true);                                                                                             \
+    const bool z = wsum != nullptr;
+    if (acc) {
+        if (z) FPTQ_PREFILL(ANY_ALIGNMENT, true, true);
+        else FPTQ_PREFILL(ANY_ALIGNMENT, true, false);
+        return hipGetLastError();
     }
     switch (store_kind(M, N)) {
-    case ANY_ALIGNMENT: FPTQ_PREFILL_OF(ANY_ALIGNMENT); break;
-    case CACHED: FPTQ_PREFILL_OF(CACHED); break;
-    default: FPTQ_PREFILL_OF(STREAMED);
+    case CACHED: if (z) FPTQ_PREFILL(CACHED, false, true); else FPTQ_PREFILL(CACHED, false, false); break;
+    case STREAMED: if (z) FPTQ_PREFILL(STREAMED, false, true); else FPTQ_PREFILL(STREAMED, false, false); break;
+    default: if (z) FPTQ_PREFILL(ANY_ALIGNMENT, false, true); else FPTQ_PREFILL(ANY_ALIGNMENT, false, false);
     }
-#undef FPTQ_PREFILL_OF
 #undef FPTQ_PREFILL
     return hipGetLastError();
 }

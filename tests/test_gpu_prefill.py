@@ -84,7 +84,7 @@ def test_epilogue_of_any_scale(forced, M, N, zp, with_d):
 
 
 def test_streamed_rows_of_partial_lines(forced):
-    """A width that is no multiple of 64 and an output above 256 MB: streaming stores whose last channels are cut off."""
+    """A width that is no multiple of 32 and an output above 256 MB: streaming stores whose last channels are cut off."""
     M, N, K = 8200, 16392, 130
     torch.manual_seed(1)
     xq = fptq.fptq_pack_weights(torch.randint(-8, 8, (M, K), dtype=torch.int8, device="cuda"))
