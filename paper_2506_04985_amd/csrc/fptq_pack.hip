@@ -30,15 +30,22 @@ __device__ inline uint32_t pack8(uint32_t lo, uint32_t hi)
 }
 
 // Bound by HBM: a byte read and half a byte written per value.  A thread makes the 16-byte granules (32 values) at one place of
-// PACK_TILES K tiles in a row: a wave reads PACK_TILES x 128 contiguous bytes of 16 rows and writes 1 KB runs.  28672 x 4096: 40 us
-// (4.4 TB/s); a byte per load, one granule per thread, took 221.  Half granules (8 lanes a row) and eight tiles per thread: the same.
+// PACK_TILES K tiles in a row: a wave reads PACK_TILES x 128 contiguous bytes of 16 rows and writes 1 KB runs.  A byte per load, one granule
+// per thread, took 221 us at 28672 x 4096; half granules (8 lanes a row) and eight tiles per thread: the same as now.
+// ALONG_K: consecutive workgroups take the K tiles of the same rows, so that whole rows are read in one go, otherwise the same K tiles of the next
+// rows, which writes longer runs.  28672 x 4096 32.8 us along K, 34.6 otherwise, 8192 x 28672 66 and 70, but 20480 x 5120 30.2 and 29.7,
+// 4096 x 14336 17.5 and 16.9, 640 x 8192 4.1 and 3.6: from 108 MB on.  STREAM: integers and packed weights together above the 256 MB last-level cache, of which then more is left to the
+// integers if the packed weights go past it: 32003 x 8192 87 -> 73 us, with the row sums behind it 122 -> 111; below, 28672 x 4096 32 and 36.
 constexpr int PACK_TILES = 4;
 
-__global__ __launch_bounds__(256) void pack_weights_kernel(const int8_t *__restrict__ w, int64_t N, int64_t K, int64_t row_blocks,
+template <bool ALONG_K, bool STREAM>
+__global__ __launch_bounds__(256) void pack_weights_kernel(const int8_t *__restrict__ w, int64_t N, int64_t K, int64_t row_blocks, int64_t tile_groups,
                                                            uint8_t *__restrict__ out)
 {
-    const int64_t row = (int64_t)(blockIdx.x % row_blocks) * 64 + (threadIdx.x >> 2);
-    const int64_t tile0 = (int64_t)(blockIdx.x / row_blocks) * PACK_TILES, tiles = k_tiles(K);
+    const int64_t row_block = ALONG_K ? blockIdx.x / tile_groups : blockIdx.x % row_blocks;
+    const int64_t tile_group = ALONG_K ? blockIdx.x % tile_groups : blockIdx.x / row_blocks;
+    const int64_t row = row_block * 64 + (threadIdx.x >> 2);
+    const int64_t tile0 = tile_group * PACK_TILES, tiles = k_tiles(K);
     const int c = threadIdx.x & 3;                 // granule inside the 64-byte segment
     if (row >= N) return;
     const int8_t *src = w + row * K;
@@ -49,9 +56,12 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const int8_t *__restr
         for (int h = 0; h < 2; ++h) v[i][h] = load_row16(src, (tile0 + i) * KT + c * 32 + h * 16, K);     // K padding is zero
 #pragma unroll
     for (int i = 0; i < PACK_TILES; ++i)
-        if (tile0 + i < tiles)
-            *reinterpret_cast<uint4 *>(out + ((tile0 + i) * N + row) * SEG + c * 16) =
-                make_uint4(pack8(v[i][0].x, v[i][0].y), pack8(v[i][0].z, v[i][0].w), pack8(v[i][1].x, v[i][1].y), pack8(v[i][1].z, v[i][1].w));
+        if (tile0 + i < tiles) {
+            const v4i p = {(int)pack8(v[i][0].x, v[i][0].y), (int)pack8(v[i][0].z, v[i][0].w), (int)pack8(v[i][1].x, v[i][1].y), (int)pack8(v[i][1].z, v[i][1].w)};
+            v4i *const dst = reinterpret_cast<v4i *>(out + ((tile0 + i) * N + row) * SEG + c * 16);
+            if (STREAM) __builtin_nontemporal_store(p, dst);
+            else *dst = p;
+        }
 }
 
 __global__ __launch_bounds__(256) void unpack_kernel(const uint8_t *__restrict__ packed, int64_t rows, int64_t K,
@@ -97,9 +107,15 @@ __global__ __launch_bounds__(256) void linear_ref_kernel(const uint8_t *__restri
 
 hipError_t launch_pack_weights(const int8_t *w, int64_t N, int64_t K, uint8_t *out, hipStream_t s)
 {
-    const int64_t row_blocks = (N + 63) / 64, blocks = row_blocks * ((k_tiles(K) + PACK_TILES - 1) / PACK_TILES);
+    const int64_t row_blocks = (N + 63) / 64, tile_groups = (k_tiles(K) + PACK_TILES - 1) / PACK_TILES, blocks = row_blocks * tile_groups;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    pack_weights_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(w, N, K, row_blocks, out);
+    const dim3 grid((unsigned)blocks), block(256);
+    if (N * K + packed_bytes(N, K) > (int64_t)256 << 20)
+        pack_weights_kernel<true, true><<<grid, block, 0, s>>>(w, N, K, row_blocks, tile_groups, out);
+    else if (N * K >= (int64_t)108 << 20)
+        pack_weights_kernel<true, false><<<grid, block, 0, s>>>(w, N, K, row_blocks, tile_groups, out);
+    else
+        pack_weights_kernel<false, false><<<grid, block, 0, s>>>(w, N, K, row_blocks, tile_groups, out);
     return hipGetLastError();
 }
 

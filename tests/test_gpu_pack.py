@@ -33,6 +33,19 @@ def test_pack_and_row_sums(N, K, offset):
     assert np.array_equal(fptq.fptq_weight_row_sums(wd).cpu().numpy(), w.sum(axis=1, dtype=np.int32))
 
 
+@pytest.mark.parametrize("N,K", [(28673, 4100), (43700, 4111)])
+def test_large_matrices(N, K):
+    """Sizes at which the workgroups go along K, and at which the packed weights are streamed."""
+    torch.manual_seed(N)
+    w = torch.randint(-8, 8, (N, K), dtype=torch.int8, device="cuda")
+    kt = (K + 127) // 128
+    codes = torch.zeros((N, kt * 128), dtype=torch.uint8, device="cuda")
+    codes[:, :K] = w.view(torch.uint8) & 15
+    want = (codes[:, 0::2] | (codes[:, 1::2] << 4)).view(N, kt, 64).transpose(0, 1).contiguous().view(-1)
+    assert torch.equal(fptq.fptq_pack_weights(w), want)
+    assert torch.equal(fptq.fptq_weight_row_sums(w), w.sum(dim=1, dtype=torch.int32))
+
+
 def test_row_sums_of_full_bytes():
     """Row sums take the int8 as it is, not its low nibble."""
     w = torch.arange(-128, 128, dtype=torch.int16).to(torch.int8).repeat(3, 5)[:, :1237].contiguous().cuda()
