@@ -125,6 +125,50 @@ __device__ inline double add_square(double ss, float v)
     return __builtin_fma(a, a, ss);
 }
 
+// Wave reductions, every lane with the result: partners 32, 16, 8, 4, 2, 1 lanes away, in the order of a loop over __shfl_xor (sums of
+// doubles round the same way), but without its round trips through LDS, six for a sum and twice as many instructions for doubles: with
+// few rows a quantizer's time is one such chain of latencies.
+template <int OFF>
+__device__ inline uint32_t other_lane(uint32_t v)        // of lane ^ OFF, OFF < 16
+{
+    if (OFF == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, false);              // row_ror:8
+    if (OFF == 4) {                                                                                             // row_shl:4, row_shr:4
+        const int up = __builtin_amdgcn_update_dpp((int)v, (int)v, 0x104, 0xF, 0x5, false);
+        return (uint32_t)__builtin_amdgcn_update_dpp(up, (int)v, 0x114, 0xF, 0xA, false);
+    }
+    if (OFF == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);               // quad_perm [2,3,0,1]
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);                             // quad_perm [1,0,3,2]
+}
+
+__device__ inline double wave_sum(double v)
+{
+    auto join = [](uint32_t lo, uint32_t hi) { return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo); };
+    auto lo = [](double d) { return (uint32_t)__builtin_bit_cast(uint64_t, d); };
+    auto hi = [](double d) { return (uint32_t)(__builtin_bit_cast(uint64_t, d) >> 32); };
+    // a swap of a register with itself leaves the values of one side of each pair in the first result, of the other in the second
+    const auto l32 = __builtin_amdgcn_permlane32_swap(lo(v), lo(v), false, false), h32 = __builtin_amdgcn_permlane32_swap(hi(v), hi(v), false, false);
+    v = join(l32[0], h32[0]) + join(l32[1], h32[1]);
+    const auto l16 = __builtin_amdgcn_permlane16_swap(lo(v), lo(v), false, false), h16 = __builtin_amdgcn_permlane16_swap(hi(v), hi(v), false, false);
+    v = join(l16[0], h16[0]) + join(l16[1], h16[1]);
+    v += join(other_lane<8>(lo(v)), other_lane<8>(hi(v)));
+    v += join(other_lane<4>(lo(v)), other_lane<4>(hi(v)));
+    v += join(other_lane<2>(lo(v)), other_lane<2>(hi(v)));
+    v += join(other_lane<1>(lo(v)), other_lane<1>(hi(v)));
+    return v;
+}
+
+__device__ inline uint32_t wave_max(uint32_t v)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = max(a[0], a[1]);
+    const auto b = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = max(b[0], b[1]);
+    v = max(v, other_lane<8>(v));
+    v = max(v, other_lane<4>(v));
+    v = max(v, other_lane<2>(v));
+    return max(v, other_lane<1>(v));
+}
+
 // Core of every activation quantizer: the code q + 8 in [0, 15] of q = clamp(rne(x * c) + z, -8, 7), NaN -> z,
 // with zoff = z + 8.  v_cvt_i32_f32 saturates and turns NaN into 0, the add saturates too, so infinities and
 // huge products end at the clamp like everything else: the same integers as rounding, adding and clamping in

@@ -28,8 +28,7 @@ __device__ inline uint32_t quant_chunk(const uint32_t (&w)[4], float c, int zoff
 
 __device__ inline double block_sum(double v, double *lds)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+    v = wave_sum(v);
     int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) lds[wave] = v;
     __syncthreads();
@@ -163,8 +162,7 @@ __global__ __launch_bounds__(QT) void quantize_act_wave_kernel(const uint16_t *_
                 ss = __builtin_fma(b, b, ss);
             }
         }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+        ss = wave_sum(ss);
         r = (float)(1.0 / sqrt(ss / (double)K + (double)eps));
     } else if (MODE == FPTQ_SCALE_GIVEN) {
         r = row_in[t];
@@ -219,8 +217,7 @@ __global__ __launch_bounds__(QT) void quantize_act_dynamic_kernel(const uint16_t
     } else {
         for (int64_t k = lane; k < K; k += 64) mx = max(mx, abs_bits_no_nan(row[k]));
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+    mx = wave_max(mx);
     const float amax = bf16_to_f32(mx);
     const float s = (amax > 0.0f && mx < 0x7f80u) ? amax / 7.0f : 1.0f;
     const float c = 1.0f / s;
@@ -270,8 +267,7 @@ __global__ __launch_bounds__(QT) void quantize_act_dynamic_row_kernel(const uint
 #pragma unroll
         for (int j = 0; j < 4; ++j) mx = max(mx, max(abs_bits_no_nan(w[j] & 0xffffu), abs_bits_no_nan(w[j] >> 16)));
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+    mx = wave_max(mx);
     if ((tid & 63) == 0) red[tid >> 6] = mx;
     __syncthreads();
 #pragma unroll

@@ -65,8 +65,7 @@ __global__ __launch_bounds__(256) void residual_norm_quantize_kernel(const uint1
             ss = add_square(ss, v);
         }
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+    ss = wave_sum(ss);
     if (WPR > 1) {
         if (lane == 0) red[wave] = ss;
         __syncthreads();
