@@ -10,16 +10,15 @@
 //
 // B = 256.  One wave per token row; a wave walks the row in super-chunks of 1024 values = 4 blocks, a
 // block per 16 lanes, 16 values per lane.  The four high strides need the lane to hold
-// x[16 j + g] (j = 0..15), the four low strides x[16 g + e]: the raw bf16 values go through LDS
-// once to get the strided view, the fp32 intermediates once more to get the contiguous view
-// (padded so that both directions are bank-conflict free).  Everything is wave-private: no
-// barriers.
+// x[16 j + g] (j = 0..15), the four low strides x[16 g + e]: the bf16 values are loaded in the strided view (16 loads side by side;
+// through LDS, as whole lines, was 2 to 4 % slower), the fp32 intermediates go through LDS to get the contiguous view
+// (padded so that both directions are bank-conflict free).  Everything is wave-private: no barriers.
 //
-// Bound by VALU issue, with HBM (2 bytes read, half a byte written per value) close behind: 17 VALU
-// instructions per value at B = 256, 20 at B = 2048 and 4096, which keep the SIMDs issuing in 64, 77 and
-// 87 % of all cycles at 4096 x 11008, 4096 x 14336 and 8192 x 28672 (the plain quantizer: 38 %).
+// Bound by HBM (2 bytes read, half a byte written per value) and VALU issue: 15 to 17 VALU instructions per value at B = 256, 21 at B = 2048
+// and 4096 with a workgroup per block, 24 with a wave per block, which keep the SIMDs issuing in about two thirds of all cycles at
+// 4096 x 11008 and in 87 % at 8192 x 28672 (the plain quantizer: 38 %).  4096 x 11008 takes 26.7 us (27.3 before the loads were direct).
 //
-// B = 64 V with V = 8, 16, 32, 64.  One block per wave iteration, V values per lane.  View 1: the lane
+// B = 64 V with V = 8, 16, 32, 64 (32 and 64: in RMS mode, and beyond the number of blocks at which a workgroup per block is the faster).  One block per wave iteration, V values per lane.  View 1: the lane
 // holds x[64 j + lane] and runs strides B/2 .. 64 in registers; view 2: the lane holds
 // x[V lane + e] and runs strides V/2 .. 1 in registers; the strides in between (32 .. V) pair lane l with
 // lane l ^ (stride / V) and are done with DPP lane exchanges, in descending order between the two
@@ -30,10 +29,12 @@
 namespace fptq {
 
 constexpr int HB = 256;                 // Hadamard block
-constexpr int H_RAW_BLK = 544;          // bytes per block of raw bf16 in LDS (512 + 32: blocks land on different banks)
 constexpr int H_F32_ROW = 20;           // words per 16-value row of the fp32 transpose patch (16 + 4)
 constexpr int H_F32_BLK = 336;          // words per block of the patch (16 * 20 + 16)
-constexpr int H_WAVE_LDS = 4 * H_RAW_BLK + 4 * H_F32_BLK * 4;   // 7552 bytes
+// 5376 bytes of patch, rounded up so that five workgroups share a CU: a line is loaded by four instructions, and the lines in flight of seven
+// workgroups do not fit L1 (8192 x 13824: 64.3 us with seven, 60.2 with five)
+constexpr int H_WAVE_LDS = 7552;
+static_assert(H_WAVE_LDS >= 4 * H_F32_BLK * 4, "");
 
 __device__ inline float h_bf16_to_f32(uint32_t bits) { return __uint_as_float(bits << 16); }
 
@@ -57,7 +58,7 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16
                                                                     float *__restrict__ row_out, int ksplit)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[4 * H_WAVE_LDS];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // ksplit waves share a row: wave `part` of them takes every ksplit-th group of four blocks
     const int64_t wid = (int64_t)blockIdx.x * 4 + wave, t = wid / ksplit;
     const int part = (int)(wid % ksplit);
@@ -77,8 +78,7 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16
                 ss = __builtin_fma(b, b, ss);
             }
         }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+        ss = wave_sum(ss);
         r = (float)(1.0 / sqrt(ss / (double)K + (double)eps));
     } else if (MODE == FPTQ_SCALE_GIVEN) {
         r = row_in[t];
@@ -87,21 +87,18 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16
     if (lane == 0 && part == 0 && row_out) row_out[t] = r;
 
     const int b = lane >> 4, g = lane & 15;
-    uint8_t *raw = lds + wave * H_WAVE_LDS + b * H_RAW_BLK;
-    float *patch = reinterpret_cast<float *>(lds + wave * H_WAVE_LDS + 4 * H_RAW_BLK) + b * H_F32_BLK;
+    // a lane's 16 results: K tile 2 b + g / 8 of the super-chunk's, bytes 8 (g % 8) of the row's segment
+    const int64_t lane_out = (int64_t)(2 * b + (g >> 3)) * M * SEG + (g & 7) * 8;
+        float *patch = reinterpret_cast<float *>(lds + wave * H_WAVE_LDS) + b * H_F32_BLK;
 
     for (int64_t sc = (int64_t)part * (4 * HB); sc < K; sc += (int64_t)ksplit * (4 * HB)) {
-        const int64_t k0 = sc + b * HB + 16 * g;          // first of this lane's 16 contiguous values
-        const bool live = sc + b * HB < K;
-        if (live) {
-            const uint4 lo = *reinterpret_cast<const uint4 *>(row + k0), hi = *reinterpret_cast<const uint4 *>(row + k0 + 8);
-            *reinterpret_cast<uint4 *>(raw + g * 32) = lo;
-            *reinterpret_cast<uint4 *>(raw + g * 32 + 16) = hi;
-        }
+        const int live_blocks = (int)min((int64_t)4, (K - sc) / HB);      // lanes of blocks past the row's end repeat the last one
         // strided view x[16 j + g]: strides 128, 64, 32, 16 of the block are strides 8, 4, 2, 1 in j
         float v[16];
+        const uint16_t *const src = row + sc;
+        const int at = min(b, live_blocks - 1) * HB + g;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) v[j] = h_bf16_to_f32(*reinterpret_cast<const uint16_t *>(raw + (16 * j + g) * 2));
+        for (int j = 0; j < 16; ++j) v[j] = h_bf16_to_f32(src[at + 16 * j]);
         butterflies16(v);
         // transpose inside the block: value (j, g) to row j, column g; read back row g
 #pragma unroll
@@ -112,7 +109,7 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16
             v[4 * i] = f.x, v[4 * i + 1] = f.y, v[4 * i + 2] = f.z, v[4 * i + 3] = f.w;
         }
         butterflies16(v);                                 // contiguous view: strides 8, 4, 2, 1
-        if (live) {
+        if (b < live_blocks) {
             uint32_t w0 = 0, w1 = 0;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -120,7 +117,7 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16
                 w1 |= quant_code(v[8 + e], c, 8) << (4 * e);
             }
             w0 ^= CODE_TO_NIBBLES, w1 ^= CODE_TO_NIBBLES;
-            *reinterpret_cast<uint2 *>(out + ((k0 / KT) * M + t) * SEG + (k0 % KT) / 2) = make_uint2(w0, w1);
+            *reinterpret_cast<uint2 *>(out + ((sc / KT) * M + t) * SEG + lane_out) = make_uint2(w0, w1);
         }
     }
 }
@@ -189,8 +186,7 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_wide_kernel(const u
                 ss = __builtin_fma(b, b, ss);
             }
         }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+        ss = wave_sum(ss);
         r = (float)(1.0 / sqrt(ss / (double)K + (double)eps));
     } else if (MODE == FPTQ_SCALE_GIVEN) {
         r = row_in[t];
@@ -240,6 +236,84 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_wide_kernel(const u
                 *reinterpret_cast<uint4 *>(dst + 16 * i) = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
         }
     }
+}
+
+// ---------------------------------------------------------------------------------- B = 2048, 4096, few blocks
+// A workgroup of B / 16 threads per block, 16 values a thread: where the whole call is the latency of one block, a wave that holds all of it
+// takes four times as many instructions one after the other (one token of 14336 values 3.4 us, now 2.7, 28672 4.8 and 2.8).  Three views of the
+// block, elements e of LOGB bits: thread = the low bits, registers = the top four (loaded as they are: 16 loads side by side); registers =
+// the next four, thread = the rest; 16 consecutive elements a thread.  The strides run from B / 2 to 1 as in the definition, four
+// (in the last view of B = 2048 three) per view.  Between views the values go through LDS, the first time across waves (a barrier), the second
+// inside the thread's wave; element e lies in word e + 4 (e / 16) + 2^(LOGB-8) (e / 2^(LOGB-4)), which leaves the reads free of bank conflicts.
+template <int MODE, int LOGB>
+__global__ __launch_bounds__(1 << (LOGB - 4)) void quantize_act_hadamard_group_kernel(const uint16_t *__restrict__ x, int64_t M, int64_t K,
+                                                                                     const float *__restrict__ row_in, float inv_s_a, float hnorm,
+                                                                                     uint8_t *__restrict__ out, float *__restrict__ row_out, int blocks)
+{
+    static_assert(LOGB == 11 || LOGB == 12, "views of four bits");
+    constexpr int B = 1 << LOGB, THREADS = B / 16, LOW = LOGB - 8;      // LOW bits below the second view's four
+    __shared__ __attribute__((aligned(16))) float lds[B + B / 4 + (16 << LOW)];
+    auto word = [](int e) { return e + 4 * (e >> 4) + ((e >> (LOGB - 4)) << LOW); };
+    const int t = threadIdx.x;
+    const int64_t m = blockIdx.x / blocks;
+    const int blk = (int)(blockIdx.x % blocks);
+    const uint16_t *row = x + m * K, *src = row + (int64_t)blk * B;
+    float v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = h_bf16_to_f32(src[j * THREADS + t]);
+
+    float r = 1.0f;
+    if (MODE == FPTQ_SCALE_GIVEN) r = row_in[m];
+    const float c = ((MODE == FPTQ_SCALE_NONE) ? inv_s_a : r * inv_s_a) * hnorm;
+    if (t == 0 && blk == 0 && row_out) row_out[m] = r;
+
+    butterflies16(v);
+    // word() of a thread's element plus that of a register's: no bit of one carries into the other
+    float *const first = lds + t + 4 * (t >> 4), *const second = lds + word(((t >> LOW) << (LOGB - 4)) | (t & ((1 << LOW) - 1)));
+#pragma unroll
+    for (int j = 0; j < 16; ++j) first[word(j * THREADS)] = v[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = second[word(j << LOW)];
+    butterflies16(v);
+    // a thread writes the elements it has read; the ones it reads next were written by its own wave, whose LDS operations complete in order
+#pragma unroll
+    for (int j = 0; j < 16; ++j) second[word(j << LOW)] = v[j];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float4 f = *reinterpret_cast<const float4 *>(lds + word(t * 16) + 4 * i);
+        v[4 * i] = f.x, v[4 * i + 1] = f.y, v[4 * i + 2] = f.z, v[4 * i + 3] = f.w;
+    }
+#pragma unroll
+    for (int s = LOGB == 12 ? 8 : 4; s >= 1; s >>= 1)
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+            if ((j & s) == 0) {
+                const float a = v[j], b = v[j + s];
+                v[j] = a + b;
+                v[j + s] = a - b;
+            }
+    uint32_t w[2] = {0, 0};
+#pragma unroll
+    for (int e = 0; e < 16; ++e) w[e / 8] |= quant_code(v[e], c, 8) << (4 * (e % 8));
+    const int64_t k0 = (int64_t)blk * B + t * 16;
+    *reinterpret_cast<uint2 *>(out + ((k0 / KT) * M + m) * SEG + (k0 % KT) / 2) = make_uint2(w[0] ^ CODE_TO_NIBBLES, w[1] ^ CODE_TO_NIBBLES);
+}
+
+template <int LOGB>
+static hipError_t launch_group(const uint16_t *x, int64_t M, int64_t K, int mode, const float *row_in, float inv_s_a, uint8_t *out,
+                               float *row_out, hipStream_t s)
+{
+    const int blocks = (int)(K >> LOGB);
+    const float hnorm = (float)(1.0 / sqrt((double)(1 << LOGB)));
+    dim3 grid((unsigned)(M * blocks)), block(1 << (LOGB - 4));
+    if (mode == FPTQ_SCALE_GIVEN)
+        quantize_act_hadamard_group_kernel<FPTQ_SCALE_GIVEN, LOGB><<<grid, block, 0, s>>>(x, M, K, row_in, inv_s_a, hnorm, out, row_out, blocks);
+    else
+        quantize_act_hadamard_group_kernel<FPTQ_SCALE_NONE, LOGB><<<grid, block, 0, s>>>(x, M, K, row_in, inv_s_a, hnorm, out, row_out, blocks);
+    return hipGetLastError();
 }
 
 // Waves per row: with few rows a wave per row leaves the device idle (one token of 11008 values took 9.5 us, as
@@ -307,6 +381,12 @@ static hipError_t launch_wide(const uint16_t *x, int64_t M, int64_t K, int mode,
 hipError_t launch_quantize_act_hadamard(const uint16_t *x, int64_t M, int64_t K, int hadamard_block, int mode, float eps,
                                         const float *row_in, float inv_s_a, uint8_t *out, float *row_out, hipStream_t s)
 {
+    // A workgroup per block, unless its scale would have to be summed in every wave of every block, over the whole row (RMS mode: 1 x 14336
+    // 8.5 -> 7.4 us, but 16 x 14336 10.6 -> 11.5, 2048 x 28672 64 -> 223)
+    // and up to 32768 blocks (4096 x 14336 35.4 -> 34.3, 2048 x 28672 42.0 -> 36.2, 4096 x 8192 25.2 -> 21.5; 8192 x 14336 66.6, 67.4)
+    if (hadamard_block >= 2048 && mode != FPTQ_SCALE_RMS && M <= 32768 && M * (K / hadamard_block) <= 32768)
+        return hadamard_block == 2048 ? launch_group<11>(x, M, K, mode, row_in, inv_s_a, out, row_out, s)
+                                      : launch_group<12>(x, M, K, mode, row_in, inv_s_a, out, row_out, s);
     switch (hadamard_block) {
     case 512: return launch_wide<8>(x, M, K, mode, eps, row_in, inv_s_a, out, row_out, s);
     case 1024: return launch_wide<16>(x, M, K, mode, eps, row_in, inv_s_a, out, row_out, s);

@@ -62,6 +62,21 @@ def test_hadamard_block_sizes_bit_exact(oracle, mode, M, K, B):
     assert largest_block_matches(K, B)
 
 
+@pytest.mark.parametrize("mode", [synth.MODE_NONE, synth.MODE_GIVEN])
+@pytest.mark.parametrize("M,K,B", [(16400, 4096, 2048), (32800, 4096, 4096)])
+def test_many_blocks_equal_few(mode, M, K, B):
+    """A wave per block beyond 32768 blocks, a workgroup per block below: the same codes."""
+    torch.manual_seed(B)
+    x = torch.randn((M, K), device="cuda").to(torch.bfloat16)
+    r = torch.rand(M, device="cuda") + 0.5 if mode == synth.MODE_GIVEN else None
+    q, s = fptq.fptq_quantize_act_hadamard(x, 0.4, B, mode, 1e-5, r)
+    q = fptq.fptq_unpack(q, M, K)
+    for i in range(0, M, M // 4):
+        part = slice(i, i + M // 4)
+        qp, sp = fptq.fptq_quantize_act_hadamard(x[part], 0.4, B, mode, 1e-5, None if r is None else r[part].clone())
+        assert torch.equal(fptq.fptq_unpack(qp, M // 4, K), q[part]) and torch.equal(sp, s[part])
+
+
 def largest_block_matches(K, B):
     return K % B == 0 and B <= T.largest_pow2_divisor(K)
 
