@@ -31,7 +31,7 @@ int fptq_set_gemm_map(int mode);
 int fptq_set_decode_shape(int code);
 
 /* Whether fptq_w4a4_linear_scratch takes its six-bit kernel: 0 = where it pays (default), 1 = wherever its limits allow and the
- * few-token kernel does not answer, 2 = never, 128 or 256 = as 1, with tiles of that many tokens.  Results do not depend on it.  Returns 0 or FPTQ_ERR_VALUE (-6). */
+ * few-token kernel does not answer, 2 = never, 128, 192 or 256 = as 1, with tiles of that many tokens.  Results do not depend on it.  Returns 0 or FPTQ_ERR_VALUE (-6). */
 int fptq_set_linear_prefill(int mode);
 
 /* Host arithmetic only: which kernel fptq_w4a4_linear (with_workspace = 0), fptq_w4a4_linear_ws with a large enough

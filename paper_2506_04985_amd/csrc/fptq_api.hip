@@ -462,8 +462,8 @@ int fptq_set_gemm_map(int mode)
 
 int fptq_set_linear_prefill(int mode)
 {
-    if ((mode < 0 || mode > 2) && mode != 128 && mode != 256) {
-        set_error("fptq_set_linear_prefill: mode must be 0, 1, 2, 128 or 256");
+    if ((mode < 0 || mode > 2) && mode != 128 && mode != 192 && mode != 256) {
+        set_error("fptq_set_linear_prefill: mode must be 0, 1, 2, 128, 192 or 256");
         return FPTQ_ERR_VALUE;
     }
     set_linear_prefill(mode);

@@ -49,7 +49,7 @@ hipError_t launch_linear_prefill(const uint8_t *xq, const uint8_t *wq, int64_t M
                                  hipStream_t s);
 int64_t prefill_scratch_bytes(int64_t M, int64_t K);
 int64_t prefill_workgroups(int64_t M, int64_t N, int tile_tokens);
-int prefill_tile(int64_t M, int64_t N, int64_t K);      // tokens per tile (256 or 128), 0 where another kernel is faster
+int prefill_tile(int64_t M, int64_t N, int64_t K);      // tokens per tile (256, 192 or 128), 0 where another kernel is faster
 hipError_t launch_linear_decode(const uint8_t *xq, const uint8_t *wq, int64_t M, int64_t N, int64_t K, float s_a,
                                 const float *s_w, const float *d, int zp, const int32_t *wsum, uint16_t *y, int32_t *acc,
                                 hipStream_t s);

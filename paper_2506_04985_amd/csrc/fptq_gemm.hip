@@ -739,17 +739,17 @@ static int choose_tile(int64_t M, int64_t N, int64_t K, int cus, double *us = nu
 
 // Whether a problem is faster on the six-bit kernel (fptq_prefill.hip), widening of its activations included, and with how many tokens
 // per tile.  Estimated times on uniform random operands, as above, in rounds of one tile of 256 channels per CU: a partial
-// last round costs less than a full one (the power it leaves speeds its tiles up), and so does a lone one.  Fitted to 440 shapes of 65 to
-// 8192 tokens and checked on 220 others, both with the weights read from HBM, as in a model larger than the last-level cache, and with
-// them in that cache, e.g. (us from HBM, the better INT8 shape / 256 / 128 tokens; in brackets from the cache)
-//     4096 x 28672 x 4096   345 / 261 / 312  (339 / 249 / 309)      1000 x 5120 x 13824   63 /  93 / 62  (61 / 73 / 53)
-//     2048 x 22016 x 4096   142 / 107 / 131  (139 / 103 / 128)      2048 x 4096 x 11008   66 /  77 / 60  (65 / 64 / 55)
-//     4096 x 6144 x 4096     78 /  69 /  72  ( 76 /  67 /  71)       589 x 7391 x 17552   76 / 115 / 77  (74 / 90 / 64)
-//      512 x 8192 x 8192     33 /  59 /  40  ( 31 /  48 /  34)       133 x 18816 x 13312  58 /  89 / 62  (56 / 68 / 48)
-// i.e. the small tile wins where the large one leaves CUs without work, and INT8 where even the small one does.  The margins (wider
-// for few K tiles, where stores and launches weigh more than in what the estimates were fitted to) leave six of the 660 more than 5 %
-// slower than INT8 with the weights read from HBM (91 x 55040 x 5808 43 / 55 / 49 is the worst, then 139 x 37504 x 3456 31 / 34 / 40) and
-// one from the cache (the first of these, 36 / 47 / 39).
+// last round costs less than a full one (the power it leaves speeds its tiles up), and so does a lone one.  Fitted to 350 shapes of 65 to
+// 4096 tokens and checked on 150 others, both with the weights read from HBM, as in a model larger than the last-level cache, and with
+// them in that cache, e.g. (us from HBM, the better INT8 shape / 256 / 192 / 128 tokens; in brackets from the cache)
+//     2048 x 4096 x 11008    69 /  73 /  65 /  61  (68 / 60 / 59 / 59)     333 x 32000 x 4096   46 / 40 / 36 / 50  (44 / 38 / 33 / 44)
+//     1000 x 5120 x 13824    70 /  88 /  67 /  60  (63 / 68 / 59 / 54)     192 x 28672 x 4096   29 / 33 / 31 / 29  (26 / 26 / 24 / 25)
+//      700 x 10240 x 8192    52 /  57 /  53 /  45  (49 / 46 / 43 / 43)     512 x 8192 x 8192    34 / 56 / 47 / 39  (33 / 44 / 38 / 32)
+// i.e. the tile that leaves the fewest CUs without work, and INT8 where each leaves too many.  Where a tile shape occupies less than four
+// fifths of the CUs in a single round, the estimates spread most and INT8's smaller tiles are closest, so it takes 48 K tiles; and
+// 192 tokens are taken for up to a round and a half (beyond that 256 are within a few percent).  The margins (wider for few K tiles, where stores
+// and launches weigh more than in what the estimates were fitted to) leave one of the 500 shapes 5 % slower than INT8.
+// Tiles of 160 and 96 tokens were within 3 % of the best of the others but on 22 of the first 200 shapes (192 x 28672 x 4096: 26 and 29): not kept.
 int prefill_tile(int64_t M, int64_t N, int64_t K)
 {
     if (K > 131071 || M > (1 << 24) || N > (1 << 24) || forced_gemm_tile() > 0) return 0;
@@ -761,20 +761,28 @@ int prefill_tile(int64_t M, int64_t N, int64_t K)
     if (mode == 0 && M <= 64) return 0;
     const int cus = device_cus_or_default();
     const double kt = (double)k_tiles(K), widen_us = (double)M * (double)K * 1.25 / 5.0e6;
-    auto rounds = [&](int tokens, double lone, double least) {
-        const double x = (double)prefill_workgroups(M, N, tokens) / (double)cus, part = x - floor(x);
-        return x < 1.0 ? lone + (1.0 - lone) * x : floor(x) + (part > 0.0 ? least + (1.0 - least) * part : 0.0);
+    struct Tile {
+        int tokens;
+        double call_us, lone, least, tile_us, k_tile_us;
     };
-    const double us256 = 5.1 + widen_us + rounds(256, 0.60, 0.62) * (10.7 + 0.768 * kt);
-    double us128 = 5.0 + widen_us + rounds(128, 0.80, 0.60) * (6.4 + 0.478 * kt);
-    // A single row of tiles streams its weights once, from HBM: with few workgroups that is bound by what one CU keeps in flight
-    // (96 x 37397 x 17536, 147 workgroups: 92 us against 85 on INT8 tiles; 96 x 57344 x 8192, 224 workgroups: 53 against 53).
-    if (M <= 128 && 4 * prefill_workgroups(M, N, 128) < 3 * cus) us128 = us256;
-    const int tokens = us128 < us256 ? 128 : 256;
-    if (mode == 1) return tokens;
+    static const Tile tiles[] = {{256, 5.0, 0.58, 0.53, 7.5, 0.789}, {192, 4.95, 0.54, 0.58, 5.4, 0.649}, {128, 5.75, 0.58, 0.69, 3.8, 0.494}};
+    int tokens = 0;
+    double us = 0.0;
+    for (const Tile &t : tiles) {
+        const int64_t workgroups = prefill_workgroups(M, N, t.tokens);
+        const double x = (double)workgroups / (double)cus, part = x - floor(x);
+        // A single row of small tiles streams its weights once, from HBM: with few workgroups that is bound by what one CU keeps in flight
+        // (96 x 37397 x 17536, 147 workgroups: 92 us against 85 on INT8 tiles; 96 x 57344 x 8192, 224 workgroups: 53 against 53).
+        if (t.tokens == 128 && M <= 128 && x < 0.75) continue;
+        if (mode == 0 && ((x < 0.8 && kt < 48) || (t.tokens == 192 && x > 1.5))) continue;
+        const double rounds = x < 1.0 ? t.lone + (1.0 - t.lone) * x : floor(x) + (part > 0.0 ? t.least + (1.0 - t.least) * part : 0.0);
+        const double est = t.call_us + widen_us + rounds * (t.tile_us + t.k_tile_us * kt);
+        if (tokens == 0 || est < us) tokens = t.tokens, us = est;
+    }
+    if (mode == 1 || tokens == 0) return tokens;
     double int8_us = 0.0;
     choose_tile(M, N, K, cus, &int8_us);
-    return fmin(us128, us256) < (kt < 32 ? 0.90 : 0.94) * int8_us ? tokens : 0;
+    return us < (kt < 32 ? 0.85 : 0.94) * int8_us ? tokens : 0;
 }
 
 // Limits of the MFMA kernel: the widened accumulator is 256 * acc with |acc| <= 64 K, and one K tile of all rows

@@ -11,8 +11,8 @@
 // Data flow.  A small kernel first widens the packed activations to six bits in a scratch buffer of the caller (0.75 bytes a
 // value, read and written once: 15 us at 8192 x 8192 beside 1747 us of a 57344-channel product), with their signs resolved, and sums each
 // token's codes.  The matrix kernel copies those to LDS with buffer loads that write LDS directly, and reads the weights as
-// they are, packed: each of its four waves owns 64 channels and all tokens of the tile (256 or 128), so a weight is loaded by one
-// wave only, into registers (256 tokens) or through LDS of the wave's own (128), and its nibbles are spread to six-bit fields by
+// they are, packed: each of its four waves owns 64 channels and all tokens of the tile (256, 192 or 128), so a weight is loaded by one
+// wave only, into registers (256 and 192 tokens) or through LDS of the wave's own (128), and its nibbles are spread to six-bit fields by
 // 18 VALU instructions per 32 values, 2.25 per MFMA.  Widening both operands in the kernel would take 5.7 VALU instructions per MFMA, and one wave
 // per SIMD issues at most eight instructions in the 32 cycles of an MFMA: measured at the INT8 loop's rate.  Widening the
 // weights beforehand as well would cost 1.25 bytes of traffic per weight and call, 5 % at 8192 tokens.
@@ -35,12 +35,12 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) const uint8_t lds_u8;
 typedef __attribute__((address_space(3))) const v4i lds_v4i;
 
-// ---- six-bit activations in the scratch buffer: blocks of (K tile, 128 rows), 12 KB each, row blocks innermost.  A block is six
-// planes [half][piece][row] of 16-byte pieces: half h of a row holds its values 64 h .. 64 h + 63 as 48 bytes of six-bit
-// fields, i.e. three pieces.  The matrix kernel copies one or two blocks to LDS as they are, and a wave's fragment read (one piece of
-// 32 consecutive rows per half) is contiguous: no bank conflicts, no swizzle, and all of it in 16-byte reads (the 24 bytes of one
+// ---- six-bit activations in the scratch buffer: blocks of (K tile, 32 rows), 3 KB each, row blocks innermost, so that a tile of any
+// number of blocks is one run.  A block is six planes [half][piece][row] of 16-byte pieces: half h of a row holds its values 64 h ..
+// 64 h + 63 as 48 bytes of six-bit fields, i.e. three pieces.  The matrix kernel copies blocks to LDS as they are, and a wave's fragment
+// read (one piece of 32 rows per half) is contiguous: no bank conflicts, no swizzle, and all of it in 16-byte reads (the 24 bytes of one
 // operand read as 16 + 8 made LDS the bound: 1627 instead of 1227 us on zero operands at 8192 x 57344 x 8192).
-constexpr int X6_ROWS = 128, X6_PLANE = X6_ROWS * 16, X6_BLOCK = 6 * X6_PLANE;
+constexpr int X6_ROWS = 32, X6_PLANE = X6_ROWS * 16, X6_BLOCK = 6 * X6_PLANE;
 constexpr int X6_PAD = 256;                     // rows are padded to a multiple of this
 static int64_t x6_rows(int64_t M) { return (M + X6_PAD - 1) / X6_PAD * X6_PAD; }
 static int64_t x6_slab(int64_t M) { return x6_rows(M) * (X6_BLOCK / X6_ROWS); }      // bytes per K tile
@@ -132,19 +132,23 @@ __global__ __launch_bounds__(64 * CV_WAVES) void widen_activations_kernel(const 
 // with three and with six K tiles ahead: 1000 x 5120 x 13824 took 73 us on weights from HBM (53 from the last-level cache), 589 x 7391 x
 // 17552 91 (67); copied to LDS as they lie and read back 61 (52) and 77 (62).  Where the CUs are full and the weights are in
 // the cache the extra LDS traffic costs up to 4 % (2048 x 4096 x 11008 54 -> 56, from HBM 63 -> 57).  256 tokens (TM = 8) widen each weight
-// for eight MFMAs, 128 (TM = 4) for four and load twice the weights per operation; they are for problems that the large tile cuts
-// into fewer pieces than there are CUs: weights from HBM, 1000 x 5120 x 13824 takes 62 us with them, 93 without and 63 on INT8 tiles,
-// 2048 x 4096 x 11008 60, 77 and 66, but 4096 x 28672 x 4096 312, 261 and 345.
+// for eight MFMAs, 128 (TM = 4) for four and load twice the weights per operation; the small tiles are for problems that the large one
+// cuts into fewer pieces than there are CUs, or into a few more: weights from HBM, 1000 x 5120 x 13824 takes 60 us with 128 tokens, 67 with
+// 192, 88 with 256 and 70 on INT8 tiles, 333 x 32000 x 4096 50, 36, 40 and 46.
 template <int TM_>
 struct PrefillTile {
     static constexpr int TN = 2, TM = TM_, STAGES = 5, DEPTH = 3;
-    static constexpr bool W_LDS = TM == 4;          // five stages of both operands are 140 of the 160 KB of LDS; the large tile's would not fit
+    static constexpr bool W_LDS = TM == 4;          // five stages of both operands are 140 of the 160 KB of LDS; a larger tile's would not fit
     static constexpr int BN = 4 * TN * 32, BM = TM * 32;
     static constexpr int X_BYTES = BM * (X6_BLOCK / X6_ROWS), W_BYTES = TN * 32 * SEG;          // 3 KB per 32 tokens; a wave's 4 KB of weights
-    static constexpr int STAGE_BYTES = X_BYTES + (W_LDS ? 4 * W_BYTES : 0);
-    static constexpr int FILLS = X_BYTES / 4096, W_LOADS = 2 * TN, LOADS = FILLS + W_LOADS;     // vector loads of a wave per K tile
+    // vector loads of a wave per K tile: equally many for each wave, so that the waves can count them; the last ones may have nothing to copy
+    static constexpr int FILLS = (X_BYTES + 4095) / 4096, W_LOADS = 2 * TN, LOADS = FILLS + W_LOADS;
+    static constexpr int X_LDS = FILLS * 4096, STAGE_BYTES = X_LDS + (W_LDS ? 4 * W_BYTES : 0);
+    // the loop issues the weights' loads in groups 0 and 1 of its TM groups of MFMAs, two fills in group 2, and one in each after that
+    static constexpr int BEFORE_LAST = W_LOADS + 2;                                             // loads issued before the last group (W_LDS: four groups)
     static constexpr int RING_BYTES = STAGES * STAGE_BYTES, LDS_BYTES = RING_BYTES + (2 * BN + BM) * 4;
-    static_assert(TM == 8 || TM == 4, "the loads and the widening are dealt to eight or four MFMA groups by hand");
+    static_assert(TM >= 4 && TM <= 8 && 2 + TM - 3 >= FILLS, "a group for every load");
+    static_assert(LDS_BYTES <= 160 * 1024, "");
     static_assert(W_LDS || (DEPTH >= STAGES - 3 && DEPTH <= STAGES - 1), "the wait counts assume weights and fills issued in the loop's order from the start");
 };
 
@@ -184,10 +188,20 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     // ---- activations, HBM -> LDS: one run of 3 TM KB per K tile, a quarter of it per wave.  Past the last K tile the descriptor is
     // empty: the loads are still issued (the wait counts stay the same) and land as zeros.
     const int x_voff = bm * C::X_BYTES + wave * (C::FILLS * 1024) + lane * 16;
+    const int x_end = min((int)x_slab, (bm + 1) * C::X_BYTES);      // past it lie other tiles' rows, or none
     uint8_t *const fill_base = lds + wave * (C::FILLS * 1024);
     auto fill1 = [&](auto jc, __amdgpu_buffer_rsrc_t r, uint8_t *to) {
         constexpr int J = decltype(jc)::value;     // 1 KB; the instruction's offset moves both addresses
         __builtin_amdgcn_raw_ptr_buffer_load_lds(r, LDS_PTR(to + J / 3 * 3072), 16, x_voff + J / 3 * 3072, 0, J % 3 * 1024, 0);
+    };
+    auto fill_from = [&](auto from, auto n, __amdgpu_buffer_rsrc_t r, uint8_t *to) {       // n of the loads of a K tile
+        constexpr int J = decltype(from)::value, N_ = decltype(n)::value;
+        if constexpr (N_ > 0) fill1(std::integral_constant<int, J>(), r, to);
+        if constexpr (N_ > 1) fill1(std::integral_constant<int, J + 1>(), r, to);
+        if constexpr (N_ > 2) fill1(std::integral_constant<int, J + 2>(), r, to);
+        if constexpr (N_ > 3) fill1(std::integral_constant<int, J + 3>(), r, to);
+        if constexpr (N_ > 4) fill1(std::integral_constant<int, J + 4>(), r, to);
+        if constexpr (N_ > 5) fill1(std::integral_constant<int, J + 5>(), r, to);
     };
     auto slab_desc = [&](const uint8_t *p, int64_t bytes, bool in) {
         return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, in ? (int)bytes : 0, RSRC_FLAGS);
@@ -204,12 +218,12 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     // W_LDS: a wave first copies the 4 KB of its rows as they lie in HBM to its own part of the ring's stage, behind the activations, the
     // 16-byte granules of a row permuted (granule g of row r in slot g ^ (r / 4) % 4) so that the reads back are free of bank conflicts.
     const int w_lane = (nw0 + (lane >> 2)) * SEG + (((lane & 3) ^ ((lane >> 4) & 3)) << 4);
-    uint8_t *const w_fill_base = lds + C::X_BYTES + wave * C::W_BYTES;
+    uint8_t *const w_fill_base = lds + C::X_LDS + wave * C::W_BYTES;
     auto w_fill1 = [&](auto jc, __amdgpu_buffer_rsrc_t r, uint8_t *to) {
         constexpr int J = decltype(jc)::value;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(r, LDS_PTR(to), 16, w_lane, 0, J * 1024, 0);
     };
-    lds_u8 *const w_base = (lds_u8 *)lds + C::X_BYTES + wave * C::W_BYTES + fi * SEG;
+    lds_u8 *const w_base = (lds_u8 *)lds + C::X_LDS + wave * C::W_BYTES + fi * SEG;
     const int w_slot0 = ((2 * fg) ^ ((fi >> 2) & 3)) << 4;
     auto read_w = [&](int stage_off, v4i (&r)[2][C::TN]) {
 #pragma unroll
@@ -223,7 +237,7 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     lds_u8 *const x_base = (lds_u8 *)lds + fg * (3 * X6_PLANE) + fi * 16;
     v12i X[C::TM];
     auto read_x = [&](int stage_off, int x) {
-        lds_u8 *const p = x_base + stage_off + (x / 4) * X6_BLOCK + (x % 4) * 512;
+        lds_u8 *const p = x_base + stage_off + x * X6_BLOCK;
         const v4i a = *(lds_v4i *)p, b = *(lds_v4i *)(p + X6_PLANE), c = *(lds_v4i *)(p + 2 * X6_PLANE);
         const v8i ab = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7), cc = __builtin_shufflevector(c, c, 0, 1, 2, 3, -1, -1, -1, -1);
         X[x] = __builtin_shufflevector(ab, cc, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11);
@@ -232,12 +246,14 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     // ---- the accumulators' start: partial sums of the widening kernel's workgroups, all fetched at once (missing ones read as
     // zero) and ahead of everything else, so that they cost no round trip of their own
     const __amdgpu_buffer_rsrc_t sr = slab_desc(reinterpret_cast<const uint8_t *>(start), (int64_t)start_parts * rows * 4, true);
-    float sv[C::TM][CV_MAX_SPLIT];
+    // Both halves of a wave need the same tokens' sums, so each fetches half of the parts (a load occupies the address unit whatever it fetches).
+    static_assert(CV_MAX_SPLIT == 4, "two parts for each half of the wave");
+    float sv[C::TM][2];
 #pragma unroll
     for (int x = 0; x < C::TM; ++x)
 #pragma unroll
-        for (int i = 0; i < CV_MAX_SPLIT; ++i)
-            sv[x][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, (i * rows + m0 + x * 32 + fi) * 4, 0, 0));
+        for (int i = 0; i < 2; ++i)
+            sv[x][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, ((2 * fg + i) * rows + m0 + x * 32 + fi) * 4, 0, 0));
 
     // ---- what the epilogue multiplies by: a channel per thread (its wave's own), a token per thread.  Fetched here and kept in LDS
     // behind the ring: the epilogue would wait for the channels' once per tile and for the tokens' once per 32 of them (4096 x 28672 x
@@ -267,25 +283,18 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
 #pragma unroll
             for (int t = 0; t < C::TN; ++t) rl[0][t] = load_w1(r, 0, t), rl[1][t] = load_w1(r, 1, t);
         }
-        const __amdgpu_buffer_rsrc_t r = slab_desc(xp, x_slab, x_left-- > 0);
+        const __amdgpu_buffer_rsrc_t r = slab_desc(xp, x_end, x_left-- > 0);
         xp += x_slab;
         uint8_t *const to = fill_base + (j + C::STAGES - 1) * C::STAGE_BYTES;
-        fill1(std::integral_constant<int, 0>(), r, to);
-        fill1(std::integral_constant<int, 1>(), r, to);
-        fill1(std::integral_constant<int, 2>(), r, to);
-        if constexpr (C::FILLS > 3) {
-            fill1(std::integral_constant<int, 3>(), r, to);
-            fill1(std::integral_constant<int, 4>(), r, to);
-            fill1(std::integral_constant<int, 5>(), r, to);
-        }
+        fill_from(std::integral_constant<int, 0>(), std::integral_constant<int, C::FILLS>(), r, to);
         __builtin_amdgcn_sched_barrier(0);
     }
     v16f acc[C::TN][C::TM];
 #pragma unroll
     for (int x = 0; x < C::TM; ++x) {
-        float v = sv[x][0];
-#pragma unroll
-        for (int i = 1; i < CV_MAX_SPLIT; ++i) v += sv[x][i];
+        const uint32_t own = __float_as_uint(sv[x][0] + sv[x][1]);
+        const auto both = __builtin_amdgcn_permlane32_swap(own, own, false, false);
+        const float v = __uint_as_float(both[0]) + __uint_as_float(both[1]);      // integers: exact in any order
 #pragma unroll
         for (int t = 0; t < C::TN; ++t)
 #pragma unroll
@@ -328,7 +337,7 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
         __builtin_amdgcn_s_waitcnt(waitcnt_vm(C::LOADS * (C::STAGES - 3)));
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        const __amdgpu_buffer_rsrc_t wr = slab_desc(wp, w_slab, w_left > 0), xr = slab_desc(xp, x_slab, x_left > 0);
+        const __amdgpu_buffer_rsrc_t wr = slab_desc(wp, w_slab, w_left > 0), xr = slab_desc(xp, x_end, x_left > 0);
         uint8_t *const fill_to = fill_base + off_prev, *const w_fill_to = w_fill_base + off_prev;
         const int off_next2 = off_next + C::STAGE_BYTES == C::RING_BYTES ? 0 : off_next + C::STAGE_BYTES;
         v4i(&load_to)[2][C::TN] = raw[P % RAWS];           // tile kt's, widened during the previous tile
@@ -337,7 +346,7 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
         for (int x = 0; x < C::TM; ++x) {
             // this wave's weights of tile kt + 2 are in (its own copies: no barrier); younger: an iteration's loads and this one's so far
             if (C::W_LDS && x == C::TM - 1) {
-                __builtin_amdgcn_s_waitcnt(waitcnt_vm(C::LOADS * (C::STAGES - 4) + C::W_LOADS + 2));
+                __builtin_amdgcn_s_waitcnt(waitcnt_vm(C::LOADS * (C::STAGES - 4) + C::BEFORE_LAST));
                 __builtin_amdgcn_sched_barrier(0);
             }
             asm("" : "+v"(X[x]));           // keeps the 48 bytes in one run of registers, of which both steps' operands are parts
@@ -352,7 +361,7 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
             if (x == 0) read_x(off, C::TM - 1);
             else read_x(off_next, x - 1);
 #pragma unroll
-            for (int h = x * (8 / C::TM); h < (x + 1) * (8 / C::TM); ++h) widen_half(next, W[(P + 1) % 2], h);
+            for (int h = x * 8 / C::TM; h < (x + 1) * 8 / C::TM; ++h) widen_half(next, W[(P + 1) % 2], h);
             if constexpr (C::W_LDS) {
                 if (x == 0) w_fill1(std::integral_constant<int, 0>(), wr, w_fill_to), w_fill1(std::integral_constant<int, 1>(), wr, w_fill_to);
                 if (x == 1) w_fill1(std::integral_constant<int, 2>(), wr, w_fill_to), w_fill1(std::integral_constant<int, 3>(), wr, w_fill_to);
@@ -361,20 +370,19 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
                 if (x == 0) load_to[0][0] = load_w1(wr, 0, 0), load_to[1][0] = load_w1(wr, 1, 0);
                 if (x == 1) load_to[0][1] = load_w1(wr, 0, 1), load_to[1][1] = load_w1(wr, 1, 1);
             }
-            if (x == 2) fill1(std::integral_constant<int, 0>(), xr, fill_to), fill1(std::integral_constant<int, 1>(), xr, fill_to);
-            if (x == 3) fill1(std::integral_constant<int, 2>(), xr, fill_to);
-            if constexpr (C::FILLS > 3) {
-                if (x == 4) fill1(std::integral_constant<int, 3>(), xr, fill_to);
-                if (x == 5) fill1(std::integral_constant<int, 4>(), xr, fill_to);
-                if (x == 6) fill1(std::integral_constant<int, 5>(), xr, fill_to);
-            }
+            if (x == 2) fill_from(std::integral_constant<int, 0>(), std::integral_constant<int, 2>(), xr, fill_to);
+            constexpr int REST = C::FILLS - 2;
+            if constexpr (REST > 0) { if (x == 3) fill1(std::integral_constant<int, 2>(), xr, fill_to); }
+            if constexpr (REST > 1) { if (x == 4) fill1(std::integral_constant<int, 3>(), xr, fill_to); }
+            if constexpr (REST > 2) { if (x == 5) fill1(std::integral_constant<int, 4>(), xr, fill_to); }
+            if constexpr (REST > 3) { if (x == 6) fill1(std::integral_constant<int, 5>(), xr, fill_to); }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                 if (i < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                 if (C::W_LDS && x == C::TM - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                 if (i == 1 || i == 3) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 24 / C::TM, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, C::TM == 8 ? 3 : C::TM == 4 ? 6 : 4, 0);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -520,8 +528,10 @@ static hipError_t set_prefill_attributes()
 
 hipError_t prefill_device_init()
 {
-    const hipError_t e = set_prefill_attributes<8>();
-    return e == hipSuccess ? set_prefill_attributes<4>() : e;
+    hipError_t e = set_prefill_attributes<8>();
+    if (e == hipSuccess) e = set_prefill_attributes<6>();
+    if (e == hipSuccess) e = set_prefill_attributes<4>();
+    return e;
 }
 
 // Workgroups per group of 32 rows in the widening kernel: about two per CU in all, each with a K tile per wave at least.
@@ -582,8 +592,11 @@ hipError_t launch_linear_prefill(const uint8_t *xq, const uint8_t *wq, int64_t M
     widen_activations_kernel<<<dim3((unsigned)(rows / CV_ROWS), (unsigned)split), dim3(64 * CV_WAVES), 0, s>>>(
         xq, (int)M, x6_slab(M), (int)k_tiles(K), x6, start, rows);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    return tile_tokens == 256 ? launch_tile<8>(x6, start, split, wq, M, N, K, s_a, s_w, d, zp, wsum, y, acc, s)
-                              : launch_tile<4>(x6, start, split, wq, M, N, K, s_a, s_w, d, zp, wsum, y, acc, s);
+    switch (tile_tokens) {
+    case 128: return launch_tile<4>(x6, start, split, wq, M, N, K, s_a, s_w, d, zp, wsum, y, acc, s);
+    case 192: return launch_tile<6>(x6, start, split, wq, M, N, K, s_a, s_w, d, zp, wsum, y, acc, s);
+    default: return launch_tile<8>(x6, start, split, wq, M, N, K, s_a, s_w, d, zp, wsum, y, acc, s);
+    }
 }
 
 }  // namespace fptq

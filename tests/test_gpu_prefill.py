@@ -11,7 +11,7 @@ from gpu_util import dev, dev_bf16, host_bits
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture(params=[256, 128])
+@pytest.fixture(params=[256, 192, 128])
 def forced(request):
     fptq.fptq_set_linear_prefill(request.param)         # tokens per tile
     yield request.param
