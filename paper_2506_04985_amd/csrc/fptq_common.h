@@ -117,6 +117,27 @@ __device__ inline uint16_t bf16_rne(float f)
     return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
 }
 
+// Eight bf16 values of a row from k0 on, zeros past its end: one 16-byte load at any alignment (the hardware takes it) but at the row's ragged end.
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+__device__ inline v4u load_row8(const uint16_t *row, int k0, int K)
+{
+    v4u v = {0, 0, 0, 0};
+    if (k0 + 8 <= K) {
+        __builtin_memcpy(&v, row + k0, 16);
+    } else if (k0 < K) {
+#pragma unroll
+        for (int i = 0; i < 7; ++i)
+            if (k0 + i < K) v[i >> 1] |= (uint32_t)row[k0 + i] << (16 * (i & 1));
+    }
+    return v;
+}
+
+// what of a word of eight codes from k0 on lies inside the row: K padding stays zero
+__device__ inline uint32_t codes_inside(uint32_t word, int k0, int K)
+{
+    return k0 + 8 <= K ? word : k0 < K ? word & ((1u << (4 * (K - k0))) - 1u) : 0u;
+}
+
 // ss + v * v in fp64 for an fp32 v: the square of a value with at most 24 significant bits is exact in fp64, so the
 // fused form rounds once, exactly like the separate multiply and add of the definition.
 __device__ inline double add_square(double ss, float v)
