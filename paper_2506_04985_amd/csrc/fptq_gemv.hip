@@ -219,6 +219,10 @@ hipError_t launch_linear_decode(const uint8_t *xq, const uint8_t *wq, int64_t M,
         if (!deep) FPTQ_DEC(8, 4, 2, 1);
         if (N <= 4096) FPTQ_DEC(16, 1, 2, 1);
         if (N < 10240) FPTQ_DEC(16, 1, 2, 2);
+        // 64 channels per workgroup in a little more than one round leave most CUs without work in the second (32 tokens: 18944 x 3584 11.7 us,
+        // with 32 channels 11.0, 20480 x 5120 16.0 and 14.3, 22016 x 4096 13.8 and 13.1, but 16384 x 6144 11.5 and 12.6, 25600 x 5120 17.1 and 17.5)
+        const int64_t cus = device_cus_or_default(), workgroups = (N + 63) / 64;
+        if (workgroups > cus && 8 * workgroups <= 11 * cus) FPTQ_DEC(16, 1, 2, 2);
         FPTQ_DEC(8, 1, 2, 4);
     }
     if (!deep) FPTQ_DEC(8, 2, 4, 1);

@@ -152,6 +152,19 @@ def test_every_prefill_tile_shape(oracle, M, N, K, tile):
     assert np.array_equal(got["y"], ref["y"])
 
 
+@pytest.mark.parametrize("M,N", [(17, 16384), (32, 16390), (20, 18944), (31, 22528), (18, 22530)])
+def test_few_tokens_around_one_round_of_wide_workgroups(M, N):
+    """17 to 32 tokens where 64 channels per workgroup would be a little more than one round of the compute units, and at both ends."""
+    K = 2100
+    torch.manual_seed(N)
+    xq = fptq.fptq_pack_weights(torch.randint(-8, 8, (M, K), dtype=torch.int8, device="cuda"))
+    wq = fptq.fptq_pack_weights(torch.randint(-8, 8, (N, K), dtype=torch.int8, device="cuda"))
+    s_w, d = torch.rand(N, device="cuda") * 0.015 + 0.005, torch.rand(M, device="cuda") + 0.5
+    y, acc = fptq.fptq_w4a4_linear(xq, wq, M, N, K, 0.37, s_w, d, want_acc=True)
+    y_ref, acc_ref = fptq.fptq_w4a4_linear_ref(xq, wq, M, N, K, 0.37, s_w, d, want_acc=True)
+    assert torch.equal(acc, acc_ref) and torch.equal(y.view(torch.int16), y_ref.view(torch.int16))
+
+
 def test_config1_tiny(oracle):
     for case in synth.config_cases("c1"):
         inp = synth.draw(case)
