@@ -14,9 +14,9 @@
 // through LDS, as whole lines, was 2 to 4 % slower), the fp32 intermediates go through LDS to get the contiguous view
 // (padded so that both directions are bank-conflict free).  Everything is wave-private: no barriers.
 //
-// Bound by HBM (2 bytes read, half a byte written per value) and VALU issue: 15 to 17 VALU instructions per value at B = 256, 21 at B = 2048
-// and 4096 with a workgroup per block, 24 with a wave per block, which keep the SIMDs issuing in about two thirds of all cycles at
-// 4096 x 11008 and in 87 % at 8192 x 28672 (the plain quantizer: 38 %).  4096 x 11008 takes 26.7 us (27.3 before the loads were direct).
+// Bound by HBM (2 bytes read, half a byte written per value) and VALU issue: 16 VALU instructions per value at B = 256, 21 at B = 2048
+// and 4096 with a workgroup per block, 20 with a wave per block, which keep the SIMDs issuing in 60 % of all cycles at 4096 x 11008,
+// 86 % at 4096 x 14336 and 88 % at 8192 x 28672 (the plain quantizer: 32 to 36 %).  4096 x 11008 takes 26.7 us (27.3 before the loads were direct).
 //
 // B = 64 V with V = 8, 16, 32, 64 (32 and 64: in RMS mode, and beyond the number of blocks at which a workgroup per block is the faster).  One block per wave iteration, V values per lane.  View 1: the lane
 // holds x[64 j + lane] and runs strides B/2 .. 64 in registers; view 2: the lane holds
