@@ -117,20 +117,59 @@ __device__ inline uint16_t bf16_rne(float f)
     return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
 }
 
-// Eight bf16 values of a row from k0 on, zeros past its end: one 16-byte load at any alignment (the hardware takes it) but at the row's ragged end.
+// Chunks of eight bf16 values of a row, from k0 on every `step` values, zeros past the row's end: 16-byte loads at any alignment (the hardware
+// takes it).  A chunk that would reach past the end is loaded from eight values before it and shifted, so that no lane loads by element and
+// no branch keeps a chunk's load behind another's: rows of few values are one latency long.
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-__device__ inline v4u load_row8(const uint16_t *row, int k0, int K)
+template <int CH>
+__device__ inline void load_row_chunks(v4u (&v)[CH], const uint16_t *row, int k0, int step, int K)
 {
-    v4u v = {0, 0, 0, 0};
-    if (k0 + 8 <= K) {
-        __builtin_memcpy(&v, row + k0, 16);
-    } else if (k0 < K) {
+    const int last = K - 8;
+    if (last < 0) {
+        uint32_t e[8] = {};
 #pragma unroll
-        for (int i = 0; i < 7; ++i)
-            if (k0 + i < K) v[i >> 1] |= (uint32_t)row[k0 + i] << (16 * (i & 1));
+        for (int i = 0; i < 7; ++i) e[i] = row[min(i, K - 1)];
+#pragma unroll
+        for (int i = 0; i < 7; ++i) e[i] = k0 == 0 && i < K ? e[i] : 0u;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) v[i] = v4u{0, 0, 0, 0};
+        v[0] = v4u{e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6]};
+        return;
     }
-    return v;
+#pragma unroll
+    for (int i = 0; i < CH; ++i) __builtin_memcpy(&v[i], row + min(k0 + i * step, last), 16);
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+        const int s = k0 + i * step - last;          // values that lie in front of the chunk
+        if (s > 0) {
+            v4u a = v[i];
+            if (s & 4) a = v4u{a.z, a.w, 0, 0};
+            if (s & 2) a = v4u{a.y, a.z, a.w, 0};
+            if (s & 1) a = v4u{a.x >> 16 | a.y << 16, a.y >> 16 | a.z << 16, a.z >> 16 | a.w << 16, a.w >> 16};
+            v[i] = s < 8 ? a : v4u{0, 0, 0, 0};
+        }
+    }
 }
+
+// Many short rows: a wave takes a row, where a workgroup per row (which spreads a row over four waves) has most of its threads idle or more
+// waves than the device runs at once.  Aligned rows: crossover at 4096 values about 1000 rows.  Ragged ones (workgroup / wave, RMS scale): 800 x 63
+// 3.3 / 2.3 us, 2048 x 333 4.6 / 2.7, 65536 x 63 82 / 23, 4000 x 3601 11.8 / 10.0; residual step 8192 x 333 19 / 6.7; but dynamic scale 1100 x 3601
+// 5.1 / 6.2, given scale 2048 x 1801 3.6 / 4.1.
+inline bool wave_per_row(bool vec, int64_t M, int64_t K) { return K <= 4096 && M > (vec || K <= 1024 ? 768 : 3072); }
+
+// Its instances: CASE(chunks a lane, ragged).  Ragged rows in finer steps, because a chunk that lies past the row's end is loaded and computed
+// all the same (800 x 777, residual step: 5.1 us with four chunks, 3.8 with two).
+#define WAVE_PER_ROW(vec, K, CASE)                        \
+    do {                                                  \
+        if (vec) {                                        \
+            if ((K) <= 2048) CASE(4, false);              \
+            else CASE(8, false);                          \
+        } else if ((K) <= 512) CASE(1, true);             \
+        else if ((K) <= 1024) CASE(2, true);              \
+        else if ((K) <= 2048) CASE(4, true);              \
+        else if ((K) <= 3072) CASE(6, true);              \
+        else CASE(8, true);                               \
+    } while (0)
 
 // what of a word of eight codes from k0 on lies inside the row: K padding stays zero
 __device__ inline uint32_t codes_inside(uint32_t word, int k0, int K)

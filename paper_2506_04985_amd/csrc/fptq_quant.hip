@@ -3,8 +3,8 @@
 //
 // The row is read once from HBM and kept in registers while the sum of squares is reduced, then
 // quantized from the registers.  Bandwidth-bound: 2 bytes read and half a byte written per
-// element.  Rows up to 12288 values are handled by one wave each (no LDS, no barrier, the scale is
-// computed once per row, and many rows are in flight per CU); longer rows by one workgroup each.
+// element.  Short rows in large numbers are handled by one wave each (no LDS, no barrier, the scale is
+// computed once per row, and many rows are in flight per CU); longer rows, or few, by one workgroup each.
 #include "fptq_common.h"
 
 namespace fptq {
@@ -50,7 +50,7 @@ constexpr int Q_STREAM = 2;      // buffer-load cache policy: non-temporal
 // registers (CH 16-byte chunks per thread) between the reduction and the quantizer and read through a row-sized
 // buffer descriptor, so chunks past the end read as zero and nothing branches but the store of a chunk past
 // the padded width.  RAGGED: the same for any K and alignment, each chunk loaded where it lies (RMS scale: 279 x 11849 21.8 us in two passes by
-// element, now 6.4, 2048 x 4366 19.2 and 9.6).  CH == 0: rows too long for the registers, two passes over the row.
+// element, now 6.1, 2048 x 4366 19.1 and 8.7).  CH == 0: rows too long for the registers, two passes over the row.
 template <int MODE, int CH, bool RAGGED>
 __global__ __launch_bounds__(QT) void quantize_act_kernel(const uint16_t *__restrict__ x, int64_t M, int64_t K, float eps,
                                                           const float *__restrict__ row_in, float inv_s_a, int zoff,
@@ -64,8 +64,7 @@ __global__ __launch_bounds__(QT) void quantize_act_kernel(const uint16_t *__rest
 
     q_v4u regs[CH > 0 ? CH : 1];
     if (RAGGED) {
-#pragma unroll
-        for (int i = 0; i < CH; ++i) regs[i] = load_row8(row, (i * QT + tid) * QCHUNK, (int)K);
+        load_row_chunks(regs, row, tid * QCHUNK, QT * QCHUNK, (int)K);
     } else if (CH > 0) {
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)row, 0, (int)K * 2, RSRC_FLAGS);
         if (stream_in) {         // an input larger than the last-level cache: streaming loads, which do not displace what is there
@@ -132,8 +131,8 @@ __global__ __launch_bounds__(QT) void quantize_act_kernel(const uint16_t *__rest
 
 // One wave per row, for rows of at most 512 * CH values (K % 8 == 0).  The row is read through a
 // row-sized buffer descriptor, so chunks past its end read as zero and neither the loads nor the
-// quantizer need a branch; only the store of a chunk past the padded width is masked off.
-template <int MODE, int CH>
+// quantizer need a branch; only the store of a chunk past the padded width is masked off.  RAGGED: any K and alignment.
+template <int MODE, int CH, bool RAGGED>
 __global__ __launch_bounds__(QT) void quantize_act_wave_kernel(const uint16_t *__restrict__ x, int64_t M, int64_t K, float eps,
                                                                const float *__restrict__ row_in, float inv_s_a, int zoff,
                                                                uint8_t *__restrict__ out, float *__restrict__ row_out, int stream_in)
@@ -146,7 +145,9 @@ __global__ __launch_bounds__(QT) void quantize_act_wave_kernel(const uint16_t *_
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)(x + t * K), 0, Ki * 2, RSRC_FLAGS);
 
     q_v4u regs[CH];
-    if (stream_in) {
+    if (RAGGED) {
+        load_row_chunks(regs, x + t * K, lane * QCHUNK, 64 * QCHUNK, Ki);
+    } else if (stream_in) {
 #pragma unroll
         for (int i = 0; i < CH; ++i) regs[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (i * 64 + lane) * 16, 0, Q_STREAM);
     } else {
@@ -180,14 +181,14 @@ __global__ __launch_bounds__(QT) void quantize_act_wave_kernel(const uint16_t *_
         const int k0 = (i * 64 + lane) * QCHUNK;
         const uint32_t w[4] = {regs[i].x, regs[i].y, regs[i].z, regs[i].w};
         uint32_t word = quant_chunk(w, c, zoff);
-        if (k0 >= Ki) word = 0u;                              // K padding stays zero
+        word = RAGGED ? codes_inside(word, k0, Ki) : k0 >= Ki ? 0u : word;      // K padding stays zero
         if (k0 < Kpad) *reinterpret_cast<uint32_t *>(orow + (int64_t)(4 * i) * M * SEG) = word;
     }
 }
 
 // Dynamic quantization (App. B of the paper): the scale is computed at run time per token,
 // s_t = max_k |x_t,k| / 7 (NaNs ignored; a zero or infinite maximum gives s_t = 1), then
-// q = clamp(rne(x * (1 / s_t)), -8, 7).  One wave per row.  CH > 0: the row (K <= 512 * CH, K % 8 == 0)
+// q = clamp(rne(x * (1 / s_t)), -8, 7).  One wave per row.  CH > 0: the row (K <= 512 * CH, K % 8 == 0 and 16-byte aligned unless RAGGED)
 // stays in registers between the max reduction and the quantizer; CH == 0: any K, two passes.
 __device__ inline uint32_t abs_bits_no_nan(uint32_t h)
 {
@@ -195,7 +196,7 @@ __device__ inline uint32_t abs_bits_no_nan(uint32_t h)
     return m > 0x7f80u ? 0u : m;       // bf16 magnitudes order like their bit patterns; NaN does not enter the max
 }
 
-template <int CH>
+template <int CH, bool RAGGED>
 __global__ __launch_bounds__(QT) void quantize_act_dynamic_kernel(const uint16_t *__restrict__ x, int64_t M, int64_t K,
                                                                   uint8_t *__restrict__ out, float *__restrict__ s_out)
 {
@@ -210,8 +211,12 @@ __global__ __launch_bounds__(QT) void quantize_act_dynamic_kernel(const uint16_t
     uint32_t mx = 0;
     if (CH > 0) {      // the row through a row-sized buffer descriptor: chunks past its end read as zero
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)row, 0, (int)K * 2, RSRC_FLAGS);
+        if (RAGGED) {
+            load_row_chunks(regs, row, lane * QCHUNK, 64 * QCHUNK, (int)K);
+        } else {
 #pragma unroll
-        for (int i = 0; i < CH; ++i) regs[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (i * 64 + lane) * 16, 0, 0);
+            for (int i = 0; i < CH; ++i) regs[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (i * 64 + lane) * 16, 0, 0);
+        }
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             const uint32_t w[4] = {regs[i].x, regs[i].y, regs[i].z, regs[i].w};
@@ -234,7 +239,7 @@ __global__ __launch_bounds__(QT) void quantize_act_dynamic_kernel(const uint16_t
             const int k0 = (i * 64 + lane) * QCHUNK;
             const uint32_t w[4] = {regs[i].x, regs[i].y, regs[i].z, regs[i].w};
             uint32_t word = quant_chunk(w, c, 8);
-            if (k0 >= (int)K) word = 0u;                          // K padding stays zero
+            word = RAGGED ? codes_inside(word, k0, (int)K) : k0 >= (int)K ? 0u : word;      // K padding stays zero
             if (k0 < (int)Kpad) *reinterpret_cast<uint32_t *>(orow + (int64_t)(4 * i) * M * SEG) = word;
         }
     } else {
@@ -251,7 +256,7 @@ __global__ __launch_bounds__(QT) void quantize_act_dynamic_kernel(const uint16_t
 }
 
 // The same with one workgroup per row (rows of at most 2048 * CH values; K % 8 == 0 and 16-byte aligned unless RAGGED): a row is
-// spread over four waves, which is faster whenever rows are long or few.  RAGGED: 2048 x 4366 40 us by element in one wave, now 9.5, 279 x 11849 78 and 6.5.
+// spread over four waves, which is faster whenever rows are long or few.  RAGGED: 2048 x 4366 40 us by element in one wave, now 8.8, 279 x 11849 78 and 6.5.
 template <int CH, bool RAGGED>
 __global__ __launch_bounds__(QT) void quantize_act_dynamic_row_kernel(const uint16_t *__restrict__ x, int64_t M, int64_t K,
                                                                       uint8_t *__restrict__ out, float *__restrict__ s_out)
@@ -262,8 +267,12 @@ __global__ __launch_bounds__(QT) void quantize_act_dynamic_row_kernel(const uint
     const int64_t Kpad = k_tiles(K) * KT;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)(x + t * K), 0, (int)K * 2, RSRC_FLAGS);
     q_v4u regs[CH];
+    if (RAGGED) {
+        load_row_chunks(regs, x + t * K, tid * QCHUNK, QT * QCHUNK, (int)K);
+    } else {
 #pragma unroll
-    for (int i = 0; i < CH; ++i) regs[i] = RAGGED ? load_row8(x + t * K, (i * QT + tid) * QCHUNK, (int)K) : __builtin_amdgcn_raw_buffer_load_b128(rs, (i * QT + tid) * 16, 0, 0);
+        for (int i = 0; i < CH; ++i) regs[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (i * QT + tid) * 16, 0, 0);
+    }
     uint32_t mx = 0;
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
@@ -298,12 +307,10 @@ hipError_t launch_quantize_act_dynamic(const uint16_t *x, int64_t M, int64_t K, 
     dim3 grid((unsigned)blocks), block(QT);
     const bool vec = K % QCHUNK == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
     const int64_t Kpad = k_tiles(K) * KT;
-    // as for the static quantizer: a wave per row only for many short rows, otherwise a workgroup per row
-    if (vec && Kpad <= 512 * 8 && M > 768) {
-        if (Kpad <= 512 * 4)
-            quantize_act_dynamic_kernel<4><<<grid, block, 0, s>>>(x, M, K, out, s_out);
-        else
-            quantize_act_dynamic_kernel<8><<<grid, block, 0, s>>>(x, M, K, out, s_out);
+    if (wave_per_row(vec, M, K)) {
+#define FPTQ_WAVE_CASE(CH, RAGGED) quantize_act_dynamic_kernel<CH, RAGGED><<<grid, block, 0, s>>>(x, M, K, out, s_out)
+        WAVE_PER_ROW(vec, Kpad, FPTQ_WAVE_CASE);
+#undef FPTQ_WAVE_CASE
         return hipGetLastError();
     }
     if (M > 0x7fffffff) return hipErrorInvalidValue;
@@ -333,7 +340,7 @@ hipError_t launch_quantize_act_dynamic(const uint16_t *x, int64_t M, int64_t K, 
     FPTQ_RAGGED_CASE(8)
     FPTQ_RAGGED_CASE(16)
 #undef FPTQ_RAGGED_CASE
-    quantize_act_dynamic_kernel<0><<<grid, block, 0, s>>>(x, M, K, out, s_out);
+    quantize_act_dynamic_kernel<0, false><<<grid, block, 0, s>>>(x, M, K, out, s_out);
     return hipGetLastError();
 }
 
@@ -347,15 +354,13 @@ static hipError_t launch_mode(const uint16_t *x, int64_t M, int64_t K, float eps
     // An input that the 256 MB last-level cache cannot hold is read with streaming loads (8192 x 28672: 119 us
     // against 142); a smaller one is usually still there from its producer, and ordinary loads are faster on it.
     const int stream_in = M * K * 2 > ((int64_t)256 << 20) ? 1 : 0;
-    // A wave per row pays only for short rows in large numbers (measured crossover at 4096 values: about 1000
-    // rows); otherwise a workgroup per row, which spreads a row over four waves (32 x 11008: 2.9 us against 5.6;
-    // 2048 x 11008: 10.8 against 12.9; 2048 x 4096 the other way, 6.0 against 5.3).
-    if (vec && Kpad <= 512 * 8 && M > 768) {
+    // A workgroup per row, which spreads a row over four waves (32 x 11008: 2.9 us against 5.6; 2048 x 11008: 10.8 against 12.9), but for
+    // short rows in large numbers (2048 x 4096 the other way, 6.0 against 5.3).
+    if (wave_per_row(vec, M, K)) {
         dim3 wgrid((unsigned)((M + QT / 64 - 1) / (QT / 64)));
-        if (Kpad <= 512 * 4)
-            quantize_act_wave_kernel<MODE, 4><<<wgrid, block, 0, s>>>(x, M, K, eps, row_in, inv_s_a, zoff, out, row_out, stream_in);
-        else
-            quantize_act_wave_kernel<MODE, 8><<<wgrid, block, 0, s>>>(x, M, K, eps, row_in, inv_s_a, zoff, out, row_out, stream_in);
+#define FPTQ_WAVE_CASE(CH, RAGGED) quantize_act_wave_kernel<MODE, CH, RAGGED><<<wgrid, block, 0, s>>>(x, M, K, eps, row_in, inv_s_a, zoff, out, row_out, stream_in)
+        WAVE_PER_ROW(vec, Kpad, FPTQ_WAVE_CASE);
+#undef FPTQ_WAVE_CASE
         return hipGetLastError();
     }
 #define FPTQ_ROW_CASE(CH)                                                                                                   \

@@ -16,17 +16,17 @@ typedef v4u r_v4u;
 
 // WPR waves per row: 1 (four rows per workgroup; no LDS, no barrier: for many short rows) or 4 (a workgroup per
 // row).  CH > 0: K % 8 == 0, K <= 512 * WPR * CH, rows 16-byte aligned, z kept in registers.
-// RAGGED (WPR = 4): the same for any K and alignment, each chunk loaded and stored where it lies (2048 x 4366 56 us by element, now 16.6, 32 x 4099 21.8 and 4.5).
+// RAGGED: the same for any K and alignment, each chunk loaded and stored where it lies (2048 x 4366 56 us by element, now 14.7, 32 x 4099 21.8 and 4.4).
 // CH == 0 (WPR = 1): rows too long for the registers, the inputs are read twice (the second time from cache).
-// x_next may be the same buffer as xr or yb (the update in place), so none of the three is declared restrict: every
-// thread reads an element of its row before it stores that element, and no thread touches another's elements.
+// x_next may be the same buffer as xr or yb (the update in place), so none of the three is declared restrict.  The row's sum needs every load,
+// so all loads of a row come before its first store (over waves: the barrier); CH == 0: a thread stores only elements that no other thread reads.
 template <int CH, int WPR, bool RAGGED>
 __global__ __launch_bounds__(256) void residual_norm_quantize_kernel(const uint16_t *xr, const uint16_t *yb,
                                                                      int64_t M, int64_t K, const float *__restrict__ s_prev,
                                                                      float eps, float inv_s_a, uint16_t *x_next,
                                                                      float *__restrict__ s_next, uint8_t *__restrict__ out)
 {
-    static_assert((WPR == 1 && !RAGGED) || (WPR == 4 && CH > 0), "a wave or a workgroup per row");
+    static_assert((WPR == 1 && (CH > 0 || !RAGGED)) || (WPR == 4 && CH > 0), "a wave or a workgroup per row");
     __shared__ double red[4];
     constexpr int S = 64 * WPR;                          // threads per row
     const int lane = threadIdx.x & 63;
@@ -44,10 +44,15 @@ __global__ __launch_bounds__(256) void residual_norm_quantize_kernel(const uint1
         const __amdgpu_buffer_rsrc_t xs = __builtin_amdgcn_make_buffer_rsrc((void *)xrow, 0, (int)K * 2, 0x00020000);
         const __amdgpu_buffer_rsrc_t ys = __builtin_amdgcn_make_buffer_rsrc((void *)yrow, 0, (int)K * 2, 0x00020000);
         r_v4u a[CH > 0 ? CH : 1], b[CH > 0 ? CH : 1];
+        if (RAGGED) {
+            load_row_chunks(a, xrow, h * 8, S * 8, (int)K);
+            load_row_chunks(b, yrow, h * 8, S * 8, (int)K);
+        } else {
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            a[i] = RAGGED ? load_row8(xrow, (i * S + h) * 8, (int)K) : __builtin_amdgcn_raw_buffer_load_b128(xs, (i * S + h) * 16, 0, 0);
-            b[i] = RAGGED ? load_row8(yrow, (i * S + h) * 8, (int)K) : __builtin_amdgcn_raw_buffer_load_b128(ys, (i * S + h) * 16, 0, 0);
+            for (int i = 0; i < CH; ++i) {
+                a[i] = __builtin_amdgcn_raw_buffer_load_b128(xs, (i * S + h) * 16, 0, 0);
+                b[i] = __builtin_amdgcn_raw_buffer_load_b128(ys, (i * S + h) * 16, 0, 0);
+            }
         }
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
@@ -132,11 +137,10 @@ hipError_t launch_residual_norm_quantize(const uint16_t *xr, const uint16_t *yb,
                                      reinterpret_cast<uintptr_t>(x_next)) & 15) == 0;
     // As for the plain quantizer: a wave per row for many short rows (2048 x 4096: 10.2 us), otherwise a workgroup per
     // row, which spreads a row over four waves (32 x 4096: 4.3 us with a wave per row).
-    if (vec && K <= 4096 && M > 768) {
-        if (K <= 2048)
-            residual_norm_quantize_kernel<4, 1, false><<<grid, block, 0, s>>>(xr, yb, M, K, s_prev, eps, inv_s_a, x_next, s_next, out);
-        else
-            residual_norm_quantize_kernel<8, 1, false><<<grid, block, 0, s>>>(xr, yb, M, K, s_prev, eps, inv_s_a, x_next, s_next, out);
+    if (wave_per_row(vec, M, K)) {
+#define FPTQ_WAVE_CASE(CH, RAGGED) residual_norm_quantize_kernel<CH, 1, RAGGED><<<grid, block, 0, s>>>(xr, yb, M, K, s_prev, eps, inv_s_a, x_next, s_next, out)
+        WAVE_PER_ROW(vec, K, FPTQ_WAVE_CASE);
+#undef FPTQ_WAVE_CASE
         return hipGetLastError();
     }
 #define FPTQ_RES_CASE(CH)                                                                                                       \

@@ -1,5 +1,7 @@
 """Quantizers on rows whose length is no multiple of eight or whose address is only 2-byte aligned: chunks loaded where they lie, at the edges
 of the rows, of the width classes and of the register path, against the oracle; nothing outside the matrix is used or written."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -13,6 +15,11 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [(3, 1, 1), (5, 7, 0), (4, 9, 1), (3, 16, 3), (2, 127, 0), (6, 1001, 1), (3, 2047, 0), (2, 2048, 1), (3, 2049, 0), (2, 4097, 5), (2, 8191, 0), (2, 8195, 1),
           (1, 16385, 0), (2, 32767, 1), (1, 32768, 1), (1, 32769, 0), (900, 333, 1), (900, 4094, 0)]
+
+
+# many short rows, which a wave takes each: rows below a chunk, the ends of the five width classes
+MANY = [(769, 1, 1), (770, 7, 0), (771, 8, 1), (1030, 9, 1), (769, 63, 0), (901, 511, 1), (769, 512, 1), (770, 513, 0), (769, 1024, 1),
+        (3073, 1025, 0), (3074, 2047, 0), (3073, 2049, 0), (3073, 3072, 1), (3073, 3073, 0)]
 
 
 def place(bits, offset):
@@ -34,7 +41,7 @@ def padding_is_zero(xq, M, K):
     return not full[:, K:].any()
 
 
-@pytest.mark.parametrize("M,K,offset", SHAPES)
+@pytest.mark.parametrize("M,K,offset", [*SHAPES, *MANY])
 def test_static_and_dynamic(oracle, M, K, offset):
     xb, rng = draw(M, K)
     x, _ = place(xb, offset)
@@ -55,7 +62,7 @@ def test_static_and_dynamic(oracle, M, K, offset):
 
 
 @pytest.mark.parametrize("alias", [None, "x", "y"])
-@pytest.mark.parametrize("M,K,offset", [*SHAPES, (2, 16392, 0), (3, 28672, 0), (1, 32760, 0)])
+@pytest.mark.parametrize("M,K,offset", [*SHAPES, *MANY, (2, 16392, 0), (3, 28672, 0), (1, 32760, 0)])
 def test_residual_step(oracle, M, K, offset, alias):
     xb, rng = draw(M, K)
     yb, _ = draw(M, K, 1)
@@ -70,3 +77,34 @@ def test_residual_step(oracle, M, K, offset, alias):
     assert np.array_equal(s_next.cpu().numpy().view(np.uint32), ref["s_next"].view(np.uint32))
     assert np.array_equal(fptq.fptq_unpack(xq, M, K).cpu().numpy(), ref["q"]) and padding_is_zero(xq, M, K)
     assert bool(base[:offset].isnan().all()) and bool(base[offset + M * K:].isnan().all())
+
+
+def workgroups(call):
+    """Workgroups of the one kernel that a call launches, from its captured graph."""
+    class Params(ctypes.Structure):
+        _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint32 * 3),
+                    ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line))
+    raw, count = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(count)) == 0 and count.value == 1
+    node, params = ctypes.c_void_p(), Params()
+    assert hip.hipGraphGetNodes(raw, ctypes.byref(node), ctypes.byref(count)) == 0
+    assert hip.hipGraphKernelNodeGetParams(node, ctypes.byref(params)) == 0
+    return params.grid[0]
+
+
+@pytest.mark.parametrize("M,K", [(769, 63), (2048, 333), (8192, 1001), (3073, 4095)])
+def test_many_short_rows_share_workgroups(M, K):
+    """A workgroup per row was up to four times as slow there as four rows to a workgroup, a wave each."""
+    x, y = (torch.randn((M, K), device="cuda").to(torch.bfloat16) for _ in range(2))
+    q = torch.empty(fptq.fptq_packed_bytes(M, K), dtype=torch.uint8, device="cuda")
+    s, o = torch.empty(M, device="cuda"), torch.empty_like(x)
+    for call in (lambda: fptq.fptq_quantize_act(x, 0.4, synth.MODE_RMS, 1e-5, None, out=q, row_scale_out=s),
+                 lambda: fptq.fptq_quantize_act_dynamic(x, out=q, token_scale_out=s),
+                 lambda: fptq.fptq_residual_norm_quantize(x, y, 0.45, None, 1e-5, x_next=o, s_next=s, out=q)):
+        assert workgroups(call) == (M + 3) // 4
