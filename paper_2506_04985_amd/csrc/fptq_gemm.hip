@@ -745,10 +745,13 @@ static int choose_tile(int64_t M, int64_t N, int64_t K, int cus, double *us = nu
 //     2048 x 4096 x 11008    69 /  73 /  65 /  61  (68 / 60 / 59 / 59)     333 x 32000 x 4096   46 / 40 / 36 / 50  (44 / 38 / 33 / 44)
 //     1000 x 5120 x 13824    70 /  88 /  67 /  60  (63 / 68 / 59 / 54)     192 x 28672 x 4096   29 / 33 / 31 / 29  (26 / 26 / 24 / 25)
 //      700 x 10240 x 8192    52 /  57 /  53 /  45  (49 / 46 / 43 / 43)     512 x 8192 x 8192    34 / 56 / 47 / 39  (33 / 44 / 38 / 32)
-// i.e. the tile that leaves the fewest CUs without work, and INT8 where each leaves too many.  Where a tile shape occupies less than four
-// fifths of the CUs in a single round, the estimates spread most and INT8's smaller tiles are closest, so it takes 48 K tiles; and
-// 192 tokens are taken for up to a round and a half (beyond that 256 are within a few percent).  The margins (wider for few K tiles, where stores
-// and launches weigh more than in what the estimates were fitted to) leave one of the 500 shapes 5 % slower than INT8.
+// i.e. the tile that leaves the fewest CUs without work, and INT8 where each leaves too many.  Where the smaller tiles occupy less than a share of
+// the CUs in a single round (least_share), the estimates spread most and INT8's smaller tiles are closest, so they take 48 K tiles: 562 x 8064 x
+// 5376 30 us on INT8 and 37 with 192 tokens, 151 x 19477 x 4472 25 and 33, 1670 x 2560 x 4936 27 and 29 with 128 (weights from HBM).  The 256-token
+// tile needs no such limit: refused below four fifths of the CUs, 512 x 23424 x 6016 took 57 us on INT8 instead of 48 (from the cache 54 and 43), 256 x
+// 50096 x 2744 36 instead of 30 (33 and 27).  192 tokens are taken for up to a round and a half (beyond that 256 are within a few
+// percent).  The margins (wider for few K tiles, where stores and launches weigh more than in what the estimates were fitted to) leave one of the 500
+// shapes 5 % slower than INT8, none of 180 others of 0.4 to 1 round, and the same one slower by that than with a choice between 256 and 128 tokens only.
 // Tiles of 160 and 96 tokens were within 3 % of the best of the others but on 22 of the first 200 shapes (192 x 28672 x 4096: 26 and 29): not kept.
 int prefill_tile(int64_t M, int64_t N, int64_t K)
 {
@@ -763,9 +766,9 @@ int prefill_tile(int64_t M, int64_t N, int64_t K)
     const double kt = (double)k_tiles(K), widen_us = (double)M * (double)K * 1.25 / 5.0e6;
     struct Tile {
         int tokens;
-        double call_us, lone, least, tile_us, k_tile_us;
+        double call_us, lone, least, tile_us, k_tile_us, least_share;
     };
-    static const Tile tiles[] = {{256, 5.0, 0.58, 0.53, 7.5, 0.789}, {192, 4.95, 0.54, 0.58, 5.4, 0.649}, {128, 5.75, 0.58, 0.69, 3.8, 0.494}};
+    static const Tile tiles[] = {{256, 5.0, 0.58, 0.53, 7.5, 0.789, 0.0}, {192, 4.95, 0.54, 0.58, 5.4, 0.649, 0.65}, {128, 5.75, 0.58, 0.69, 3.8, 0.494, 0.76}};
     int tokens = 0;
     double us = 0.0;
     for (const Tile &t : tiles) {
@@ -774,7 +777,7 @@ int prefill_tile(int64_t M, int64_t N, int64_t K)
         // A single row of small tiles streams its weights once, from HBM: with few workgroups that is bound by what one CU keeps in flight
         // (96 x 37397 x 17536, 147 workgroups: 92 us against 85 on INT8 tiles; 96 x 57344 x 8192, 224 workgroups: 53 against 53).
         if (t.tokens == 128 && M <= 128 && x < 0.75) continue;
-        if (mode == 0 && ((x < 0.8 && kt < 48) || (t.tokens == 192 && x > 1.5))) continue;
+        if (mode == 0 && ((x < t.least_share && kt < 48) || (t.tokens == 192 && x > 1.5))) continue;
         const double rounds = x < 1.0 ? t.lone + (1.0 - t.lone) * x : floor(x) + (part > 0.0 ? t.least + (1.0 - t.least) * part : 0.0);
         const double est = t.call_us + widen_us + rounds * (t.tile_us + t.k_tile_us * kt);
         if (tokens == 0 || est < us) tokens = t.tokens, us = est;

@@ -117,6 +117,7 @@ def test_testing_knobs_validate_and_the_launch_plan_is_host_arithmetic():
     (1050, 18832, 3072, 0), (512, 8192, 8192, 0),
     # faster on six-bit tiles from either
     (333, 32000, 4096, 192), (333, 32003, 2504, 192), (700, 10240, 8192, 128),
+    (512, 22016, 4096, 256), (512, 23424, 6016, 256), (501, 22704, 5520, 256), (256, 50096, 2744, 256), (153, 42880, 4992, 192), (1536, 6144, 4096, 192),
     (96, 57344, 8192, 128), (1000, 5120, 13824, 128), (2048, 4096, 11008, 128), (4096, 6144, 4096, 256), (4096, 28672, 4096, 256), (2048, 22016, 4096, 256)])
 def test_where_the_six_bit_kernel_is_taken(M, N, K, tokens):
     """Measured on an MI355X, a matrix at a time, with the weights cycled through copies that no cache holds and with one copy."""
