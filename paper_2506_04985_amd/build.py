@@ -17,7 +17,8 @@ NATIVE_SOURCE, NATIVE = "fptq_native.cpp", os.path.join(HERE, "_native.so")     
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 # The first 14 words of a kernel's arguments arrive in scalar registers with the dispatch, so a wave's first loads do not wait for a load of
 # their addresses (firmware without it enters at a prologue that loads them).  What bounds the short launches is latency: 333 x 32003 x 2504
-# 28.2 -> 27.8 us, Hadamard and RMS quantizers of 4096 rows 40.6 -> 40.0, a decode block 41.2 -> 41.0; large products as before.
+# 28.2 -> 27.8 us, Hadamard and RMS quantizers of 4096 rows 40.6 -> 40.0, a decode block 41.2 -> 41.0; large products as before.  The dispatch
+# itself takes about 0.1 us longer, which shows where a launch is hardly more than that: up to 4 rows of 4096 values, scale given, 1.97 -> 2.08.
 KERNARG_PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -5,6 +5,8 @@
 // quantized from the registers.  Bandwidth-bound: 2 bytes read and half a byte written per
 // element.  Short rows in large numbers are handled by one wave each (no LDS, no barrier, the scale is
 // computed once per row, and many rows are in flight per CU); longer rows, or few, by one workgroup each.
+#include <type_traits>
+
 #include "fptq_common.h"
 
 namespace fptq {
@@ -51,11 +53,19 @@ constexpr int Q_STREAM = 2;      // buffer-load cache policy: non-temporal
 // buffer descriptor, so chunks past the end read as zero and nothing branches but the store of a chunk past
 // the padded width.  RAGGED: the same for any K and alignment, each chunk loaded where it lies (RMS scale: 279 x 11849 21.8 us in two passes by
 // element, now 6.1, 2048 x 4366 19.1 and 8.7).  CH == 0: rows too long for the registers, two passes over the row.
+//
+// Arguments: the first 14 words of a kernel's arguments come with the dispatch, and a wait for one beyond them is a memory latency at the start of
+// every wave; so the width is one word where the row fits the registers, and zoff has the input's streaming in its second byte.  Scale given,
+// with that flag as the 17th word / without any argument preloaded / now: 4096 x 4096 9.5, 9.8, 9.15 us, 256 x 8192 3.3, 3.3, 3.1, 32 x 4096 2.34, 2.32, 2.28.
+template <int CH> using width_t = std::conditional_t<(CH > 0), int, int64_t>;
+constexpr int STREAM_IN = 256;
+
 template <int MODE, int CH, bool RAGGED>
-__global__ __launch_bounds__(QT) void quantize_act_kernel(const uint16_t *__restrict__ x, int64_t M, int64_t K, float eps,
-                                                          const float *__restrict__ row_in, float inv_s_a, int zoff,
-                                                          uint8_t *__restrict__ out, float *__restrict__ row_out, int stream_in)
+__global__ __launch_bounds__(QT) void quantize_act_kernel(const uint16_t *__restrict__ x, uint8_t *__restrict__ out, float *__restrict__ row_out,
+                                                          const float *__restrict__ row_in, int64_t M, width_t<CH> K, float inv_s_a, int zoff_stream,
+                                                          float eps)
 {
+    const int zoff = zoff_stream & 255, stream_in = zoff_stream & STREAM_IN;
     __shared__ double red[QT / 64];
     const int64_t t = blockIdx.x;
     const uint16_t *row = x + t * K;
@@ -133,15 +143,17 @@ __global__ __launch_bounds__(QT) void quantize_act_kernel(const uint16_t *__rest
 // row-sized buffer descriptor, so chunks past its end read as zero and neither the loads nor the
 // quantizer need a branch; only the store of a chunk past the padded width is masked off.  RAGGED: any K and alignment.
 template <int MODE, int CH, bool RAGGED>
-__global__ __launch_bounds__(QT) void quantize_act_wave_kernel(const uint16_t *__restrict__ x, int64_t M, int64_t K, float eps,
-                                                               const float *__restrict__ row_in, float inv_s_a, int zoff,
-                                                               uint8_t *__restrict__ out, float *__restrict__ row_out, int stream_in)
+__global__ __launch_bounds__(QT) void quantize_act_wave_kernel(const uint16_t *__restrict__ x, uint8_t *__restrict__ out, float *__restrict__ row_out,
+                                                               const float *__restrict__ row_in, int64_t M, int Ki, float inv_s_a, int zoff_stream,
+                                                               float eps)
 {
+    const int zoff = zoff_stream & 255, stream_in = zoff_stream & STREAM_IN;
+    const int64_t K = Ki;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t t = (int64_t)blockIdx.x * (QT / 64) + wave;
     if (t >= M) return;
-    const int Ki = (int)K, Kpad = (int)(k_tiles(K) * KT);
+    const int Kpad = (int)(k_tiles(K) * KT);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)(x + t * K), 0, Ki * 2, RSRC_FLAGS);
 
     q_v4u regs[CH];
@@ -353,19 +365,19 @@ static hipError_t launch_mode(const uint16_t *x, int64_t M, int64_t K, float eps
     const int64_t Kpad = k_tiles(K) * KT;
     // An input that the 256 MB last-level cache cannot hold is read with streaming loads (8192 x 28672: 119 us
     // against 142); a smaller one is usually still there from its producer, and ordinary loads are faster on it.
-    const int stream_in = M * K * 2 > ((int64_t)256 << 20) ? 1 : 0;
+    const int stream_in = M * K * 2 > ((int64_t)256 << 20) ? STREAM_IN : 0;
     // A workgroup per row, which spreads a row over four waves (32 x 11008: 2.9 us against 5.6; 2048 x 11008: 10.8 against 12.9), but for
     // short rows in large numbers (2048 x 4096 the other way, 6.0 against 5.3).
     if (wave_per_row(vec, M, K)) {
         dim3 wgrid((unsigned)((M + QT / 64 - 1) / (QT / 64)));
-#define FPTQ_WAVE_CASE(CH, RAGGED) quantize_act_wave_kernel<MODE, CH, RAGGED><<<wgrid, block, 0, s>>>(x, M, K, eps, row_in, inv_s_a, zoff, out, row_out, stream_in)
+#define FPTQ_WAVE_CASE(CH, RAGGED) quantize_act_wave_kernel<MODE, CH, RAGGED><<<wgrid, block, 0, s>>>(x, out, row_out, row_in, M, (int)K, inv_s_a, zoff | stream_in, eps)
         WAVE_PER_ROW(vec, Kpad, FPTQ_WAVE_CASE);
 #undef FPTQ_WAVE_CASE
         return hipGetLastError();
     }
 #define FPTQ_ROW_CASE(CH)                                                                                                   \
     if (vec && Kpad <= 2048 * CH) {                                                                                         \
-        quantize_act_kernel<MODE, CH, false><<<grid, block, 0, s>>>(x, M, K, eps, row_in, inv_s_a, zoff, out, row_out, stream_in);            \
+        quantize_act_kernel<MODE, CH, false><<<grid, block, 0, s>>>(x, out, row_out, row_in, M, (int)K, inv_s_a, zoff | stream_in, eps); \
         return hipGetLastError();                                                                                           \
     }
     // chunks per thread: 6 covers the Llama-2 FFN width 11008, 7 and 14 are the Llama-3 FFN widths 14336 and 28672
@@ -381,7 +393,7 @@ static hipError_t launch_mode(const uint16_t *x, int64_t M, int64_t K, float eps
 #undef FPTQ_ROW_CASE
 #define FPTQ_RAGGED_CASE(CH)                                                                                                \
     if (Kpad <= 2048 * CH) {                                                                                                \
-        quantize_act_kernel<MODE, CH, true><<<grid, block, 0, s>>>(x, M, K, eps, row_in, inv_s_a, zoff, out, row_out, 0);   \
+        quantize_act_kernel<MODE, CH, true><<<grid, block, 0, s>>>(x, out, row_out, row_in, M, (int)K, inv_s_a, zoff, eps);   \
         return hipGetLastError();                                                                                           \
     }
     FPTQ_RAGGED_CASE(1)
@@ -390,7 +402,7 @@ static hipError_t launch_mode(const uint16_t *x, int64_t M, int64_t K, float eps
     FPTQ_RAGGED_CASE(8)
     FPTQ_RAGGED_CASE(16)
 #undef FPTQ_RAGGED_CASE
-    quantize_act_kernel<MODE, 0, false><<<grid, block, 0, s>>>(x, M, K, eps, row_in, inv_s_a, zoff, out, row_out, stream_in);
+    quantize_act_kernel<MODE, 0, false><<<grid, block, 0, s>>>(x, out, row_out, row_in, M, K, inv_s_a, zoff, eps);
     return hipGetLastError();
 }
 

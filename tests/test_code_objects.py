@@ -1,0 +1,45 @@
+"""What the compiler made of the kernels, from the metadata of the library's code objects."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_2506_04985_amd import build
+
+LLVM = "/opt/rocm/llvm/bin"
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """name -> metadata text of every kernel of the built library."""
+    if not os.path.exists(build.LIB):
+        build.build()
+    tmp = tmp_path_factory.mktemp("code_objects")
+    fat, co = str(tmp / "fat"), str(tmp / "co")
+    subprocess.check_call([f"{LLVM}/llvm-objcopy", f"--dump-section=.hip_fatbin={fat}", build.LIB, str(tmp / "copy")])
+    data, found = open(fat, "rb").read(), {}
+    for bundle in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", data):          # one per source file: entries of offset, size, length of name, name
+        at, (entries,) = bundle.start() + 32, struct.unpack_from("<Q", data, bundle.start() + 24)
+        for _ in range(entries):
+            offset, size, length = struct.unpack_from("<QQQ", data, at)
+            target, at = data[at + 24:at + 24 + length], at + 24 + length
+            if b"gfx950" in target and size:
+                open(co, "wb").write(data[bundle.start() + offset:bundle.start() + offset + size])
+                notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", co], capture_output=True, text=True, check=True).stdout
+                for text in notes.split("  - .agpr_count")[1:]:
+                    found[re.search(r"\.name:\s+(_Z\S+)\n", text).group(1)] = text
+    assert found
+    return found
+
+
+def test_arguments_of_the_static_quantizers_come_with_the_dispatch(kernels):
+    """Fourteen words are preloaded; an argument beyond them that a wave needs early is a memory latency of its own."""
+    seen = 0
+    for name, text in kernels.items():
+        if re.search(r"quantize_act_(wave_)?kernelILi\dELi[1-9]", name):
+            explicit = [(int(o), int(s)) for o, s, kind in re.findall(r"\.offset:\s+(\d+)\n\s+\.size:\s+(\d+)\n\s+\.value_kind:\s+(\w+)", text) if not kind.startswith("hidden")]
+            assert len(explicit) == 9 and all(o + s <= 56 for o, s in explicit), (name, explicit)
+            seen += 1
+    assert seen > 30
