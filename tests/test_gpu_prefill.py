@@ -90,9 +90,11 @@ def test_streamed_rows_of_partial_lines(forced):
     xq = fptq.fptq_pack_weights(torch.randint(-8, 8, (M, K), dtype=torch.int8, device="cuda"))
     wq = fptq.fptq_pack_weights(torch.randint(-8, 8, (N, K), dtype=torch.int8, device="cuda"))
     s_w = torch.rand(N, device="cuda") * 0.015 + 0.005
-    got = fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, 0.37, s_w, scratch_for(M, N, K))
-    want = fptq.fptq_w4a4_linear_noalloc(xq, wq, M, N, K, 0.37, s_w)
-    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    got, noalloc = (torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, 0.37, s_w, scratch_for(M, N, K), out=got)
+    fptq.fptq_w4a4_linear_noalloc(xq, wq, M, N, K, 0.37, s_w, out=noalloc)
+    want = fptq.fptq_w4a4_linear_ref(xq, wq, M, N, K, 0.37, s_w)
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16)) and torch.equal(noalloc.view(torch.int16), want.view(torch.int16))
 
 
 @pytest.mark.parametrize("K", [131071, 131070])
