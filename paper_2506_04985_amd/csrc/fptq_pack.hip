@@ -33,9 +33,12 @@ __device__ inline uint32_t pack8(uint32_t lo, uint32_t hi)
 // PACK_TILES K tiles in a row: a wave reads PACK_TILES x 128 contiguous bytes of 16 rows and writes 1 KB runs.  A byte per load, one granule
 // per thread, took 221 us at 28672 x 4096; half granules (8 lanes a row) and eight tiles per thread: the same as now.
 // ALONG_K: consecutive workgroups take the K tiles of the same rows, so that whole rows are read in one go, otherwise the same K tiles of the next
-// rows, which writes longer runs.  28672 x 4096 32.8 us along K, 34.6 otherwise, 8192 x 28672 66 and 70, but 20480 x 5120 30.2 and 29.7,
-// 4096 x 14336 17.5 and 16.9, 640 x 8192 4.1 and 3.6: from 108 MB on.  STREAM: integers and packed weights together above the 256 MB last-level cache, of which then more is left to the
-// integers if the packed weights go past it: 32003 x 8192 87 -> 73 us, with the row sums behind it 122 -> 111; below, 28672 x 4096 32 and 36.
+// rows, which writes longer runs.  The first pays for large matrices whose rows are 4, 8, 12 or 16 KB (integers from HBM, across / along K: 28672 x 4096
+// 36.1 / 32.3 us, 32768 x 4096 40.9 / 34.3, 10261 x 16384 48.0 / 43.1, 13824 x 8192 30.8 / 30.4; 28672 x 4096 from the cache 26.2 / 27.3), costs at others (37888 x
+// 3584 35.0 / 38.0, 28160 x 4352 33.1 / 37.5, 18944 x 7168 35.2 / 38.0, 20949 x 5003 36.0 / 38.8, 4352 x 28672 33.5 / 34.2) and in smaller ones (4096 x 8192
+// 10.5 / 11.2).  Of 57 widths at 120 MB one other gained, 11008 (39.5 / 34.9), its neighbours 10752 and 11264 not.
+// STREAM: integers of more than 192 MB, of which the last-level cache keeps more if the packed weights go past it (cached / streamed, from HBM and
+// again at once: 35882 x 7168 74.4 / 69.3 and 73.4 / 54.6, 29290 x 7168, 200 MB, 57.0 / 57.0 and 54.0 / 46.7, but 26304 x 7168, 180 MB, 48.0 / 51.6 and 46.3 / 40.5).
 constexpr int PACK_TILES = 4;
 
 template <bool ALONG_K, bool STREAM>
@@ -110,12 +113,13 @@ hipError_t launch_pack_weights(const int8_t *w, int64_t N, int64_t K, uint8_t *o
     const int64_t row_blocks = (N + 63) / 64, tile_groups = (k_tiles(K) + PACK_TILES - 1) / PACK_TILES, blocks = row_blocks * tile_groups;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks), block(256);
-    if (N * K + packed_bytes(N, K) > (int64_t)256 << 20)
-        pack_weights_kernel<true, true><<<grid, block, 0, s>>>(w, N, K, row_blocks, tile_groups, out);
-    else if (N * K >= (int64_t)108 << 20)
-        pack_weights_kernel<true, false><<<grid, block, 0, s>>>(w, N, K, row_blocks, tile_groups, out);
+    const bool along_k = K % 4096 == 0 && K <= 16384 && N * K >= (int64_t)108 << 20, stream = N * K > (int64_t)192 << 20;
+#define FPTQ_PACK(ALONG_K, STREAM) pack_weights_kernel<ALONG_K, STREAM><<<grid, block, 0, s>>>(w, N, K, row_blocks, tile_groups, out)
+    if (along_k)
+        stream ? FPTQ_PACK(true, true) : FPTQ_PACK(true, false);
     else
-        pack_weights_kernel<false, false><<<grid, block, 0, s>>>(w, N, K, row_blocks, tile_groups, out);
+        stream ? FPTQ_PACK(false, true) : FPTQ_PACK(false, false);
+#undef FPTQ_PACK
     return hipGetLastError();
 }
 

@@ -3,6 +3,8 @@
 Comparison bar: per-token scales, quantized values and int32 accumulators bit-exact; bf16 outputs
 within 1e-2 of the oracle, max-abs normalised (the tests also report how many differ at all).
 """
+import ctypes
+
 import numpy as np
 import torch
 
@@ -61,3 +63,22 @@ def run_gpu_linear(inp, M=None, use_ref=False, want_acc=True, undo_scale=False):
     torch.cuda.synchronize()
     return {"r": r.cpu().numpy(), "q": q.cpu().numpy(), "acc": None if acc is None else acc.cpu().numpy(),
             "y": host_bits(y), "d": None if d is None else d.cpu().numpy()}
+
+
+def launched(call):
+    """(kernel, workgroups) of the one launch that a call makes, from its captured graph; kernels are told apart by their handles."""
+    class Params(ctypes.Structure):
+        _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint32 * 3),
+                    ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line))
+    raw, count = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(count)) == 0 and count.value == 1
+    node, params = ctypes.c_void_p(), Params()
+    assert hip.hipGraphGetNodes(raw, ctypes.byref(node), ctypes.byref(count)) == 0
+    assert hip.hipGraphKernelNodeGetParams(node, ctypes.byref(params)) == 0
+    return params.func, params.grid[0]

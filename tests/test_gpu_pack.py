@@ -6,7 +6,7 @@ import torch
 
 from paper_2506_04985_amd import binding as fptq
 
-from gpu_util import layout_from_canonical
+from gpu_util import launched, layout_from_canonical
 
 pytestmark = pytest.mark.gpu
 
@@ -33,9 +33,9 @@ def test_pack_and_row_sums(N, K, offset):
     assert np.array_equal(fptq.fptq_weight_row_sums(wd).cpu().numpy(), w.sum(axis=1, dtype=np.int32))
 
 
-@pytest.mark.parametrize("N,K", [(28673, 4100), (43700, 4111)])
+@pytest.mark.parametrize("N,K", [(28673, 4100), (43700, 4111), (28673, 4096), (49250, 4111), (24701, 8192)])
 def test_large_matrices(N, K):
-    """Sizes at which the workgroups go along K, and at which the packed weights are streamed."""
+    """Sizes around those at which the workgroups go along K, and at which the packed weights are streamed."""
     torch.manual_seed(N)
     w = torch.randint(-8, 8, (N, K), dtype=torch.int8, device="cuda")
     kt = (K + 127) // 128
@@ -50,3 +50,18 @@ def test_row_sums_of_full_bytes():
     """Row sums take the int8 as it is, not its low nibble."""
     w = torch.arange(-128, 128, dtype=torch.int16).to(torch.int8).repeat(3, 5)[:, :1237].contiguous().cuda()
     assert torch.equal(fptq.fptq_weight_row_sums(w).cpu(), w.cpu().sum(dim=1, dtype=torch.int32))
+
+
+def test_order_and_stores_by_size_and_width():
+    """Along K only where rows are 4, 8, 12 or 16 KB and the matrix is large (other widths were up to 13 % slower that way), streamed only where little of
+    the integers would stay in the last-level cache (matrices of 171 to 192 MB were up to 27 % slower streamed)."""
+    def kernel(N, K):
+        w = torch.zeros((N, K), dtype=torch.int8, device="cuda")
+        out = torch.empty(fptq.fptq_packed_bytes(N, K), dtype=torch.uint8, device="cuda")
+        return launched(lambda: fptq.fptq_pack_weights(w, out=out))[0]
+    plain, along, streamed = kernel(512, 512), kernel(28672, 4096), kernel(39400, 5120)
+    assert len({plain, along, streamed, kernel(49200, 4096)}) == 4
+    for N, K in ((28672, 4000), (28672, 4352), (18944, 7168), (29312, 6144), (4096, 28672), (6272, 28672), (39200, 5120)):
+        assert kernel(N, K) == plain, (N, K)
+    for N, K in ((14336, 8192), (9600, 12288), (7200, 16384), (49100, 4096)):
+        assert kernel(N, K) == along, (N, K)

@@ -1,7 +1,5 @@
 """Quantizers on rows whose length is no multiple of eight or whose address is only 2-byte aligned: chunks loaded where they lie, at the edges
 of the rows, of the width classes and of the register path, against the oracle; nothing outside the matrix is used or written."""
-import ctypes
-
 import numpy as np
 import pytest
 import torch
@@ -9,7 +7,7 @@ import torch
 from paper_2506_04985_amd import binding as fptq
 import fptq_workloads as synth
 
-from gpu_util import dev, host_bits
+from gpu_util import dev, host_bits, launched
 
 pytestmark = pytest.mark.gpu
 
@@ -79,25 +77,6 @@ def test_residual_step(oracle, M, K, offset, alias):
     assert bool(base[:offset].isnan().all()) and bool(base[offset + M * K:].isnan().all())
 
 
-def workgroups(call):
-    """Workgroups of the one kernel that a call launches, from its captured graph."""
-    class Params(ctypes.Structure):
-        _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint32 * 3),
-                    ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
-    call()
-    torch.cuda.synchronize()
-    graph = torch.cuda.CUDAGraph(keep_graph=True)
-    with torch.cuda.graph(graph):
-        call()
-    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line))
-    raw, count = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
-    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(count)) == 0 and count.value == 1
-    node, params = ctypes.c_void_p(), Params()
-    assert hip.hipGraphGetNodes(raw, ctypes.byref(node), ctypes.byref(count)) == 0
-    assert hip.hipGraphKernelNodeGetParams(node, ctypes.byref(params)) == 0
-    return params.grid[0]
-
-
 @pytest.mark.parametrize("M,K", [(769, 63), (2048, 333), (8192, 1001), (3073, 4095)])
 def test_many_short_rows_share_workgroups(M, K):
     """A workgroup per row was up to four times as slow there as four rows to a workgroup, a wave each."""
@@ -107,4 +86,4 @@ def test_many_short_rows_share_workgroups(M, K):
     for call in (lambda: fptq.fptq_quantize_act(x, 0.4, synth.MODE_RMS, 1e-5, None, out=q, row_scale_out=s),
                  lambda: fptq.fptq_quantize_act_dynamic(x, out=q, token_scale_out=s),
                  lambda: fptq.fptq_residual_norm_quantize(x, y, 0.45, None, 1e-5, x_next=o, s_next=s, out=q)):
-        assert workgroups(call) == (M + 3) // 4
+        assert launched(call)[1] == (M + 3) // 4
