@@ -253,8 +253,11 @@ __device__ inline int32_t remove_zero_point(int32_t acc, int zp, const int32_t *
 // 1365; dense 1632 and 1658; INT8 kernel, 1000 x 5120 x 4096 22.9 and 23.7, 300 x 20000 x 1000 11.8 and 12.7).  Other widths leave two
 // parts of a piece to two waves, which meet in L2 when cached; streamed, each goes to memory by itself: 3000 x 11000 x 2048 76 us, cached
 // 66, 4096 x 4104 x 4096 70 and 65, 1000 x 9000 x 3000 36 and 34, on the INT8 kernel 333 x 32008 x 2504 30.2 and 29.7.  An output that the
-// 256 MB last-level cache cannot hold is streamed all the same: cached, 8192 x 28680 x 1024 took 271 us instead of 255, 8192 x 16392 x
-// 2048 213 instead of 203.
+// 256 MB last-level cache cannot hold is streamed all the same if its rows are multiples of 16 bytes: cached, 8192 x 28680 x 1024 took 271 us instead of
+// 255, 8192 x 16392 x 2048 213 instead of 203.  Other rows are cached at any size: streamed, 8192 x 32003 x 1024 takes 319 us instead of 251, 4096 x
+// 32003 x 4096 300 instead of 283, 3000 x 11001 x 2048 80 instead of 66, 2048 x 128257 x 2048 391 instead of 389 (INT8 kernel 291 and 276, 382 and 382, 71
+// and 65, 435 and 444).  64 bytes are half a line: on the six-bit kernel rows of an odd number of them lose up to 3 % streamed (3000 x 11040 x 2048 56.7 us,
+// cached 55.0, 4096 x 4128 x 4096 55.0 and 54.1) and gain 5 % where the output is large (4096 x 28704 x 1024 112 and 118, 8192 x 14368 x 1024 116 and 121).
 enum { ANY_ALIGNMENT, CACHED, STREAMED };          // ANY_ALIGNMENT: serves every N, chosen for N % 8 != 0
 inline int store_kind(int64_t M, int64_t N)
 {

@@ -205,8 +205,8 @@ hipError_t launch_linear_decode(const uint8_t *xq, const uint8_t *wq, int64_t M,
     // on every CU, and with the weights on streaming loads one K tile in flight per wave and more resident
     // workgroups beat deeper unrolling (except for very long K against few channels).  Up to 4096 channels a
     // workgroup takes 16 of them, beyond that 32, which halves the activation re-reads, and 64 from 16384 channels
-    // on (fewer, longer-lived workgroups: the matrix is several rounds of workgroups long either way); with more
-    // than 16 tokens, 64 from 10240 channels on.  Each choice is within about 10 % of the best shape of its case.
+    // on (fewer, longer-lived workgroups: the matrix is several rounds of workgroups long either way); with 17 to 32 tokens, 64 from 10240 channels
+    // on but for widths of a little more than a round (below); with 33 to 64, never more than 32.  Each choice is within about 10 % of the best shape of its case.
     const bool deep = kt >= 16;          // at least one K tile for each of 16 waves
     if (M <= 16) {
         if (!deep) FPTQ_DEC(8, 4, 1, 1);

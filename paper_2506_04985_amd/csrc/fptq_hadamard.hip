@@ -15,8 +15,8 @@
 // (padded so that both directions are bank-conflict free).  Everything is wave-private: no barriers.
 //
 // Bound by HBM (2 bytes read, half a byte written per value) and VALU issue: 16 VALU instructions per value at B = 256, 21 at B = 2048
-// and 4096 with a workgroup per block, 20 with a wave per block, which keep the SIMDs issuing in 60 % of all cycles at 4096 x 11008,
-// 86 % at 4096 x 14336 and 88 % at 8192 x 28672 (the plain quantizer: 32 to 36 %).  4096 x 11008 takes 26.7 us (27.3 before the loads were direct).
+// and 4096 with a workgroup per block, 20 with a wave per block, which keep the SIMDs issuing in 62 % of all cycles at 4096 x 11008,
+// 88 % at 4096 x 14336 and 90 % at 8192 x 28672 (the plain quantizer: 33 to 39 %).  4096 x 11008 takes 26.7 us (27.3 before the loads were direct).
 //
 // B = 64 V with V = 8, 16, 32, 64 (32 and 64: in RMS mode, and beyond the number of blocks at which a workgroup per block is the faster).  One block per wave iteration, V values per lane.  View 1: the lane
 // holds x[64 j + lane] and runs strides B/2 .. 64 in registers; view 2: the lane holds
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16
     const int b = lane >> 4, g = lane & 15;
     // a lane's 16 results: K tile 2 b + g / 8 of the super-chunk's, bytes 8 (g % 8) of the row's segment
     const int64_t lane_out = (int64_t)(2 * b + (g >> 3)) * M * SEG + (g & 7) * 8;
-        float *patch = reinterpret_cast<float *>(lds + wave * H_WAVE_LDS) + b * H_F32_BLK;
+    float *patch = reinterpret_cast<float *>(lds + wave * H_WAVE_LDS) + b * H_F32_BLK;
 
     for (int64_t sc = (int64_t)part * (4 * HB); sc < K; sc += (int64_t)ksplit * (4 * HB)) {
         const int live_blocks = (int)min((int64_t)4, (K - sc) / HB);      // lanes of blocks past the row's end repeat the last one
@@ -244,7 +244,9 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_wide_kernel(const u
 // block, elements e of LOGB bits: thread = the low bits, registers = the top four (loaded as they are: 16 loads side by side); registers =
 // the next four, thread = the rest; 16 consecutive elements a thread.  The strides run from B / 2 to 1 as in the definition, four
 // (in the last view of B = 2048 three) per view.  Between views the values go through LDS, the first time across waves (a barrier), the second
-// inside the thread's wave; element e lies in word e + 4 (e / 16) + 2^(LOGB-8) (e / 2^(LOGB-4)), which leaves the reads free of bank conflicts.
+// inside the thread's wave; element e lies in word e + 4 (e / 16) + 2^(LOGB-8) (e / 2^(LOGB-4)), which leaves the second view free of bank conflicts, and
+// the third one's reads for B = 4096.  For B = 2048 threads t and t + 6 of 16 meet there, and in the first view's stores lanes 52 to 63 of a wave meet 0 to 11:
+// 64 conflict cycles a wave counted at 4096 x 14336.
 template <int MODE, int LOGB>
 __global__ __launch_bounds__(1 << (LOGB - 4)) void quantize_act_hadamard_group_kernel(const uint16_t *__restrict__ x, int64_t M, int64_t K,
                                                                                      const float *__restrict__ row_in, float inv_s_a, float hnorm,

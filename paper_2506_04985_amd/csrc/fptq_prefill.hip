@@ -9,7 +9,7 @@
 // what they hold at the end is sum_k q w and not sum_k q (w + 8).
 //
 // Data flow.  A small kernel first widens the packed activations to six bits in a scratch buffer of the caller (0.75 bytes a
-// value, read and written once: 15 us at 8192 x 8192 beside 1747 us of a 57344-channel product), with their signs resolved, and sums each
+// value, read and written once: 15 us at 8192 x 8192 beside 1637 us of a 57344-channel product), with their signs resolved, and sums each
 // token's codes.  The matrix kernel copies those to LDS with buffer loads that write LDS directly, and reads the weights as
 // they are, packed: each of its four waves owns 64 channels and all tokens of the tile (256, 192 or 128), so a weight is loaded by one
 // wave only, into registers (256 and 192 tokens) or through LDS of the wave's own (128), and its nibbles are spread to six-bit fields by
@@ -18,8 +18,8 @@
 // weights beforehand as well would cost 1.25 bytes of traffic per weight and call, 5 % at 8192 tokens.
 //
 // What bounds it: the board's power, and the cycles without an MFMA in flight.  On uniform random INT4 operands 8192 x 57344 x 8192 takes
-// 1757 us, widening included (4380 TOP/s; boards differ by 4 %), the INT8 kernel 2537, on all-zero operands 1240.  The matrix pipe is
-// busy in 61 % of the cycles at about 1.9 of 2.4 GHz.  An MFMA-only loop on such operands that never change reaches 6700 TOP/s, with
+// 1653 us, widening included (4660 TOP/s; boards differ by 4 %), the INT8 kernel 2537, on all-zero operands 1090.  The matrix pipe is
+// busy in 66 % of the cycles at about 1.9 of 2.4 GHz.  An MFMA-only loop on such operands that never change reaches 6700 TOP/s, with
 // this kernel's LDS reads of activations 5900 to 6250.
 #include <cstdio>
 #include <type_traits>
@@ -414,7 +414,8 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     // One wave per SIMD has nothing to hide a latency under, so the 32 (64 with a zero point) channel constants are read once, into the
     // registers that the K loop's operands leave free, and the results of a group of 32 tokens are read back from LDS while the next
     // group's are computed and written: 6.1 us a tile with the constants read where they are used and one patch for all groups,
-    // PLACEHOLDER now.  The two halves of a wave exchange quads, so that a lane holds eight consecutive channels (16 bytes); those go
+    // 3.6 now (2.8 to 4.2 from workgroup to workgroup).  With token scales and no zero point the registers do not suffice on the 256-token tile: 17
+    // go through scratch, 15 operations a lane (2048 x 22016 x 4096 104.9 us, 101.5 without token scales, 102.0 with both).  The two halves of a wave exchange quads, so that a lane holds eight consecutive channels (16 bytes); those go
     // through a wave-private LDS patch of 32 rows of 128 bytes per group, granule g of row r in slot g ^ (r % 8) (no bank
     // conflicts in either direction), so that HBM sees rows of 128 bytes.  A wave's LDS operations complete in order, so only the
     // compiler has to be kept from exchanging them.

@@ -43,3 +43,14 @@ def test_arguments_of_the_static_quantizers_come_with_the_dispatch(kernels):
             assert len(explicit) == 9 and all(o + s <= 56 for o, s in explicit), (name, explicit)
             seen += 1
     assert seen > 30
+
+
+def test_scratch_only_where_it_is_stated(kernels):
+    """Of the instances that calls run: the INT8 256 x 256 tile at any width or with a zero point, the six-bit 256-token tile of whole 16-byte rows."""
+    stated = (r"linear_mfma_kernelINS_7GemmCfgILi2ELi2ELi4ELi4ELi4ELi1ELi1ELb0EEE(Li0ELb0ELb[01]E|Li[12]ELb0ELb1E)",
+              r"linear_prefill_kernelILi8ELi[12]ELb0ELb[01]E",
+              r"linear_(mfma|prefill)_kernel.*Li0ELb1ELb[01]E",                 # parity dumps of the accumulators
+              r"linear_decode_kernelILi16ELi4ELi[24]E")                         # shapes that only fptq_set_decode_shape reaches
+    for name, text in kernels.items():
+        if int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", text).group(1)):
+            assert any(re.search(s, name) for s in stated), name
