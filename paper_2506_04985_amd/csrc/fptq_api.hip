@@ -52,7 +52,6 @@ hipError_t device_info(const DeviceInfo **out)
             info.cus = cus > 0 ? cus : DEFAULT_CUS;
             if ((e = gemm_device_init(&info)) != hipSuccess) return e;
             if ((e = prefill_device_init()) != hipSuccess) return e;
-            if ((e = hadamard_device_init(dev)) != hipSuccess) return e;
             g_devices[dev] = info;
             g_device_ready[dev].store(true, std::memory_order_release);
         }

@@ -84,7 +84,6 @@ int device_cus_or_default();                     // compute units of the current
 // what each translation unit contributes to that set-up (called with the device current, under the set-up lock)
 hipError_t gemm_device_init(DeviceInfo *info);
 hipError_t prefill_device_init();
-hipError_t hadamard_device_init(int device);
 
 // ---- what several kernel sources share
 
@@ -159,17 +158,29 @@ inline bool wave_per_row(bool vec, int64_t M, int64_t K) { return K <= 4096 && M
 
 // Its instances: CASE(chunks a lane, ragged).  Ragged rows in finer steps, because a chunk that lies past the row's end is loaded and computed
 // all the same (800 x 777, residual step: 5.1 us with four chunks, 3.8 with two).
-#define WAVE_PER_ROW(vec, K, CASE)                        \
+#define WAVE_PER_ROW_RAGGED(K, CASE)                      \
     do {                                                  \
-        if (vec) {                                        \
-            if ((K) <= 2048) CASE(4, false);              \
-            else CASE(8, false);                          \
-        } else if ((K) <= 512) CASE(1, true);             \
+        if ((K) <= 512) CASE(1, true);                    \
         else if ((K) <= 1024) CASE(2, true);              \
         else if ((K) <= 2048) CASE(4, true);              \
         else if ((K) <= 3072) CASE(6, true);              \
         else CASE(8, true);                               \
     } while (0)
+#define WAVE_PER_ROW(vec, K, CASE)                        \
+    do {                                                  \
+        if (!(vec)) WAVE_PER_ROW_RAGGED(K, CASE);         \
+        else if ((K) <= 2048) CASE(4, false);             \
+        else CASE(8, false);                              \
+    } while (0)
+
+// a / n and a % n with m = reciprocal(n), in a few scalar instructions: the estimate is the quotient or one less (the division that the compiler makes of
+// a run-time divisor is a chain of twenty, 0.1 us at the start of every wave)
+inline uint32_t reciprocal(uint32_t n) { return n == 1 ? 0xffffffffu : (uint32_t)(((uint64_t)1 << 32) / n); }
+__device__ inline void divide(uint32_t a, uint32_t n, uint32_t m, uint32_t &quotient, uint32_t &remainder)
+{
+    const uint32_t q = __umulhi(a, m), r = a - q * n;
+    quotient = r >= n ? q + 1 : q, remainder = r >= n ? r - n : r;
+}
 
 // what of a word of eight codes from k0 on lies inside the row: K padding stays zero
 __device__ inline uint32_t codes_inside(uint32_t word, int k0, int K)
@@ -242,6 +253,38 @@ __device__ inline uint32_t quant_code(float x, float c, int zoff)
     return (uint32_t)min(max(j, 0), 15);
 }
 constexpr uint32_t CODE_TO_NIBBLES = 0x88888888u;
+
+// The same codes on the symmetric grid in 3.25 instructions a value instead of 6, for products x * c that are no NaN: clamped between the grid's
+// ends first (integers, so the order does not matter), then rounded by adding 1.5 * 2^23, whose sum holds the code in its low bits, written to a byte of a
+// register at once; the even values' bytes and the odd ones' make the word of nibbles, value e in nibble e.  Two writes to one register need a
+// wait state between them, and so does its first reader.
+__device__ inline uint32_t quantize_tame(const float *x, float c)
+{
+    float t[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) t[e] = __builtin_amdgcn_fmed3f(x[e] * c, -8.0f, 7.0f);
+    uint32_t even, odd;
+    asm("v_add_f32_sdwa %0, %2, %10 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:DWORD\n\t"
+        "v_add_f32_sdwa %1, %3, %10 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:DWORD\n\t"
+        "v_add_f32_sdwa %0, %4, %10 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD\n\t"
+        "v_add_f32_sdwa %1, %5, %10 dst_sel:BYTE_1 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD\n\t"
+        "v_add_f32_sdwa %0, %6, %10 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD\n\t"
+        "v_add_f32_sdwa %1, %7, %10 dst_sel:BYTE_2 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD\n\t"
+        "v_add_f32_sdwa %0, %8, %10 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD\n\t"
+        "v_add_f32_sdwa %1, %9, %10 dst_sel:BYTE_3 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:DWORD\n\t"
+        "s_nop 0"
+        : "=&v"(even), "=&v"(odd)
+        : "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]), "v"(t[7]), "v"(12582912.0f));
+    return (even & 0x0F0F0F0Fu) | (odd << 4 & 0xF0F0F0F0u);
+}
+
+// What shows that no product is a NaN: a sum of squares of the inputs (two to an instruction) below TAME bounds them by 2^62, so the sums of any 4096 of
+// them are finite, and so is a multiplier below it.
+constexpr float TAME = 0x1p123f;
+__device__ inline float add_squares(float sum, uint32_t pair)
+{
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, pair), __builtin_bit_cast(bf16x2_t, pair), sum, false);
+}
 
 // Zero-point correction of an accumulator: sum_k (v - z) w = acc - z * sum_k w (wsum == NULL: symmetric grid).
 __device__ inline int32_t remove_zero_point(int32_t acc, int zp, const int32_t *wsum, int64_t o)

@@ -5,67 +5,120 @@
 // down projection's width is 256 for 11008, 2048 for 14336, 4096 for 28672), one pass over X.
 //
 // The transform is evaluated by the in-place butterfly network in fp32 with strides
-// 128, 64, ..., 1, each pair (a, b) -> (a + b, a - b): every output is a fixed tree of fp32
+// B / 2, B / 4, ..., 1, each pair (a, b) -> (a + b, a - b): every output is a fixed tree of fp32
 // additions, so the result does not depend on how the work is spread over lanes.
 //
-// B = 256.  One wave per token row; a wave walks the row in super-chunks of 1024 values = 4 blocks, a
-// block per 16 lanes, 16 values per lane.  The four high strides need the lane to hold
-// x[16 j + g] (j = 0..15), the four low strides x[16 g + e]: the bf16 values are loaded in the strided view (16 loads side by side;
-// through LDS, as whole lines, was 2 to 4 % slower), the fp32 intermediates go through LDS to get the contiguous view
-// (padded so that both directions are bank-conflict free).  Everything is wave-private: no barriers.
-//
-// Bound by HBM (2 bytes read, half a byte written per value) and VALU issue: 16 VALU instructions per value at B = 256, 21 at B = 2048
-// and 4096 with a workgroup per block, 20 with a wave per block, which keep the SIMDs issuing in 62 % of all cycles at 4096 x 11008,
-// 88 % at 4096 x 14336 and 90 % at 8192 x 28672 (the plain quantizer: 33 to 39 %).  4096 x 11008 takes 26.7 us (27.3 before the loads were direct).
-//
-// B = 64 V with V = 8, 16, 32, 64 (32 and 64: in RMS mode, and beyond the number of blocks at which a workgroup per block is the faster).  One block per wave iteration, V values per lane.  View 1: the lane
-// holds x[64 j + lane] and runs strides B/2 .. 64 in registers; view 2: the lane holds
-// x[V lane + e] and runs strides V/2 .. 1 in registers; the strides in between (32 .. V) pair lane l with
-// lane l ^ (stride / V) and are done with DPP lane exchanges, in descending order between the two
-// register passes, so the stage order is that of the definition.  The raw block and the fp32
-// transposition patch share the wave's LDS region (a wave's LDS operations complete in order).
+// A wave holds 1024 consecutive values of a row (a block of 2048 or 4096) in registers from the load to the codes, without LDS: the first
+// strides run over registers, then over lanes, then over registers again.  Where the scale is given, every wave is done after one such
+// span, consecutive waves take consecutive spans, and memory is read in the order it lies in; waves that walked a row each, or several spans
+// a row apart, were up to a sixth slower on inputs that come from HBM (us, the kernel that walked rows through LDS and this one):
+//     4096 x 11008, B = 256    29.2  24.2     4096 x 13824, B = 512   38.6  31.0     4096 x 11264, B = 1024   29.0  26.3
+//     8192 x 14336, B = 2048   66.0  63.0     8192 x 13824, B = 512   66.0  57.9     8192 x 28672, B = 4096  137.9 114.0
+// (the read alone, as one burst: 16.3 us at 4096 x 11008, 80.6 at 8192 x 28672; from the last-level cache 4096 x 11008 21.2 and 20.7).
+// Bound by memory there and by VALU issue from the cache: 13 instructions per value at B = 256, 17 at 2048, 18 at 4096.
 #include "fptq_common.h"
 
 namespace fptq {
 
-constexpr int HB = 256;                 // Hadamard block
-constexpr int H_F32_ROW = 20;           // words per 16-value row of the fp32 transpose patch (16 + 4)
-constexpr int H_F32_BLK = 336;          // words per block of the patch (16 * 20 + 16)
-// 5376 bytes of patch, rounded up so that five workgroups share a CU: a line is loaded by four instructions, and the lines in flight of seven
-// workgroups do not fit L1 (8192 x 13824: 64.3 us with seven, 60.2 with five)
-constexpr int H_WAVE_LDS = 7552;
-static_assert(H_WAVE_LDS >= 4 * H_F32_BLK * 4, "");
+// 1 / sqrt(2^logb) as the nearest float
+constexpr float hadamard_norm(int logb) { return (logb % 2 ? 0x1.6a09e6p-1f : 1.0f) / (float)(1 << (logb / 2)); }
 
 __device__ inline float h_bf16_to_f32(uint32_t bits) { return __uint_as_float(bits << 16); }
 
-__device__ inline void butterflies16(float (&v)[16])
+// one butterfly stage over registers
+template <int S, int V>
+__device__ inline void register_stage(float (&v)[V])
 {
 #pragma unroll
-    for (int s = 8; s >= 1; s >>= 1)
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-            if ((j & s) == 0) {
-                float a = v[j], b = v[j + s];
-                v[j] = a + b;
-                v[j + s] = a - b;
-            }
+    for (int j = 0; j < V; ++j)
+        if ((j & S) == 0) {
+            const float a = v[j], b = v[j + S];
+            v[j] = a + b;
+            v[j + S] = a - b;
+        }
 }
 
-template <int MODE>
-__global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16_t *__restrict__ x, int64_t M, int64_t K,
-                                                                    float eps, const float *__restrict__ row_in,
-                                                                    float inv_s_a, float hnorm, uint8_t *__restrict__ out,
-                                                                    float *__restrict__ row_out, int ksplit)
+// One butterfly stage over lanes, an instruction a value: own + sgn * other, with sgn = 1 in a pair's lower lane (a + b) and -1 in its upper
+// one, where that is -(a - b): exactly the difference with its sign changed (a product with +-1 and one rounding).  Later stages pair lanes of the same
+// sign, so it stays the lane's and goes into the quantizer's multiplier, exactly again.  A DPP operand needs two wait states
+// after the instruction that wrote it.
+#define FPTQ_LANE_STAGE(name, ctrl)                                                                                                     \
+    template <int V>                                                                                                                    \
+    __device__ inline void name(float (&v)[V], float sgn)                                                                               \
+    {                                                                                                                                   \
+        _Pragma("unroll") for (int i = 0; i < V; i += 8) asm("s_nop 1\n\t"                                                              \
+            "v_fmac_f32_dpp %0, %0, %8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                                         \
+            "v_fmac_f32_dpp %1, %1, %8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                                         \
+            "v_fmac_f32_dpp %2, %2, %8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                                         \
+            "v_fmac_f32_dpp %3, %3, %8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                                         \
+            "v_fmac_f32_dpp %4, %4, %8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                                         \
+            "v_fmac_f32_dpp %5, %5, %8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                                         \
+            "v_fmac_f32_dpp %6, %6, %8 " ctrl " row_mask:0xf bank_mask:0xf\n\t"                                                         \
+            "v_fmac_f32_dpp %7, %7, %8 " ctrl " row_mask:0xf bank_mask:0xf"                                                             \
+            : "+v"(v[i]), "+v"(v[i + 1]), "+v"(v[i + 2]), "+v"(v[i + 3]), "+v"(v[i + 4]), "+v"(v[i + 5]), "+v"(v[i + 6]), "+v"(v[i + 7]) \
+            : "v"(sgn));                                                                                                                \
+    }
+FPTQ_LANE_STAGE(lanes_xor1, "quad_perm:[1,0,3,2]")
+FPTQ_LANE_STAGE(lanes_xor2, "quad_perm:[2,3,0,1]")
+FPTQ_LANE_STAGE(lanes_xor7, "row_half_mirror")
+FPTQ_LANE_STAGE(lanes_xor8, "row_ror:8")
+#undef FPTQ_LANE_STAGE
+
+// bit S of the register index and bit 5 (LANE 32) or 4 (LANE 16) of the lane change places
+template <int LANE, int S, int V>
+__device__ inline void swap_with_lanes(float (&v)[V])
 {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[4 * H_WAVE_LDS];
+#pragma unroll
+    for (int j = 0; j < V; ++j)
+        if ((j & S) == 0) {
+            const uint32_t a = __float_as_uint(v[j]), b = __float_as_uint(v[j + S]);
+            if (LANE == 32) {
+                const auto p = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+                v[j] = __uint_as_float(p[0]), v[j + S] = __uint_as_float(p[1]);
+            } else {
+                const auto p = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+                v[j] = __uint_as_float(p[0]), v[j + S] = __uint_as_float(p[1]);
+            }
+        }
+}
+
+// A wave takes a span of SPAN values: CH chunks of eight consecutive values a lane (16-byte loads).  Bits 0 .. 2 of an element's place in the
+// span are the value in its chunk, bits 3 .. 6 the low four bits of the lane, the rest lane bits 5 and 4 and the chunk's number:
+//     B = 256    lanes: block, block; chunks: bit 7            B = 2048   lanes: bits 8, 7; chunks: bits 10, 9
+//     B = 512    lanes: bit 7, block; chunks: bit 8            B = 4096   lanes: bits 8, 7; chunks: bits 11, 10, 9
+//     B = 1024   lanes: bits 8, 7;    chunks: bit 9
+// The chunks' bits come first.  Bits 8 and 7 then change places with chunk bits that are done (permlane swaps).  Bits 6 .. 3 pair lanes that
+// differ by 8, 7, 2 and 1, which DPP reaches: with lane bits l3 .. l0 they are l3, l2, l1 ^ l2, l0 ^ l2.  What is left is in the chunk.  A lane
+// ends up with whole words of codes, 16 lanes with the 64 bytes of a row in a K tile.
+//
+// RMS: the scale comes from the whole row, which every wave of it sums, so `parts` waves share a row and walk its spans.  STREAM: inputs that the
+// last-level cache cannot hold (8192 x 28672: 123.0 us, 117.6 with; 4096 x 11008 from the cache 20.7 and 23.6).
+template <int MODE, int LOGB, bool STREAM>
+__global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16_t *__restrict__ x, const float *__restrict__ row_in,
+                                                                    uint8_t *__restrict__ out, float *__restrict__ row_out, int M, int64_t K,
+                                                                    float inv_s_a, uint32_t parts, uint32_t per_parts, float eps)
+{
+    constexpr int R = LOGB <= 10 ? 1 : LOGB - 9, CH = 1 << R, V = 8 * CH, SPAN = 64 * V, B = 1 << LOGB;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // ksplit waves share a row: wave `part` of them takes every ksplit-th group of four blocks
-    const int64_t wid = (int64_t)blockIdx.x * 4 + wave, t = wid / ksplit;
-    const int part = (int)(wid % ksplit);
-    if (t >= M) return;                                  // whole waves leave; nothing below synchronises
-    const uint16_t *row = x + t * K;
+    uint32_t t, part;
+    divide(blockIdx.x * 4 + wave, parts, per_parts, t, part);
+    if (t >= (uint32_t)M) return;                        // whole waves leave; nothing below synchronises
+    const uint16_t *row = x + (int64_t)t * K;
+    const int l5 = lane >> 5, l4 = lane >> 4 & 1;
+    const int chunk = (lane & 12) | ((lane & 3) ^ (lane & 4 ? 3 : 0));       // bits 3 .. 6
+    const int from = chunk * 8 + (LOGB == 8 ? (l5 * 2 + l4) * 256 : LOGB == 9 ? l4 * 512 + l5 * 128 : l5 * 256 + l4 * 128);
+    constexpr int FROM_STEP = LOGB == 8 ? 128 : LOGB == 9 ? 256 : 512;
+    v4u regs[CH];
+    auto load = [&](int64_t at) {
+        const int live = (int)min((int64_t)SPAN, K - at);      // lanes of blocks past the row's end repeat the span's first one
+        const v4u *src = reinterpret_cast<const v4u *>(row + at + (SPAN > B && from >= live ? from % B : from));
+#pragma unroll
+        for (int r = 0; r < CH; ++r) regs[r] = STREAM ? __builtin_nontemporal_load(src + r * (FROM_STEP / 8)) : src[r * (FROM_STEP / 8)];
+    };
+    int64_t at = (int64_t)part * SPAN;
+    load(at);
 
-    float r = 1.0f;
+    float s = 1.0f;
     if (MODE == FPTQ_SCALE_RMS) {                        // S_t from the row as the norm layer sees it
         double ss = 0.0;
         for (int64_t k0 = (int64_t)lane * 8; k0 < K; k0 += 512) {
@@ -79,162 +132,58 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16
             }
         }
         ss = wave_sum(ss);
-        r = (float)(1.0 / sqrt(ss / (double)K + (double)eps));
+        s = (float)(1.0 / sqrt(ss / (double)K + (double)eps));
     } else if (MODE == FPTQ_SCALE_GIVEN) {
-        r = row_in[t];
+        s = row_in[t];
     }
-    const float c = ((MODE == FPTQ_SCALE_NONE) ? inv_s_a : r * inv_s_a) * hnorm;
-    if (lane == 0 && part == 0 && row_out) row_out[t] = r;
+    if (lane == 0 && part == 0 && row_out) row_out[t] = s;
+    auto sign = [&](int bit) { return chunk & bit ? -1.0f : 1.0f; };
+    const float c = ((MODE == FPTQ_SCALE_NONE) ? inv_s_a : s * inv_s_a) * hadamard_norm(LOGB) * (sign(1) * sign(2) * sign(4) * sign(8));
 
-    const int b = lane >> 4, g = lane & 15;
-    // a lane's 16 results: K tile 2 b + g / 8 of the super-chunk's, bytes 8 (g % 8) of the row's segment
-    const int64_t lane_out = (int64_t)(2 * b + (g >> 3)) * M * SEG + (g & 7) * 8;
-    float *patch = reinterpret_cast<float *>(lds + wave * H_WAVE_LDS) + b * H_F32_BLK;
-
-    for (int64_t sc = (int64_t)part * (4 * HB); sc < K; sc += (int64_t)ksplit * (4 * HB)) {
-        const int live_blocks = (int)min((int64_t)4, (K - sc) / HB);      // lanes of blocks past the row's end repeat the last one
-        // strided view x[16 j + g]: strides 128, 64, 32, 16 of the block are strides 8, 4, 2, 1 in j
-        float v[16];
-        const uint16_t *const src = row + sc;
-        const int at = min(b, live_blocks - 1) * HB + g;
+    const int tile_l = LOGB == 8 ? l5 * 4 + l4 * 2 : LOGB == 9 ? l4 * 4 + l5 * 2 : LOGB == 10 ? l5 * 4 + l4 * 2 : LOGB == 11 ? l5 * 8 + l4 * 4 : l5 * 16 + l4 * 8;
+    for (;;) {
+        float v[V], squares = 0.0f;
 #pragma unroll
-        for (int j = 0; j < 16; ++j) v[j] = h_bf16_to_f32(src[at + 16 * j]);
-        butterflies16(v);
-        // transpose inside the block: value (j, g) to row j, column g; read back row g
-#pragma unroll
-        for (int j = 0; j < 16; ++j) patch[H_F32_ROW * j + g] = v[j];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float4 f = *reinterpret_cast<const float4 *>(patch + H_F32_ROW * g + 4 * i);
-            v[4 * i] = f.x, v[4 * i + 1] = f.y, v[4 * i + 2] = f.z, v[4 * i + 3] = f.w;
-        }
-        butterflies16(v);                                 // contiguous view: strides 8, 4, 2, 1
-        if (b < live_blocks) {
-            uint32_t w0 = 0, w1 = 0;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                w0 |= quant_code(v[e], c, 8) << (4 * e);
-                w1 |= quant_code(v[8 + e], c, 8) << (4 * e);
-            }
-            w0 ^= CODE_TO_NIBBLES, w1 ^= CODE_TO_NIBBLES;
-            *reinterpret_cast<uint2 *>(out + ((sc / KT) * M + t) * SEG + lane_out) = make_uint2(w0, w1);
-        }
-    }
-}
-
-
-// ---------------------------------------------------------------------------------- B = 512 .. 4096
-template <int V>
-__device__ inline void butterflies(float (&v)[V])
-{
-#pragma unroll
-    for (int s = V / 2; s >= 1; s >>= 1)
-#pragma unroll
-        for (int j = 0; j < V; ++j)
-            if ((j & s) == 0) {
-                float a = v[j], b = v[j + s];
-                v[j] = a + b;
-                v[j + s] = a - b;
-            }
-}
-
-// value of lane (l ^ MASK), MASK = 1, 2 (DPP quad permutation) or 4 (swizzle within 32 lanes)
-template <int MASK>
-__device__ inline float lane_xor(float x)
-{
-    const int i = __float_as_int(x);
-    if (MASK == 1) return __int_as_float(__builtin_amdgcn_update_dpp(0, i, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
-    if (MASK == 2) return __int_as_float(__builtin_amdgcn_update_dpp(0, i, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
-    return __int_as_float(__builtin_amdgcn_ds_swizzle(i, 0x101F));                                   // and 0x1f, xor 4
-}
-
-// one butterfly stage across lanes: the lower lane of a pair gets a + b, the upper one a - b, where a
-// is the lower lane's value: both are other + (upper ? -own : own), and negation is exact
-template <int MASK, int V>
-__device__ inline void cross_stage(float (&v)[V], int lane)
-{
-    const uint32_t flip = (lane & MASK) ? 0x80000000u : 0u;
-#pragma unroll
-    for (int e = 0; e < V; ++e) v[e] = lane_xor<MASK>(v[e]) + __uint_as_float(__float_as_uint(v[e]) ^ flip);
-}
-
-template <int MODE, int V>
-__global__ __launch_bounds__(256) void quantize_act_hadamard_wide_kernel(const uint16_t *__restrict__ x, int64_t M, int64_t K,
-                                                                         float eps, const float *__restrict__ row_in,
-                                                                         float inv_s_a, float hnorm, uint8_t *__restrict__ out,
-                                                                         float *__restrict__ row_out, int ksplit)
-{
-    constexpr int B = 64 * V;
-    constexpr int WAVE_WORDS = B + 256;          // fp32 patch: 4 pad words after every V elements (64 groups)
-    extern __shared__ __attribute__((aligned(16))) uint8_t wide_lds[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t wid = (int64_t)blockIdx.x * 4 + wave, t = wid / ksplit;     // ksplit waves share a row, block by block
-    const int part = (int)(wid % ksplit);
-    if (t >= M) return;                                  // whole waves leave; nothing below synchronises
-    const uint16_t *row = x + t * K;
-
-    float r = 1.0f;
-    if (MODE == FPTQ_SCALE_RMS) {                        // S_t from the row as the norm layer sees it
-        double ss = 0.0;
-        for (int64_t k0 = (int64_t)lane * 8; k0 < K; k0 += 512) {
-            const uint4 u = *reinterpret_cast<const uint4 *>(row + k0);
-            const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+        for (int r = 0; r < CH; ++r) {
+            const uint32_t w[4] = {regs[r].x, regs[r].y, regs[r].z, regs[r].w};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                double a = (double)h_bf16_to_f32(w[j] & 0xffffu), b = (double)h_bf16_to_f32(w[j] >> 16);
-                ss = __builtin_fma(a, a, ss);
-                ss = __builtin_fma(b, b, ss);
+                v[8 * r + 2 * j] = __uint_as_float(w[j] << 16), v[8 * r + 2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
+                squares = add_squares(squares, w[j]);
             }
         }
-        ss = wave_sum(ss);
-        r = (float)(1.0 / sqrt(ss / (double)K + (double)eps));
-    } else if (MODE == FPTQ_SCALE_GIVEN) {
-        r = row_in[t];
-    }
-    const float c = ((MODE == FPTQ_SCALE_NONE) ? inv_s_a : r * inv_s_a) * hnorm;
-    if (lane == 0 && part == 0 && row_out) row_out[t] = r;
-
-    uint8_t *raw = wide_lds + wave * (WAVE_WORDS * 4);
-    float *patch = reinterpret_cast<float *>(raw);
-
-    for (int64_t sc = (int64_t)part * B; sc < K; sc += (int64_t)ksplit * B) {
-        // linear copy of the block into LDS, 1 KB per wave-level load
+        const bool tame = __builtin_amdgcn_ballot_w64(!(squares < TAME && __builtin_fabsf(c) < TAME)) == 0;
+        const int64_t here = at;
+        at += (int64_t)parts * SPAN;
+        if (MODE == FPTQ_SCALE_RMS && at < K) load(at);
+        if constexpr (R == 3) register_stage<32>(v);
+        if constexpr (R >= 2) register_stage<16>(v);
+        register_stage<8>(v);
+        constexpr int S5 = 8 << (R - 1), S4 = R == 1 ? 8 : S5 / 2;
+        if constexpr (LOGB >= 9) swap_with_lanes<32, S5>(v), register_stage<S5>(v);
+        if constexpr (LOGB >= 10) swap_with_lanes<16, S4>(v), register_stage<S4>(v);
+        lanes_xor8(v, sign(8));
+        lanes_xor7(v, sign(4));
+        lanes_xor2(v, sign(2));
+        lanes_xor1(v, sign(1));
+        register_stage<4>(v);
+        register_stage<2>(v);
+        register_stage<1>(v);
 #pragma unroll
-        for (int i = 0; i < V / 8; ++i)
-            *reinterpret_cast<uint4 *>(raw + (i * 64 + lane) * 16) = *reinterpret_cast<const uint4 *>(row + sc + (i * 64 + lane) * 8);
-        float v[V];
+        for (int r = 0; r < CH; ++r) {
+            uint32_t w;
+            if (tame) {
+                w = quantize_tame(v + 8 * r, c);
+            } else {
+                w = CODE_TO_NIBBLES;
 #pragma unroll
-        for (int j = 0; j < V; ++j) v[j] = h_bf16_to_f32(*reinterpret_cast<const uint16_t *>(raw + (64 * j + lane) * 2));
-        butterflies<V>(v);                                // strides B/2 .. 64
-        // element e = 64 j + lane goes to word e + 4 (e / V); the lane then reads its V contiguous elements
-#pragma unroll
-        for (int j = 0; j < V; ++j) patch[j * (64 + 256 / V) + lane + 4 * (lane / V)] = v[j];
-#pragma unroll
-        for (int i = 0; i < V / 4; ++i) {
-            const float4 f = *reinterpret_cast<const float4 *>(patch + lane * (V + 4) + 4 * i);
-            v[4 * i] = f.x, v[4 * i + 1] = f.y, v[4 * i + 2] = f.z, v[4 * i + 3] = f.w;
+                for (int e = 0; e < 8; ++e) w ^= quant_code(v[8 * r + e], c, 8) << (4 * e);
+            }
+            // K tile of the chunk: the bits that the swaps have left in its number, and in lane bits 5 and 4
+            const int64_t tile = here / KT + tile_l + (LOGB <= 11 ? r : (r & 1) * 4 + (r >> 2) * 2 + (r >> 1 & 1));
+            if (SPAN == B || tile * KT < K) *reinterpret_cast<uint32_t *>(out + (tile * M + t) * SEG + chunk * 4) = w;
         }
-        if (V <= 8) cross_stage<4, V>(v, lane);           // stride 32 at V = 8
-        if (V <= 16) cross_stage<2, V>(v, lane);          // stride 32 at V = 16, stride 16 at V = 8
-        if (V <= 32) cross_stage<1, V>(v, lane);          // stride V
-        butterflies<V>(v);                                // strides V/2 .. 1
-        uint32_t w[V / 8];
-#pragma unroll
-        for (int i = 0; i < V / 8; ++i) {
-            w[i] = 0;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) w[i] |= quant_code(v[8 * i + e], c, 8) << (4 * e);
-            w[i] ^= CODE_TO_NIBBLES;
-        }
-        const int64_t k0 = sc + (int64_t)V * lane;        // V <= 128 values never straddle a K tile
-        uint8_t *dst = out + ((k0 / KT) * M + t) * SEG + (k0 % KT) / 2;
-        if (V == 8) *reinterpret_cast<uint32_t *>(dst) = w[0];
-        if (V == 16) *reinterpret_cast<uint2 *>(dst) = make_uint2(w[0], w[1]);
-        if (V >= 32) {
-#pragma unroll
-            for (int i = 0; i < V / 32; ++i)
-                *reinterpret_cast<uint4 *>(dst + 16 * i) = make_uint4(w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]);
-        }
+        if (MODE != FPTQ_SCALE_RMS || at >= K) return;
     }
 }
 
@@ -247,26 +196,34 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_wide_kernel(const u
 // inside the thread's wave; element e lies in word e + 4 (e / 16) + 2^(LOGB-8) (e / 2^(LOGB-4)), which leaves the second view free of bank conflicts, and
 // the third one's reads for B = 4096.  For B = 2048 threads t and t + 6 of 16 meet there, and in the first view's stores lanes 52 to 63 of a wave meet 0 to 11:
 // 64 conflict cycles a wave counted at 4096 x 14336.
+__device__ inline void butterflies16(float (&v)[16])
+{
+    register_stage<8>(v);
+    register_stage<4>(v);
+    register_stage<2>(v);
+    register_stage<1>(v);
+}
+
 template <int MODE, int LOGB>
-__global__ __launch_bounds__(1 << (LOGB - 4)) void quantize_act_hadamard_group_kernel(const uint16_t *__restrict__ x, int64_t M, int64_t K,
-                                                                                     const float *__restrict__ row_in, float inv_s_a, float hnorm,
-                                                                                     uint8_t *__restrict__ out, float *__restrict__ row_out, int blocks)
+__global__ __launch_bounds__(1 << (LOGB - 4)) void quantize_act_hadamard_group_kernel(const uint16_t *__restrict__ x, const float *__restrict__ row_in,
+                                                                                     uint8_t *__restrict__ out, float *__restrict__ row_out, int M, int64_t K,
+                                                                                     float inv_s_a, uint32_t blocks, uint32_t per_blocks)
 {
     static_assert(LOGB == 11 || LOGB == 12, "views of four bits");
     constexpr int B = 1 << LOGB, THREADS = B / 16, LOW = LOGB - 8;      // LOW bits below the second view's four
     __shared__ __attribute__((aligned(16))) float lds[B + B / 4 + (16 << LOW)];
     auto word = [](int e) { return e + 4 * (e >> 4) + ((e >> (LOGB - 4)) << LOW); };
     const int t = threadIdx.x;
-    const int64_t m = blockIdx.x / blocks;
-    const int blk = (int)(blockIdx.x % blocks);
-    const uint16_t *row = x + m * K, *src = row + (int64_t)blk * B;
+    uint32_t m, blk;
+    divide(blockIdx.x, blocks, per_blocks, m, blk);
+    const uint16_t *row = x + (int64_t)m * K, *src = row + (int64_t)blk * B;
     float v[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) v[j] = h_bf16_to_f32(src[j * THREADS + t]);
 
     float r = 1.0f;
     if (MODE == FPTQ_SCALE_GIVEN) r = row_in[m];
-    const float c = ((MODE == FPTQ_SCALE_NONE) ? inv_s_a : r * inv_s_a) * hnorm;
+    const float c = ((MODE == FPTQ_SCALE_NONE) ? inv_s_a : r * inv_s_a) * hadamard_norm(LOGB);
     if (t == 0 && blk == 0 && row_out) row_out[m] = r;
 
     butterflies16(v);
@@ -288,15 +245,10 @@ __global__ __launch_bounds__(1 << (LOGB - 4)) void quantize_act_hadamard_group_k
         const float4 f = *reinterpret_cast<const float4 *>(lds + word(t * 16) + 4 * i);
         v[4 * i] = f.x, v[4 * i + 1] = f.y, v[4 * i + 2] = f.z, v[4 * i + 3] = f.w;
     }
-#pragma unroll
-    for (int s = LOGB == 12 ? 8 : 4; s >= 1; s >>= 1)
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-            if ((j & s) == 0) {
-                const float a = v[j], b = v[j + s];
-                v[j] = a + b;
-                v[j + s] = a - b;
-            }
+    if constexpr (LOGB == 12) register_stage<8>(v);
+    register_stage<4>(v);
+    register_stage<2>(v);
+    register_stage<1>(v);
     uint32_t w[2] = {0, 0};
 #pragma unroll
     for (int e = 0; e < 16; ++e) w[e / 8] |= quant_code(v[e], c, 8) << (4 * (e % 8));
@@ -308,111 +260,55 @@ template <int LOGB>
 static hipError_t launch_group(const uint16_t *x, int64_t M, int64_t K, int mode, const float *row_in, float inv_s_a, uint8_t *out,
                                float *row_out, hipStream_t s)
 {
-    const int blocks = (int)(K >> LOGB);
-    const float hnorm = (float)(1.0 / sqrt((double)(1 << LOGB)));
-    dim3 grid((unsigned)(M * blocks)), block(1 << (LOGB - 4));
+    const uint32_t blocks = (uint32_t)(K >> LOGB);
+    const dim3 grid((unsigned)(M * blocks)), block(1 << (LOGB - 4));
     if (mode == FPTQ_SCALE_GIVEN)
-        quantize_act_hadamard_group_kernel<FPTQ_SCALE_GIVEN, LOGB><<<grid, block, 0, s>>>(x, M, K, row_in, inv_s_a, hnorm, out, row_out, blocks);
+        quantize_act_hadamard_group_kernel<FPTQ_SCALE_GIVEN, LOGB><<<grid, block, 0, s>>>(x, row_in, out, row_out, (int)M, K, inv_s_a, blocks, reciprocal(blocks));
     else
-        quantize_act_hadamard_group_kernel<FPTQ_SCALE_NONE, LOGB><<<grid, block, 0, s>>>(x, M, K, row_in, inv_s_a, hnorm, out, row_out, blocks);
+        quantize_act_hadamard_group_kernel<FPTQ_SCALE_NONE, LOGB><<<grid, block, 0, s>>>(x, row_in, out, row_out, (int)M, K, inv_s_a, blocks, reciprocal(blocks));
     return hipGetLastError();
 }
 
-// Waves per row: with few rows a wave per row leaves the device idle (one token of 11008 values took 9.5 us, as
-// long as 512 tokens), so the blocks of a row are dealt to as many waves as it takes to have about 4096 in all
-// (16384 was slower again: 2048 x 11008 17.1 us against 13.9).
-// In RMS mode every wave of a row sums the whole row again, which only pays while there are few rows.
-static int waves_per_row(int64_t M, int64_t chunks, int mode)
+// The scale given or none: a wave per span.  RMS: every wave of a row sums the whole row again, which only pays while there are few rows (2048 x 28672
+// in workgroups per block 64 -> 223 us); up to 256 of them are dealt to as many waves as it takes to have about 4096.
+template <int LOGB>
+static hipError_t launch_spans(const uint16_t *x, int64_t M, int64_t K, int mode, float eps, const float *row_in, float inv_s_a, uint8_t *out,
+                               float *row_out, hipStream_t s)
 {
-    if (M >= 4096 || (mode == FPTQ_SCALE_RMS && M > 256)) return 1;
-    const int64_t want = (4096 + M - 1) / M;
-    return (int)(want < chunks ? want : chunks);
-}
-
-constexpr int wide_lds_bytes(int v) { return 4 * (64 * v + 256) * 4; }
-
-template <int MODE, int V>
-static hipError_t set_wide_attribute()
-{
-    if (wide_lds_bytes(V) <= 65536) return hipSuccess;
-    return hipFuncSetAttribute((const void *)quantize_act_hadamard_wide_kernel<MODE, V>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               wide_lds_bytes(V));
-}
-
-// Once per device: more than 64 KB of dynamic LDS has to be asked for before the first launch.
-hipError_t hadamard_device_init(int)
-{
-    hipError_t e = hipSuccess;
-    auto one = [&](hipError_t r) { if (e == hipSuccess) e = r; };
-#define FPTQ_WIDE_ATTR(V) one(set_wide_attribute<FPTQ_SCALE_NONE, V>()), one(set_wide_attribute<FPTQ_SCALE_RMS, V>()), one(set_wide_attribute<FPTQ_SCALE_GIVEN, V>())
-    FPTQ_WIDE_ATTR(8);
-    FPTQ_WIDE_ATTR(16);
-    FPTQ_WIDE_ATTR(32);
-    FPTQ_WIDE_ATTR(64);
-#undef FPTQ_WIDE_ATTR
-    return e;
-}
-
-template <int V>
-static hipError_t launch_wide(const uint16_t *x, int64_t M, int64_t K, int mode, float eps, const float *row_in, float inv_s_a,
-                              uint8_t *out, float *row_out, hipStream_t s)
-{
-    const int ksplit = waves_per_row(M, (K + 64 * V - 1) / (64 * V), mode);
-    const int64_t blocks = (M * ksplit + 3) / 4;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    constexpr int LDS_BYTES = wide_lds_bytes(V);
-    const DeviceInfo *info;
-    hipError_t e0 = device_info(&info);       // the kernels that need more than 64 KB of dynamic LDS got their limit there
-    if (e0 != hipSuccess) return e0;
-    const float hnorm = (float)(1.0 / sqrt((double)(64 * V)));
-    dim3 grid((unsigned)blocks), block(256);
-#define FPTQ_LAUNCH_WIDE(MODE)                                                                                             \
-    do {                                                                                                                   \
-        auto kern = quantize_act_hadamard_wide_kernel<MODE, V>;                                                            \
-        kern<<<grid, block, LDS_BYTES, s>>>(x, M, K, eps, row_in, inv_s_a, hnorm, out, row_out, ksplit);                   \
-    } while (0)
-    switch (mode) {
-    case FPTQ_SCALE_NONE: FPTQ_LAUNCH_WIDE(FPTQ_SCALE_NONE); break;
-    case FPTQ_SCALE_RMS: FPTQ_LAUNCH_WIDE(FPTQ_SCALE_RMS); break;
-    default: FPTQ_LAUNCH_WIDE(FPTQ_SCALE_GIVEN);
-    }
-#undef FPTQ_LAUNCH_WIDE
+    constexpr int64_t SPAN = LOGB <= 10 ? 1024 : 1 << LOGB;
+    int64_t parts = (K + SPAN - 1) / SPAN;
+    if (mode == FPTQ_SCALE_RMS) parts = M > 256 ? 1 : parts < (4096 + M - 1) / M ? parts : (4096 + M - 1) / M;
+    if (M > 0x7fffffff || M * parts > 0xffffffff) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((M * parts + 3) / 4)), block(256);
+#define FPTQ_LAUNCH_SPANS(MODE, STREAM) \
+    quantize_act_hadamard_kernel<MODE, LOGB, STREAM><<<grid, block, 0, s>>>(x, row_in, out, row_out, (int)M, K, inv_s_a, (uint32_t)parts, reciprocal((uint32_t)parts), eps)
+    const bool stream = M * K * 2 > ((int64_t)256 << 20);
+    if (mode == FPTQ_SCALE_RMS) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_RMS, false);      // reads the row twice
+    else if (mode == FPTQ_SCALE_GIVEN && stream) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_GIVEN, true);
+    else if (mode == FPTQ_SCALE_GIVEN) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_GIVEN, false);
+    else if (stream) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_NONE, true);
+    else FPTQ_LAUNCH_SPANS(FPTQ_SCALE_NONE, false);
+#undef FPTQ_LAUNCH_SPANS
     return hipGetLastError();
 }
 
 hipError_t launch_quantize_act_hadamard(const uint16_t *x, int64_t M, int64_t K, int hadamard_block, int mode, float eps,
                                         const float *row_in, float inv_s_a, uint8_t *out, float *row_out, hipStream_t s)
 {
-    // A workgroup per block, unless its scale would have to be summed in every wave of every block, over the whole row (RMS mode: 1 x 14336
-    // 8.5 -> 7.4 us, but 16 x 14336 10.6 -> 11.5, 2048 x 28672 64 -> 223)
-    // and up to 32768 blocks (4096 x 14336 35.4 -> 34.3, 2048 x 28672 42.0 -> 36.2, 4096 x 8192 25.2 -> 21.5; 8192 x 14336 66.6, 67.4)
-    if (hadamard_block >= 2048 && mode != FPTQ_SCALE_RMS && M <= 32768 && M * (K / hadamard_block) <= 32768)
-        return hadamard_block == 2048 ? launch_group<11>(x, M, K, mode, row_in, inv_s_a, out, row_out, s)
-                                      : launch_group<12>(x, M, K, mode, row_in, inv_s_a, out, row_out, s);
+    // Up to 32768 large blocks: a workgroup per block, which is done sooner with one and keeps more of a row's loads in flight (graph of calls, us, a wave
+    // per block behind it; in brackets inputs from the cache: 1 x 14336 2.6, 2.95; 512 x 14336 6.7, 7.4; 4096 x 14336 33.0, 32.9 (27.7, 28.8); 1 x 28672 2.8, 4.3;
+    // 1024 x 28672 17.6, 19.7 (16.0, 18.1); 2048 x 28672 34.0, 34.7 (28.5, 31.3); beyond: 8192 x 14336 66, 63)
+    const bool few = mode != FPTQ_SCALE_RMS && M <= 32768 && M * (K / hadamard_block) <= 32768;
+    if (few && hadamard_block == 2048) return launch_group<11>(x, M, K, mode, row_in, inv_s_a, out, row_out, s);
+    if (few && hadamard_block == 4096) return launch_group<12>(x, M, K, mode, row_in, inv_s_a, out, row_out, s);
     switch (hadamard_block) {
-    case 512: return launch_wide<8>(x, M, K, mode, eps, row_in, inv_s_a, out, row_out, s);
-    case 1024: return launch_wide<16>(x, M, K, mode, eps, row_in, inv_s_a, out, row_out, s);
-    case 2048: return launch_wide<32>(x, M, K, mode, eps, row_in, inv_s_a, out, row_out, s);
-    case 4096: return launch_wide<64>(x, M, K, mode, eps, row_in, inv_s_a, out, row_out, s);
-    case 256: break;
+    case 256: return launch_spans<8>(x, M, K, mode, eps, row_in, inv_s_a, out, row_out, s);
+    case 512: return launch_spans<9>(x, M, K, mode, eps, row_in, inv_s_a, out, row_out, s);
+    case 1024: return launch_spans<10>(x, M, K, mode, eps, row_in, inv_s_a, out, row_out, s);
+    case 2048: return launch_spans<11>(x, M, K, mode, eps, row_in, inv_s_a, out, row_out, s);
+    case 4096: return launch_spans<12>(x, M, K, mode, eps, row_in, inv_s_a, out, row_out, s);
     default: return hipErrorInvalidValue;
     }
-    const int ksplit = waves_per_row(M, (K + 4 * HB - 1) / (4 * HB), mode);
-    const int64_t blocks = (M * ksplit + 3) / 4;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    const float hnorm = 1.0f / 16.0f;       // 1 / sqrt(256)
-    dim3 grid((unsigned)blocks), block(256);
-    switch (mode) {
-    case FPTQ_SCALE_NONE:
-        quantize_act_hadamard_kernel<FPTQ_SCALE_NONE><<<grid, block, 0, s>>>(x, M, K, eps, row_in, inv_s_a, hnorm, out, row_out, ksplit);
-        break;
-    case FPTQ_SCALE_RMS:
-        quantize_act_hadamard_kernel<FPTQ_SCALE_RMS><<<grid, block, 0, s>>>(x, M, K, eps, row_in, inv_s_a, hnorm, out, row_out, ksplit);
-        break;
-    default:
-        quantize_act_hadamard_kernel<FPTQ_SCALE_GIVEN><<<grid, block, 0, s>>>(x, M, K, eps, row_in, inv_s_a, hnorm, out, row_out, ksplit);
-    }
-    return hipGetLastError();
 }
 
 }  // namespace fptq

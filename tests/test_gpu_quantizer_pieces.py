@@ -1,0 +1,48 @@
+"""The quantizers that cut a row into pieces of a wave each (scale given or none, and the Hadamard quantizers): edges of the pieces, the classes of
+the dispatch, and inputs whose products are no numbers."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2506_04985_amd import binding as fptq
+import fptq_workloads as synth
+
+from gpu_util import dev, dev_bf16
+
+pytestmark = pytest.mark.gpu
+MODES = [synth.MODE_NONE, synth.MODE_GIVEN]
+
+
+def draw(M, K, mode, seed):
+    return synth.draw(synth.LinearCase("p", f"m{M}k{K}", M, 8, K, "normal", 0.0, 3, 20.0, mode, seed), with_weights=False)
+
+
+def with_specials(bits, every):
+    """NaNs, infinities, values near the largest and the smallest, zeros of both signs, all over."""
+    v = torch.tensor([float("nan"), float("inf"), -float("inf"), 3e38, -3e38, 1e-40, -0.0, 1e30]).to(torch.bfloat16).view(torch.int16).numpy().view(np.uint16)
+    b = bits.copy().reshape(-1)
+    at = np.arange(every // 2, b.size, every)
+    b[at] = v[np.arange(at.size) % 8]
+    return b.reshape(bits.shape)
+
+
+@pytest.mark.parametrize("mode", [synth.MODE_NONE, synth.MODE_RMS, synth.MODE_GIVEN])
+@pytest.mark.parametrize("M,K,B", [(3, 256, 256), (5, 768, 256), (6, 1280, 256), (2, 512, 512), (5, 1536, 512), (7, 3072, 1024), (300, 2560, 512),
+                                   (4100, 16384, 2048), (4100, 32768, 4096)])
+def test_hadamard_special_values(oracle, mode, M, K, B):
+    """What the transform spreads over a block is the same tree of additions, so NaNs and infinities come out where the definition has them."""
+    if M > 4096 and mode == synth.MODE_RMS:
+        pytest.skip("the launch of (300, 2560, 512): rows are not cut")
+    inp = draw(min(M, 400), K, mode, seed=M + K + B)
+    bits = with_specials(inp.x_bits, 5 * B + 3)
+    rep = -(-M // bits.shape[0])
+    full = np.tile(bits, (rep, 1))[:M]
+    scale = None if inp.row_scale_in is None else np.tile(inp.row_scale_in, rep)[:M]
+    xq, r = fptq.fptq_quantize_act_hadamard(dev_bf16(full), 0.5, B, mode, 1e-5, dev(scale))
+    q = fptq.fptq_unpack(xq, M, K)
+    rows = np.arange(0, bits.shape[0], max(1, bits.shape[0] // 40))
+    r_ref = oracle.row_scale(bits[rows], mode, 1e-5, None if scale is None else scale[rows])
+    ref = oracle.quantize_hadamard(bits[rows], np.float32(0.5), B, None if mode == synth.MODE_NONE else r_ref)
+    assert np.array_equal(q[torch.from_numpy(rows).cuda()].cpu().numpy(), ref)
+    if M > bits.shape[0]:
+        assert torch.equal(q[:bits.shape[0]], q[bits.shape[0]:2 * bits.shape[0]])
