@@ -4,7 +4,8 @@
 // The row is read once from HBM and kept in registers while the sum of squares is reduced, then
 // quantized from the registers.  Bandwidth-bound: 2 bytes read and half a byte written per
 // element.  Short rows in large numbers are handled by one wave each (no LDS, no barrier, the scale is
-// computed once per row, and many rows are in flight per CU); longer rows, or few, by one workgroup each.
+// computed once per row, and many rows are in flight per CU); longer rows, or few, by one workgroup each.  Where the scale is given there
+// is nothing to reduce and a wave takes a piece of a row.
 #include <type_traits>
 
 #include "fptq_common.h"
@@ -356,6 +357,60 @@ hipError_t launch_quantize_act_dynamic(const uint16_t *x, int64_t M, int64_t K, 
     return hipGetLastError();
 }
 
+// Scale given or none, aligned rows: a wave takes 512 CH consecutive values, consecutive waves consecutive pieces, and no wave waits for another.
+// Bound by memory (us, a workgroup or wave per row before / now; inputs from HBM, in brackets from the last-level cache): 4096 x 14336 33.1 / 29.0 (24.1 /
+// 24.0), 4096 x 11008 26.4 / 23.1 (18.7 / 18.2), 8192 x 8192 37.9 / 34.2 (25.9 / 26.9), 4096 x 4096 10.4 / 9.7 (7.6 / 7.1), 8192 x 28672 117.1 / 104.4; 64 x 13824
+// 3.20 / 2.49, 1 x 13824 2.63 / 2.23, 1 x 4096 2.11 / 2.10.
+template <int MODE, int CH, bool STREAM>
+__global__ __launch_bounds__(QT) void quantize_act_flat_kernel(const uint16_t *__restrict__ x, uint8_t *__restrict__ out, float *__restrict__ row_out,
+                                                               const float *__restrict__ row_in, int M, int K, float inv_s_a, int zoff, uint32_t pieces,
+                                                               uint32_t per_pieces)
+{
+    static_assert(MODE != FPTQ_SCALE_RMS, "that scale takes the whole row");
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t t, piece;
+    divide(blockIdx.x * (QT / 64) + wave, pieces, per_pieces, t, piece);
+    if (t >= (uint32_t)M) return;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)(x + (int64_t)t * K), 0, K * 2, RSRC_FLAGS);
+    const int k0 = (int)piece * (512 * CH) + lane * QCHUNK;
+    q_v4u regs[CH];
+#pragma unroll
+    for (int i = 0; i < CH; ++i) regs[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (k0 + i * 512) * 2, 0, STREAM ? Q_STREAM : 0);
+    const float r = MODE == FPTQ_SCALE_GIVEN ? row_in[t] : 1.0f;
+    const float c = MODE == FPTQ_SCALE_NONE ? inv_s_a : r * inv_s_a;
+    if (lane == 0 && piece == 0 && row_out) row_out[t] = r;
+    // chunk i of lane l is values k0 + 512 i ..: K tile 4 (CH piece + i) + l / 16, byte 4 (l % 16) of the row's segment
+    uint8_t *orow = out + (((int64_t)(piece * (4 * CH) + (lane >> 4)) * M + t) * SEG + (lane & 15) * 4);
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+        const int k = k0 + i * 512;
+        const uint32_t w[4] = {regs[i].x, regs[i].y, regs[i].z, regs[i].w};
+        const uint32_t word = quant_chunk(w, c, zoff);
+        if (k < (K + KT - 1) / KT * KT) *reinterpret_cast<uint32_t *>(orow + (int64_t)(4 * i) * M * SEG) = k >= K ? 0u : word;      // K padding stays zero
+    }
+}
+
+// More than the last-level cache holds: streaming loads, four chunks a lane (8192 x 28672: 104 us, one chunk 110, without streaming 113 to 124).  16 to
+// 40 MB: four chunks (4096 x 4096 9.7 us, one 10.2, from the cache 7.1 and 8.5; 1000 x 13824 9.0 and 9.1, 6.2 and 6.8).  Otherwise one (768 x
+// 4096 3.1 us, four 3.8; 2048 x 11008 12.9 and 13.8; 4096 x 14336 29.0 and 30.1).
+template <int MODE>
+static hipError_t launch_flat(const uint16_t *x, int64_t M, int64_t K, const float *row_in, float inv_s_a, int zoff, uint8_t *out, float *row_out, hipStream_t s)
+{
+    const int64_t mb = M * K * 2 >> 20;
+    const bool stream = M * K * 2 > ((int64_t)256 << 20);
+    const int ch = stream || (mb >= 16 && mb < 40) ? 4 : 1;
+    const int64_t pieces = (K + 512 * ch - 1) / (512 * ch);
+    if (M * pieces > 0xffffffff) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((M * pieces + QT / 64 - 1) / (QT / 64))), block(QT);
+#define FPTQ_FLAT(CH, STREAM) quantize_act_flat_kernel<MODE, CH, STREAM><<<grid, block, 0, s>>>(x, out, row_out, row_in, (int)M, (int)K, inv_s_a, zoff, (uint32_t)pieces, reciprocal((uint32_t)pieces))
+    if (stream) FPTQ_FLAT(4, true);
+    else if (ch == 4) FPTQ_FLAT(4, false);
+    else FPTQ_FLAT(1, false);
+#undef FPTQ_FLAT
+    return hipGetLastError();
+}
+
 template <int MODE>
 static hipError_t launch_mode(const uint16_t *x, int64_t M, int64_t K, float eps, const float *row_in, float inv_s_a,
                               int zoff, uint8_t *out, float *row_out, hipStream_t s)
@@ -363,45 +418,51 @@ static hipError_t launch_mode(const uint16_t *x, int64_t M, int64_t K, float eps
     dim3 grid((unsigned)M), block(QT);
     const bool vec = K % QCHUNK == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
     const int64_t Kpad = k_tiles(K) * KT;
-    // An input that the 256 MB last-level cache cannot hold is read with streaming loads (8192 x 28672: 119 us
-    // against 142); a smaller one is usually still there from its producer, and ordinary loads are faster on it.
-    const int stream_in = M * K * 2 > ((int64_t)256 << 20) ? STREAM_IN : 0;
-    // A workgroup per row, which spreads a row over four waves (32 x 11008: 2.9 us against 5.6; 2048 x 11008: 10.8 against 12.9), but for
-    // short rows in large numbers (2048 x 4096 the other way, 6.0 against 5.3).
-    if (wave_per_row(vec, M, K)) {
-        dim3 wgrid((unsigned)((M + QT / 64 - 1) / (QT / 64)));
+    dim3 wgrid((unsigned)((M + QT / 64 - 1) / (QT / 64)));
 #define FPTQ_WAVE_CASE(CH, RAGGED) quantize_act_wave_kernel<MODE, CH, RAGGED><<<wgrid, block, 0, s>>>(x, out, row_out, row_in, M, (int)K, inv_s_a, zoff | stream_in, eps)
-        WAVE_PER_ROW(vec, Kpad, FPTQ_WAVE_CASE);
-#undef FPTQ_WAVE_CASE
-        return hipGetLastError();
-    }
-#define FPTQ_ROW_CASE(CH)                                                                                                   \
-    if (vec && Kpad <= 2048 * CH) {                                                                                         \
-        quantize_act_kernel<MODE, CH, false><<<grid, block, 0, s>>>(x, out, row_out, row_in, M, (int)K, inv_s_a, zoff | stream_in, eps); \
-        return hipGetLastError();                                                                                           \
-    }
-    // chunks per thread: 6 covers the Llama-2 FFN width 11008, 7 and 14 are the Llama-3 FFN widths 14336 and 28672
-    FPTQ_ROW_CASE(1)
-    FPTQ_ROW_CASE(2)
-    FPTQ_ROW_CASE(4)
-    FPTQ_ROW_CASE(6)
-    FPTQ_ROW_CASE(7)
-    FPTQ_ROW_CASE(8)
-    FPTQ_ROW_CASE(12)
-    FPTQ_ROW_CASE(14)
-    FPTQ_ROW_CASE(16)
-#undef FPTQ_ROW_CASE
-#define FPTQ_RAGGED_CASE(CH)                                                                                                \
+#define FPTQ_ROW_CASE(CH, RAGGED)                                                                                           \
     if (Kpad <= 2048 * CH) {                                                                                                \
-        quantize_act_kernel<MODE, CH, true><<<grid, block, 0, s>>>(x, out, row_out, row_in, M, (int)K, inv_s_a, zoff, eps);   \
+        quantize_act_kernel<MODE, CH, RAGGED><<<grid, block, 0, s>>>(x, out, row_out, row_in, M, (int)K, inv_s_a, zoff | stream_in, eps); \
         return hipGetLastError();                                                                                           \
     }
-    FPTQ_RAGGED_CASE(1)
-    FPTQ_RAGGED_CASE(2)
-    FPTQ_RAGGED_CASE(4)
-    FPTQ_RAGGED_CASE(8)
-    FPTQ_RAGGED_CASE(16)
-#undef FPTQ_RAGGED_CASE
+    if constexpr (MODE != FPTQ_SCALE_RMS) {
+        if (vec && K <= (1 << 28)) return launch_flat<MODE>(x, M, K, row_in, inv_s_a, zoff, out, row_out, s);
+    } else if (vec) {
+        // An input that the 256 MB last-level cache cannot hold is read with streaming loads (8192 x 28672: 119 us
+        // against 142); a smaller one is usually still there from its producer, and ordinary loads are faster on it.
+        const int stream_in = M * K * 2 > ((int64_t)256 << 20) ? STREAM_IN : 0;
+        // A workgroup per row, which spreads a row over four waves (32 x 11008: 2.9 us against 5.6; 2048 x 11008: 10.8 against 12.9), but for
+        // short rows in large numbers (2048 x 4096 the other way, 6.0 against 5.3).
+        if (wave_per_row(true, M, K)) {
+            if (Kpad <= 2048) FPTQ_WAVE_CASE(4, false);
+            else FPTQ_WAVE_CASE(8, false);
+            return hipGetLastError();
+        }
+        // chunks per thread: 6 covers the Llama-2 FFN width 11008, 7 and 14 are the Llama-3 FFN widths 14336 and 28672
+        FPTQ_ROW_CASE(1, false)
+        FPTQ_ROW_CASE(2, false)
+        FPTQ_ROW_CASE(4, false)
+        FPTQ_ROW_CASE(6, false)
+        FPTQ_ROW_CASE(7, false)
+        FPTQ_ROW_CASE(8, false)
+        FPTQ_ROW_CASE(12, false)
+        FPTQ_ROW_CASE(14, false)
+        FPTQ_ROW_CASE(16, false)
+    }
+    constexpr int stream_in = 0;
+    if (!vec) {
+        if (wave_per_row(false, M, K)) {
+            WAVE_PER_ROW_RAGGED(Kpad, FPTQ_WAVE_CASE);
+            return hipGetLastError();
+        }
+        FPTQ_ROW_CASE(1, true)
+        FPTQ_ROW_CASE(2, true)
+        FPTQ_ROW_CASE(4, true)
+        FPTQ_ROW_CASE(8, true)
+        FPTQ_ROW_CASE(16, true)
+    }
+#undef FPTQ_WAVE_CASE
+#undef FPTQ_ROW_CASE
     quantize_act_kernel<MODE, 0, false><<<grid, block, 0, s>>>(x, out, row_out, row_in, M, K, inv_s_a, zoff, eps);
     return hipGetLastError();
 }

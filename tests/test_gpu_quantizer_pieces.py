@@ -26,6 +26,35 @@ def with_specials(bits, every):
     return b.reshape(bits.shape)
 
 
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("M,K", [(1, 8), (3, 504), (3, 512), (5, 520), (2, 2040), (2, 2048), (3, 2056), (700, 72), (257, 1024),
+                                 (1024, 8192), (1030, 8200), (2047, 9992),          # 16 to 40 MB: four chunks a lane, and above
+                                 (2, 32768), (3, 40000)])
+def test_static_quantizer_in_pieces(oracle, mode, M, K):
+    inp = draw(M, K, mode, seed=M + K)
+    for bits in (inp.x_bits, with_specials(inp.x_bits, 97)):
+        xq, r = fptq.fptq_quantize_act(dev_bf16(bits), 0.4, mode, 0.0, dev(inp.row_scale_in))
+        rows = np.unique(np.r_[0, M - 1, np.linspace(0, M - 1, 40).astype(int)])
+        r_ref = oracle.row_scale(bits, mode, 0.0, inp.row_scale_in)
+        assert np.array_equal(r.cpu().numpy().view(np.uint32), r_ref.view(np.uint32))
+        q = fptq.fptq_unpack(xq, M, K).cpu().numpy()
+        assert np.array_equal(q[rows], oracle.quantize(bits[rows], np.float32(0.4), r_ref[rows]))
+
+
+@pytest.mark.parametrize("mode", MODES)
+def test_static_quantizer_beyond_the_last_level_cache(mode):
+    """More than 256 MB: streamed.  Codes of the whole call and of its parts."""
+    M, K = 8200, 16392
+    torch.manual_seed(3)
+    x = torch.randn((M, K), device="cuda").to(torch.bfloat16)
+    r = torch.rand(M, device="cuda") + 0.5 if mode == synth.MODE_GIVEN else None
+    q = fptq.fptq_unpack(fptq.fptq_quantize_act(x, 0.4, mode, 0.0, r)[0], M, K)
+    for i in (0, 4096, M - 100):
+        part = slice(i, i + 100)
+        p = fptq.fptq_unpack(fptq.fptq_quantize_act(x[part], 0.4, mode, 0.0, None if r is None else r[part].clone())[0], 100, K)
+        assert torch.equal(p, q[part])
+
+
 @pytest.mark.parametrize("mode", [synth.MODE_NONE, synth.MODE_RMS, synth.MODE_GIVEN])
 @pytest.mark.parametrize("M,K,B", [(3, 256, 256), (5, 768, 256), (6, 1280, 256), (2, 512, 512), (5, 1536, 512), (7, 3072, 1024), (300, 2560, 512),
                                    (4100, 16384, 2048), (4100, 32768, 4096)])
