@@ -320,7 +320,7 @@ hipError_t launch_quantize_act_dynamic(const uint16_t *x, int64_t M, int64_t K, 
     dim3 grid((unsigned)blocks), block(QT);
     const bool vec = K % QCHUNK == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
     const int64_t Kpad = k_tiles(K) * KT;
-    if (wave_per_row(vec, M, K)) {
+    if (wave_per_row(vec, M, K, 3072)) {
 #define FPTQ_WAVE_CASE(CH, RAGGED) quantize_act_dynamic_kernel<CH, RAGGED><<<grid, block, 0, s>>>(x, M, K, out, s_out)
         WAVE_PER_ROW(vec, Kpad, FPTQ_WAVE_CASE);
 #undef FPTQ_WAVE_CASE

@@ -135,9 +135,9 @@ hipError_t launch_residual_norm_quantize(const uint16_t *xr, const uint16_t *yb,
     dim3 grid((unsigned)blocks), rows((unsigned)M), block(256);
     const bool vec = K % 8 == 0 && ((reinterpret_cast<uintptr_t>(xr) | reinterpret_cast<uintptr_t>(yb) |
                                      reinterpret_cast<uintptr_t>(x_next)) & 15) == 0;
-    // As for the plain quantizer: a wave per row for many short rows (2048 x 4096: 10.2 us), otherwise a workgroup per
+    // As for the plain quantizer: a wave per row for many short rows, otherwise a workgroup per
     // row, which spreads a row over four waves (32 x 4096: 4.3 us with a wave per row).
-    if (wave_per_row(vec, M, K)) {
+    if (wave_per_row(vec, M, K, 3072)) {
 #define FPTQ_WAVE_CASE(CH, RAGGED) residual_norm_quantize_kernel<CH, 1, RAGGED><<<grid, block, 0, s>>>(xr, yb, M, K, s_prev, eps, inv_s_a, x_next, s_next, out)
         WAVE_PER_ROW(vec, K, FPTQ_WAVE_CASE);
 #undef FPTQ_WAVE_CASE
