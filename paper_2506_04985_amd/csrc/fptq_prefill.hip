@@ -53,12 +53,18 @@ __device__ inline uint32_t masked_xor(uint32_t a, uint32_t m, uint32_t t) { retu
 // bits from it, and reaches the fields in between by a shift of two; field 5 straddles two dwords, and its upper half comes
 // out of the funnel shift that moves the other dword.  FLIP inverts every nibble's top bit: two's complement to value + 8.
 template <bool FLIP>
-__device__ inline void spread6(uint32_t a, uint32_t b, uint32_t (&o)[3])
+__device__ inline uint32_t spread6_part(uint32_t a, uint32_t b, int part)
 {
     const uint32_t a2 = a << 2, b2 = __builtin_amdgcn_alignbit(b, a, 30);      // b2: b << 2, a's top two bits below
-    o[0] = masked_xor(a2, 0xC03C03C0u, masked_xor(a, 0x0F00F00Fu, FLIP ? 0x08208208u : 0u));
-    o[1] = masked_xor(b2, 0x00000003u, masked_xor(a2, 0x03C03C00u, masked_xor(b, 0xF00F00F0u, FLIP ? 0x82082082u : 0u)));
-    o[2] = masked_xor(b2, 0x3C03C03Cu, masked_xor(b, 0x00F00F00u, FLIP ? 0x20820820u : 0u));
+    if (part == 0) return masked_xor(a2, 0xC03C03C0u, masked_xor(a, 0x0F00F00Fu, FLIP ? 0x08208208u : 0u));
+    if (part == 1) return masked_xor(b2, 0x00000003u, masked_xor(a2, 0x03C03C00u, masked_xor(b, 0xF00F00F0u, FLIP ? 0x82082082u : 0u)));
+    return masked_xor(b2, 0x3C03C03Cu, masked_xor(b, 0x00F00F00u, FLIP ? 0x20820820u : 0u));
+}
+template <bool FLIP>
+__device__ inline void spread6(uint32_t a, uint32_t b, uint32_t (&o)[3])
+{
+#pragma unroll
+    for (int p = 0; p < 3; ++p) o[p] = spread6_part<FLIP>(a, b, p);
 }
 
 // eight two's complement nibbles as magnitudes and sign bits
@@ -225,23 +231,17 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     };
     lds_u8 *const w_base = (lds_u8 *)lds + C::X_LDS + wave * C::W_BYTES + fi * SEG;
     const int w_slot0 = ((2 * fg) ^ ((fi >> 2) & 3)) << 4;
-    auto read_w = [&](int stage_off, v4i (&r)[2][C::TN]) {
-#pragma unroll
-        for (int t = 0; t < C::TN; ++t) {
-            lds_u8 *const p = w_base + stage_off + t * (32 * SEG);
-            r[0][t] = *(lds_v4i *)(p + w_slot0);
-            r[1][t] = *(lds_v4i *)(p + (w_slot0 ^ 16));
-        }
-    };
+    auto read_w1 = [&](int stage_off, v4i (&r)[2][C::TN], int i) { r[i % 2][i / 2] = *(lds_v4i *)(w_base + stage_off + i / 2 * (32 * SEG) + (w_slot0 ^ (i % 2 * 16))); };
+    auto read_w = [&](int stage_off, v4i (&r)[2][C::TN]) { read_w1(stage_off, r, 0), read_w1(stage_off, r, 1), read_w1(stage_off, r, 2), read_w1(stage_off, r, 3); };
     // ---- fragments: the 48 bytes of token 32 x + fi, half fg; the first 24 feed MFMA step 0, the others step 1
     lds_u8 *const x_base = (lds_u8 *)lds + fg * (3 * X6_PLANE) + fi * 16;
     v12i X[C::TM];
-    auto read_x = [&](int stage_off, int x) {
-        lds_u8 *const p = x_base + stage_off + x * X6_BLOCK;
-        const v4i a = *(lds_v4i *)p, b = *(lds_v4i *)(p + X6_PLANE), c = *(lds_v4i *)(p + 2 * X6_PLANE);
-        const v8i ab = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7), cc = __builtin_shufflevector(c, c, 0, 1, 2, 3, -1, -1, -1, -1);
-        X[x] = __builtin_shufflevector(ab, cc, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11);
+    auto read_piece = [&](int stage_off, int x, int p) {       // 16 of the 48 bytes
+        const v4i a = *(lds_v4i *)(x_base + stage_off + x * X6_BLOCK + p * X6_PLANE);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) X[x][4 * p + e] = a[e];
     };
+    auto read_x = [&](int stage_off, int x) { read_piece(stage_off, x, 0), read_piece(stage_off, x, 1), read_piece(stage_off, x, 2); };
 
     // ---- the accumulators' start: partial sums of the widening kernel's workgroups, all fetched at once (missing ones read as
     // zero) and ahead of everything else, so that they cost no round trip of their own
@@ -308,87 +308,84 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(C::W_LDS ? C::LOADS * (C::STAGES - 3) : C::FILLS * (C::STAGES - 2)));
     __builtin_amdgcn_s_barrier();
     v8i W[2][2][C::TN];                            // widened weights of this K tile and of the next one: [tile][step][t]
-    auto widen_half = [&](const v4i (&r)[2][C::TN], v8i (&w)[2][C::TN], int h) {   // 16 of the 128 values a lane widens per K tile
+    // A lane widens 128 values per K tile, 16 at a time (h: step h / 4, t = h / 2 % 2), one of the three dwords of fields at a time.
+    auto widen_third = [&](const v4i (&r)[2][C::TN], v8i (&w)[2][C::TN], int h, int part) {
         const int s = h / 4, t = (h / 2) % 2, o = h % 2;
-        uint32_t f[3];
-        spread6<true>((uint32_t)r[s][t][2 * o], (uint32_t)r[s][t][2 * o + 1], f);
-#pragma unroll
-        for (int e = 0; e < 3; ++e) w[s][t][3 * o + e] = (int)f[e];
+        w[s][t][3 * o + part] = (int)spread6_part<true>((uint32_t)r[s][t][2 * o], (uint32_t)r[s][t][2 * o + 1], part);
     };
 #pragma unroll
     for (int x = 0; x < C::TM - 1; ++x) read_x(0, x);
     if constexpr (C::W_LDS) read_w(0, raw[0]), read_w(C::STAGE_BYTES, raw[1]);
 #pragma unroll
-    for (int h = 0; h < 8; ++h) widen_half(raw[0], W[0], h);
+    for (int i = 0; i < 24; ++i) widen_third(raw[0], W[0], i / 3, i % 3);
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- K loop.  A K tile is TM groups of four MFMAs, group x on the tokens 32 x ..: two steps of 64 values times two runs of 32
-    // channels.  Beside group x run: 1 / TM of the next K tile's weights being widened (9 VALU per eighth), the fragment reads of
-    // the tokens that are done (three; X[x - 1] of the next K tile, in group 0 the last X of this one, whose old value the
-    // previous tile's last group still used), and one or two of the loads of later tiles.
-    int off = 0;                                   // ring position of tile kt, in bytes
+    // channels.  Behind every MFMA goes what one wave can issue while it runs, fenced, because the compiler keeps to the order of the source where registers
+    // are scarce: a fragment read (three a group: X[x - 1] of the next K tile, in group 0 the last X of this one, whose old value the
+    // previous tile's last group still used), a share of the next K tile's weights being widened (9 VALU per 16 values), a load of a later tile.  Four MFMAs
+    // followed by all of that, as most groups of the large tiles were, took 1255 clocks a K tile of 256 tokens and 1056 of 192 (1024 and 768 of MFMAs), now
+    // 1236 and 957; the clock gives most of it back (1.52 instead of 1.64 GHz at 192 tokens).  The loads of a run of rows go in pairs, so that two loads
+    // that touch the same lines (and a wave's copies of one page) meet: 500 x 21000 x 8192 55.1 us apart, 53.5 in pairs, 589 x 7391 x 17552 76.8 and 75.5; all
+    // four at once, or all fills at once, is 1 to 5 % slower again.  Together 8192 x 57344 x 8192 1627 -> 1606, 8192 x 8192 x 28672 799 -> 788, 500 x 21000 x
+    // 8192 55.4 -> 53.5, 2048 x 4096 x 11008 56.0 -> 55.6.
+    int off = 0, off_next = C::STAGE_BYTES, off_prev = C::RING_BYTES - C::STAGE_BYTES;      // ring positions of tiles kt, kt + 1, kt - 1, in bytes
+    __amdgpu_buffer_rsrc_t wr = slab_desc(wp, w_slab, w_left > 0), xr = slab_desc(xp, x_end, x_left > 0);
     __builtin_amdgcn_s_setprio(2);
     auto tile = [&](auto pc) {
         constexpr int P = decltype(pc)::value;     // position in the unrolled loop: P % 2 names the W set, P % DEPTH the raw set
-        const int off_next = off + C::STAGE_BYTES == C::RING_BYTES ? 0 : off + C::STAGE_BYTES;
-        const int off_prev = off == 0 ? C::RING_BYTES - C::STAGE_BYTES : off - C::STAGE_BYTES;
-        // this wave's part of tile kt + 1 has landed (younger: whole iterations of loads); the barrier extends that to every
-        // wave's part, and says every wave has read all of tile kt - 1
-        __builtin_amdgcn_s_waitcnt(waitcnt_vm(C::LOADS * (C::STAGES - 3)));
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        const __amdgpu_buffer_rsrc_t wr = slab_desc(wp, w_slab, w_left > 0), xr = slab_desc(xp, x_end, x_left > 0);
-        uint8_t *const fill_to = fill_base + off_prev, *const w_fill_to = w_fill_base + off_prev;
-        const int off_next2 = off_next + C::STAGE_BYTES == C::RING_BYTES ? 0 : off_next + C::STAGE_BYTES;
         v4i(&load_to)[2][C::TN] = raw[P % RAWS];           // tile kt's, widened during the previous tile
         const v4i(&next)[2][C::TN] = raw[(P + 1) % RAWS];
+        uint8_t *const fill_to = fill_base + off_prev, *const w_fill_to = w_fill_base + off_prev;
 #pragma unroll
         for (int x = 0; x < C::TM; ++x) {
-            // this wave's weights of tile kt + 2 are in (its own copies: no barrier); younger: an iteration's loads and this one's so far
-            if (C::W_LDS && x == C::TM - 1) {
-                __builtin_amdgcn_s_waitcnt(waitcnt_vm(C::LOADS * (C::STAGES - 4) + C::BEFORE_LAST));
-                __builtin_amdgcn_sched_barrier(0);
-            }
             asm("" : "+v"(X[x]));           // keeps the 48 bytes in one run of registers, of which both steps' operands are parts
 #pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-                for (int t = 0; t < C::TN; ++t) {
-                    const v8i b = s == 0 ? __builtin_shufflevector(X[x], X[x], 0, 1, 2, 3, 4, 5, -1, -1)
-                                         : __builtin_shufflevector(X[x], X[x], 6, 7, 8, 9, 10, 11, -1, -1);
-                    acc[t][x] = mfma6(W[P % 2][s][t], b, acc[t][x]);
-                }
-            if (x == 0) read_x(off, C::TM - 1);
-            else read_x(off_next, x - 1);
-#pragma unroll
-            for (int h = x * 8 / C::TM; h < (x + 1) * 8 / C::TM; ++h) widen_half(next, W[(P + 1) % 2], h);
-            if constexpr (C::W_LDS) {
-                if (x == 0) w_fill1(std::integral_constant<int, 0>(), wr, w_fill_to), w_fill1(std::integral_constant<int, 1>(), wr, w_fill_to);
-                if (x == 1) w_fill1(std::integral_constant<int, 2>(), wr, w_fill_to), w_fill1(std::integral_constant<int, 3>(), wr, w_fill_to);
-                if (x == C::TM - 1) read_w(off_next2, load_to);
-            } else {
-                if (x == 0) load_to[0][0] = load_w1(wr, 0, 0), load_to[1][0] = load_w1(wr, 1, 0);
-                if (x == 1) load_to[0][1] = load_w1(wr, 0, 1), load_to[1][1] = load_w1(wr, 1, 1);
-            }
-            if (x == 2) fill_from(std::integral_constant<int, 0>(), std::integral_constant<int, 2>(), xr, fill_to);
-            constexpr int REST = C::FILLS - 2;
-            if constexpr (REST > 0) { if (x == 3) fill1(std::integral_constant<int, 2>(), xr, fill_to); }
-            if constexpr (REST > 1) { if (x == 4) fill1(std::integral_constant<int, 3>(), xr, fill_to); }
-            if constexpr (REST > 2) { if (x == 5) fill1(std::integral_constant<int, 4>(), xr, fill_to); }
-            if constexpr (REST > 3) { if (x == 6) fill1(std::integral_constant<int, 5>(), xr, fill_to); }
-#pragma unroll
             for (int i = 0; i < 4; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                if (i < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                if (C::W_LDS && x == C::TM - 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                if (i == 1 || i == 3) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, C::TM == 8 ? 3 : C::TM == 4 ? 6 : 4, 0);
+                const int s = i / 2, t = i % 2;
+                const v8i b = s == 0 ? __builtin_shufflevector(X[x], X[x], 0, 1, 2, 3, 4, 5, -1, -1)
+                                     : __builtin_shufflevector(X[x], X[x], 6, 7, 8, 9, 10, 11, -1, -1);
+                acc[t][x] = mfma6(W[P % 2][s][t], b, acc[t][x]);
+                __builtin_amdgcn_sched_barrier(0);
+                // Before the first read of tile kt + 1: this wave's part of it has landed (younger: whole iterations of loads and this one's of group 0);
+                // the barrier extends that to every wave's part, and says every wave has read all of tile kt - 1, whose place the fills
+                // from group 2 on take (a wave's own weights in LDS were read before that).
+                if (x == (C::W_LDS ? 0 : 1) && i == 0) {
+                    __builtin_amdgcn_s_waitcnt(waitcnt_vm(C::LOADS * (C::STAGES - 3) + (C::W_LDS ? 0 : 2)));
+                    __builtin_amdgcn_s_barrier();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                // this wave's weights of tile kt + 2 are in (its own copies: no barrier); younger: an iteration's loads and this one's so far
+                if (C::W_LDS && x == C::TM - 1 && i == 0) {
+                    __builtin_amdgcn_s_waitcnt(waitcnt_vm(C::LOADS * (C::STAGES - 4) + C::BEFORE_LAST));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (i < 3) read_piece(x == 0 ? off : off_next, x == 0 ? C::TM - 1 : x - 1, i);
+                if (C::W_LDS && x == C::TM - 1) read_w1(off_next + C::STAGE_BYTES == C::RING_BYTES ? 0 : off_next + C::STAGE_BYTES, load_to, i);
+                const int slot = 4 * x + i;        // of 4 TM: 24 thirds go into them
+#pragma unroll
+                for (int k = slot * 6 / C::TM; k < (slot + 1) * 6 / C::TM; ++k) widen_third(next, W[(P + 1) % 2], k / 3, k % 3);
+                if constexpr (C::W_LDS) {
+                    if (x == 0 && i == 3) w_fill1(std::integral_constant<int, 0>(), wr, w_fill_to), w_fill1(std::integral_constant<int, 1>(), wr, w_fill_to);
+                    if (x == 1 && i == 3) w_fill1(std::integral_constant<int, 2>(), wr, w_fill_to), w_fill1(std::integral_constant<int, 3>(), wr, w_fill_to);
+                } else {
+                    if (x < 2 && i == 3) load_to[0][x] = load_w1(wr, 0, x), load_to[1][x] = load_w1(wr, 1, x);
+                }
+                if (x == 2 && i == 3) fill_from(std::integral_constant<int, 0>(), std::integral_constant<int, 2>(), xr, fill_to);
+                constexpr int REST = C::FILLS - 2;
+                if constexpr (REST > 0) { if (x == 3 && i == 1) fill1(std::integral_constant<int, 2>(), xr, fill_to); }
+                if constexpr (REST > 1) { if (x == 4 && i == 1) fill1(std::integral_constant<int, 3>(), xr, fill_to); }
+                if constexpr (REST > 2) { if (x == 5 && i == 1) fill1(std::integral_constant<int, 4>(), xr, fill_to); }
+                if constexpr (REST > 3) { if (x == 6 && i == 1) fill1(std::integral_constant<int, 5>(), xr, fill_to); }
+                if (x == C::TM - 1 && i == 3) {    // addresses of the next iteration
+                    wp += w_slab, xp += x_slab;
+                    --w_left, --x_left;
+                    wr = slab_desc(wp, w_slab, w_left > 0), xr = slab_desc(xp, x_end, x_left > 0);
+                    off_prev = off, off = off_next, off_next = off_next + C::STAGE_BYTES == C::RING_BYTES ? 0 : off_next + C::STAGE_BYTES;
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
         }
-        wp += w_slab, xp += x_slab;
-        --w_left, --x_left;
-        off = off_next;
     };
     // unrolled by six, so that the weights' two or three register sets rotate without copies
     int left = ktiles;
