@@ -16,6 +16,7 @@
 // reads are bank-conflict free.
 #include <cmath>
 #include <cstdio>
+#include <type_traits>
 
 #include "fptq_common.h"
 
@@ -46,9 +47,17 @@ struct GemmCfg {
     static constexpr int LOADS = W_LOADS + X_LOADS;
     static constexpr int RING_BYTES = STAGES * STAGE_BYTES, LDS_BYTES = KS * RING_BYTES;
     static_assert(W_BYTES % (WAVES * 1024) == 0 && X_BYTES % (WAVES * 1024) == 0, "tile must split over waves");
-    static_assert(W_LOADS >= 1 && W_LOADS <= 4 && X_LOADS >= 1 && X_LOADS <= 4, "the fill schedule issues at most one W and one X chunk per quarter");
-    // loads issued by fill quarters 0 and 1 (a quarter q carries W chunk q and X chunk q if they exist)
-    static constexpr int HALF_LOADS = (W_LOADS < 2 ? W_LOADS : 2) + (X_LOADS < 2 ? X_LOADS : 2);
+    static_assert(W_LOADS >= 1 && W_LOADS <= 4 && X_LOADS >= 1 && X_LOADS <= 4, "the fill schedule issues at most two chunks per quarter");
+    // A K tile's fill goes in quarters: W chunk q and X chunk q (KS = 1), or two W chunks, two X chunks, the other W chunks, the other X chunks: loads of
+    // adjacent lines side by side, and one LDS base for both.
+    static constexpr int W_FIRST = W_LOADS < 2 ? W_LOADS : 2, X_FIRST = X_LOADS < 2 ? X_LOADS : 2, HALF_LOADS = W_FIRST + X_FIRST;      // quarters 0 and 1
+    // Steps in the unrolled loop, so that the sets of descriptors and (KS > 1) the ring positions are known at compile time.  A wave alone on its SIMD waits
+    // for every instruction, and of the 190 that a 64 x 64 block took per K tile, 55 were scalar ones for addresses; now 155.  us, before / now, weights
+    // from HBM (in brackets from the last-level cache): 256 x 4096 x 4096 8.3 / 7.4 (7.7 / 6.8), 256 x 2048 x 8192 in two K ranges 10.6 / 9.5 (10.3 / 9.1), 512
+    // x 8192 x 8192 33.3 / 29.4, 96 x 28672 x 4096 19.5 / 17.6 (17.7 / 15.5), 64 x 57344 x 8192 51.2 / 49.1 (42.7 / 40.7).  Six steps, with two sets of descriptors instead of
+    // three, are as fast from the cache and up to 11 % slower from HBM, with their code cold too (100 x 30000 x 3000 16.4, 18.1; three steps 15.9).  The 256 x 256 tile
+    // would spill.
+    static constexpr int UNROLL = ACC_REGS == 256 ? 1 : KS == 1 ? 2 : STAGES;
     static_assert(STAGES >= 3, "pipeline needs three stages");
     static_assert(TN <= 4, "a wave's channel run must fit 16 lanes of 8 channels in the epilogue");
     // After the K loop the K groups exchange accumulators so that each ends up with the sum of SUBS of the wave's
@@ -320,38 +329,42 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void linear_mfma_kernel(
 
     // per-slab descriptors: rows past N (M) fail the bounds check and read as zero.  Step j of this K group
     // is K tile kt_begin + j * KS + kg; a step past the last tile gets an empty descriptor, so its loads are still
-    // issued (the outstanding-load count stays uniform) but read nothing and land as zeros.
+    // issued (the outstanding-load count stays uniform) but read nothing and land as zeros.  The steps are asked for in order, so that
+    // an addition makes the next addresses.
     int kt_begin = 0, kt_end = ktiles;               // K tiles of this workgroup
     if (C::SPLIT) {
         const int per = (ktiles + splits - 1) / splits;
         kt_begin = split * per;
         kt_end = min(ktiles, kt_begin + per);
     }
-    auto w_desc = [&](int j) {
-        const int kt = kt_begin + j * C::KS + kg;
-        const bool in = kt < kt_end;
-        return __builtin_amdgcn_make_buffer_rsrc((void *)(wq + (in ? kt : 0) * w_slab), 0, in ? (int)w_slab : 0, RSRC_FLAGS);
+    const uint8_t *w_next = wq + (kt_begin + kg) * w_slab, *x_next = xq + (kt_begin + kg) * x_slab;
+    int tiles_left = kt_end - kt_begin - kg;
+    const int64_t w_step = C::KS * w_slab, x_step = C::KS * x_slab;
+    auto next_descs = [&](__amdgpu_buffer_rsrc_t &w, __amdgpu_buffer_rsrc_t &x) {
+        w = __builtin_amdgcn_make_buffer_rsrc((void *)w_next, 0, tiles_left > 0 ? (int)w_slab : 0, RSRC_FLAGS);
+        x = __builtin_amdgcn_make_buffer_rsrc((void *)x_next, 0, tiles_left > 0 ? (int)x_slab : 0, RSRC_FLAGS);
+        w_next += w_step, x_next += x_step, tiles_left -= C::KS;
     };
-    auto x_desc = [&](int j) {
-        const int kt = kt_begin + j * C::KS + kg;
-        const bool in = kt < kt_end;
-        return __builtin_amdgcn_make_buffer_rsrc((void *)(xq + (in ? kt : 0) * x_slab), 0, in ? (int)x_slab : 0, RSRC_FLAGS);
+    // quarter q (0..3) of the fill of one K tile
+    auto chunk = [&](auto which, __amdgpu_buffer_rsrc_t r, uint8_t *base, int voff, int loads) {
+        if (decltype(which)::value < loads) load_chunk<decltype(which)::value>(r, base, voff);
     };
-    // quarter q (0..3) of the fill of one K tile: W chunk q and X chunk q, where they exist
     auto fill_quarter = [&](__amdgpu_buffer_rsrc_t wr, __amdgpu_buffer_rsrc_t xr, int stage, int q) {
-        uint8_t *sb = ring + stage * C::STAGE_BYTES;
-        if (q == 0) { load_chunk<0>(wr, sb + w_lds0, w_voff); load_chunk<0>(xr, sb + x_lds0, x_voff); }
-        if (q == 1) {
-            if (C::W_LOADS > 1) load_chunk<1>(wr, sb + w_lds0, w_voff);
-            if (C::X_LOADS > 1) load_chunk<1>(xr, sb + x_lds0, x_voff);
-        }
-        if (q == 2) {
-            if (C::W_LOADS > 2) load_chunk<2>(wr, sb + w_lds0, w_voff);
-            if (C::X_LOADS > 2) load_chunk<2>(xr, sb + x_lds0, x_voff);
-        }
-        if (q == 3) {
-            if (C::W_LOADS > 3) load_chunk<3>(wr, sb + w_lds0, w_voff);
-            if (C::X_LOADS > 3) load_chunk<3>(xr, sb + x_lds0, x_voff);
+        const std::integral_constant<int, 0> c0;
+        const std::integral_constant<int, 1> c1;
+        const std::integral_constant<int, 2> c2;
+        const std::integral_constant<int, 3> c3;
+        uint8_t *const wb = ring + stage * C::STAGE_BYTES + w_lds0, *const xb = ring + stage * C::STAGE_BYTES + x_lds0;
+        if constexpr (C::KS == 1) {
+            if (q == 0) chunk(c0, wr, wb, w_voff, C::W_LOADS), chunk(c0, xr, xb, x_voff, C::X_LOADS);
+            if (q == 1) chunk(c1, wr, wb, w_voff, C::W_LOADS), chunk(c1, xr, xb, x_voff, C::X_LOADS);
+            if (q == 2) chunk(c2, wr, wb, w_voff, C::W_LOADS), chunk(c2, xr, xb, x_voff, C::X_LOADS);
+            if (q == 3) chunk(c3, wr, wb, w_voff, C::W_LOADS), chunk(c3, xr, xb, x_voff, C::X_LOADS);
+        } else {
+            if (q == 0) chunk(c0, wr, wb, w_voff, C::W_LOADS), chunk(c1, wr, wb, w_voff, C::W_LOADS);
+            if (q == 1) chunk(c0, xr, xb, x_voff, C::X_LOADS), chunk(c1, xr, xb, x_voff, C::X_LOADS);
+            if (q == 2) chunk(c2, wr, wb, w_voff, C::W_LOADS), chunk(c3, wr, wb, w_voff, C::W_LOADS);
+            if (q == 3) chunk(c2, xr, xb, x_voff, C::X_LOADS), chunk(c3, xr, xb, x_voff, C::X_LOADS);
         }
     };
 
@@ -415,7 +428,8 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void linear_mfma_kernel(
     // quarter q in the middle
     auto pin = [&](bool reads, int q) {
         constexpr int NM = C::TN * C::TM, NOP = C::TN + C::TM, VPM = (6 * NOP + NM - 1) / NM;
-        const int n_vmem = (q < C::W_LOADS ? 1 : 0) + (q < C::X_LOADS ? 1 : 0);
+        const int n_vmem = C::KS == 1 ? (q < C::W_LOADS ? 1 : 0) + (q < C::X_LOADS ? 1 : 0)
+                                      : q == 0 ? C::W_FIRST : q == 1 ? C::X_FIRST : q == 2 ? C::W_LOADS - C::W_FIRST : C::X_LOADS - C::X_FIRST;
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -440,15 +454,19 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void linear_mfma_kernel(
     const int steps = (max(kt_end - kt_begin, 0) + C::KS - 1) / C::KS;      // the same for every K group: they share the barriers
 #pragma unroll
     for (int s = 0; s < C::STAGES - 1; ++s) {
-        __amdgpu_buffer_rsrc_t wr = w_desc(s), xr = x_desc(s);
+        __amdgpu_buffer_rsrc_t wr, xr;
+        next_descs(wr, xr);
 #pragma unroll
         for (int q = 0; q < 4; ++q) fill_quarter(wr, xr, s, q);
     }
-    // descriptors of the fill that is half way (step kt+S-1) and of the one that starts in G2 (step kt+S)
-    __amdgpu_buffer_rsrc_t wr_a = w_desc(C::STAGES - 1), xr_a = x_desc(C::STAGES - 1);
-    __amdgpu_buffer_rsrc_t wr_b = w_desc(C::STAGES), xr_b = x_desc(C::STAGES);
-    fill_quarter(wr_a, xr_a, C::STAGES - 1, 0);
-    fill_quarter(wr_a, xr_a, C::STAGES - 1, 1);
+    // descriptors of fills
+    struct Descs {
+        __amdgpu_buffer_rsrc_t w, x;
+    } fills[3];      // the one that is half way (step kt+S-1), the one that starts in G2 (step kt+S), and the next
+    next_descs(fills[0].w, fills[0].x);
+    next_descs(fills[1].w, fills[1].x);
+    fill_quarter(fills[0].w, fills[0].x, C::STAGES - 1, 0);
+    fill_quarter(fills[0].w, fills[0].x, C::STAGES - 1, 1);
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(C::LOADS * (C::STAGES - 2) + C::HALF_LOADS));   // tile 0 is in
     __builtin_amdgcn_s_barrier();
     read_frags(0, 0, rawW[0], rawX[0]);
@@ -458,18 +476,18 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void linear_mfma_kernel(
     for (int tm = 0; tm < C::TM; ++tm) opX[0][tm] = widen(rawX[0][tm][0], rawX[0][tm][1]);
     __builtin_amdgcn_sched_barrier(0);
 
-    int stage = 0;      // ring position of tile kt
     __builtin_amdgcn_s_setprio(2);     // MFMA loop: ahead of other workgroups' prologues and epilogues on this SIMD
-    for (int kt = 0; kt < steps; ++kt) {
+    // one K tile, in the ring's position `stage`; a: the fill that is half way, b: the next one, c receives the one after that (unrolled, the sets take turns)
+    auto step = [&](int stage, Descs &a, Descs &b, Descs &c) {
         const int stage_next = stage + 1 == C::STAGES ? 0 : stage + 1;
         const int stage_prev = stage == 0 ? C::STAGES - 1 : stage - 1;   // holds tile kt+S-1 (being filled)
         // G0
         read_frags(stage, 1, rawW[1], rawX[1]);
-        fill_quarter(wr_a, xr_a, stage_prev, 2);
+        fill_quarter(a.w, a.x, stage_prev, 2);
         group(opW[0], opX[0], opW[1], opX[1], rawW[0], rawX[0], 1);
         pin(true, 2);
         // G1
-        fill_quarter(wr_a, xr_a, stage_prev, 3);
+        fill_quarter(a.w, a.x, stage_prev, 3);
         group(opW[1], opX[1], opW[0], opX[0], rawW[1], rawX[1], 0);
         pin(false, 3);
         // own loads of tile kt+1 have landed (younger: all of tiles kt+2 .. kt+S-1); the barrier
@@ -479,18 +497,41 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void linear_mfma_kernel(
         __builtin_amdgcn_sched_barrier(0);
         // G2 (after the last tile the fragment reads hit a repeated copy; its results are unused)
         read_frags(stage_next, 0, rawW[0], rawX[0]);
-        fill_quarter(wr_b, xr_b, stage, 0);
+        fill_quarter(b.w, b.x, stage, 0);
         group(opW[0], opX[0], opW[1], opX[1], rawW[1], rawX[1], 1);
         pin(true, 0);
         // G3
-        fill_quarter(wr_b, xr_b, stage, 1);
-        wr_a = wr_b;
-        xr_a = xr_b;
-        wr_b = w_desc(kt + C::STAGES + 1);
-        xr_b = x_desc(kt + C::STAGES + 1);
+        fill_quarter(b.w, b.x, stage, 1);
+        if constexpr (C::UNROLL == 1) a = b;
+        next_descs(c.w, c.x);
         group(opW[1], opX[1], opW[0], opX[0], rawW[0], rawX[0], 0);
         pin(false, 1);
-        stage = stage_next;
+    };
+    int left = steps;
+    if constexpr (C::UNROLL == 1) {
+        for (int stage = 0; left > 0; --left, stage = stage + 1 == C::STAGES ? 0 : stage + 1) step(stage, fills[0], fills[1], fills[1]);
+    } else if constexpr (C::UNROLL == 2) {
+        auto after = [](int i) { return i + 1 == C::STAGES ? 0 : i + 1; };
+        int stage = 0;
+        for (; left >= 2; left -= 2) {
+            step(stage, fills[0], fills[1], fills[0]);
+            step(after(stage), fills[1], fills[0], fills[1]);
+            stage = after(after(stage));
+        }
+        if (left > 0) step(stage, fills[0], fills[1], fills[0]);
+    } else {
+        constexpr int SETS = C::UNROLL == 3 ? 3 : 2;
+        static_assert(C::UNROLL % SETS == 0 && C::UNROLL <= 4, "");
+        auto at = [&](int p) { step(p, fills[p % SETS], fills[(p + 1) % SETS], fills[(p + 2) % SETS]); };
+        for (; left >= C::UNROLL; left -= C::UNROLL) {
+            at(0), at(1), at(2);
+            if constexpr (C::UNROLL == 4) at(3);
+        }
+        if (left > 0) at(0);
+        if (left > 1) at(1);
+        if constexpr (C::UNROLL == 4) {
+            if (left > 2) at(2);
+        }
     }
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the tail loads before LDS is reused
