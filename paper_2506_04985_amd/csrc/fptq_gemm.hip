@@ -792,9 +792,13 @@ static int choose_tile(int64_t M, int64_t N, int64_t K, int cus, double *us = nu
 // the CUs in a single round (least_share), the estimates spread most and INT8's smaller tiles are closest, so they take 48 K tiles: 562 x 8064 x
 // 5376 30 us on INT8 and 37 with 192 tokens, 151 x 19477 x 4472 25 and 33, 1670 x 2560 x 4936 27 and 29 with 128 (weights from HBM).  The 256-token
 // tile needs no such limit: refused below four fifths of the CUs, 512 x 23424 x 6016 took 57 us on INT8 instead of 48 (from the cache 54 and 43), 256 x
-// 50096 x 2744 36 instead of 30 (33 and 27).  192 tokens are taken for up to a round and a half (beyond that 256 are within a few
-// percent).  The margins (wider for few K tiles, where stores and launches weigh more than in what the estimates were fitted to) leave one of the 500
-// shapes 5 % slower than INT8, none of 180 others of 0.4 to 1 round, and the same one slower by that than with a choice between 256 and 128 tokens only.
+// 50096 x 2744 36 instead of 30 (33 and 27).  Beyond a round and a half 192 tokens are taken from 25 K tiles on only, where
+// they take 2 to 14 % less than what was taken instead on 57 of the 59 shapes of 960 that this concerns, and as long on the other two (2048 x 10240 x
+// 8192 91 us against 102 with 256 tokens, 1500 x 14336 x 4096 52 against 62, 3000 x 8192 x 28672 327 against 332; the 256-token tile stays where its
+// last round is fuller: 6000 x 5120 x 5120 83 against 88); below that INT8 is as fast.  The margins (wider for few K tiles, where stores and launches
+// weigh more than in what the estimates were fitted to, but for the 256-token tile in more than 1.6 rounds from 14 K tiles on: 1732 x 15160 x 3064 55 us
+// against 66 on INT8, 1025 x 24520 x 3256 59 against 71) leave 6 of the 960 shapes 5 % or more slower than INT8 with the weights from HBM and 3 from the
+// cache, by 12 % at most; the choice takes 0.6 and 0.8 % longer than the best of the four on average (1.2 and 1.6 % without these two rules).
 // Tiles of 160 and 96 tokens were within 3 % of the best of the others but on 22 of the first 200 shapes (192 x 28672 x 4096: 26 and 29): not kept.
 int prefill_tile(int64_t M, int64_t N, int64_t K)
 {
@@ -813,22 +817,23 @@ int prefill_tile(int64_t M, int64_t N, int64_t K)
     };
     static const Tile tiles[] = {{256, 5.0, 0.58, 0.53, 7.5, 0.789, 0.0}, {192, 4.95, 0.54, 0.58, 5.4, 0.649, 0.65}, {128, 5.75, 0.58, 0.69, 3.8, 0.494, 0.76}};
     int tokens = 0;
-    double us = 0.0;
+    double us = 0.0, tile_rounds = 0.0;
     for (const Tile &t : tiles) {
         const int64_t workgroups = prefill_workgroups(M, N, t.tokens);
         const double x = (double)workgroups / (double)cus, part = x - floor(x);
         // A single row of small tiles streams its weights once, from HBM: with few workgroups that is bound by what one CU keeps in flight
         // (96 x 37397 x 17536, 147 workgroups: 92 us against 85 on INT8 tiles; 96 x 57344 x 8192, 224 workgroups: 53 against 53).
         if (t.tokens == 128 && M <= 128 && x < 0.75) continue;
-        if (mode == 0 && ((x < t.least_share && kt < 48) || (t.tokens == 192 && x > 1.5))) continue;
+        if (mode == 0 && ((x < t.least_share && kt < 48) || (t.tokens == 192 && x > 1.5 && kt < 25))) continue;
         const double rounds = x < 1.0 ? t.lone + (1.0 - t.lone) * x : floor(x) + (part > 0.0 ? t.least + (1.0 - t.least) * part : 0.0);
         const double est = t.call_us + widen_us + rounds * (t.tile_us + t.k_tile_us * kt);
-        if (tokens == 0 || est < us) tokens = t.tokens, us = est;
+        if (tokens == 0 || est < us) tokens = t.tokens, us = est, tile_rounds = x;
     }
     if (mode == 1 || tokens == 0) return tokens;
     double int8_us = 0.0;
     choose_tile(M, N, K, cus, &int8_us);
-    return us < (kt < 32 ? 0.85 : 0.94) * int8_us ? tokens : 0;
+    const bool fitted = kt >= 32 || (kt >= 14 && tokens == 256 && tile_rounds > 1.6);
+    return us < (fitted ? 0.94 : 0.85) * int8_us ? tokens : 0;
 }
 
 // Limits of the MFMA kernel: the widened accumulator is 256 * acc with |acc| <= 64 K, and one K tile of all rows

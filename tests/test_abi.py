@@ -128,3 +128,12 @@ def test_where_the_six_bit_kernel_is_taken(M, N, K, tokens):
     else:
         assert plan == fptq.fptq_linear_launch_plan(M, N, K)
     assert (fptq.fptq_linear_scratch_bytes(M, N, K) > 0) == (tokens > 0)
+
+
+@pytest.mark.parametrize("M,N,K,tokens", [
+    # 192 tokens in more than a round and a half, from 25 K tiles on
+    (2048, 10240, 8192, 192), (1500, 14336, 4096, 192), (4096, 5120, 5120, 192), (874, 20832, 3360, 192), (6000, 5120, 5120, 256), (8192, 28672, 4096, 256),
+    # 256 tokens in more than 1.6 rounds, 14 to 31 K tiles
+    (1732, 15160, 3064, 256), (1025, 24520, 3256, 256), (3608, 6784, 3080, 0), (3590, 6528, 2440, 0)])
+def test_the_six_bit_tile_in_several_rounds(M, N, K, tokens):
+    test_where_the_six_bit_kernel_is_taken(M, N, K, tokens)
