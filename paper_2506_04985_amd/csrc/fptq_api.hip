@@ -88,13 +88,19 @@ static int check_align(const char *fn, const void *p, unsigned a, const char *na
     return FPTQ_OK;
 }
 
-// The few-token kernel serves M <= 32 and, for matrices of fewer than 10240 channels, M <= 64; above that, or
-// whenever a prefill tile shape is forced, the MFMA GEMM runs: its 64 x 64 and 128 x 64 tiles with four K groups
-// are faster from 65 tokens on everywhere, and from 33 tokens on wide matrices (measured over cold weights at 64
-// tokens, best few-token launch shape against the MFMA kernel: 6144 x 4096 7.0 us against 9.1, 4096 x 14336 13.9
-// against 19.5, but 28672 x 4096 19.1 against 15.9 and 22016 x 4096 16.7 against 14.4, with 10240 to 15360
-// channels about even; at 80 tokens 4096 x 14336 22.1 against 17.0).
-static bool few_token_shape(int64_t M, int64_t N) { return M <= 32 || (M <= 64 && N < 10240); }
+// The few-token kernel serves up to 32 tokens and, where its workgroups of 32 channels are a single round of the CUs, up to 64;
+// above that, or whenever a prefill tile shape is forced, the MFMA GEMM runs: its 64 x 64 and 128 x 64 tiles with four K groups
+// are faster from 65 tokens on everywhere, and from 33 tokens on where a second round begins (33 to 64 tokens over cold weights, few tokens /
+// tiles: 8168 channels of K = 3872 7.4 us / 8.8, 9784 x 4968 13.1 / 10.4, 8384 x 8416 18.5 / 13.5, 8824 x 14944 31.1 / 20.2; of 81 matrices of 8200 to
+// 10239 channels the tiles take 12 to 36 % less on each).  They are also faster with 17 to 32 tokens against more than 12288 channels of fewer than
+// 16 K tiles, too few for the 16 waves that share a K otherwise: 15208 x 992 6.2 us / 5.7, 29040 x 1352 11.7 / 8.5, 36536 x 1384 14.0 / 13.0, 57288 x 736
+// 17.3 / 11.5; 2 % more to 34 % less on 87 matrices of up to 62000 channels, and up to 6 % more below 12288.
+static bool few_token_shape(int64_t M, int64_t N, int64_t K)
+{
+    if (M > 64 || N > (1 << 24)) return M <= 32;
+    if (M > 32) return N <= 32 * (int64_t)device_cus_or_default() || (K > 65535 && N < 10240);     // that long, tiles serve no zero point
+    return M <= 16 || N <= 12288 || k_tiles(K) >= 16;
+}
 
 typedef hipError_t (*linear_fn)(const uint8_t *, const uint8_t *, int64_t, int64_t, int64_t, float, const float *,
                                 const float *, int, const int32_t *, uint16_t *, int32_t *, hipStream_t);
@@ -141,7 +147,7 @@ static int linear_common(const char *fn, linear_fn force, const void *xq, const 
         set_error("%s: negative scratch_bytes", fn);
         return FPTQ_ERR_SIZE;
     }
-    linear_fn f = force ? force : (few_token_shape(M, N) && forced_gemm_tile() == 0 ? launch_linear_decode : launch_linear_mfma);
+    linear_fn f = force ? force : (few_token_shape(M, N, K) && forced_gemm_tile() == 0 ? launch_linear_decode : launch_linear_mfma);
     hipError_t e;
     const int tile_tokens = f == launch_linear_mfma && scratch ? prefill_tile(M, N, K) : 0;
     if (tile_tokens && scratch_bytes >= prefill_scratch_bytes(M, K))
@@ -364,7 +370,7 @@ int64_t fptq_linear_workspace_bytes(int64_t M, int64_t N, int64_t K)
         set_error("%s: K=%lld exceeds %lld, the longest sum INT32 holds exactly", fn, (long long)K, (long long)MAX_K);
         return FPTQ_ERR_SHAPE;
     }
-    return few_token_shape(M, N) ? 0 : linear_workspace_bytes(M, N, K);
+    return few_token_shape(M, N, K) ? 0 : linear_workspace_bytes(M, N, K);
 }
 
 int fptq_w4a4_linear_ws(const void *xq_packed, const void *w_packed, int64_t M, int64_t N, int64_t K, float s_a,
@@ -381,7 +387,7 @@ int fptq_w4a4_linear_noalloc(const void *xq_packed, const void *w_packed, int64_
     const char *fn = "fptq_w4a4_linear_noalloc";
     // shapes that would not split K anyway need no scratch: the plain layer (which allocates nothing either)
     const int64_t need = (M >= 1 && N >= 1 && K >= 1 && K <= MAX_K && M <= MAX_ELEMS / K && N <= MAX_ELEMS / K && M <= MAX_ELEMS / N &&
-                          !few_token_shape(M, N))
+                          !few_token_shape(M, N, K))
                              ? linear_workspace_bytes(M, N, K)
                              : 0;
     if (need == 0)
@@ -409,7 +415,7 @@ int64_t fptq_linear_scratch_bytes(int64_t M, int64_t N, int64_t K)
         set_error("%s: K=%lld exceeds %lld, the longest sum INT32 holds exactly", fn, (long long)K, (long long)MAX_K);
         return FPTQ_ERR_SHAPE;
     }
-    return !few_token_shape(M, N) && prefill_tile(M, N, K) ? prefill_scratch_bytes(M, K) : 0;
+    return !few_token_shape(M, N, K) && prefill_tile(M, N, K) ? prefill_scratch_bytes(M, K) : 0;
 }
 
 int fptq_w4a4_linear_scratch(const void *xq_packed, const void *w_packed, int64_t M, int64_t N, int64_t K, float s_a,
@@ -432,7 +438,7 @@ int fptq_linear_launch_plan(int64_t M, int64_t N, int64_t K, int with_workspace,
     if ((rc = check_dims(fn, M, K, "M", "K")) || (rc = check_dims(fn, N, K, "N", "K")) || (rc = check_dims(fn, M, N, "M", "N")))
         return rc;
     LinearPlan plan = {};
-    if (few_token_shape(M, N) && forced_gemm_tile() == 0) {
+    if (few_token_shape(M, N, K) && forced_gemm_tile() == 0) {
         snprintf(plan.kernel, sizeof plan.kernel, "linear_decode_kernel");
         plan.workgroups = 0;
         plan.threads = 0;

@@ -137,3 +137,11 @@ def test_where_the_six_bit_kernel_is_taken(M, N, K, tokens):
     (1732, 15160, 3064, 256), (1025, 24520, 3256, 256), (3608, 6784, 3080, 0), (3590, 6528, 2440, 0)])
 def test_the_six_bit_tile_in_several_rounds(M, N, K, tokens):
     test_where_the_six_bit_kernel_is_taken(M, N, K, tokens)
+
+
+@pytest.mark.parametrize("M,N,K,few", [
+    (33, 8192, 4096, True), (33, 8193, 4096, False), (64, 8192, 512, True), (64, 10239, 8192, False), (65, 1024, 4096, False), (40, 9000, 65536, True),
+    (16, 57344, 512, True), (17, 12288, 512, True), (17, 12289, 1920, False), (32, 32000, 1024, False), (32, 32000, 1921, True)])
+def test_where_the_few_token_kernel_is_taken(M, N, K, few):
+    assert (fptq.fptq_linear_launch_plan(M, N, K)[0] == "linear_decode_kernel") == few
+    assert fptq.fptq_linear_workspace_bytes(M, N, K) == 0 or not few

@@ -1,4 +1,5 @@
-"""The INT8 tiles' unrolled K loops at every remainder: each tile shape, and the split over workgroups, against the simple kernel."""
+"""The INT8 tiles' unrolled K loops at every remainder: each tile shape, and the split over workgroups, against the simple kernel; and both sides of the
+lines between the few-token kernel and the tiles."""
 import pytest
 import torch
 
@@ -41,3 +42,18 @@ def test_split_over_workgroups(tiles):
     for _ in range(2):
         y, a = fptq.fptq_w4a4_linear_ws(xq, wq, M, N, K, 0.37, s_w, ws, want_acc=True)
         assert torch.equal(a, a_ref) and torch.equal(y.view(torch.int16), y_ref.view(torch.int16))
+
+
+@pytest.mark.parametrize("M,N,K", [(33, 8192, 300), (33, 8193, 300), (64, 8200, 2100), (47, 10239, 1000), (16, 12296, 640), (17, 12288, 640), (17, 12289, 640),
+                                   (32, 12400, 1920), (32, 12400, 1921), (25, 33001, 100)])
+def test_both_sides_of_the_few_token_lines(M, N, K):
+    xq, wq, s_w = operands(M, N, K)
+    d = torch.rand(M, device="cuda") + 0.5
+    y_ref, a_ref = fptq.fptq_w4a4_linear_ref(xq, wq, M, N, K, 0.37, s_w, d, want_acc=True)
+    y, a = fptq.fptq_w4a4_linear(xq, wq, M, N, K, 0.37, s_w, d, want_acc=True)
+    assert torch.equal(a, a_ref) and torch.equal(y.view(torch.int16), y_ref.view(torch.int16))
+    assert torch.equal(fptq.fptq_w4a4_linear_noalloc(xq, wq, M, N, K, 0.37, s_w, d).view(torch.int16), y_ref.view(torch.int16))
+    wsum = torch.randint(-500, 500, (N,), dtype=torch.int32, device="cuda")
+    y, a = fptq.fptq_w4a4_linear_zp(xq, wq, M, N, K, 0.37, s_w, 3, wsum, d, want_acc=True)
+    want = ((a_ref - 3 * wsum).float() * (s_w * 0.37) * d[:, None]).to(torch.bfloat16)        # the epilogue's products in their order, each rounded
+    assert torch.equal(a, a_ref) and torch.equal(y, want)
