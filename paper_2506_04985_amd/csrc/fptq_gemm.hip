@@ -52,11 +52,14 @@ struct GemmCfg {
     // adjacent lines side by side, and one LDS base for both.
     static constexpr int W_FIRST = W_LOADS < 2 ? W_LOADS : 2, X_FIRST = X_LOADS < 2 ? X_LOADS : 2, HALF_LOADS = W_FIRST + X_FIRST;      // quarters 0 and 1
     // Steps in the unrolled loop, so that the sets of descriptors and (KS > 1) the ring positions are known at compile time.  A wave alone on its SIMD waits
-    // for every instruction, and of the 190 that a 64 x 64 block took per K tile, 55 were scalar ones for addresses; now 155.  us, before / now, weights
-    // from HBM (in brackets from the last-level cache): 256 x 4096 x 4096 8.3 / 7.4 (7.7 / 6.8), 256 x 2048 x 8192 in two K ranges 10.6 / 9.5 (10.3 / 9.1), 512
-    // x 8192 x 8192 33.3 / 29.4, 96 x 28672 x 4096 19.5 / 17.6 (17.7 / 15.5), 64 x 57344 x 8192 51.2 / 49.1 (42.7 / 40.7).  Six steps, with two sets of descriptors instead of
-    // three, are as fast from the cache and up to 11 % slower from HBM, with their code cold too (100 x 30000 x 3000 16.4, 18.1; three steps 15.9).  The 256 x 256 tile
-    // would spill.
+    // for every instruction, and of the 190 that a 64 x 64 block took per K tile, 55 were scalar ones for addresses; now 155.  A wave of these launches turns
+    // the loop a few times only (twice at 256 x 2048 x 8192 in two K ranges), so it is bound by how fast code arrives as well, and that differs from card to card.
+    // The steps that are left after the last whole turn are therefore the loop's own, each behind a test, and not copies behind the loop, which cost time even
+    // where none is taken.  us, rolled / copies behind the loop / tests in it, on a card where code arrives fast and on one where it arrives slowly:
+    //     256 x 2048 x 8192, with its quantizer   13.4 / 12.4 / 12.5,  13.8 / 14.5 / 13.5     96 x 28672 x 4096, weights from HBM   17.8 / 18.7 / 17.1,  19.1 / 20.0 / 18.7
+    //     1000 x 4096 x 4096, weights from HBM    17.6 / 16.2 / 16.6,  18.0 / 21.6 / 17.6     512 x 8192 x 8192, weights from HBM   31.9 / 28.5 / 29.3,  33.0 / 30.6 / 30.7
+    // of 32 launches on three cards none is slower than rolled by more than 1 %.  Six steps, with two sets of descriptors instead of three: up to 11 % slower
+    // from HBM (100 x 30000 x 3000 16.4, 18.1; three steps 15.9).  The 256 x 256 tile would spill.
     static constexpr int UNROLL = ACC_REGS == 256 ? 1 : KS == 1 ? 2 : STAGES;
     static_assert(STAGES >= 3, "pipeline needs three stages");
     static_assert(TN <= 4, "a wave's channel run must fit 16 lanes of 8 channels in the epilogue");
@@ -523,14 +526,13 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void linear_mfma_kernel(
         constexpr int SETS = C::UNROLL == 3 ? 3 : 2;
         static_assert(C::UNROLL % SETS == 0 && C::UNROLL <= 4, "");
         auto at = [&](int p) { step(p, fills[p % SETS], fills[(p + 1) % SETS], fills[(p + 2) % SETS]); };
-        for (; left >= C::UNROLL; left -= C::UNROLL) {
-            at(0), at(1), at(2);
-            if constexpr (C::UNROLL == 4) at(3);
-        }
-        if (left > 0) at(0);
-        if (left > 1) at(1);
-        if constexpr (C::UNROLL == 4) {
+        for (; left > 0; left -= C::UNROLL) {
+            at(0);
+            if (left > 1) at(1);
             if (left > 2) at(2);
+            if constexpr (C::UNROLL == 4) {
+                if (left > 3) at(3);
+            }
         }
     }
     __builtin_amdgcn_s_setprio(0);

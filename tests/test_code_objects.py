@@ -12,26 +12,50 @@ LLVM = "/opt/rocm/llvm/bin"
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """name -> metadata text of every kernel of the built library."""
+def code_objects(tmp_path_factory):
+    """The built library's code objects, one file per source."""
     if not os.path.exists(build.LIB):
         build.build()
     tmp = tmp_path_factory.mktemp("code_objects")
-    fat, co = str(tmp / "fat"), str(tmp / "co")
+    fat = str(tmp / "fat")
     subprocess.check_call([f"{LLVM}/llvm-objcopy", f"--dump-section=.hip_fatbin={fat}", build.LIB, str(tmp / "copy")])
-    data, found = open(fat, "rb").read(), {}
+    data, found = open(fat, "rb").read(), []
     for bundle in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", data):          # one per source file: entries of offset, size, length of name, name
         at, (entries,) = bundle.start() + 32, struct.unpack_from("<Q", data, bundle.start() + 24)
         for _ in range(entries):
             offset, size, length = struct.unpack_from("<QQQ", data, at)
             target, at = data[at + 24:at + 24 + length], at + 24 + length
             if b"gfx950" in target and size:
-                open(co, "wb").write(data[bundle.start() + offset:bundle.start() + offset + size])
-                notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", co], capture_output=True, text=True, check=True).stdout
-                for text in notes.split("  - .agpr_count")[1:]:
-                    found[re.search(r"\.name:\s+(_Z\S+)\n", text).group(1)] = text
+                found.append(str(tmp / f"co{len(found)}"))
+                open(found[-1], "wb").write(data[bundle.start() + offset:bundle.start() + offset + size])
     assert found
     return found
+
+
+@pytest.fixture(scope="module")
+def kernels(code_objects):
+    """name -> metadata text of every kernel of the built library."""
+    found = {}
+    for co in code_objects:
+        notes = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", co], capture_output=True, text=True, check=True).stdout
+        for text in notes.split("  - .agpr_count")[1:]:
+            found[re.search(r"\.name:\s+(_Z\S+)\n", text).group(1)] = text
+    return found
+
+
+@pytest.fixture(scope="module")
+def assembly(code_objects, kernels):
+    """pattern -> {name: assembly} of the kernels whose names it matches."""
+    def of(pattern):
+        names, found = [n for n in kernels if re.search(pattern, n)], {}
+        for co in code_objects:
+            text = subprocess.run([f"{LLVM}/llvm-objdump", "-d", "--no-show-raw-insn", "--disassemble-symbols=" + ",".join(names), co],
+                                  capture_output=True, text=True, check=True).stdout
+            for part in re.split(r"\n(?=[0-9a-f]+ <)", text)[1:]:
+                found[re.match(r"[0-9a-f]+ <(\S+)>", part).group(1)] = part
+        assert sorted(found) == sorted(names) and names
+        return found
+    return of
 
 
 def test_arguments_of_the_static_quantizers_come_with_the_dispatch(kernels):
@@ -54,3 +78,10 @@ def test_scratch_only_where_it_is_stated(kernels):
     for name, text in kernels.items():
         if int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", text).group(1)):
             assert any(re.search(s, name) for s in stated), name
+
+
+def test_no_step_of_an_unrolled_loop_is_there_twice(assembly):
+    """INT8 tiles with K groups: a launch turns the loop so seldom that the time in which code arrives counts, so the steps left over are not copies of their own."""
+    for name, text in assembly(r"linear_mfma_kernelINS_7GemmCfgI(Li\dE){5}Li1ELi[24]ELb[01]EEELi[012]ELb0E").items():
+        wn, wm, tn, tm, stages = (int(v) for v in re.search(r"GemmCfgILi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)E", name).groups())
+        assert text.count("v_mfma") == stages * 4 * tn * tm, name
