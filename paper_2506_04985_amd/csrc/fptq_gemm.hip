@@ -512,7 +512,12 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void linear_mfma_kernel(
     };
     int left = steps;
     if constexpr (C::UNROLL == 1) {
-        for (int stage = 0; left > 0; --left, stage = stage + 1 == C::STAGES ? 0 : stage + 1) step(stage, fills[0], fills[1], fills[1]);
+        // Counted upwards: downwards from `left` the compiler sets the 256 accumulators twice (4000 x 8200 x 1000 57.4 us, 58.7 with it; 8192 x 8192 x 8192 389 and 394).
+        int stage = 0;
+        for (int kt = 0; kt < steps; ++kt) {
+            step(stage, fills[0], fills[1], fills[1]);
+            stage = stage + 1 == C::STAGES ? 0 : stage + 1;
+        }
     } else if constexpr (C::UNROLL == 2) {
         auto after = [](int i) { return i + 1 == C::STAGES ? 0 : i + 1; };
         int stage = 0;

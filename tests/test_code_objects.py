@@ -85,3 +85,10 @@ def test_no_step_of_an_unrolled_loop_is_there_twice(assembly):
     for name, text in assembly(r"linear_mfma_kernelINS_7GemmCfgI(Li\dE){5}Li1ELi[24]ELb[01]EEELi[012]ELb0E").items():
         wn, wm, tn, tm, stages = (int(v) for v in re.search(r"GemmCfgILi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)E", name).groups())
         assert text.count("v_mfma") == stages * 4 * tn * tm, name
+
+
+def test_accumulators_are_set_once(assembly):
+    for name, text in assembly(r"linear_mfma_kernelINS_7GemmCfg\w*EEELi2ELb0ELb0E").items():
+        tn, tm = (int(v) for v in re.search(r"GemmCfgILi\dELi\dELi(\d)ELi(\d)E", name).groups())
+        before = text[:text.index("v_mfma")]
+        assert len(re.findall(r"v_accvgpr_write_b32 a\d+, 0\b|v_mov_b32_e32 v\d+, 0\b", before)) < 1.5 * 16 * tn * tm, name
