@@ -141,9 +141,15 @@ __global__ __launch_bounds__(64 * CV_WAVES) void widen_activations_kernel(const 
 // for eight MFMAs, 128 (TM = 4) for four and load twice the weights per operation; the small tiles are for problems that the large one
 // cuts into fewer pieces than there are CUs, or into a few more: weights from HBM, 1000 x 5120 x 13824 takes 60 us with 128 tokens, 67 with
 // 192, 88 with 256 and 70 on INT8 tiles, 333 x 32000 x 4096 50, 36, 40 and 46.
-template <int TM_>
+//
+// DEPTH 3 takes a loop unrolled by six (W sets in twos, packed sets in threes), DEPTH 2 by two.  A launch of few K tiles goes through most of the code of six
+// once or twice, at the speed at which code arrives, on some cards slower than the MFMAs; so up to 32 K tiles take DEPTH 2.  us, weights from HBM, DEPTH 3 / 2, on a
+// card where code arrives slowly and on one where it arrives fast: 333 x 32000 x 2504 28.0 / 26.7, 25.8 / 25.1; 333 x 32003 x 2504 with its quantizer 30.8 / 29.8,
+// 29.4 / 29.4; 2048 x 22016 x 1280 49.2 / 48.3, 45.4 / 44.8; 333 x 32000 x 4096 33.1 / 32.8, 32.5 / 32.6.  From there on two K tiles ahead count for more: 500 x 21000
+// x 8192 54.8 / 56.8, 1500 x 14336 x 6144 74.4 / 75.5.  128 tokens keep six at any length (W_LDS; unrolled by two 1000 x 5120 x 2504 15.6 -> 16.0).
+template <int TM_, int DEPTH_>
 struct PrefillTile {
-    static constexpr int TN = 2, TM = TM_, STAGES = 5, DEPTH = 3;
+    static constexpr int TN = 2, TM = TM_, STAGES = 5, DEPTH = DEPTH_, UNROLL = DEPTH == 2 ? 2 : 6;
     static constexpr bool W_LDS = TM == 4;          // five stages of both operands are 140 of the 160 KB of LDS; a larger tile's would not fit
     static constexpr int BN = 4 * TN * 32, BM = TM * 32;
     static constexpr int X_BYTES = BM * (X6_BLOCK / X6_ROWS), W_BYTES = TN * 32 * SEG;          // 3 KB per 32 tokens; a wave's 4 KB of weights
@@ -164,13 +170,13 @@ __device__ inline v16f mfma6(v8i w, v8i x, v16f c)
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w, x, c, 2, 2, 0, 0, 0, 0);
 }
 
-template <int TM, int STORE, bool DUMP, bool ZP>
+template <int TM, int STORE, bool DUMP, bool ZP, int DEPTH>
 __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     const uint8_t *__restrict__ x6, int64_t x_slab, const float *__restrict__ start, int start_parts, int rows,
     const uint8_t *__restrict__ wq, int M, int N, int ktiles, int tiles_m, int tiles_n, float s_a, const float *__restrict__ s_w,
     const float *__restrict__ d, int zp, const int32_t *__restrict__ wsum, uint16_t *__restrict__ y, int32_t *__restrict__ acc_out)
 {
-    typedef PrefillTile<TM> C;
+    typedef PrefillTile<TM, DEPTH> C;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -387,15 +393,20 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
             }
         }
     };
-    // unrolled by six, so that the weights' two or three register sets rotate without copies
+    // unrolled, so that the weights' two or three register sets rotate without copies
     int left = ktiles;
 #define FPTQ_TILE(i) tile(std::integral_constant<int, i>())
-    for (; left >= 6; left -= 6) FPTQ_TILE(0), FPTQ_TILE(1), FPTQ_TILE(2), FPTQ_TILE(3), FPTQ_TILE(4), FPTQ_TILE(5);
-    if (left > 0) FPTQ_TILE(0);
-    if (left > 1) FPTQ_TILE(1);
-    if (left > 2) FPTQ_TILE(2);
-    if (left > 3) FPTQ_TILE(3);
-    if (left > 4) FPTQ_TILE(4);
+    if constexpr (C::UNROLL == 2) {
+        for (; left >= 2; left -= 2) FPTQ_TILE(0), FPTQ_TILE(1);
+        if (left > 0) FPTQ_TILE(0);
+    } else {
+        for (; left >= 6; left -= 6) FPTQ_TILE(0), FPTQ_TILE(1), FPTQ_TILE(2), FPTQ_TILE(3), FPTQ_TILE(4), FPTQ_TILE(5);
+        if (left > 0) FPTQ_TILE(0);
+        if (left > 1) FPTQ_TILE(1);
+        if (left > 2) FPTQ_TILE(2);
+        if (left > 3) FPTQ_TILE(3);
+        if (left > 4) FPTQ_TILE(4);
+    }
 #undef FPTQ_TILE
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));   // drain the tail loads before LDS is reused
@@ -505,30 +516,32 @@ __global__ __launch_bounds__(256, 1) void linear_prefill_kernel(
     }
 }
 
-template <int TM, int STORE, bool DUMP, bool ZP>
+template <int TM, int STORE, bool DUMP, bool ZP, int DEPTH>
 static hipError_t set_prefill_attribute()
 {
-    return hipFuncSetAttribute((const void *)linear_prefill_kernel<TM, STORE, DUMP, ZP>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               PrefillTile<TM>::LDS_BYTES);
+    return hipFuncSetAttribute((const void *)linear_prefill_kernel<TM, STORE, DUMP, ZP, DEPTH>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               PrefillTile<TM, DEPTH>::LDS_BYTES);
 }
 
-template <int TM>
+template <int TM, int DEPTH>
 static hipError_t set_prefill_attributes()
 {
     hipError_t e = hipSuccess;
     auto one = [&](hipError_t r) { if (e == hipSuccess) e = r; };
-    one(set_prefill_attribute<TM, ANY_ALIGNMENT, true, false>()), one(set_prefill_attribute<TM, ANY_ALIGNMENT, true, true>());
-    one(set_prefill_attribute<TM, ANY_ALIGNMENT, false, false>()), one(set_prefill_attribute<TM, ANY_ALIGNMENT, false, true>());
-    one(set_prefill_attribute<TM, CACHED, false, false>()), one(set_prefill_attribute<TM, CACHED, false, true>());
-    one(set_prefill_attribute<TM, STREAMED, false, false>()), one(set_prefill_attribute<TM, STREAMED, false, true>());
+    one(set_prefill_attribute<TM, ANY_ALIGNMENT, true, false, DEPTH>()), one(set_prefill_attribute<TM, ANY_ALIGNMENT, true, true, DEPTH>());
+    one(set_prefill_attribute<TM, ANY_ALIGNMENT, false, false, DEPTH>()), one(set_prefill_attribute<TM, ANY_ALIGNMENT, false, true, DEPTH>());
+    one(set_prefill_attribute<TM, CACHED, false, false, DEPTH>()), one(set_prefill_attribute<TM, CACHED, false, true, DEPTH>());
+    one(set_prefill_attribute<TM, STREAMED, false, false, DEPTH>()), one(set_prefill_attribute<TM, STREAMED, false, true, DEPTH>());
     return e;
 }
 
 hipError_t prefill_device_init()
 {
-    hipError_t e = set_prefill_attributes<8>();
-    if (e == hipSuccess) e = set_prefill_attributes<6>();
-    if (e == hipSuccess) e = set_prefill_attributes<4>();
+    hipError_t e = set_prefill_attributes<8, 3>();
+    if (e == hipSuccess) e = set_prefill_attributes<8, 2>();
+    if (e == hipSuccess) e = set_prefill_attributes<6, 3>();
+    if (e == hipSuccess) e = set_prefill_attributes<6, 2>();
+    if (e == hipSuccess) e = set_prefill_attributes<4, 3>();
     return e;
 }
 
@@ -548,18 +561,18 @@ int64_t prefill_scratch_bytes(int64_t M, int64_t K) { return start_bytes(M) + k_
 
 int64_t prefill_workgroups(int64_t M, int64_t N, int tile_tokens)
 {
-    return ((M + tile_tokens - 1) / tile_tokens) * ((N + PrefillTile<8>::BN - 1) / PrefillTile<8>::BN);
+    return ((M + tile_tokens - 1) / tile_tokens) * ((N + PrefillTile<8, 3>::BN - 1) / PrefillTile<8, 3>::BN);
 }
 
-template <int TM>
+template <int TM, int DEPTH>
 static hipError_t launch_tile(const uint8_t *x6, const float *start, int split, const uint8_t *wq, int64_t M, int64_t N, int64_t K, float s_a,
                               const float *s_w, const float *d, int zp, const int32_t *wsum, uint16_t *y, int32_t *acc, hipStream_t s)
 {
-    typedef PrefillTile<TM> C;
+    typedef PrefillTile<TM, DEPTH> C;
     const int64_t tiles_m = (M + C::BM - 1) / C::BM, tiles_n = (N + C::BN - 1) / C::BN;
     if (tiles_m * tiles_n > 0x7fffffff) return hipErrorInvalidValue;
 #define FPTQ_PREFILL(A, D, Z)                                                                                                        \
-    linear_prefill_kernel<TM, A, D, Z><<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), C::LDS_BYTES, s>>>(                          \
+    linear_prefill_kernel<TM, A, D, Z, DEPTH><<<dim3((unsigned)(tiles_m * tiles_n)), dim3(256), C::LDS_BYTES, s>>>(                          \
         x6, x6_slab(M), start, split, (int)x6_rows(M), wq, (int)M, (int)N, (int)k_tiles(K), (int)tiles_m, (int)tiles_n, s_a, s_w, d,   \
         zp, wsum, y, acc)
     const bool z = wsum != nullptr;
@@ -590,11 +603,14 @@ hipError_t launch_linear_prefill(const uint8_t *xq, const uint8_t *wq, int64_t M
     widen_activations_kernel<<<dim3((unsigned)(rows / CV_ROWS), (unsigned)split), dim3(64 * CV_WAVES), 0, s>>>(
         xq, (int)M, x6_slab(M), (int)k_tiles(K), x6, start, rows);
     if ((e = hipGetLastError()) != hipSuccess) return e;
+    const bool few = k_tiles(K) <= 32;
+#define FPTQ_TOKENS(TM, DEPTH) launch_tile<TM, DEPTH>(x6, start, split, wq, M, N, K, s_a, s_w, d, zp, wsum, y, acc, s)
     switch (tile_tokens) {
-    case 128: return launch_tile<4>(x6, start, split, wq, M, N, K, s_a, s_w, d, zp, wsum, y, acc, s);
-    case 192: return launch_tile<6>(x6, start, split, wq, M, N, K, s_a, s_w, d, zp, wsum, y, acc, s);
-    default: return launch_tile<8>(x6, start, split, wq, M, N, K, s_a, s_w, d, zp, wsum, y, acc, s);
+    case 128: return FPTQ_TOKENS(4, 3);
+    case 192: return few ? FPTQ_TOKENS(6, 2) : FPTQ_TOKENS(6, 3);
+    default: return few ? FPTQ_TOKENS(8, 2) : FPTQ_TOKENS(8, 3);
     }
+#undef FPTQ_TOKENS
 }
 
 }  // namespace fptq

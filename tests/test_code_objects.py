@@ -92,3 +92,11 @@ def test_accumulators_are_set_once(assembly):
         tn, tm = (int(v) for v in re.search(r"GemmCfgILi\dELi\dELi(\d)ELi(\d)E", name).groups())
         before = text[:text.index("v_mfma")]
         assert len(re.findall(r"v_accvgpr_write_b32 a\d+, 0\b|v_mov_b32_e32 v\d+, 0\b", before)) < 1.5 * 16 * tn * tm, name
+
+
+def test_few_k_tiles_run_little_code(assembly):
+    """The six-bit kernel of up to 32 K tiles: two steps' code, and one for what is left over."""
+    found = assembly(r"linear_prefill_kernelILi[68]E\w*ELi2EEEv")
+    assert len(found) == 16
+    for name, text in found.items():
+        assert text.count("v_mfma") == 3 * 4 * int(re.search(r"ILi(\d)E", name).group(1)), name

@@ -54,6 +54,21 @@ def test_equals_the_int8_kernel(forced, M, N, K, zp):
     assert torch.equal(got[1], want[1]) and torch.equal(got[0].view(torch.int16), want[0].view(torch.int16))
 
 
+@pytest.mark.parametrize("tiles", range(30, 41))
+def test_k_tiles_around_the_line_of_the_loops(forced, tiles):
+    """Up to 32 K tiles run the loop unrolled by two (256 and 192 tokens), more of them the one unrolled by six, at each of its remainders."""
+    M, N, K = 203, 264 + tiles % 3, tiles * 128 - tiles % 4 * 41
+    torch.manual_seed(K)
+    xq = fptq.fptq_pack_weights(torch.randint(-8, 8, (M, K), dtype=torch.int8, device="cuda"))
+    wq = fptq.fptq_pack_weights(torch.randint(-8, 8, (N, K), dtype=torch.int8, device="cuda"))
+    s_w, d = torch.rand(N, device="cuda") * 0.015 + 0.005, torch.rand(M, device="cuda") + 0.5
+    want, acc = fptq.fptq_w4a4_linear_ref(xq, wq, M, N, K, 0.37, s_w, d, want_acc=True)
+    got = fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, 0.37, s_w, scratch_for(M, N, K), row_out_scale=d, want_acc=True)
+    assert torch.equal(got[1], acc) and torch.equal(got[0].view(torch.int16), want.view(torch.int16))
+    got = fptq.fptq_w4a4_linear_scratch(xq, wq, M, N, K, 0.37, s_w, scratch_for(M, N, K), row_out_scale=d)
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
 @pytest.mark.parametrize("M,N,zp,with_d", [(289, 264, None, False), (65, 257, None, False), (289, 264, None, True), (255, 72, 3, False), (130, 515, -8, True)])
 def test_epilogue_of_any_scale(forced, M, N, zp, with_d):
     """Channel scales from subnormal to infinite and NaN (the kernel folds a factor of 64 into ordinary ones), with and without token
