@@ -95,8 +95,8 @@ __device__ inline void swap_with_lanes(float (&v)[V])
 // last-level cache cannot hold (8192 x 28672: 123.0 us, 117.6 with; 4096 x 11008 from the cache 20.7 and 23.6).
 template <int MODE, int LOGB, bool STREAM>
 __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16_t *__restrict__ x, const float *__restrict__ row_in,
-                                                                    uint8_t *__restrict__ out, float *__restrict__ row_out, int M, int64_t K,
-                                                                    float inv_s_a, uint32_t parts, uint32_t per_parts, float eps)
+                                                                    uint8_t *__restrict__ out, float *__restrict__ row_out, uint32_t parts, uint32_t per_parts,
+                                                                    int M, float inv_s_a, int64_t K, float eps)
 {
     constexpr int R = LOGB <= 10 ? 1 : LOGB - 9, CH = 1 << R, V = 8 * CH, SPAN = 64 * V, B = 1 << LOGB;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -206,8 +206,8 @@ __device__ inline void butterflies16(float (&v)[16])
 
 template <int MODE, int LOGB>
 __global__ __launch_bounds__(1 << (LOGB - 4)) void quantize_act_hadamard_group_kernel(const uint16_t *__restrict__ x, const float *__restrict__ row_in,
-                                                                                     uint8_t *__restrict__ out, float *__restrict__ row_out, int M, int64_t K,
-                                                                                     float inv_s_a, uint32_t blocks, uint32_t per_blocks)
+                                                                                     uint8_t *__restrict__ out, float *__restrict__ row_out, uint32_t blocks,
+                                                                                     uint32_t per_blocks, int M, float inv_s_a, int64_t K)
 {
     static_assert(LOGB == 11 || LOGB == 12, "views of four bits");
     constexpr int B = 1 << LOGB, THREADS = B / 16, LOW = LOGB - 8;      // LOW bits below the second view's four
@@ -263,9 +263,9 @@ static hipError_t launch_group(const uint16_t *x, int64_t M, int64_t K, int mode
     const uint32_t blocks = (uint32_t)(K >> LOGB);
     const dim3 grid((unsigned)(M * blocks)), block(1 << (LOGB - 4));
     if (mode == FPTQ_SCALE_GIVEN)
-        quantize_act_hadamard_group_kernel<FPTQ_SCALE_GIVEN, LOGB><<<grid, block, 0, s>>>(x, row_in, out, row_out, (int)M, K, inv_s_a, blocks, reciprocal(blocks));
+        quantize_act_hadamard_group_kernel<FPTQ_SCALE_GIVEN, LOGB><<<grid, block, 0, s>>>(x, row_in, out, row_out, blocks, reciprocal(blocks), (int)M, inv_s_a, K);
     else
-        quantize_act_hadamard_group_kernel<FPTQ_SCALE_NONE, LOGB><<<grid, block, 0, s>>>(x, row_in, out, row_out, (int)M, K, inv_s_a, blocks, reciprocal(blocks));
+        quantize_act_hadamard_group_kernel<FPTQ_SCALE_NONE, LOGB><<<grid, block, 0, s>>>(x, row_in, out, row_out, blocks, reciprocal(blocks), (int)M, inv_s_a, K);
     return hipGetLastError();
 }
 
@@ -281,7 +281,7 @@ static hipError_t launch_spans(const uint16_t *x, int64_t M, int64_t K, int mode
     if (M > 0x7fffffff || M * parts > 0xffffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((M * parts + 3) / 4)), block(256);
 #define FPTQ_LAUNCH_SPANS(MODE, STREAM) \
-    quantize_act_hadamard_kernel<MODE, LOGB, STREAM><<<grid, block, 0, s>>>(x, row_in, out, row_out, (int)M, K, inv_s_a, (uint32_t)parts, reciprocal((uint32_t)parts), eps)
+    quantize_act_hadamard_kernel<MODE, LOGB, STREAM><<<grid, block, 0, s>>>(x, row_in, out, row_out, (uint32_t)parts, reciprocal((uint32_t)parts), (int)M, inv_s_a, K, eps)
     const bool stream = M * K * 2 > ((int64_t)256 << 20);
     if (mode == FPTQ_SCALE_RMS) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_RMS, false);      // reads the row twice
     else if (mode == FPTQ_SCALE_GIVEN && stream) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_GIVEN, true);

@@ -69,6 +69,18 @@ def test_arguments_of_the_static_quantizers_come_with_the_dispatch(kernels):
     assert seen > 30
 
 
+def test_arguments_that_addresses_need_come_with_the_dispatch(kernels):
+    """The quantizers that cut a row into pieces divide by the pieces of a row before their first load.  Only eps, which the sum comes before, may lie beyond."""
+    seen = 0
+    for name, text in kernels.items():
+        if re.search(r"quantize_act_(flat|hadamard|hadamard_group)_kernel", name):
+            ends = [int(o) + int(s) for o, s, kind in re.findall(r"\.offset:\s+(\d+)\n\s+\.size:\s+(\d+)\n\s+\.value_kind:\s+(\w+)", text) if not kind.startswith("hidden")]
+            late = 1 if "hadamard_kernel" in name else 0
+            assert len(ends) == (9 if "group" in name else 10) and sum(e > 56 for e in ends) == late and ends[-1] <= 60, (name, ends)
+            seen += 1
+    assert seen == 6 + 25 + 4
+
+
 def test_scratch_only_where_it_is_stated(kernels):
     """Of the instances that calls run: the INT8 256 x 256 tile at any width or with a zero point, the six-bit 256-token tile of whole 16-byte rows."""
     stated = (r"linear_mfma_kernelINS_7GemmCfgILi2ELi2ELi4ELi4ELi4ELi1ELi1ELb0EEE(Li0ELb0ELb[01]E|Li[12]ELb0ELb1E)",
