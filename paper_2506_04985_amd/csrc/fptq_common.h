@@ -217,6 +217,7 @@ __device__ inline uint32_t other_lane(uint32_t v)        // of lane ^ OFF, OFF <
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);                             // quad_perm [1,0,3,2]
 }
 
+template <bool ALL = true>                               // else: every lane with the sum of those whose bit 4 is the same
 __device__ inline double wave_sum(double v)
 {
     auto join = [](uint32_t lo, uint32_t hi) { return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo); };
@@ -225,8 +226,10 @@ __device__ inline double wave_sum(double v)
     // a swap of a register with itself leaves the values of one side of each pair in the first result, of the other in the second
     const auto l32 = __builtin_amdgcn_permlane32_swap(lo(v), lo(v), false, false), h32 = __builtin_amdgcn_permlane32_swap(hi(v), hi(v), false, false);
     v = join(l32[0], h32[0]) + join(l32[1], h32[1]);
-    const auto l16 = __builtin_amdgcn_permlane16_swap(lo(v), lo(v), false, false), h16 = __builtin_amdgcn_permlane16_swap(hi(v), hi(v), false, false);
-    v = join(l16[0], h16[0]) + join(l16[1], h16[1]);
+    if (ALL) {
+        const auto l16 = __builtin_amdgcn_permlane16_swap(lo(v), lo(v), false, false), h16 = __builtin_amdgcn_permlane16_swap(hi(v), hi(v), false, false);
+        v = join(l16[0], h16[0]) + join(l16[1], h16[1]);
+    }
     v += join(other_lane<8>(lo(v)), other_lane<8>(hi(v)));
     v += join(other_lane<4>(lo(v)), other_lane<4>(hi(v)));
     v += join(other_lane<2>(lo(v)), other_lane<2>(hi(v)));

@@ -7,7 +7,7 @@ from oracle import transforms as T
 from paper_2506_04985_amd import binding as fptq
 import fptq_workloads as synth
 
-from gpu_util import dev, dev_bf16, host_bits, y_error, Y_TOL
+from gpu_util import launched, dev, dev_bf16, host_bits, y_error, Y_TOL
 
 pytestmark = pytest.mark.gpu
 
@@ -75,6 +75,22 @@ def test_many_blocks_equal_few(mode, M, K, B):
         part = slice(i, i + M // 4)
         qp, sp = fptq.fptq_quantize_act_hadamard(x[part], 0.4, B, mode, 1e-5, None if r is None else r[part].clone())
         assert torch.equal(fptq.fptq_unpack(qp, M // 4, K), q[part]) and torch.equal(sp, s[part])
+
+
+@pytest.mark.parametrize("mode", [synth.MODE_NONE, synth.MODE_RMS, synth.MODE_GIVEN])
+@pytest.mark.parametrize("M,K", [(1, 512), (2, 512), (3, 512), (256, 512), (257, 512), (1000, 512), (1, 1536), (2, 1536), (301, 1536), (3, 2560), (258, 4608)])
+def test_odd_numbers_of_blocks_of_512(oracle, mode, M, K):
+    """A wave takes two consecutive blocks, also of two rows (RMS scale: rows of one block): no wave of a row's end is half idle."""
+    inp = synth.draw(case(M, K, mode, seed=M * 3 + K), with_weights=False)
+    xb = inp.x_bits
+    r_ref = oracle.row_scale(xb, mode, 1e-5, inp.row_scale_in)
+    x, given, out, r = dev_bf16(xb), dev(inp.row_scale_in), torch.full((fptq.fptq_packed_bytes(M, K),), 0xEE, dtype=torch.uint8, device="cuda"), dev(np.zeros(M, np.float32))
+    call = lambda: fptq.fptq_quantize_act_hadamard(x, 0.5, 512, mode, 1e-5, given, out=out, row_scale_out=r)
+    call()
+    assert np.array_equal(r.cpu().numpy().view(np.uint32), r_ref.view(np.uint32))
+    assert np.array_equal(fptq.fptq_unpack(out, M, K).cpu().numpy(), oracle.quantize_hadamard(xb, np.float32(0.5), 512, None if mode == synth.MODE_NONE else r_ref))
+    if mode != synth.MODE_RMS or K == 512:
+        assert launched(call)[1] == ((M * K // 512 + 1) // 2 + 3) // 4
 
 
 def largest_block_matches(K, B):
