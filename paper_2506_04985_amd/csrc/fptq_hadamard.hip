@@ -91,14 +91,16 @@ __device__ inline void swap_with_lanes(float (&v)[V])
 // differ by 8, 7, 2 and 1, which DPP reaches: with lane bits l3 .. l0 they are l3, l2, l1 ^ l2, l0 ^ l2.  What is left is in the chunk.  A lane
 // ends up with whole words of codes, 16 lanes with the 64 bytes of a row in a K tile.
 //
-// RMS: the scale comes from the whole row, which every wave of it sums, so `parts` waves share a row and walk its spans.  STREAM: inputs that the
+// WALK: `parts` waves share a row and walk its spans.  RMS scale: it comes from the whole row, which every wave of it sums.  Given or none: calls of more spans
+// than a launch may have waves.  STREAM: inputs that the
 // last-level cache cannot hold (8192 x 28672: 123.0 us, 117.6 with; 4096 x 11008 from the cache 20.7 and 23.6).
 //
 // PAIRS (B = 512, rows of an odd number of blocks; with RMS scale of one, whose sum the wave then has in registers): a wave takes two consecutive blocks
 // whatever rows they are of, `parts` is the blocks of a row.  With half a wave idle at the end of every row, short rows were slower than in the kernel that walked
 // rows a block at a time (us, that kernel / half idle / now; in brackets inputs from the cache): 65536 x 512 26.8 / 32.9 / 22.1 (23.0 / 30.7 / 19.3), 30000 x
 // 1536 33.1 / 32.5 / 27.7 (26.2 / 29.4 / 23.3), 3000 x 512 3.6 / 4.0 / 3.5, 4096 x 4608 15.6 / 13.3 / 12.6; RMS 65536 x 512 38.6 / 43.4 / 23.6.
-template <int MODE, int LOGB, bool STREAM, bool PAIRS>
+enum { SPANS, WALK, PAIRS };
+template <int MODE, int LOGB, bool STREAM, int FORM>
 __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16_t *__restrict__ x, const float *__restrict__ row_in,
                                                                     uint8_t *__restrict__ out, float *__restrict__ row_out, uint32_t parts, uint32_t per_parts,
                                                                     int M, float inv_s_a, int64_t K, float eps)
@@ -106,7 +108,7 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16
     constexpr int R = LOGB <= 10 ? 1 : LOGB - 9, CH = 1 << R, V = 8 * CH, SPAN = 64 * V, B = 1 << LOGB;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint32_t t, part;
-    divide((blockIdx.x * 4 + wave) * (PAIRS ? 2 : 1), parts, per_parts, t, part);
+    divide((blockIdx.x * 4 + wave) * (FORM == PAIRS ? 2 : 1), parts, per_parts, t, part);
     if (t >= (uint32_t)M) return;                        // whole waves leave; nothing below synchronises
     const uint16_t *row = x + (int64_t)t * K;
     const int l5 = lane >> 5, l4 = lane >> 4 & 1;
@@ -114,17 +116,17 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16
     const int from = chunk * 8 + (LOGB == 8 ? (l5 * 2 + l4) * 256 : LOGB == 9 ? l4 * 512 + l5 * 128 : l5 * 256 + l4 * 128);
     constexpr int FROM_STEP = LOGB == 8 ? 128 : LOGB == 9 ? 256 : 512;
     // PAIRS: the second block may be the next row's first, or none
-    const bool next_row = PAIRS && part + 1 == parts, second = !next_row || t + 1 < (uint32_t)M;
-    const uint32_t own_t = next_row && l4 ? (second ? t + 1 : t) : t, own_block = PAIRS && l4 ? (next_row ? 0 : part + 1) : part;
+    const bool next_row = FORM == PAIRS && part + 1 == parts, second = !next_row || t + 1 < (uint32_t)M;
+    const uint32_t own_t = next_row && l4 ? (second ? t + 1 : t) : t, own_block = FORM == PAIRS && l4 ? (next_row ? 0 : part + 1) : part;
     v4u regs[CH];
     auto load = [&](int64_t at) {
         // lanes of blocks past the row's end (PAIRS: the last row's) repeat the span's first one
-        const int live = PAIRS ? (second ? SPAN : B) : (int)min((int64_t)SPAN, K - at);
+        const int live = FORM == PAIRS ? (second ? SPAN : B) : (int)min((int64_t)SPAN, K - at);
         const v4u *src = reinterpret_cast<const v4u *>(row + at + (SPAN > B && from >= live ? from % B : from));
 #pragma unroll
         for (int r = 0; r < CH; ++r) regs[r] = STREAM ? __builtin_nontemporal_load(src + r * (FROM_STEP / 8)) : src[r * (FROM_STEP / 8)];
     };
-    int64_t at = (int64_t)part * (PAIRS ? B : SPAN);
+    int64_t at = (int64_t)part * (FORM == PAIRS ? B : SPAN);
     load(at);
 
     float s = 1.0f;
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16
                 ss = __builtin_fma(b, b, ss);
             }
         };
-        if (PAIRS) {                                     // rows of one block, which the lanes with the same l4 hold
+        if (FORM == PAIRS) {                                     // rows of one block, which the lanes with the same l4 hold
 #pragma unroll
             for (int r = 0; r < CH; ++r) add({regs[r].x, regs[r].y, regs[r].z, regs[r].w});
         } else {
@@ -147,12 +149,12 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16
                 add({u.x, u.y, u.z, u.w});
             }
         }
-        ss = wave_sum<!PAIRS>(ss);
+        ss = wave_sum<FORM != PAIRS>(ss);
         s = (float)(1.0 / sqrt(ss / (double)K + (double)eps));
     } else if (MODE == FPTQ_SCALE_GIVEN) {
-        s = row_in[PAIRS ? own_t : t];
+        s = row_in[own_t];
     }
-    if (PAIRS) {
+    if (FORM == PAIRS) {
         if ((lane & ~16) == 0 && own_block == 0 && (l4 == 0 || second) && row_out) row_out[own_t] = s;
     } else if (lane == 0 && part == 0 && row_out) {
         row_out[t] = s;
@@ -160,7 +162,7 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16
     auto sign = [&](int bit) { return chunk & bit ? -1.0f : 1.0f; };
     const float c = ((MODE == FPTQ_SCALE_NONE) ? inv_s_a : s * inv_s_a) * hadamard_norm(LOGB) * (sign(1) * sign(2) * sign(4) * sign(8));
 
-    const int tile_l = LOGB == 8 ? l5 * 4 + l4 * 2 : LOGB == 9 ? (PAIRS ? 0 : l4 * 4) + l5 * 2 : LOGB == 10 ? l5 * 4 + l4 * 2 : LOGB == 11 ? l5 * 8 + l4 * 4 : l5 * 16 + l4 * 8;
+    const int tile_l = LOGB == 8 ? l5 * 4 + l4 * 2 : LOGB == 9 ? (FORM == PAIRS ? 0 : l4 * 4) + l5 * 2 : LOGB == 10 ? l5 * 4 + l4 * 2 : LOGB == 11 ? l5 * 8 + l4 * 4 : l5 * 16 + l4 * 8;
     for (;;) {
         float v[V], squares = 0.0f;
 #pragma unroll
@@ -175,7 +177,7 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16
         const bool tame = __builtin_amdgcn_ballot_w64(!(squares < TAME && __builtin_fabsf(c) < TAME)) == 0;
         const int64_t here = at;
         at += (int64_t)parts * SPAN;
-        if (MODE == FPTQ_SCALE_RMS && !PAIRS && at < K) load(at);
+        if (FORM == WALK && at < K) load(at);
         if constexpr (R == 3) register_stage<32>(v);
         if constexpr (R >= 2) register_stage<16>(v);
         register_stage<8>(v);
@@ -200,10 +202,10 @@ __global__ __launch_bounds__(256) void quantize_act_hadamard_kernel(const uint16
                 for (int e = 0; e < 8; ++e) w ^= quant_code(v[8 * r + e], c, 8) << (4 * e);
             }
             // K tile of the chunk: the bits that the swaps have left in its number, and in lane bits 5 and 4
-            const int64_t tile = (PAIRS ? (int64_t)own_block * (B / KT) : here / KT) + tile_l + (LOGB <= 11 ? r : (r & 1) * 4 + (r >> 2) * 2 + (r >> 1 & 1));
-            if (PAIRS ? l4 == 0 || second : SPAN == B || tile * KT < K) *reinterpret_cast<uint32_t *>(out + (tile * M + own_t) * SEG + chunk * 4) = w;
+            const int64_t tile = (FORM == PAIRS ? (int64_t)own_block * (B / KT) : here / KT) + tile_l + (LOGB <= 11 ? r : (r & 1) * 4 + (r >> 2) * 2 + (r >> 1 & 1));
+            if (FORM == PAIRS ? l4 == 0 || second : SPAN == B || tile * KT < K) *reinterpret_cast<uint32_t *>(out + (tile * M + own_t) * SEG + chunk * 4) = w;
         }
-        if (PAIRS || MODE != FPTQ_SCALE_RMS || at >= K) return;
+        if (FORM != WALK || at >= K) return;
     }
 }
 
@@ -296,35 +298,38 @@ static hipError_t launch_spans(const uint16_t *x, int64_t M, int64_t K, int mode
                                float *row_out, hipStream_t s)
 {
     constexpr int64_t SPAN = LOGB <= 10 ? 1024 : 1 << LOGB;
-    int64_t parts = (K + SPAN - 1) / SPAN, waves;
-    const bool pairs = LOGB == 9 && K % 1024 == 512 && (mode != FPTQ_SCALE_RMS || K == 512);
+    if (M > MAX_WAVES) return hipErrorInvalidConfiguration;
+    int64_t parts = (K + SPAN - 1) / SPAN, waves = M * parts;
+    const bool rms = mode == FPTQ_SCALE_RMS, stream = M * K * 2 > ((int64_t)256 << 20);
+    const bool pairs = LOGB == 9 && K % 1024 == 512 && (!rms || K == 512) && M * (K / 512) <= 2 * MAX_WAVES, walk = !pairs && (rms || waves > MAX_WAVES);
     if (pairs) {
         parts = K / 512;
         waves = (M * parts + 1) / 2;
-    } else {
-        if (mode == FPTQ_SCALE_RMS) parts = M > 256 ? 1 : parts < (4096 + M - 1) / M ? parts : (4096 + M - 1) / M;
+    } else if (walk) {
+        const int64_t want = !rms ? MAX_WAVES / M : M > 256 ? 1 : (4096 + M - 1) / M;
+        parts = parts < want ? parts : want;
         waves = M * parts;
     }
-    if (M > 0x7fffffff || waves > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((waves + 3) / 4)), block(256);
-#define FPTQ_LAUNCH_SPANS(MODE, STREAM, PAIRS) \
-    quantize_act_hadamard_kernel<MODE, LOGB, STREAM, PAIRS><<<grid, block, 0, s>>>(x, row_in, out, row_out, (uint32_t)parts, reciprocal((uint32_t)parts), (int)M, inv_s_a, K, eps)
-    const bool stream = M * K * 2 > ((int64_t)256 << 20);
+#define FPTQ_LAUNCH_SPANS(MODE, STREAM, FORM) \
+    quantize_act_hadamard_kernel<MODE, LOGB, STREAM, FORM><<<grid, block, 0, s>>>(x, row_in, out, row_out, (uint32_t)parts, reciprocal((uint32_t)parts), (int)M, inv_s_a, K, eps)
     if constexpr (LOGB == 9) {
         if (pairs) {
-            if (mode == FPTQ_SCALE_RMS) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_RMS, false, true);
-            else if (mode == FPTQ_SCALE_GIVEN && stream) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_GIVEN, true, true);
-            else if (mode == FPTQ_SCALE_GIVEN) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_GIVEN, false, true);
-            else if (stream) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_NONE, true, true);
-            else FPTQ_LAUNCH_SPANS(FPTQ_SCALE_NONE, false, true);
+            if (rms) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_RMS, false, PAIRS);
+            else if (mode == FPTQ_SCALE_GIVEN && stream) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_GIVEN, true, PAIRS);
+            else if (mode == FPTQ_SCALE_GIVEN) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_GIVEN, false, PAIRS);
+            else if (stream) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_NONE, true, PAIRS);
+            else FPTQ_LAUNCH_SPANS(FPTQ_SCALE_NONE, false, PAIRS);
             return hipGetLastError();
         }
     }
-    if (mode == FPTQ_SCALE_RMS) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_RMS, false, false);      // reads the row twice
-    else if (mode == FPTQ_SCALE_GIVEN && stream) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_GIVEN, true, false);
-    else if (mode == FPTQ_SCALE_GIVEN) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_GIVEN, false, false);
-    else if (stream) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_NONE, true, false);
-    else FPTQ_LAUNCH_SPANS(FPTQ_SCALE_NONE, false, false);
+    if (rms) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_RMS, false, WALK);                   // reads the row twice
+    else if (mode == FPTQ_SCALE_GIVEN && walk) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_GIVEN, true, WALK);
+    else if (mode == FPTQ_SCALE_GIVEN && stream) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_GIVEN, true, SPANS);
+    else if (mode == FPTQ_SCALE_GIVEN) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_GIVEN, false, SPANS);
+    else if (walk) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_NONE, true, WALK);
+    else if (stream) FPTQ_LAUNCH_SPANS(FPTQ_SCALE_NONE, true, SPANS);
+    else FPTQ_LAUNCH_SPANS(FPTQ_SCALE_NONE, false, SPANS);
 #undef FPTQ_LAUNCH_SPANS
     return hipGetLastError();
 }

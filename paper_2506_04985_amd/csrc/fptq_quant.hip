@@ -394,14 +394,19 @@ __global__ __launch_bounds__(QT) void quantize_act_flat_kernel(const uint16_t *_
 // More than the last-level cache holds: streaming loads, four chunks a lane (8192 x 28672: 104 us, one chunk 110, without streaming 113 to 124).  16 to
 // 40 MB: four chunks (4096 x 4096 9.7 us, one 10.2, from the cache 7.1 and 8.5; 1000 x 13824 9.0 and 9.1, 6.2 and 6.8).  Otherwise one (768 x
 // 4096 3.1 us, four 3.8; 2048 x 11008 12.9 and 13.8; 4096 x 14336 29.0 and 30.1).
+static int flat_chunks(int64_t M, int64_t K)
+{
+    const int64_t mb = M * K * 2 >> 20;
+    return M * K * 2 > ((int64_t)256 << 20) || (mb >= 16 && mb < 40) ? 4 : 1;
+}
+static int64_t flat_pieces(int64_t M, int64_t K) { return (K + 512 * flat_chunks(M, K) - 1) / (512 * flat_chunks(M, K)); }
+
 template <int MODE>
 static hipError_t launch_flat(const uint16_t *x, int64_t M, int64_t K, const float *row_in, float inv_s_a, int zoff, uint8_t *out, float *row_out, hipStream_t s)
 {
-    const int64_t mb = M * K * 2 >> 20;
     const bool stream = M * K * 2 > ((int64_t)256 << 20);
-    const int ch = stream || (mb >= 16 && mb < 40) ? 4 : 1;
-    const int64_t pieces = (K + 512 * ch - 1) / (512 * ch);
-    if (M * pieces > 0xffffffff) return hipErrorInvalidValue;
+    const int ch = flat_chunks(M, K);
+    const int64_t pieces = flat_pieces(M, K);
     const dim3 grid((unsigned)((M * pieces + QT / 64 - 1) / (QT / 64))), block(QT);
 #define FPTQ_FLAT(CH, STREAM) quantize_act_flat_kernel<MODE, CH, STREAM><<<grid, block, 0, s>>>(x, out, row_out, row_in, (int)M, (int)K, inv_s_a, zoff, (uint32_t)pieces, reciprocal((uint32_t)pieces))
     if (stream) FPTQ_FLAT(4, true);
@@ -426,7 +431,7 @@ static hipError_t launch_mode(const uint16_t *x, int64_t M, int64_t K, float eps
         return hipGetLastError();                                                                                           \
     }
     if constexpr (MODE != FPTQ_SCALE_RMS) {
-        if (vec && K <= (1 << 28)) return launch_flat<MODE>(x, M, K, row_in, inv_s_a, zoff, out, row_out, s);
+        if (vec && K <= (1 << 28) && M * flat_pieces(M, K) <= MAX_WAVES) return launch_flat<MODE>(x, M, K, row_in, inv_s_a, zoff, out, row_out, s);
     } else if (vec) {
         // An input that the 256 MB last-level cache cannot hold is read with streaming loads (8192 x 28672: 119 us
         // against 142); a smaller one is usually still there from its producer, and ordinary loads are faster on it.
@@ -450,7 +455,7 @@ static hipError_t launch_mode(const uint16_t *x, int64_t M, int64_t K, float eps
         FPTQ_ROW_CASE(16, false)
     }
     constexpr int stream_in = 0;
-    if (!vec) {
+    if (!vec || MODE != FPTQ_SCALE_RMS) {
         if (wave_per_row(false, M, K)) {
             WAVE_PER_ROW_RAGGED(Kpad, FPTQ_WAVE_CASE);
             return hipGetLastError();

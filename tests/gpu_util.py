@@ -65,13 +65,11 @@ def run_gpu_linear(inp, M=None, use_ref=False, want_acc=True, undo_scale=False):
             "y": host_bits(y), "d": None if d is None else d.cpu().numpy()}
 
 
-def launched(call):
-    """(kernel, workgroups) of the one launch that a call makes, from its captured graph; kernels are told apart by their handles."""
+def captured(call):
+    """(kernel, workgroups, threads of one) of the one launch that a call makes, from its captured graph, which is not run; kernels are told apart by their handles."""
     class Params(ctypes.Structure):
         _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint32 * 3),
                     ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
-    call()
-    torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph(keep_graph=True)
     with torch.cuda.graph(graph):
         call()
@@ -81,4 +79,11 @@ def launched(call):
     node, params = ctypes.c_void_p(), Params()
     assert hip.hipGraphGetNodes(raw, ctypes.byref(node), ctypes.byref(count)) == 0
     assert hip.hipGraphKernelNodeGetParams(node, ctypes.byref(params)) == 0
-    return params.func, params.grid[0]
+    return params.func, params.grid[0], params.block[0]
+
+
+def launched(call):
+    """(kernel, workgroups) of the one launch that a call makes, after an ordinary one."""
+    call()
+    torch.cuda.synchronize()
+    return captured(call)[:2]
