@@ -391,13 +391,22 @@ __global__ __launch_bounds__(QT) void quantize_act_flat_kernel(const uint16_t *_
     }
 }
 
-// More than the last-level cache holds: streaming loads, four chunks a lane (8192 x 28672: 104 us, one chunk 110, without streaming 113 to 124).  16 to
-// 40 MB: four chunks (4096 x 4096 9.7 us, one 10.2, from the cache 7.1 and 8.5; 1000 x 13824 9.0 and 9.1, 6.2 and 6.8).  Otherwise one (768 x
-// 4096 3.1 us, four 3.8; 2048 x 11008 12.9 and 13.8; 4096 x 14336 29.0 and 30.1).
+// Chunks a lane.  One below 16 MB, where larger pieces would leave waves' places empty (768 x 4096 3.1 us, four chunks 3.8), and for rows of up to 512 values.
+// Other short rows are a piece each: cut by 512 values, their last piece is mostly padding (85481 x 1104 55.2 us, in one piece 48.3; 45900 x 2056 51.4 and 44.7, from the
+// cache 24320 x 2048 39.0 and 36.0), and chunks that lie past a row's end are computed all the same (40000 x 256 in pieces of four 15.0 us, of one 9.9; 524288 x 512 170
+// and 126; 97280 x 1024 in pieces of four 46.3, of two 44.2).  Longer rows, up to 40 MB, which four chunks a lane bring to the CUs in one round or little more: four (4096 x
+// 4096 9.8 us, one 10.05, from the cache 7.1 and 8.3), but not where a sixteenth or more is padding (1700 x 11008 11.7, one 10.6); beyond, one (4096 x
+// 14336 29.0, four 30.1), but not where so much is padding with one (19660 x 3200 33.1, four 30.8; 22995 x 4104 49.4, six 47.3).  More than the last-level cache holds:
+// streaming loads, four chunks (8192 x 28672 102 us, one 110, without streaming 113 to 124).
 static int flat_chunks(int64_t M, int64_t K)
 {
     const int64_t mb = M * K * 2 >> 20;
-    return M * K * 2 > ((int64_t)256 << 20) || (mb >= 16 && mb < 40) ? 4 : 1;
+    auto little_padding = [&](int64_t piece) { return (K + piece - 1) / piece * piece * 16 <= K * 17; };
+    if (mb < 16 || K <= 512) return 1;
+    if (K <= 3072) return K <= 1024 ? 2 : K <= 2048 ? 4 : 6;
+    if (M * K * 2 > ((int64_t)256 << 20)) return K <= 4096 ? 8 : 4;
+    if (mb < 40) return K <= 4096 || little_padding(2048) ? 4 : 1;
+    return little_padding(512) ? 1 : K <= 4096 ? 4 : 6;
 }
 static int64_t flat_pieces(int64_t M, int64_t K) { return (K + 512 * flat_chunks(M, K) - 1) / (512 * flat_chunks(M, K)); }
 
@@ -405,13 +414,22 @@ template <int MODE>
 static hipError_t launch_flat(const uint16_t *x, int64_t M, int64_t K, const float *row_in, float inv_s_a, int zoff, uint8_t *out, float *row_out, hipStream_t s)
 {
     const bool stream = M * K * 2 > ((int64_t)256 << 20);
-    const int ch = flat_chunks(M, K);
     const int64_t pieces = flat_pieces(M, K);
     const dim3 grid((unsigned)((M * pieces + QT / 64 - 1) / (QT / 64))), block(QT);
 #define FPTQ_FLAT(CH, STREAM) quantize_act_flat_kernel<MODE, CH, STREAM><<<grid, block, 0, s>>>(x, out, row_out, row_in, (int)M, (int)K, inv_s_a, zoff, (uint32_t)pieces, reciprocal((uint32_t)pieces))
-    if (stream) FPTQ_FLAT(4, true);
-    else if (ch == 4) FPTQ_FLAT(4, false);
-    else FPTQ_FLAT(1, false);
+#define FPTQ_FLAT_CASE(CH)                    \
+    case CH:                                  \
+        if (stream) FPTQ_FLAT(CH, true);      \
+        else FPTQ_FLAT(CH, false);            \
+        break
+    switch (flat_chunks(M, K)) {
+        FPTQ_FLAT_CASE(1);
+        FPTQ_FLAT_CASE(2);
+        FPTQ_FLAT_CASE(4);
+        FPTQ_FLAT_CASE(6);
+    default: FPTQ_FLAT(8, true);
+    }
+#undef FPTQ_FLAT_CASE
 #undef FPTQ_FLAT
     return hipGetLastError();
 }

@@ -78,7 +78,7 @@ def test_arguments_that_addresses_need_come_with_the_dispatch(kernels):
             late = 1 if "hadamard_kernel" in name else 0
             assert len(ends) == (9 if "group" in name else 10) and sum(e > 56 for e in ends) == late and ends[-1] <= 60, (name, ends)
             seen += 1
-    assert seen == 6 + 40 + 4
+    assert seen == 18 + 40 + 4
 
 
 def test_scratch_only_where_it_is_stated(kernels):

@@ -7,7 +7,7 @@ import torch
 from paper_2506_04985_amd import binding as fptq
 import fptq_workloads as synth
 
-from gpu_util import dev, dev_bf16
+from gpu_util import dev, dev_bf16, launched
 
 pytestmark = pytest.mark.gpu
 MODES = [synth.MODE_NONE, synth.MODE_GIVEN]
@@ -39,6 +39,29 @@ def test_static_quantizer_in_pieces(oracle, mode, M, K):
         assert np.array_equal(r.cpu().numpy().view(np.uint32), r_ref.view(np.uint32))
         q = fptq.fptq_unpack(xq, M, K).cpu().numpy()
         assert np.array_equal(q[rows], oracle.quantize(bits[rows], np.float32(0.4), r_ref[rows]))
+
+
+@pytest.mark.parametrize("M,K,pieces", [(2048, 4088, 8), (2056, 4096, 2), (40000, 256, 1), (20000, 512, 1), (14000, 1024, 1), (13297, 1104, 1), (7140, 2056, 1), (85481, 1104, 1),
+                                        (45900, 2056, 1), (4000, 3080, 2), (1790, 8200, 17), (1700, 11008, 22), (1000, 13824, 7), (4096, 14336, 28), (8000, 3200, 2),
+                                        (10000, 4104, 2), (524288, 512, 1), (35000, 4096, 1), (33000, 4400, 3)])
+def test_pieces_of_a_row(M, K, pieces):
+    """Short rows are not cut, and no piece is mostly padding; codes as those of ten rows, which are cut by 512 values."""
+    torch.manual_seed(M)
+    x, r = torch.randn((M, K), device="cuda").to(torch.bfloat16), torch.rand(M, device="cuda") + 0.5
+    out, r_out = torch.full((fptq.fptq_packed_bytes(M, K),), 0xEE, dtype=torch.uint8, device="cuda"), torch.empty_like(r)
+    assert launched(lambda: fptq.fptq_quantize_act(x, 0.4, synth.MODE_GIVEN, 0.0, r, out=out, row_scale_out=r_out))[1] == (M * pieces + 3) // 4
+    assert torch.equal(r, r_out)
+    for i in (0, M // 2 + 1, M - 10):
+        part, _ = fptq.fptq_quantize_act(x[i:i + 10], 0.4, synth.MODE_GIVEN, 0.0, r[i:i + 10].clone())
+        assert torch.equal(out.view(-1, M, 64)[:, i:i + 10], part.view(-1, 10, 64))
+
+
+def test_one_chunk_for_the_shortest_rows():
+    """Chunks that lie past a row's end are loaded and computed all the same."""
+    def kernel(M, K):
+        x, out = torch.zeros((M, K), dtype=torch.bfloat16, device="cuda"), torch.empty(fptq.fptq_packed_bytes(M, K), dtype=torch.uint8, device="cuda")
+        return launched(lambda: fptq.fptq_quantize_act(x, 0.4, synth.MODE_NONE, 0.0, None, out=out, want_row_scale=False))[0]
+    assert kernel(40000, 256) == kernel(20000, 512) == kernel(100, 512) != kernel(14000, 1024)
 
 
 @pytest.mark.parametrize("mode", MODES)
