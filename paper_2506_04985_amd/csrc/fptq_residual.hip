@@ -136,8 +136,10 @@ hipError_t launch_residual_norm_quantize(const uint16_t *xr, const uint16_t *yb,
     const bool vec = K % 8 == 0 && ((reinterpret_cast<uintptr_t>(xr) | reinterpret_cast<uintptr_t>(yb) |
                                      reinterpret_cast<uintptr_t>(x_next)) & 15) == 0;
     // As for the plain quantizer: a wave per row for many short rows, otherwise a workgroup per
-    // row, which spreads a row over four waves (32 x 4096: 4.3 us with a wave per row).
-    if (wave_per_row(vec, M, K, 3072)) {
+    // row, which spreads a row over four waves (32 x 4096: 4.3 us with a wave per row).  Of 3073 to 4096 values only up to 16384 rows: beyond, what a
+    // workgroup gains at a call's start and end no longer shows (wave / workgroup, from HBM and from the cache: 8192 x 4096 43.9 / 44.2, 33.3 / 32.5; 16000 x 4096 79.3 /
+    // 81.5, 79.7 / 82.7; 20000 x 3200 77.1 / 79.4, 77.1 / 78.9; 30000 x 4096 148 / 157, 148 / 157).
+    if (wave_per_row(vec, M, K, M < 16384 ? 3072 : 4096)) {
 #define FPTQ_WAVE_CASE(CH, RAGGED) residual_norm_quantize_kernel<CH, 1, RAGGED><<<grid, block, 0, s>>>(xr, yb, M, K, s_prev, eps, inv_s_a, x_next, s_next, out)
         WAVE_PER_ROW(vec, K, FPTQ_WAVE_CASE);
 #undef FPTQ_WAVE_CASE

@@ -6,7 +6,7 @@ import torch
 from paper_2506_04985_amd import binding as fptq
 import fptq_workloads as synth
 
-from gpu_util import dev, dev_bf16, host_bits
+from gpu_util import dev, dev_bf16, host_bits, launched
 
 pytestmark = pytest.mark.gpu
 
@@ -65,3 +65,16 @@ def test_residual_step_in_place_on_the_two_pass_path(oracle, M, K, alias):
     assert np.array_equal(host_bits(target), ref["x_next"])
     assert np.array_equal(s_next.cpu().numpy().view(np.uint32), ref["s_next"].view(np.uint32))
     assert np.array_equal(fptq.fptq_unpack(xq, M, K).cpu().numpy(), ref["q"])
+
+
+@pytest.mark.parametrize("M,K,workgroups", [(16383, 3080, 16383), (16384, 3080, 4096), (16390, 4096, 4098), (16383, 3072, 4096)])
+def test_rows_to_a_workgroup(M, K, workgroups):
+    """Very many rows of 3073 to 4096 values take a wave each again, and give what a workgroup each gives."""
+    torch.manual_seed(M)
+    x, y = (torch.randn((M, K), device="cuda").to(torch.bfloat16) for _ in range(2))
+    q, s, o = torch.empty(fptq.fptq_packed_bytes(M, K), dtype=torch.uint8, device="cuda"), torch.empty(M, device="cuda"), torch.empty_like(x)
+    assert launched(lambda: fptq.fptq_residual_norm_quantize(x, y, 0.45, None, 1e-5, x_next=o, s_next=s, out=q))[1] == workgroups
+    for i in (0, M - 500):
+        po, ps, pq = fptq.fptq_residual_norm_quantize(x[i:i + 500], y[i:i + 500], 0.45, None, 1e-5)
+        assert torch.equal(po.view(torch.int16), o[i:i + 500].view(torch.int16)) and torch.equal(ps, s[i:i + 500])
+        assert torch.equal(pq.view(-1, 500, 64), q.view(-1, M, 64)[:, i:i + 500])
