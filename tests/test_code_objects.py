@@ -82,9 +82,8 @@ def test_arguments_that_addresses_need_come_with_the_dispatch(kernels):
 
 
 def test_scratch_only_where_it_is_stated(kernels):
-    """Of the instances that calls run: the INT8 256 x 256 tile at any width or with a zero point, the six-bit 256-token tile of whole 16-byte rows."""
-    stated = (r"linear_mfma_kernelINS_7GemmCfgILi2ELi2ELi4ELi4ELi4ELi1ELi1ELb0EEE(Li0ELb0ELb[01]E|Li[12]ELb0ELb1E)",
-              r"linear_prefill_kernelILi8ELi[12]ELb0ELb[01]E",
+    """Of the instances that calls run: the six-bit 256-token tile of whole 16-byte rows."""
+    stated = (r"linear_prefill_kernelILi8ELi[12]ELb0ELb[01]E",
               r"linear_(mfma|prefill)_kernel.*Li0ELb1ELb[01]E",                 # parity dumps of the accumulators
               r"linear_decode_kernelILi16ELi4ELi[24]E")                         # shapes that only fptq_set_decode_shape reaches
     for name, text in kernels.items():

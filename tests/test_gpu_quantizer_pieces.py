@@ -78,13 +78,13 @@ def test_static_quantizer_beyond_the_last_level_cache(mode):
         assert torch.equal(p, q[part])
 
 
-@pytest.mark.parametrize("mode", [synth.MODE_NONE, synth.MODE_RMS, synth.MODE_GIVEN])
-@pytest.mark.parametrize("M,K,B", [(3, 256, 256), (5, 768, 256), (6, 1280, 256), (2, 512, 512), (5, 1536, 512), (7, 3072, 1024), (300, 2560, 512),
-                                   (4100, 16384, 2048), (4100, 32768, 4096)])
+# the last three: with RMS scale a wave walks a row, several spans of one and of two, four and eight chunks a lane; without, the many rows are a wave per block
+@pytest.mark.parametrize("mode,M,K,B", [(mode, *shape) for shape in ((3, 256, 256), (5, 768, 256), (6, 1280, 256), (2, 512, 512), (5, 1536, 512), (7, 3072, 1024), (300, 2560, 512))
+                                        for mode in (synth.MODE_NONE, synth.MODE_RMS, synth.MODE_GIVEN)]
+                         + [(mode, *shape) for shape in ((4100, 16384, 2048), (4100, 32768, 4096)) for mode in MODES]
+                         + [(synth.MODE_RMS, *shape) for shape in ((300, 3072, 1024), (300, 6144, 2048), (300, 12288, 4096))])
 def test_hadamard_special_values(oracle, mode, M, K, B):
     """What the transform spreads over a block is the same tree of additions, so NaNs and infinities come out where the definition has them."""
-    if M > 4096 and mode == synth.MODE_RMS:
-        pytest.skip("the launch of (300, 2560, 512): rows are not cut")
     inp = draw(min(M, 400), K, mode, seed=M + K + B)
     bits = with_specials(inp.x_bits, 5 * B + 3)
     rep = -(-M // bits.shape[0])
@@ -98,3 +98,18 @@ def test_hadamard_special_values(oracle, mode, M, K, B):
     assert np.array_equal(q[torch.from_numpy(rows).cuda()].cpu().numpy(), ref)
     if M > bits.shape[0]:
         assert torch.equal(q[:bits.shape[0]], q[bits.shape[0]:2 * bits.shape[0]])
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("M,K,B", [(12400, 11008, 256), (9800, 13824, 512), (11000, 12288, 512), (12000, 11264, 1024), (9400, 14336, 2048), (4700, 28672, 4096)])
+def test_hadamard_beyond_the_last_level_cache(mode, M, K, B):
+    """More than 256 MB: streamed.  Codes of the whole call and of its parts, which are not."""
+    assert M * K * 2 > 256 << 20
+    torch.manual_seed(B)
+    x = torch.randn((M, K), device="cuda").to(torch.bfloat16)
+    r = torch.rand(M, device="cuda") + 0.5 if mode == synth.MODE_GIVEN else None
+    xq, s = fptq.fptq_quantize_act_hadamard(x, 0.4, B, mode, 1e-5, r)
+    for i in range(0, M, M // 4):
+        n = min(M // 4, M - i)
+        part, ps = fptq.fptq_quantize_act_hadamard(x[i:i + n], 0.4, B, mode, 1e-5, None if r is None else r[i:i + n].clone())
+        assert torch.equal(xq.view(-1, M, 64)[:, i:i + n], part.view(-1, n, 64)) and torch.equal(s[i:i + n], ps)
