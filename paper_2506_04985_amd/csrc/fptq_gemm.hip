@@ -533,10 +533,10 @@ __global__ __launch_bounds__(C::THREADS, C::OCC) void linear_mfma_kernel(
         auto at = [&](int p) { step(p, fills[p % SETS], fills[(p + 1) % SETS], fills[(p + 2) % SETS]); };
         for (; left > 0; left -= C::UNROLL) {
             at(0);
-            if (left > 1) at(1);
-            if (left > 2) at(2);
+            if (__builtin_expect(left > 1, 1)) at(1);          // falls through: a taken branch per turn (1 % of a launch less than two or three)
+            if (__builtin_expect(left > 2, 1)) at(2);
             if constexpr (C::UNROLL == 4) {
-                if (left > 3) at(3);
+                if (__builtin_expect(left > 3, 1)) at(3);
             }
         }
     }
