@@ -136,10 +136,12 @@ hipError_t launch_residual_norm_quantize(const uint16_t *xr, const uint16_t *yb,
     const bool vec = K % 8 == 0 && ((reinterpret_cast<uintptr_t>(xr) | reinterpret_cast<uintptr_t>(yb) |
                                      reinterpret_cast<uintptr_t>(x_next)) & 15) == 0;
     // As for the plain quantizer: a wave per row for many short rows, otherwise a workgroup per
-    // row, which spreads a row over four waves (32 x 4096: 4.3 us with a wave per row).  Of 3073 to 4096 values only up to 16384 rows: beyond, what a
-    // workgroup gains at a call's start and end no longer shows (wave / workgroup, from HBM and from the cache: 8192 x 4096 43.9 / 44.2, 33.3 / 32.5; 16000 x 4096 79.3 /
-    // 81.5, 79.7 / 82.7; 20000 x 3200 77.1 / 79.4, 77.1 / 78.9; 30000 x 4096 148 / 157, 148 / 157).
-    if (wave_per_row(vec, M, K, M < 16384 ? 3072 : 4096)) {
+    // row, which spreads a row over four waves (32 x 4096: 4.3 us with a wave per row).  Of 3073 to 4096 values a workgroup gains at a call's start and end,
+    // and its second chunk leaves waves idle where a row is not nearly 4096 values, so for many rows only those, and for very many none (wave / workgroup, from
+    // HBM and from the cache: 1500 x 3584 9.3 / 8.4, 6.9 / 6.9; 2048 x 3584 10.8 / 10.2, 8.5 / 8.6; 3000 x 3080 12.8 / 14.1, 11.1 / 11.7; 4096 x 3584 18.6 / 18.2,
+    // 15.4 / 16.1; 4096 x 4096 21.2 / 20.0, 17.0 / 17.3; 8192 x 3080 29.5 / 30.6, 26.1 / 26.3; 8192 x 4096 38.7 / 38.0, 33.3 / 32.5; 12000 x 4096 58.3 / 58.3,
+    // 55.5 / 55.8; 16000 x 4096 80.5 / 82.0, 78.7 / 81.0; 30000 x 4096 148 / 157, 148 / 157).
+    if (wave_per_row(vec, M, K, M <= 2560 ? 3072 : M < 12288 ? 3840 : 4096)) {
 #define FPTQ_WAVE_CASE(CH, RAGGED) residual_norm_quantize_kernel<CH, 1, RAGGED><<<grid, block, 0, s>>>(xr, yb, M, K, s_prev, eps, inv_s_a, x_next, s_next, out)
         WAVE_PER_ROW(vec, K, FPTQ_WAVE_CASE);
 #undef FPTQ_WAVE_CASE

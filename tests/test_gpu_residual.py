@@ -67,9 +67,9 @@ def test_residual_step_in_place_on_the_two_pass_path(oracle, M, K, alias):
     assert np.array_equal(fptq.fptq_unpack(xq, M, K).cpu().numpy(), ref["q"])
 
 
-@pytest.mark.parametrize("M,K,workgroups", [(16383, 3080, 16383), (16384, 3080, 4096), (16390, 4096, 4098), (16383, 3072, 4096)])
+@pytest.mark.parametrize("M,K,workgroups", [(2560, 3080, 2560), (2561, 3080, 641), (2561, 3840, 641), (2561, 3848, 2561), (12287, 4096, 12287), (12290, 4096, 3073), (2560, 3072, 640)])
 def test_rows_to_a_workgroup(M, K, workgroups):
-    """Very many rows of 3073 to 4096 values take a wave each again, and give what a workgroup each gives."""
+    """Many rows a little above 3072 values, and very many of up to 4096, take a wave each, and give what a workgroup each gives."""
     torch.manual_seed(M)
     x, y = (torch.randn((M, K), device="cuda").to(torch.bfloat16) for _ in range(2))
     q, s, o = torch.empty(fptq.fptq_packed_bytes(M, K), dtype=torch.uint8, device="cuda"), torch.empty(M, device="cuda"), torch.empty_like(x)
