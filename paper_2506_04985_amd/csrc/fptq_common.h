@@ -150,20 +150,20 @@ __device__ inline void load_row_chunks(v4u (&v)[CH], const uint16_t *row, int k0
     }
 }
 
-// HIP refuses a launch of 2^32 threads or more: waves of a launch of workgroups of 256 threads, and such workgroups.  Kernels that spread a row over more waves
+// HIP refuses a launch of 2^32 threads or more: waves of a launch of workgroups of 256 threads.  Kernels that spread a row over more waves
 // than another one that serves it leave calls beyond that to the other.
-constexpr int64_t MAX_WAVES = ((int64_t)1 << 26) - 4, MAX_WORKGROUPS = MAX_WAVES / 4;
+constexpr int64_t MAX_WAVES = ((int64_t)1 << 26) - 4;
 
 // Many short rows: a wave takes a row, where a workgroup per row (which spreads a row over four waves) has most of its threads idle or more
 // waves than the device runs at once.  Aligned rows: crossover at 4096 values about 1000 rows with RMS scale (4096 x 4096 from HBM 11.0 us with a wave,
-// 10.8 with a workgroup, from the last-level cache 8.8 and 9.5); the residual step and the dynamic scale, which have more to do per value, take a workgroup from
-// 3072 values on (4096 x 4096, wave / workgroup, from HBM and from the cache: 23.5 / 21.5, 17.1 / 17.4 and 11.0 / 10.4, 8.9 / 8.8; 4096 x 3072 18.3 / 17.2,
-// 13.7 / 14.6).  Ragged ones (workgroup / wave, RMS scale): 800 x 63
+// 10.8 with a workgroup, from the last-level cache 8.8 and 9.5); the residual step and the dynamic scale, which have more to do per value, take a workgroup for
+// some rows above 3072 values, by lines of their own (4096 x 4096, wave / workgroup, from HBM and from the cache: 21.2 / 20.0, 17.0 / 17.3 and 11.0 / 10.4, 8.9 / 8.8; 4096 x
+// 3072 18.3 / 17.2, 13.7 / 14.6).  Ragged ones (workgroup / wave, RMS scale): 800 x 63
 // 3.3 / 2.3 us, 2048 x 333 4.6 / 2.7, 65536 x 63 82 / 23, 4000 x 3601 11.8 / 10.0; residual step 8192 x 333 19 / 6.7; but dynamic scale 1100 x 3601
 // 5.1 / 6.2, given scale 2048 x 1801 3.6 / 4.1.
 inline bool wave_per_row(bool vec, int64_t M, int64_t K, int64_t longest_aligned = 4096)
 {
-    return K <= (vec && M <= MAX_WORKGROUPS ? longest_aligned : 4096) && M > (vec || K <= 1024 ? 768 : 3072);
+    return K <= (vec ? longest_aligned : 4096) && M > (vec || K <= 1024 ? 768 : 3072);
 }
 
 // Its instances: CASE(chunks a lane, ragged).  Ragged rows in finer steps, because a chunk that lies past the row's end is loaded and computed

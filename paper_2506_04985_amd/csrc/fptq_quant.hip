@@ -320,7 +320,12 @@ hipError_t launch_quantize_act_dynamic(const uint16_t *x, int64_t M, int64_t K, 
     dim3 grid((unsigned)blocks), block(QT);
     const bool vec = K % QCHUNK == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
     const int64_t Kpad = k_tiles(K) * KT;
-    if (wave_per_row(vec, M, K, 3072)) {
+    // Of 3073 to 4096 values as in the residual step, with other lines, as there is less to do per value.  2048 workgroups run at once: between one and a quarter and two
+    // rounds of them the second costs more than the spreading gains (wave / workgroup, from HBM and from the cache: 1500 x 3584
+    // 6.0 / 5.2, 4.5 / 4.2; 2560 x 3584 7.9 / 7.3, 6.0 / 5.9; 3000 x 3584 8.3 / 7.9, 6.4 / 6.8; 4096 x 3080 9.7 / 9.7, 7.6 / 8.4; 4096 x 3584 10.1 / 10.1, 8.0 / 8.7; 4096 x
+    // 4096 11.0 / 10.6, 8.9 / 9.0; 6000 x 3584 13.3 / 13.1, 12.0 / 11.3; 8192 x 3080 15.9 / 16.6, 14.2 / 14.2; 8192 x 3584 17.2 / 17.6, 15.1 / 14.5; 16384 x 3840 31.2 / 31.2, 27.4 / 26.9;
+    // 20000 x 3328 33.1 / 36, 29.9 / 31.1; 30000 x 3840 54.9 / 58.2, 46.3 / 53; 30000 x 4096 59.6 / 56.0, 53.6 / 54.9; 65536 x 4096 134.5 / 137.6, 134.6 / 138.6).
+    if (wave_per_row(vec, M, K, M <= 2560 ? 3072 : M <= 4096 ? 3840 : M <= 16384 ? 3200 : M <= 32768 ? 3840 : 4096)) {
 #define FPTQ_WAVE_CASE(CH, RAGGED) quantize_act_dynamic_kernel<CH, RAGGED><<<grid, block, 0, s>>>(x, M, K, out, s_out)
         WAVE_PER_ROW(vec, Kpad, FPTQ_WAVE_CASE);
 #undef FPTQ_WAVE_CASE

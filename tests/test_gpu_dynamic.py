@@ -6,7 +6,7 @@ import torch
 from paper_2506_04985_amd import binding as fptq
 import fptq_workloads as synth
 
-from gpu_util import Y_TOL, dev, dev_bf16, host_bits, y_error
+from gpu_util import Y_TOL, dev, dev_bf16, host_bits, launched, y_error
 
 pytestmark = pytest.mark.gpu
 
@@ -67,3 +67,16 @@ def test_dynamic_needs_the_scale_buffer():
     out = torch.empty(fptq.fptq_packed_bytes(4, 128), dtype=torch.uint8, device="cuda")
     import ctypes
     assert L.fptq_quantize_act_dynamic(ctypes.c_void_p(x.data_ptr()), 4, 128, ctypes.c_void_p(out.data_ptr()), out.numel(), None, None) == -1
+
+
+@pytest.mark.parametrize("M,K,workgroups", [(2560, 3080, 2560), (2561, 3080, 641), (2561, 3840, 641), (4096, 3848, 4096), (4097, 3200, 1025), (4097, 3208, 4097), (16384, 3208, 16384), (16385, 3840, 4097), (16385, 3848, 16385), (32768, 4096, 32768),
+                                            (32769, 4096, 8193), (2560, 3072, 640)])
+def test_rows_to_a_workgroup(M, K, workgroups):
+    """Many rows a little above 3072 values, and very many of up to 4096, take a wave each, and give what a workgroup each gives."""
+    torch.manual_seed(M)
+    x = torch.randn((M, K), device="cuda").to(torch.bfloat16)
+    q, s = torch.empty(fptq.fptq_packed_bytes(M, K), dtype=torch.uint8, device="cuda"), torch.empty(M, device="cuda")
+    assert launched(lambda: fptq.fptq_quantize_act_dynamic(x, out=q, token_scale_out=s))[1] == workgroups
+    for i in (0, M - 500):
+        pq, ps = fptq.fptq_quantize_act_dynamic(x[i:i + 500])
+        assert torch.equal(ps, s[i:i + 500]) and torch.equal(pq.view(-1, 500, 64), q.view(-1, M, 64)[:, i:i + 500])
