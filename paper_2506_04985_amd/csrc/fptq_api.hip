@@ -94,7 +94,8 @@ static int check_align(const char *fn, const void *p, unsigned a, const char *na
 // tiles: 8168 channels of K = 3872 7.4 us / 8.8, 9784 x 4968 13.1 / 10.4, 8384 x 8416 18.5 / 13.5, 8824 x 14944 31.1 / 20.2; of 81 matrices of 8200 to
 // 10239 channels the tiles take 12 to 36 % less on each).  They are also faster with 17 to 32 tokens against more than 12288 channels of fewer than
 // 16 K tiles, too few for the 16 waves that share a K otherwise: 15208 x 992 6.2 us / 5.7, 29040 x 1352 11.7 / 8.5, 36536 x 1384 14.0 / 13.0, 57288 x 736
-// 17.3 / 11.5; 2 % more to 34 % less on 87 matrices of up to 62000 channels, and up to 6 % more below 12288.
+// 17.3 / 11.5; 2 % more to 34 % less on 87 matrices of up to 62000 channels, and up to 6 % more below 12288: where both kernels
+// fill the 256 CUs that it was measured on.  With fewer of them (a partitioned card) nothing was measured, and the line stays.
 static bool few_token_shape(int64_t M, int64_t N, int64_t K)
 {
     if (M > 64 || N > (1 << 24)) return M <= 32;

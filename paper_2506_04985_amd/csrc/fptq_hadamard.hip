@@ -12,10 +12,11 @@
 // strides run over registers, then over lanes, then over registers again.  Where the scale is given, every wave is done after one such
 // span, consecutive waves take consecutive spans, and memory is read in the order it lies in; waves that walked a row each, or several spans
 // a row apart, were up to a sixth slower on inputs that come from HBM (us, the kernel that walked rows through LDS and this one):
-//     4096 x 11008, B = 256    29.2  24.2     4096 x 13824, B = 512   38.6  31.0     4096 x 11264, B = 1024   29.0  26.3
-//     8192 x 14336, B = 2048   66.0  63.0     8192 x 13824, B = 512   66.0  57.9     8192 x 28672, B = 4096  137.9 114.0
-// (the read alone, as one burst: 16.3 us at 4096 x 11008, 80.6 at 8192 x 28672; from the last-level cache 4096 x 11008 21.2 and 20.7).
-// Bound by memory there and by VALU issue from the cache: 13 instructions per value at B = 256, 17 at 2048, 18 at 4096.
+//     4096 x 11008, B = 256    28.8  24.4     4096 x 13824, B = 512   40.7  30.7     4096 x 11264, B = 1024   30.8  27.3
+//     8192 x 14336, B = 2048   70.2  66.2     8192 x 13824, B = 512   72.0  61.2     8192 x 28672, B = 4096  137.0 121.0
+// (one card; the read alone, as one burst: 16.3 us at 4096 x 11008, 80.6 at 8192 x 28672; from the last-level cache 4096 x 11008 22.1 and 21.8).
+// Bound by memory there and by VALU issue from the cache: 17.5 instructions per value counted at B = 256, 18.6 at 512, 19.1 at 1024, 18.8 at 2048
+// and 19.1 at 4096, a wave's set-up among them.  At B = 256 that is more than the 16.1 of the kernel that walked rows: what it gains is the order of memory.
 #include "fptq_common.h"
 
 namespace fptq {
@@ -93,7 +94,7 @@ __device__ inline void swap_with_lanes(float (&v)[V])
 //
 // WALK: `parts` waves share a row and walk its spans.  RMS scale: it comes from the whole row, which every wave of it sums.  Given or none: calls of more spans
 // than a launch may have waves.  STREAM: inputs that the
-// last-level cache cannot hold (8192 x 28672: 123.0 us, 117.6 with; 4096 x 11008 from the cache 20.7 and 23.6).
+// last-level cache cannot hold (on a faster card than the table's 8192 x 28672 123.0 us, 117.6 with; 4096 x 11008 from the cache 20.7 and 23.6).
 //
 // PAIRS (B = 512, rows of an odd number of blocks; with RMS scale of one, whose sum the wave then has in registers): a wave takes two consecutive blocks
 // whatever rows they are of, `parts` is the blocks of a row.  With half a wave idle at the end of every row, short rows were slower than in the kernel that walked

@@ -56,8 +56,9 @@ constexpr int Q_STREAM = 2;      // buffer-load cache policy: non-temporal
 // element, now 6.1, 2048 x 4366 19.1 and 8.7).  CH == 0: rows too long for the registers, two passes over the row.
 //
 // Arguments: the first 14 words of a kernel's arguments come with the dispatch, and a wait for one beyond them is a memory latency at the start of
-// every wave; so the width is one word where the row fits the registers, and zoff has the input's streaming in its second byte.  Scale given,
-// with that flag as the 17th word / without any argument preloaded / now: 4096 x 4096 9.5, 9.8, 9.15 us, 256 x 8192 3.3, 3.3, 3.1, 32 x 4096 2.34, 2.32, 2.28.
+// every wave; so the width is one word where the row fits the registers, and zoff has the input's streaming in its second byte.  With that
+// flag as the 17th word / without any argument preloaded / now, measured when this kernel still served aligned rows of a given scale: 4096 x 4096 9.5, 9.8,
+// 9.15 us, 256 x 8192 3.3, 3.3, 3.1, 32 x 4096 2.34, 2.32, 2.28.
 template <int CH> using width_t = std::conditional_t<(CH > 0), int, int64_t>;
 constexpr int STREAM_IN = 256;
 
